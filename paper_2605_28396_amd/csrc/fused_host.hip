@@ -17,7 +17,6 @@ struct FusedLayout {
   bool use_dma;      // logit passes staged by direct global->LDS loads
   bool single;       // single-sweep scheme (needs use_dma)
   size_t o_wt_img, o_ws_img, o_ht_img, o_hs_img;   // tile images of the logit operands (use_dma)
-  int strips1;       // vocabulary strips of the single sweep
   size_t o_ref_t2, o_delta, o_invz, o_mu0t;
   int strips, ksplit;
   int64_t slab_rows, Vp;
@@ -57,6 +56,61 @@ static bool needs_gradient(const adwin_opd_problem* p) {
                                  (p->cand_rho_pooled || p->cand_rho_field || p->cand_batch))));
 }
 
+// Vocabulary strips of a sweep over `n_tiles` token tiles: the grid is n_tiles x strips
+// workgroups, one per compute unit at a time, dealt in equal shares to the 8 XCDs of 32, so a
+// sweep costs rounds x (vocabulary tiles of the longest strip + a start, taken as a quarter of a
+// tile).  32 strips is what the large slabs were tuned with (64 token tiles: 16 and 64 strips
+// are 1 to 4 % slower although 16 has the better-filled rounds) and stays wherever it is within
+// 5 % of the cheapest count; a call of few token tiles, which left most of the chip without
+// work, takes more strips, and one whose rounds are badly filled takes the count that fills
+// them.  256 rows, V = 151,936, H = 2048 + 4096: 2612 us with 32 strips.
+static int sweep_strips(int n_tiles, int vt_total) {
+  const int most = vt_total < kMaxSweepStrips ? vt_total : kMaxSweepStrips;
+  auto cost = [&](int s) {
+    const int per_xcd = (n_tiles * s + 7) / 8, rounds = (per_xcd + 31) / 32;
+    return rounds * ((vt_total + s - 1) / s + 0.25);
+  };
+  int tuned = env_int("ADWIN_STRIPS2", 32);
+  if (tuned > most) tuned = most;
+  if (getenv("ADWIN_STRIPS2")) return tuned;
+  int best = tuned;
+  double least = 0.95 * cost(tuned);
+  for (int s = 1; s <= most; ++s)
+    if (cost(s) < least) { best = s; least = cost(s); }
+  return best;
+}
+
+// Rows per slab and k-splits of the gradient GEMM.  Its 256 x 256 output tiles run in rounds of
+// 256 compute units; with ksplit > 1 the contraction over the vocabulary is cut into ksplit
+// pieces, one workgroup each, whose partial planes of g finalize_kernel adds in index order.
+// Cost in k-steps (1.6 us): rounds x (k-steps of a piece + 20 for the start and the epilogue of a
+// tile, from 256-step and 2374-step launches), and the partial planes written and read once at
+// 4 TB/s.  Slabs are multiples of 8 token tiles between 4,096 and 16,384 rows; ties go to the
+// larger slab (fewer launches, each of which ends in a partly idle round) and to fewer pieces.
+// One row tile of V = 151,936, H_s = 2048 ran on 128 compute units with the split bounded by 16.
+struct GradGeometry { int64_t slab_rows; int ksplit; };
+static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
+  GradGeometry best{0, 1};
+  double least = -1.0;
+  const bool forced = getenv("ADWIN_SLAB_ROWS") != nullptr;
+  const int64_t first = forced ? (int64_t)align_up((size_t)env_int("ADWIN_SLAB_ROWS", 8192), kTileTokens) : 16384;
+  for (int64_t r = first; r >= (forced ? first : 4096); r -= 2048) {
+    const int64_t slab = r < n_pad ? r : n_pad;
+    // pieces only where one slab holds every row: the partial planes cover all rows of the call
+    const int most = slab == n_pad ? (nk < 32 ? nk : 32) : 1;
+    for (int ks = 1; ks <= most; ++ks) {
+      double cost = ks > 1 ? (double)ks * (double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 : 0.0;
+      for (int64_t r0 = 0; r0 < n_pad; r0 += slab) {
+        const int64_t rows = n_pad - r0 < slab ? n_pad - r0 : slab;
+        const int64_t rounds = ((rows / kGradTile) * h_tiles * ks + 255) / 256;
+        cost += (double)rounds * ((nk + ks - 1) / ks + 20);
+      }
+      if (least < 0.0 || cost < least) { least = cost; best = GradGeometry{slab, ks}; }
+    }
+  }
+  return best;
+}
+
 static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) {
   FusedLayout L;
   const int64_t n_pad = hp.n_pad > 0 ? hp.n_pad : kTileTokens;
@@ -67,47 +121,26 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   if (strips > kMaxStrips) strips = kMaxStrips;
   L.strips = strips;
   (void)resolve_scheme(p, &L.use_dma, &L.single);     // validity was checked with the problem
-  int strips1 = env_int("ADWIN_STRIPS2", 32);
-  if (strips1 > vt_total) strips1 = vt_total;
-  if (strips1 > kMaxStrips) strips1 = kMaxStrips;
-  L.strips1 = strips1;
   const int halves = L.single ? 2 : 1;     // the single sweep stores two factors per logit
-  // ... but the gradient GEMM contracts one: the combined logit gradient, or E2 (sampled estimator)
-  const int gemm_halves = 1;
+  // (the gradient GEMM contracts one: the combined logit gradient, or E2 with the sampled estimator)
   const int h_tiles = (p->H_s + kGradTile - 1) / kGradTile;
-  // Rows per slab: a multiple of 8 token tiles (whole rounds of the sweep's workgroups on
-  // 256 compute units) between 4,096 and 16,384, chosen so that the gradient GEMM's
-  // 256 x 256 output tiles of all slabs fill the fewest rounds; ties go to the larger slab
-  // (fewer launches, each of which ends in a partly idle round).
-  int64_t slab = 0;
-  if (getenv("ADWIN_SLAB_ROWS")) {
-    slab = (int64_t)align_up((size_t)env_int("ADWIN_SLAB_ROWS", 8192), kTileTokens);
-  } else {
-    int64_t best_rounds = -1;
-    for (int64_t r = 16384; r >= 4096; r -= 2048) {
-      int64_t rounds = 0;
-      for (int64_t r0 = 0; r0 < n_pad; r0 += r) {
-        const int64_t rows = n_pad - r0 < r ? n_pad - r0 : r;
-        rounds += (gemm_halves * (rows / kGradTile) * h_tiles + 255) / 256;
-      }
-      if (best_rounds < 0 || rounds < best_rounds) { best_rounds = rounds; slab = r; }
-    }
-  }
-  if (slab > n_pad) slab = n_pad;
+  const GradGeometry gg = grad_geometry(n_pad, h_tiles, (int)(L.Vp / kBK));
+  const int64_t slab = gg.slab_rows;
+  const int ks = gg.ksplit;
   L.slab_rows = slab;
-  const int64_t tiles = gemm_halves * (slab / kGradTile) * h_tiles;
-  int ks = (int)(256 / (tiles > 0 ? tiles : 1));
-  const int nk = (int)(L.Vp / kBK);
-  if (ks > 16) ks = 16;
-  if (ks > nk) ks = nk;
-  if (ks < 1) ks = 1;
   L.ksplit = ks;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
   L.o_plan = take(PlanBlobLayout(p->B).bytes);
   L.o_row_idx = take(sizeof(int32_t) * (size_t)n_pad);
   L.o_row_seq = take(sizeof(int32_t) * (size_t)n_pad);
-  L.o_part = take(sizeof(float) * 5 * (size_t)(strips > strips1 ? strips : strips1) * (size_t)n_pad);
+  // strip partials of the widest launch: the slabs are swept one after the other
+  int part_strips = strips;
+  for (int64_t r0 = 0; r0 < n_pad; r0 += slab) {
+    const int s = sweep_strips((int)((n_pad - r0 < slab ? n_pad - r0 : slab) / kTileTokens), vt_total);
+    if (s > part_strips) part_strips = s;
+  }
+  L.o_part = take(sizeof(float) * 5 * (size_t)part_strips * (size_t)n_pad);
   L.o_ref_t2 = take(sizeof(float) * (size_t)n_pad);
   L.o_delta = take(sizeof(float) * (size_t)n_pad);
   L.o_mu0t = take((L.single && p->estimator != ADWIN_EST_SAMPLED)
@@ -348,8 +381,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       // slab's rows, the combine pass over the factors and the GEMM of dz with W_s.
       la.tile0 = 0; la.n_tiles = n_tiles; la.strips = 1; la.vt_total = 1;
       {
-        const int groups = (n_tiles + la.tg - 1) / la.tg;
-        ADWIN_HIP_TRY(launch_logit_pass(kModeStats, true, la, (unsigned)(groups * la.tg), stream));
+        ADWIN_HIP_TRY(launch_logit_pass(kModeStats, true, la, stream));
         if (p->ids || diag) {      // without ids: id -1 on every row, which the diagnostics sweep expects
           TokenLogitArgs ta;
           ta.row_idx = pl.row_idx; ta.ids = p->ids;
@@ -365,24 +397,23 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
                                        (float*)(ws + L.o_lse2), (float*)(ws + L.o_ref_t2),
                                        (float*)(ws + L.o_mu), stream));
       }
-      la.vt_total = vt_total; la.strips = L.strips1;
+      la.vt_total = vt_total;
       la.zy_t = (const float*)(ws + L.o_zy_t); la.yid = (const int32_t*)(ws + L.o_yid);
       ga.g_rows = 2 * n_pad; ga.half_off = n_pad;
       for (int64_t r0 = 0; r0 < n_pad; r0 += L.slab_rows) {
         const int64_t rows = (n_pad - r0 < L.slab_rows) ? n_pad - r0 : L.slab_rows;
         la.tile0 = (int)(r0 / kTileTokens); la.n_tiles = (int)(rows / kTileTokens);
         la.e2_off = rows * L.Vp;
-        const int groups = (la.n_tiles + la.tg - 1) / la.tg;
+        la.strips = sweep_strips(la.n_tiles, vt_total);
         phase(ADWIN_PHASE_STATS);
-        const unsigned sweep_grid = (unsigned)(groups * la.tg * L.strips1);
         const int sweep_mode = !need_g ? (diag ? kModeSingleFwdDiag : kModeSingleFwd)
                                : sampled ? (diag ? kModeSingleE2Diag : kModeSingleE2)
                                          : (diag ? kModeSingleDiag : kModeSingle);
-        ADWIN_HIP_TRY(launch_logit_pass(sweep_mode, true, la, sweep_grid, stream));
+        ADWIN_HIP_TRY(launch_logit_pass(sweep_mode, true, la, stream));
         // this slab's rows are complete: KL_t, c_t, mu; then the logit gradient proper
         phase(ADWIN_PHASE_MERGE);
         MergeSingleArgs ms;
-        ms.m = m; ms.m.strips = L.strips1;
+        ms.m = m; ms.m.strips = la.strips;
         ms.ref_s2 = la.ref_s2; ms.ref_t2 = la.ref_t2;
         ms.mu_out = (float*)(ws + L.o_delta); ms.inv_z = (float*)(ws + L.o_invz);
         ms.row0 = r0; ms.rows = rows;
@@ -442,20 +473,17 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       phase(ADWIN_PHASE_STATS);
       {
         la.tile0 = 0; la.n_tiles = n_tiles; la.strips = L.strips;
-        const int groups = (n_tiles + la.tg - 1) / la.tg;
-        ADWIN_HIP_TRY(launch_logit_pass(kModeStats, use_dma, la, (unsigned)(groups * la.tg * L.strips), stream));
+        ADWIN_HIP_TRY(launch_logit_pass(kModeStats, use_dma, la, stream));
       }
       phase(ADWIN_PHASE_MERGE);
       ADWIN_HIP_TRY(launch_merge_stats(m, stream));
-      const int strips2 = L.strips1;
       ga.g_rows = n_pad; ga.half_off = 0;
       for (int64_t r0 = 0; r0 < n_pad; r0 += L.slab_rows) {
         const int64_t rows = (n_pad - r0 < L.slab_rows) ? n_pad - r0 : L.slab_rows;
         la.tile0 = (int)(r0 / kTileTokens); la.n_tiles = (int)(rows / kTileTokens);
-        la.strips = strips2;
-        const int groups = (la.n_tiles + la.tg - 1) / la.tg;
+        la.strips = sweep_strips(la.n_tiles, vt_total);
         phase(ADWIN_PHASE_DZ);
-        ADWIN_HIP_TRY(launch_logit_pass(kModeDz, use_dma, la, (unsigned)(groups * la.tg * strips2), stream));
+        ADWIN_HIP_TRY(launch_logit_pass(kModeDz, use_dma, la, stream));
         phase(ADWIN_PHASE_GRAD);
         ga.slab_row0 = r0;
         ga.row_tiles = (int)(rows / kGradTile); ga.half_tiles = ga.row_tiles;

@@ -24,6 +24,19 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nb) {
   return xcd * base + (xcd < rem ? xcd : rem) + loc;
 }
 
+// Workgroup `vid` of a logit pass -> (strip, token tile): groups of `tg` token tiles, inside a
+// group strip-major, so that consecutive ids share a strip's W tiles and a group's h tiles.  The
+// last group holds the tiles that remain: every workgroup of the grid (n_tiles x strips) has
+// work.  With the last group padded to `tg` tiles instead, a call of one token tile left three
+// of four workgroups empty and the XCDs of a 13-tile call unevenly loaded.
+__device__ __forceinline__ void strip_and_tile(int vid, int tg, int strips, int n_tiles, int* strip, int* tile) {
+  const int per_group = tg * strips, g = vid / per_group;
+  const int within = vid - g * per_group, left = n_tiles - g * tg;
+  const int h = left < tg ? left : tg;
+  *strip = within / h;
+  *tile = g * tg + within % h;
+}
+
 // One wave instruction of a direct global->LDS load: lane l moves the 16 bytes at
 // sbase + voff(l) to LDS address lds_base + IMM + 16 l (M0 = LDS destination of the wave;
 // scalar base + 32-bit lane offset).  Such loads return in order and are waited for with an
@@ -274,7 +287,7 @@ struct PoolArgs {
 hipError_t sweep_kernels_opt_in();       // large dynamic LDS of the logit kernels, once per device
 hipError_t launch_row_image(const RowImageArgs& a, unsigned tiles, hipStream_t st);
 // mode: one of kMode*; dma false selects the register-staged kernel (kModeStats, kModeDz only)
-hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, unsigned grid, hipStream_t st);
+hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStream_t st);
 hipError_t launch_token_logit(const TokenLogitArgs& a, hipStream_t st);
 hipError_t launch_make_refs(const float* part, int64_t n_pad, const float* zy_s, const float* zy_t,
                             const int32_t* yid, float* ref_s2, float* ref_t2, float* mu0, hipStream_t st);

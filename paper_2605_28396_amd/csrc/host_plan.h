@@ -16,7 +16,8 @@ constexpr int kTileVocab  = 128;   // vocabulary rows per tile step of the logit
 constexpr int kBK         = 64;    // bf16 elements staged per k-step (128 B per row)
 constexpr int kGradTile   = 256;   // rows and columns of one dZ*W_s output tile
 constexpr int kChunkRows  = 128;   // rows per partial of the pooled-gradient reduction
-constexpr int kMaxStrips  = 64;    // vocabulary strips of the statistics pass
+constexpr int kMaxStrips  = 64;    // vocabulary strips of the running-maximum statistics pass
+constexpr int kMaxSweepStrips = 256;   // vocabulary strips of the single sweep (one per compute unit)
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 

@@ -372,12 +372,8 @@ template <bool PASS2>
 __global__ __launch_bounds__(256) void logit_pass_kernel(LogitPassArgs a) {
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // virtual id -> (group of 4 token tiles, strip, tile in group)
-  const int vid = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int per_group = a.tg * a.strips;
-  const int tg = vid / per_group, within = vid % per_group;
-  const int strip = within / a.tg, tt_local = tg * a.tg + (within % a.tg);
-  if (tt_local >= a.n_tiles) return;
+  int strip, tt_local;
+  strip_and_tile(xcd_contiguous_id(blockIdx.x, gridDim.x), a.tg, a.strips, a.n_tiles, &strip, &tt_local);
   const int tt = a.tile0 + tt_local;
   const int vt_begin = (int)((int64_t)a.vt_total * strip / a.strips);
   const int vt_end = (int)((int64_t)a.vt_total * (strip + 1) / a.strips);
@@ -591,11 +587,8 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int vid = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int per_group = a.tg * a.strips;
-  const int tg = vid / per_group, within = vid % per_group;
-  const int strip = within / a.tg, tt_local = tg * a.tg + (within % a.tg);
-  if (tt_local >= a.n_tiles) return;
+  int strip, tt_local;
+  strip_and_tile(xcd_contiguous_id(blockIdx.x, gridDim.x), a.tg, a.strips, a.n_tiles, &strip, &tt_local);
   const int tt = a.tile0 + tt_local;
   const int vt_begin = (int)((int64_t)a.vt_total * strip / a.strips);
   const int vt_end = (int)((int64_t)a.vt_total * (strip + 1) / a.strips);
@@ -858,10 +851,10 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   if (r >= b.row0 + b.rows) return;
   const int64_t plane = (int64_t)a.strips * a.n_pad;
   float Zs = 0.f, A = 0.f, Zt = 0.f, Bt = 0.f, cnt = 0.f;
-  if (lane < a.strips) {
-    const float* p = a.part + (int64_t)lane * a.n_pad + r;
-    Zs = p[0]; A = p[plane]; Zt = p[2 * plane];
-    if (a.diag) { Bt = p[3 * plane]; cnt = p[4 * plane]; }
+  for (int s = lane; s < a.strips; s += 64) {
+    const float* p = a.part + (int64_t)s * a.n_pad + r;
+    Zs += p[0]; A += p[plane]; Zt += p[2 * plane];
+    if (a.diag) { Bt += p[3 * plane]; cnt += p[4 * plane]; }
   }
   Zs = wave_sum(Zs); A = wave_sum(A); Zt = wave_sum(Zt);
   if (a.diag) { Bt = wave_sum(Bt); cnt = wave_sum(cnt); }
@@ -958,7 +951,8 @@ hipError_t launch_row_image(const RowImageArgs& a, unsigned tiles, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, unsigned grid, hipStream_t st) {
+hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStream_t st) {
+  const unsigned grid = (unsigned)a.n_tiles * (unsigned)a.strips;
   if (!dma) {
     if (mode == kModeStats) logit_pass_kernel<false><<<grid, 256, kLogitLds, st>>>(a);
     else if (mode == kModeDz) logit_pass_kernel<true><<<grid, 256, kLogitLds, st>>>(a);

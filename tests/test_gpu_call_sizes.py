@@ -1,0 +1,31 @@
+"""Calls of few rows: the launch geometry, the operand staging and the split of the work follow
+the number of token tiles, so the sizes on both sides of each rule are compared with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import adwin_oracle as O
+from paper_2605_28396_amd import synth
+from tests import helpers as Hp
+from tests.test_gpu_parity import B, _check_fused, _run_fused  # noqa: F401  (B is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("estimator", [O.EST_EXPECTED, O.EST_SAMPLED])
+@pytest.mark.parametrize("V,H_s,H_t,lens,win", [
+    (16648, 192, 256, [17], [16]),               # one token tile, 131 vocabulary tiles of which the last holds 8
+    (16648, 128, 320, [200, 57], [200, 57]),     # one row into the second token tile
+    (16616, 320, 128, [700], [513]),             # three token tiles; a last half block that is all padding
+    (4104, 256, 192, [900, 390], [900, 390]),    # six token tiles: a group of four and one of two
+    (4096, 128, 128, [2100], [2049]),            # nine token tiles, whole vocabulary tiles
+])
+def test_few_rows_match_oracle(B, V, H_s, H_t, lens, win, estimator):  # noqa: F811
+    for mode in (synth.MODE_PREFIX_ONLY, synth.MODE_PREFIX_AND_FULL):
+        w = synth.Workload(f"few_{V}_{H_s}_{H_t}", V, H_s, H_t, synth._offsets(lens), np.array(win, np.int32), mode)
+        p = synth.hidden_problem(w)
+        f = Hp.oracle_inputs(p)
+        ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                          reduction=O.RED_SEQ_MEAN, mode=mode, estimator=estimator)
+        got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator)
+        _check_fused(w, got, ref, O.RED_SEQ_MEAN)
