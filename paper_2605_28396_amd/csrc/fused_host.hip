@@ -20,8 +20,8 @@ struct FusedLayout {
   size_t o_ref_t2, o_delta, o_invz, o_mu0t;
   int strips, ksplit;
   int64_t slab_rows, Vp;
-  size_t o_plan, o_row_idx, o_row_seq, o_part, o_lse2, o_mu, o_klr, o_rownorm, o_WsT, o_slab, o_g,
-      o_pp, o_pf, o_up, o_uf, o_seg, o_racc, o_uc, o_cacc, o_cS, o_cr, o_zy_s, o_zy_t, o_yid, o_dzT_p, o_dzT_f, o_hsT, o_summ, o_cosp,
+  size_t o_plan, o_row_idx, o_row_seq, o_part, o_lse2, o_mu, o_klr, o_rownorm, o_slab, o_g,
+      o_pp, o_pf, o_up, o_uf, o_seg, o_racc, o_uc, o_cacc, o_cS, o_cr, o_zy_s, o_zy_t, o_yid, o_dzT_p, o_dzT_f, o_hsg, o_summ, o_cosp,
       o_lse_s, o_heavy_cnt, o_heavy_v, total;
 };
 
@@ -84,8 +84,8 @@ static int sweep_strips(int n_tiles, int vt_total) {
 // 256 compute units; with ksplit > 1 the contraction over the vocabulary is cut into ksplit
 // pieces, one workgroup each, whose partial planes of g finalize_kernel adds in index order.
 // Cost in k-steps (1.6 us): rounds x (k-steps of a piece + 20 for the start and the epilogue of a
-// tile, from 256-step and 2374-step launches), and the partial planes written and read once at
-// 4 TB/s.  Slabs are multiples of 8 token tiles between 4,096 and 16,384 rows; ties go to the
+// tile, from 256-step and 2374-step launches), and per piece the partial plane written and read
+// once at 4 TB/s plus 0.4 for finalize_kernel's turn around one more load.  Slabs are multiples of 8 token tiles between 4,096 and 16,384 rows; ties go to the
 // larger slab (fewer launches, each of which ends in a partly idle round) and to fewer pieces.
 // One row tile of V = 151,936, H_s = 2048 ran on 128 compute units with the split bounded by 16.
 struct GradGeometry { int64_t slab_rows; int ksplit; };
@@ -99,7 +99,7 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
     // pieces only where one slab holds every row: the partial planes cover all rows of the call
     const int most = slab == n_pad ? (nk < 32 ? nk : 32) : 1;
     for (int ks = 1; ks <= most; ++ks) {
-      double cost = ks > 1 ? (double)ks * (double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 : 0.0;
+      double cost = ks > 1 ? (double)ks * ((double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 + 0.4) : 0.0;
       for (int64_t r0 = 0; r0 < n_pad; r0 += slab) {
         const int64_t rows = n_pad - r0 < slab ? n_pad - r0 : slab;
         const int64_t rounds = ((rows / kGradTile) * h_tiles * ks + 255) / 256;
@@ -150,7 +150,6 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   L.o_mu = take(sizeof(float) * (size_t)n_pad);
   L.o_klr = take(sizeof(float) * (size_t)n_pad);
   L.o_rownorm = take(sizeof(float) * (size_t)n_pad);
-  L.o_WsT = take(2 * (size_t)h_tiles * kGradTile * (size_t)L.Vp);
   L.o_wt_img = take(L.use_dma ? 2 * (size_t)L.Vp * (size_t)p->H_t : 0);
   L.o_ws_img = take(L.use_dma ? 2 * (size_t)L.Vp * (size_t)p->H_s : 0);
   L.o_ht_img = take(L.use_dma ? 2 * (size_t)n_pad * (size_t)p->H_t : 0);
@@ -174,13 +173,13 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   L.o_zy_s = take(sizeof(float) * (size_t)n_pad);
   L.o_zy_t = take(sizeof(float) * (size_t)n_pad);
   L.o_yid = take(sizeof(int32_t) * (size_t)n_pad);
-  const bool head = p->dW_prefix || p->dW_full;       // transposed slab + weighted h_s^T images
+  const bool head = p->dW_prefix || p->dW_full;       // transposed slab + gathered h_s rows
   // vocabulary tiles of 256 image rows: the last one may be half used (its upper rows are
   // never written, and their output rows do not exist)
   const size_t v_img = align_up((size_t)L.Vp, (size_t)kGradTile);
   L.o_dzT_p = take(p->dW_prefix ? 2 * (size_t)slab * v_img : 0);
   L.o_dzT_f = take(p->dW_full ? 2 * (size_t)slab * v_img : 0);
-  L.o_hsT = take(head ? 2 * (size_t)h_tiles * kGradTile * (size_t)slab : 0);
+  L.o_hsg = take(head ? 2 * (size_t)slab * (size_t)p->H_s : 0);
   L.o_cosp = take((p->dW_prefix && p->dW_full) ? sizeof(double) * 3 * kCosineBlocks : 0);
   L.o_summ = take((p->t_first_reject || p->t_logp_mean || p->cand_loss_share)
                       ? sizeof(double) * (size_t)p->B * kSummarySlots : 0);
@@ -323,11 +322,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     ADWIN_HIP_TRY(launch_fill_u32((uint32_t*)heavy.cnt, n_pad, 0u, stream));
     const int vt_total = (int)(L.Vp / kTileVocab);
     const int n_tiles = (int)(n_pad / kTileTokens);
-    // tile images of W_s^T for the gradient GEMM
     const int h_tiles = (p->H_s + kGradTile - 1) / kGradTile;
-    if (need_g) {
-      ADWIN_HIP_TRY(launch_wst_image(p->W_s, ws + L.o_WsT, p->V, p->H_s, (int)(L.Vp / kBK), h_tiles, stream));
-    }
     const bool use_dma = L.use_dma;
     if (use_dma) {
       // tile images of the logit operands: vocabulary tiles of 128 rows (zero beyond V),
@@ -371,7 +366,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     m.diag = diag ? 1 : 0; m.t_logp = p->t_logp; m.t_entropy = p->t_entropy; m.t_rank = p->t_rank;
     m.cr = sampled ? (float*)(ws + L.o_cr) : nullptr;
     GradArgs ga;
-    ga.slab = la.slab; ga.WsT = (const __bf16*)(ws + L.o_WsT); ga.nk_total = (int)(L.Vp / kBK);
+    ga.slab = la.slab; ga.Bm = (const __bf16*)p->W_s; ga.nk_total = (int)(L.Vp / kBK); ga.k_rows = p->V;
     ga.g = gws; ga.H = p->H_s; ga.h_tiles = h_tiles; ga.ksplit = L.ksplit;
     ga.out_rows = (int64_t)1 << 62; ga.accumulate = 0;
     if (L.single) {
@@ -447,17 +442,15 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         if (head) {
           // head-weight gradient of this slab: dW += dz^T (w h_s), k = the slab's rows
           GradArgs wa = ga;
-          wa.WsT = (const __bf16*)(ws + L.o_hsT);
-          wa.nk_total = (int)(rows / kBK);
+          wa.Bm = (const __bf16*)(ws + L.o_hsg);
+          wa.nk_total = (int)(rows / kBK); wa.k_rows = rows;
           wa.H = p->H_s; wa.h_tiles = h_tiles; wa.ksplit = 1;
           wa.slab_row0 = 0; wa.row_tiles = (int)((L.Vp + kGradTile - 1) / kGradTile); wa.half_tiles = wa.row_tiles;
           wa.half_off = 0; wa.g_rows = 0; wa.out_rows = p->V; wa.accumulate = r0 > 0;
-          HstImageArgs ha;
-          ha.h_s = (const uint16_t*)p->h_s; ha.row_idx = pl.row_idx;
-          ha.row0 = r0; ha.H = p->H_s; ha.nkr = wa.nk_total;
-          ha.img = (uint16_t*)(ws + L.o_hsT);
-          ha.alive = (const float*)(ws + L.o_invz);
-          ADWIN_HIP_TRY(launch_hst_image(ha, h_tiles, stream));
+          HsGatherArgs ha;
+          ha.h_s = (const uint4*)p->h_s; ha.row_idx = pl.row_idx; ha.row0 = r0; ha.H = p->H_s;
+          ha.out = (uint4*)(ws + L.o_hsg); ha.alive = (const float*)(ws + L.o_invz);
+          ADWIN_HIP_TRY(launch_hs_gather(ha, rows, stream));
           for (int which = 0; which < 2; ++which) {
             float* out = which == 0 ? p->dW_prefix : p->dW_full;
             if (!out) continue;

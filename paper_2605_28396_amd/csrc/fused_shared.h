@@ -67,6 +67,9 @@ template <int BYTES>
 __device__ __forceinline__ void addr_advance(uint32_t& lo, uint32_t& hi) {
   asm volatile("s_add_u32 %0, %0, %2\n\ts_addc_u32 %1, %1, 0" : "+s"(lo), "+s"(hi) : "n"(BYTES) : "scc");
 }
+__device__ __forceinline__ void addr_advance(uint32_t& lo, uint32_t& hi, uint32_t bytes) {
+  asm volatile("s_add_u32 %0, %0, %2\n\ts_addc_u32 %1, %1, 0" : "+s"(lo), "+s"(hi) : "s"(bytes) : "scc");
+}
 __device__ __forceinline__ const char* addr_of(uint32_t lo, uint32_t hi) {
   return (const char*)(((uint64_t)hi << 32) | lo);
 }
@@ -87,9 +90,8 @@ __device__ __forceinline__ void wait_vm() {
 constexpr int kSlabBlock = kTileTokens * kBK;   // elements per block
 constexpr int kImgBytesSlab = kSlabBlock * 2;   // 32 KiB
 
-// Blocks of the gradient GEMM's operand images: 256 rows x 64 k-entries (see grad_kernels.hip).
-constexpr int kImgElems = kGradTile * kBK;            // bf16 elements per block
-constexpr int kImgBytes = kImgElems * 2;              // 32 KiB
+// A staged block of either operand of the gradient GEMM: 256 x 64 entries (see grad_kernels.hip).
+constexpr int kImgBytes = kGradTile * kBK * 2;        // 32 KiB
 
 // Heavy entries.  The logit gradient dz = p_s ((z_s - z_t) - mu) is contracted with W_s as
 // bf16.  On a peaked row a handful of entries carry the whole gradient row and their rounding
@@ -232,19 +234,21 @@ struct CombineArgs {
   HeavyList heavy;             // entries with p_s >= kHeavyP leave the bf16 operand (expected estimator)
 };
 
-// Transposed h_s images of one slab (see hst_image_kernel).
-struct HstImageArgs {
-  const uint16_t* h_s; const int32_t* row_idx;
+// h_s rows of one slab (see hs_gather_kernel).
+struct HsGatherArgs {
+  const uint4* h_s; const int32_t* row_idx;
   int64_t row0;
-  int H, nkr;
-  uint16_t* img;
-  const float* alive;     // per computed row; 0: excluded row, its column is written as zeros
+  int H;
+  uint4* out;
+  const float* alive;     // per computed row; 0: excluded row, written as zeros
 };
 
-// Gradient GEMM over tile images (see grad_gemm_kernel).
+// Gradient GEMM (see grad_gemm_kernel).
 struct GradArgs {
-  const __bf16* slab; const __bf16* WsT;   // tile images
-  int nk_total;             // k-steps (blocks) per tile
+  const __bf16* slab;       // A: tile images
+  const __bf16* Bm;         // B: row-major [k_rows][H]
+  int nk_total;             // A blocks per tile, k_rows of B rounded up
+  int64_t k_rows;
   float* g;                 // [ksplit][g_rows][H]
   int64_t g_rows; int H;
   int64_t slab_row0;        // computed-row index of slab row 0
@@ -295,8 +299,7 @@ hipError_t launch_merge_stats(const MergeArgs& a, hipStream_t st);
 hipError_t launch_merge_single(const MergeSingleArgs& a, hipStream_t st);
 // grad_kernels.hip
 hipError_t grad_kernels_opt_in();
-hipError_t launch_wst_image(const void* W_s, void* img, int V, int H, int nk, int h_tiles, hipStream_t st);
-hipError_t launch_hst_image(const HstImageArgs& a, int h_tiles, hipStream_t st);
+hipError_t launch_hs_gather(const HsGatherArgs& a, int64_t rows, hipStream_t st);
 hipError_t launch_combine(bool transposed, bool sampled, const CombineArgs& a, int row_tiles, hipStream_t st);
 hipError_t launch_grad_gemm(const GradArgs& a, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t st);

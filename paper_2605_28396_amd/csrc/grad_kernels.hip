@@ -13,44 +13,13 @@
 namespace adwin {
 
 // ---------------------------------------------------------------------------------------
-// Tile images.  Both operands of the gradient GEMM live in memory as the exact LDS images
+// Tile images.  The A operand of the gradient GEMM lives in memory as the exact LDS images
 // of its k-steps: block (tile, kt) is 256 rows x 64 k-entries = 32 KiB, row r at r * 128 B,
 // its 16-byte chunk c (k-entries 8 c .. 8 c + 7) at chunk position c ^ ((r >> 1) & 7).
-// Blocks of one tile are consecutive in kt, so a workgroup streams each operand as one
-// sequential run and every wave-load moves 1 KiB of consecutive bytes.
+// Blocks of one tile are consecutive in kt, so a workgroup streams the operand as one
+// sequential run and every wave-load moves 1 KiB of consecutive bytes.  The B operand is read
+// from its row-major rows (one row per k-entry) and transposed on the way out of the LDS.
 // ---------------------------------------------------------------------------------------
-
-// element offset of (row r of the tile, k-entry k of the k-step) inside a block
-__device__ __forceinline__ int img_elem(int r, int k) {
-  return r * kBK + ((((k >> 3) ^ (r >> 1)) & 7) << 3) + (k & 7);
-}
-
-// W_s [V, H] -> images of W_s^T: tile = 256 hidden columns, k = vocabulary (zero beyond V).
-// One workgroup per (k-step, hidden tile): reads 64 rows of W_s, writes one block.
-__global__ __launch_bounds__(256) void wst_image_kernel(const uint16_t* __restrict__ W,
-                                                        uint16_t* __restrict__ img, int V, int H,
-                                                        int nk) {
-  __shared__ uint16_t tile[kBK][kGradTile + 2];
-  const int kt = blockIdx.x, ht = blockIdx.y;
-  const int tid = threadIdx.x;
-  for (int i = 0; i < kBK; ++i) {
-    const int v = kt * kBK + i, h = ht * kGradTile + tid;
-    tile[i][tid] = (v < V && h < H) ? W[(int64_t)v * H + h] : (uint16_t)0;
-  }
-  __syncthreads();
-  uint16_t* blk = img + ((int64_t)ht * nk + kt) * kImgElems;
-  // thread -> (row r, chunk position): 2048 chunks of 8 entries, 8 per thread
-  for (int q = tid; q < kGradTile * 8; q += 256) {
-    const int r = q >> 3, pos = q & 7, c = pos ^ ((r >> 1) & 7);
-    uint16_t w[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = tile[c * 8 + e][r];
-    uint4 o;
-    o.x = w[0] | ((uint32_t)w[1] << 16); o.y = w[2] | ((uint32_t)w[3] << 16);
-    o.z = w[4] | ((uint32_t)w[5] << 16); o.w = w[6] | ((uint32_t)w[7] << 16);
-    *(uint4*)(blk + q * 8) = o;
-  }
-}
 
 // ---------------------------------------------------------------------------------------
 // Combine.  Once a slab's rows have their mu (all strips merged), the two stored factors
@@ -177,37 +146,31 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   }
 }
 
-// Tile images of the transpose of the student hidden states of one slab, the B operand of
-// the head-weight GEMMs: image row = hidden column (tiles of 256), k = slab row; entry =
-// h_s[row_idx[r0 + r]][h] (zero beyond H).  One workgroup per (k-step of 64 rows, hidden tile).
-
-__global__ __launch_bounds__(256) void hst_image_kernel(HstImageArgs a) {
-  __shared__ uint16_t tile[kBK][kGradTile + 2];
-  const int kr = blockIdx.x, ht = blockIdx.y, tid = threadIdx.x;
-  for (int i = 0; i < kBK; ++i) {
-    const int64_t r = a.row0 + (int64_t)kr * kBK + i;
-    const int h = ht * kGradTile + tid;
-    // an excluded row carries weight 0 in the other operand; its own entries (possibly inf or
-    // NaN) must not meet that 0 in the product
-    tile[i][tid] = (h < a.H && a.alive[r] != 0.f) ? a.h_s[(int64_t)a.row_idx[r] * a.H + h] : (uint16_t)0;
-  }
-  __syncthreads();
-  uint16_t* blk = a.img + ((int64_t)ht * a.nkr + kr) * kImgElems;
-  for (int q = tid; q < kGradTile * 8; q += 256) {
-    const int r = q >> 3, pos = q & 7, c = pos ^ ((r >> 1) & 7);
-    uint4 o;
-    o.x = tile[c * 8 + 0][r] | ((uint32_t)tile[c * 8 + 1][r] << 16);
-    o.y = tile[c * 8 + 2][r] | ((uint32_t)tile[c * 8 + 3][r] << 16);
-    o.z = tile[c * 8 + 4][r] | ((uint32_t)tile[c * 8 + 5][r] << 16);
-    o.w = tile[c * 8 + 6][r] | ((uint32_t)tile[c * 8 + 7][r] << 16);
-    *(uint4*)(blk + q * 8) = o;
-  }
+// The student hidden states of one slab, the B operand of the head-weight GEMMs: row r =
+// h_s[row_idx[row0 + r]], zeros for an excluded row (it carries weight 0 in the other operand;
+// its own entries, possibly inf or NaN, must not meet that 0 in the product).  One wave per row.
+__global__ __launch_bounds__(256) void hs_gather_kernel(HsGatherArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), r = a.row0 + k;   // rows: a multiple of 4
+  const bool alive = a.alive[r] != 0.f;
+  const uint4* src = a.h_s + (int64_t)a.row_idx[r] * (a.H >> 3);
+  uint4* dst = a.out + k * (a.H >> 3);
+  const uint4 zero = {0u, 0u, 0u, 0u};
+  for (int q = lane; q < (a.H >> 3); q += 64) dst[q] = alive ? src[q] : zero;
 }
 
 // ---------------------------------------------------------------------------------------
 // Pass 3: g[r][h] = sum_v dz[r][v] W_s[v][h].  256 x 256 output tile, 2 x 2 waves of
-// 128 x 128.  A = slab rows (i = row), B = rows of W_s^T (j = hidden column, contiguous in
-// g).  The k-steps (one 32 KiB block of each operand) go through five block buffers in the
+// 128 x 128.  A = slab rows (i = row), B = columns of W_s (j = hidden column, contiguous in
+// g).  B stays row-major: a k-step stages 64 rows of W_s x 256 columns, 512 B of a row at a time,
+// and the fragments (one column, 8 consecutive rows) come out of the LDS by transposing reads
+// (ds_read_b64_tr_b16: each group of 16 lanes reads a 4 x 16 block and lane i receives its
+// column i).  No transposed copy of W_s exists: building one took 730 us of every call at
+// V = 151,936, H_s = 2048 (1.25 GB) and a workspace of the size of W_s.
+// Row v of a staged block lies at 512 v, its 16-byte chunk c (columns 8 c .. 8 c + 7) at chunk
+// position c ^ (4 (v & 3)): the four rows that 16 lanes read then fall on four different
+// 64-byte quarters of the 256 bytes that the 64 banks cover.
+// The k-steps (one 32 KiB block of each operand) go through five block buffers in the
 // LDS, three for B and two for A, by direct global->LDS loads.  Per k-step a wave issues
 // its 16 wave-loads of the k-step after next in the shadow of MFMAs (see grad_kstep), so
 // that they have a k-step or more (upwards of 2000 matrix-pipe cycles) to land.  The one
@@ -221,6 +184,21 @@ __global__ __launch_bounds__(256) void hst_image_kernel(HstImageArgs a) {
 constexpr int kGradRing3 = 3;
 constexpr int kGradRing2Off = kGradRing3 * kImgBytes;         // the ring of two follows
 constexpr int kGradLds = (kGradRing3 + 2) * kImgBytes;        // 160 KiB
+constexpr int kGradRowBytes = kGradTile * 2;                  // a staged row of B: 256 columns
+constexpr int kGradSubBytes = 16 * kGradRowBytes;             // the 16 rows of a sub-step
+
+// A B fragment: 8 consecutive rows (k-entries) of one column, as two transposing reads of four.
+// addr: the lane's address in rows 0..3 of its half of sub-step 0; OFF: the sub-step.
+template <int OFF>
+__device__ __forceinline__ bf16x8 lds_frag_tr(uint32_t addr) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  typedef __attribute__((address_space(3))) s16x4* Ptr;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Ptr)(uintptr_t)addr + OFF / 8);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Ptr)(uintptr_t)addr + (OFF + 4 * kGradRowBytes) / 8);
+  const s16x8 f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, f);
+}
 
 // LOADS: in k-step s the B block of k-step s + 2 is loaded in sub-steps 1 and 2, four
 // wave-loads behind the last MFMAs of each (`early`: into the third buffer of its ring, which
@@ -242,37 +220,45 @@ __device__ __forceinline__ void grad_kstep(f32x16 (&acc)[4][4], bf16x8 (&fa)[2][
                                            uint32_t& r_a, uint32_t& r_b, uint32_t a_begin, uint32_t a_end,
                                            uint32_t b_begin, uint32_t b_end, const uint32_t (&swA)[4],
                                            const uint32_t (&swB)[4], const uint32_t (&voffd)[8],
+                                           const uint32_t (&voffb)[8], uint32_t b_step,
                                            uint32_t& pa_lo, uint32_t& pa_hi, uint32_t& pb_lo, uint32_t& pb_hi) {
   uint32_t r_a_nx = 0, r_b_nx = 0, r_b_wr = 0;
-  uint32_t xa = 0, xb = 0;      // the lane's LDS addresses of its first A and B fragment of a sub-step
+  uint32_t xa = 0;              // the lane's LDS address of its first A fragment of a sub-step
+  uint32_t xb[4];               // ... and of its part of the four B fragments of a sub-step
 #define ADWIN_FENCE __builtin_amdgcn_sched_barrier(0);
 #define ADWIN_MM(KK, I, J)                                                                    \
   acc[I][J] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[(KK) & 1][I], fb[(KK) & 1][J],       \
                                                       acc[I][J], 0, 0, 0);                    \
   ADWIN_FENCE
   // side operation M (0..15) in the shadow of MFMA M of sub-step KK: fragment reads of the
-  // next sub-step (from this step's buffers, in sub-step 3 from the next step's), the ring and
+  // next sub-step (from this step's buffers, in sub-step 3 from the next step's; a B fragment is
+  // two transposing reads, k-entries 0..3 and 4..7 of the lane's eight), the ring and
   // address arithmetic (sub-step 0), then (sub-steps 1, 2 and 3) the wave-loads of the k-step
   // after next: 4 KiB groups d = 0..7 of the early block, then of the late block
 #define ADWIN_SIDE(KK, M)                                                                           \
   if constexpr ((M) < 8 && ((KK) < 3 || !LAST)) {                                                   \
+    constexpr int ad_n = ((KK) + 1) & 3, ad_f = ((M) >> 1) & 3;                                     \
     if constexpr ((M) == 0) {                                                                       \
-      xa = ((KK) < 3 ? r_a : r_a_nx) + swA[((KK) + 1) & 3];                                         \
-      xb = ((KK) < 3 ? r_b : r_b_nx) + swB[((KK) + 1) & 3];                                         \
-      asm volatile("" : "+v"(xa), "+v"(xb));                                                        \
+      xa = ((KK) < 3 ? r_a : r_a_nx) + swA[ad_n];                                                   \
+      asm volatile("" : "+v"(xa));                                                                  \
     }                                                                                               \
-    if constexpr (((M) & 1) == 0)                                                                   \
-      fa[((KK) + 1) & 1][((M) >> 1) & 3] = lds_frag(xa)[(((M) >> 1) & 3) * 32 * kRowBytes / 16]; \
-    else                                                                                            \
-      fb[((KK) + 1) & 1][((M) >> 1) & 3] = lds_frag(xb)[(((M) >> 1) & 3) * 32 * kRowBytes / 16]; \
+    if constexpr (((M) & 1) == 0) {                                                                 \
+      fa[ad_n & 1][ad_f] = lds_frag(xa)[ad_f * 32 * kRowBytes / 16];                                \
+      if constexpr ((KK) == 0 || (KK) == 3) {                                                       \
+        xb[ad_f] = ((KK) < 3 ? r_b : r_b_nx) + swB[ad_f];                                           \
+        asm volatile("" : "+v"(xb[ad_f]));                                                          \
+      }                                                                                             \
+    } else {                                                                                        \
+      fb[ad_n & 1][ad_f] = lds_frag_tr<ad_n * kGradSubBytes>(xb[ad_f]);                             \
+    }                                                                                               \
     if constexpr ((KK) == 0 && (M) == 0 && !LAST) r_b_nx = ring_next<kImgBytes>(r_b, b_begin, b_end); \
     if constexpr ((KK) == 0 && (M) == 1 && !LAST) r_a_nx = ring_next<kImgBytes>(r_a, a_begin, a_end); \
     if constexpr ((KK) == 0 && (M) == 2 && LOADS) r_b_wr = ring_next<kImgBytes>(r_b_nx, b_begin, b_end); \
-    if constexpr ((KK) == 0 && (M) == 3 && LOADS) addr_advance<kImgBytes>(pb_lo, pb_hi);            \
+    if constexpr ((KK) == 0 && (M) == 3 && LOADS) addr_advance(pb_lo, pb_hi, b_step);               \
     if constexpr ((KK) == 0 && (M) == 4 && LOADS) addr_advance<kImgBytes>(pa_lo, pa_hi);            \
     ADWIN_FENCE                                                                                     \
   } else if constexpr (((KK) == 1 || (KK) == 2) && (M) >= 12 && LOADS) {                            \
-    dma16_at<(((KK) - 1) * 4 + (M) - 12) * 4096>(r_b_wr, voffd[(((KK) - 1) * 4 + (M) - 12) & 7], addr_of(pb_lo, pb_hi)); \
+    dma16_at<(((KK) - 1) * 4 + (M) - 12) * 4096>(r_b_wr, voffb[(((KK) - 1) * 4 + (M) - 12) & 7], addr_of(pb_lo, pb_hi)); \
     ADWIN_FENCE                                                                                     \
   } else if constexpr ((KK) == 3 && (M) >= 8 && LOADS) {                                            \
     dma16_at<((M) - 8) * 4096>(r_a, voffd[((M) - 8) & 7], addr_of(pa_lo, pa_hi));                         \
@@ -320,8 +306,11 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
   const int split = vid / tiles;
   vid -= split * tiles;
   const int rt = vid / a.h_tiles, ht = vid % a.h_tiles;
-  const int k_begin = (int)((int64_t)a.nk_total * split / a.ksplit);
-  const int k_end = (int)((int64_t)a.nk_total * (split + 1) / a.ksplit);
+  // k-steps that hold rows of B: the A blocks are padded to whole vocabulary tiles, of which the
+  // last k-step may lie beyond k_rows altogether (its A entries are exact zeros)
+  const int nk_rows = (int)((a.k_rows + kBK - 1) / kBK);
+  const int k_begin = (int)((int64_t)nk_rows * split / a.ksplit);
+  const int k_end = (int)((int64_t)nk_rows * (split + 1) / a.ksplit);
   const int nk = k_end - k_begin;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
@@ -334,9 +323,29 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
     asm volatile("" : "+v"(voffd[d]));   // kept in registers, not recomputed at every load
   }
   const char* sA = (const char*)a.slab + ((int64_t)rt * a.nk_total + k_begin) * kImgBytes;
-  const char* sB = (const char*)a.WsT + ((int64_t)ht * a.nk_total + k_begin) * kImgBytes;
+  // the B rows: wave-load d moves rows 2 wave + 8 d and the next, lane l the chunk that belongs at
+  // position l % 32 of row l / 32 of the two.  Columns at or beyond H (their output does not
+  // exist) re-read the row's first chunk; rows at or beyond k_rows (their A entries are zero)
+  // re-read its last row.
+  const uint32_t ldb = (uint32_t)a.H * 2u, b_step = kBK * ldb;
+  const char* sB = (const char*)a.Bm + (int64_t)k_begin * b_step + ht * kGradRowBytes;
+  uint32_t voffb[8];
+  auto b_rows = [&](int kt) __attribute__((always_inline)) {
+    const int row = 2 * wave + (lane >> 5);
+    int c = (lane & 31) ^ ((row & 3) << 2);
+    if (ht * kGradTile + c * 8 >= a.H) c = 0;
+    const int64_t left = a.k_rows - (int64_t)kt * kBK;      // >= 1
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+      int v = row + 8 * d;
+      if (v >= left) v = (int)left - 1;
+      voffb[d] = (uint32_t)v * ldb + (uint32_t)c * 16u;
+      asm volatile("" : "+v"(voffb[d]));
+    }
+  };
+  b_rows(k_begin);
   const uint32_t ldsw = lds0 + (uint32_t)wave * 1024u;
-  // the ring of three (offset 0) holds the W_s^T blocks, the ring of two the slab blocks
+  // the ring of three (offset 0) holds the B blocks, the ring of two the slab blocks
   const uint32_t b_begin = ldsw, b_end = ldsw + kGradRing3 * kImgBytes;
   const uint32_t a_begin = ldsw + kGradRing2Off, a_end = a_begin + 2 * kImgBytes;
   const std::make_integer_sequence<int, 8> all8{};
@@ -351,7 +360,7 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
 
   if (nk > 0) {
     // first the blocks of k-step 0, then its first fragments
-    dma_block(b_begin, voffd, sB, all8);
+    dma_block(b_begin, voffb, sB, all8);
     dma_block(a_begin, voffd, sA, all8);
     wait_vm<0>();
     __syncthreads();
@@ -364,31 +373,45 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
       for (int kk = 0; kk < 4; ++kk) {
         const uint32_t x = rowoff + (uint32_t)(((kk * 2 + half) ^ key) << 4);
         swA[kk] = x + (uint32_t)(wm * 128 * kRowBytes);
-        swB[kk] = x + (uint32_t)(wn * 128 * kRowBytes);
       }
+      // B fragment fn: the lane reads row q = (lane % 16) / 4 (+ 8 for the upper half of the wave) and
+      // 8 bytes of columns 128 wn + 32 fn + 16 ((lane / 16) % 2) + 4 (lane % 4); the chunk swizzle
+      // moves the fragment's 64 bytes
+      const int q = (lane & 15) >> 2;
+      const uint32_t rowb = (uint32_t)(8 * half + q) * kGradRowBytes - (uint32_t)wave * 1024u +
+                            (uint32_t)(wn * 256 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+#pragma unroll
+      for (int fn = 0; fn < 4; ++fn) swB[fn] = rowb + (uint32_t)((fn ^ q) << 6);
     }
     uint32_t r_a = a_begin, r_b = b_begin;     // k-step s reads B buffer s % 3 and A buffer s % 2
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       fa[0][i] = lds_frag(r_a + swA[0])[i * 32 * kRowBytes / 16];
-      fb[0][i] = lds_frag(r_b + swB[0])[i * 32 * kRowBytes / 16];
+      fb[0][i] = lds_frag_tr<0>(r_b + swB[i]);
     }
     // blocks of k-step 1 (k-step s of the loop loads those of k-step s + 2)
     uint64_t pa = (uint64_t)sA, pb = (uint64_t)sB;
     if (nk > 1) {
-      pa += kImgBytes; pb += kImgBytes;
-      dma_block(b_begin + kImgBytes, voffd, (const char*)pb, all8);
+      pa += kImgBytes; pb += b_step;
+      if (nk == 2) b_rows(k_end - 1);
+      dma_block(b_begin + kImgBytes, voffb, (const char*)pb, all8);
       dma_block(a_begin + kImgBytes, voffd, (const char*)pa, all8);
     }
     uint32_t pa_lo = (uint32_t)pa, pa_hi = (uint32_t)(pa >> 32), pb_lo = (uint32_t)pb, pb_hi = (uint32_t)(pb >> 32);
     int s = 0;
-    for (; s + 2 < nk; ++s)
-      grad_kstep<true, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd,
+    for (; s + 3 < nk; ++s)
+      grad_kstep<true, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
                               pa_lo, pa_hi, pb_lo, pb_hi);
+    if (s + 2 < nk) {           // the step that loads the last k-step, which may hold fewer rows
+      b_rows(k_end - 1);
+      grad_kstep<true, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
+                              pa_lo, pa_hi, pb_lo, pb_hi);
+      ++s;
+    }
     if (s + 1 < nk)
-      grad_kstep<false, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd,
+      grad_kstep<false, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
                                pa_lo, pa_hi, pb_lo, pb_hi);
-    grad_kstep<false, true>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd,
+    grad_kstep<false, true>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
                             pa_lo, pa_hi, pb_lo, pb_hi);
   }
   float* g = a.g + (int64_t)split * a.g_rows * a.H;
@@ -594,14 +617,8 @@ hipError_t grad_kernels_opt_in() {
                              kGradLds);
 }
 
-hipError_t launch_wst_image(const void* W_s, void* img, int V, int H, int nk, int h_tiles, hipStream_t st) {
-  wst_image_kernel<<<dim3((unsigned)nk, (unsigned)h_tiles), 256, 0, st>>>((const uint16_t*)W_s, (uint16_t*)img,
-                                                                          V, H, nk);
-  return hipGetLastError();
-}
-
-hipError_t launch_hst_image(const HstImageArgs& a, int h_tiles, hipStream_t st) {
-  hst_image_kernel<<<dim3((unsigned)a.nkr, (unsigned)h_tiles), 256, 0, st>>>(a);
+hipError_t launch_hs_gather(const HsGatherArgs& a, int64_t rows, hipStream_t st) {
+  hs_gather_kernel<<<(unsigned)(rows / 4), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
