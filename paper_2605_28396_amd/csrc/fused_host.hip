@@ -16,6 +16,7 @@ namespace adwin {
 struct FusedLayout {
   bool use_dma;      // logit passes staged by direct global->LDS loads
   bool single;       // single-sweep scheme (needs use_dma)
+  bool direct_w;     // ... whose W tiles come from the row-major weights, not from images
   size_t o_wt_img, o_ws_img, o_ht_img, o_hs_img;   // tile images of the logit operands (use_dma)
   size_t o_ref_t2, o_delta, o_invz, o_mu0t;
   int strips, ksplit;
@@ -111,6 +112,16 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
   return best;
 }
 
+// Whether the logit passes stage their W tiles from the row-major weights rather than from tile
+// images.  The images cost a pass over both weights (0.75 ms at V = 151,936, H = 2048 + 4096); a
+// tile pair staged from them is faster by about the same amount at every hidden size (eight
+// 128-byte pieces per wave-load against 1 KiB in one piece: 0.4 to 2 % of a sweep).  The line
+// lies where the two meet.  us per call, direct against images: H = 2048 + 4096, 64 token tiles
+// 35620 / 35884, 128 tiles 70313 / 70595, 256 tiles 140609 / 140325; H = 256 + 384, 16 tiles
+// 2359 / 2387, 64 tiles 9396 / 9357; H = 1024 + 1024 (V = 32,776), 16 tiles 1062 / 1112, 64 tiles
+// 3800 / 3781.
+static bool stage_w_directly(int64_t n_tiles, int H_s, int H_t) { return n_tiles * 40 <= H_s + H_t; }
+
 static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) {
   FusedLayout L;
   const int64_t n_pad = hp.n_pad > 0 ? hp.n_pad : kTileTokens;
@@ -150,8 +161,9 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   L.o_mu = take(sizeof(float) * (size_t)n_pad);
   L.o_klr = take(sizeof(float) * (size_t)n_pad);
   L.o_rownorm = take(sizeof(float) * (size_t)n_pad);
-  L.o_wt_img = take(L.use_dma ? 2 * (size_t)L.Vp * (size_t)p->H_t : 0);
-  L.o_ws_img = take(L.use_dma ? 2 * (size_t)L.Vp * (size_t)p->H_s : 0);
+  L.direct_w = stage_w_directly(n_pad / kTileTokens, p->H_s, p->H_t);
+  L.o_wt_img = take(L.use_dma && !L.direct_w ? 2 * (size_t)L.Vp * (size_t)p->H_t : 0);
+  L.o_ws_img = take(L.use_dma && !L.direct_w ? 2 * (size_t)L.Vp * (size_t)p->H_s : 0);
   L.o_ht_img = take(L.use_dma ? 2 * (size_t)n_pad * (size_t)p->H_t : 0);
   L.o_hs_img = take(L.use_dma ? 2 * (size_t)n_pad * (size_t)p->H_s : 0);
   // statistics-only calls (no output depends on the gradients) need neither the slab nor g
@@ -328,11 +340,13 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       // tile images of the logit operands: vocabulary tiles of 128 rows (zero beyond V),
       // token tiles of 256 computed rows gathered through row_idx
       RowImageArgs ia;
-      ia.row_idx = nullptr; ia.n_rows = p->V; ia.th = kTileVocab; ia.permute = 1;
-      ia.src = (const uint4*)p->W_t; ia.img = (uint4*)(ws + L.o_wt_img); ia.H = p->H_t; ia.nk = p->H_t / kBK;
-      ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
-      ia.src = (const uint4*)p->W_s; ia.img = (uint4*)(ws + L.o_ws_img); ia.H = p->H_s; ia.nk = p->H_s / kBK;
-      ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
+      if (!L.direct_w) {
+        ia.row_idx = nullptr; ia.n_rows = p->V; ia.th = kTileVocab; ia.permute = 1;
+        ia.src = (const uint4*)p->W_t; ia.img = (uint4*)(ws + L.o_wt_img); ia.H = p->H_t; ia.nk = p->H_t / kBK;
+        ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
+        ia.src = (const uint4*)p->W_s; ia.img = (uint4*)(ws + L.o_ws_img); ia.H = p->H_s; ia.nk = p->H_s / kBK;
+        ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
+      }
       ia.row_idx = pl.row_idx; ia.n_rows = n_pad; ia.th = kTileTokens; ia.permute = 0;
       ia.src = (const uint4*)p->h_t; ia.img = (uint4*)(ws + L.o_ht_img); ia.H = p->H_t; ia.nk = p->H_t / kBK;
       ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)n_tiles, stream));
@@ -354,7 +368,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     la.tg = env_int("ADWIN_TG", 4);      // tuning override
     la.Wt_img = (const char*)(ws + L.o_wt_img); la.Ws_img = (const char*)(ws + L.o_ws_img);
     la.ht_img = (const char*)(ws + L.o_ht_img); la.hs_img = (const char*)(ws + L.o_hs_img);
-    la.heavy = heavy;
+    la.heavy = heavy; la.direct_w = L.direct_w;
     MergeArgs m;
     m.part = la.part; m.strips = L.strips; m.n_pad = n_pad; m.n_rows = hp.n_rows;
     m.row_idx = pl.row_idx;

@@ -158,6 +158,7 @@ struct LogitPassArgs {
   const float* zy_t; const int32_t* yid;
   // direct-to-LDS kernel: tile images of the four operands (see row_image_kernel)
   const char* Wt_img; const char* Ws_img; const char* ht_img; const char* hs_img;
+  bool direct_w;               // stage W from W_s / W_t themselves; there are no W images
   HeavyList heavy;             // second sweep of the two-sweep scheme: entries taken out of dz
 };
 

@@ -486,12 +486,13 @@ constexpr int kImgBBytes = kTileTokens * kRowBytes;   // 32 KiB: one h block
 // Wave-load I (0..11) of this wave for one stage: KiB (wave + 4 I) of the A block, then of
 // the B block; lane l moves bytes 16 l .. 16 l + 15 of that KiB.  lds_wave = the stage's LDS
 // address + 1024 wave; voffw[j] = 16 lane + 1024 (wave + 4 j): the wave's part of both addresses
-// is folded into operands that are set up once, the rest is a literal.
+// is folded into operands that are set up once, the rest is a literal.  voffa: the same for the
+// A block, or the lane's offsets in the row-major W (direct staging).
 template <int I>
-__device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voffw)[8], const char* sA,
-                                        const char* sB) {
+__device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voffa)[4], const uint32_t (&voffw)[8],
+                                        const char* sA, const char* sB) {
   if constexpr (I < kTileVocab / 32)
-    dma16_at<4 * I * 1024>(lds_wave, voffw[I], sA);
+    dma16_at<4 * I * 1024>(lds_wave, voffa[I], sA);
   else
     dma16_at<(kTileVocab / 8 + 4 * (I - kTileVocab / 32)) * 1024>(lds_wave, voffw[I - kTileVocab / 32], sB);
 }
@@ -516,11 +517,13 @@ __device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voff
 // return that of the next k-step; swA/swB = the lane's fragment offsets from such an address
 // per sub-step; (a_lo, a_hi), (b_lo, b_hi) = the blocks that the previous k-step loaded, on
 // return those that this one loaded.
-template <bool LAST, bool FRESH, int RELAXED>
+// A_STEP: bytes from one A block to the next (a W image's block, or a row-major W's 64 entries).
+template <bool LAST, bool FRESH, int RELAXED, int A_STEP>
 __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][2], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][2],
                                             uint32_t& r_rd, uint32_t ring_begin, uint32_t ring_end,
                                             const uint32_t (&swA)[4], const uint32_t (&swB)[4],
-                                            const uint32_t (&voffw)[8], uint32_t& a_lo, uint32_t& a_hi,
+                                            const uint32_t (&voffa)[4], const uint32_t (&voffw)[8],
+                                            uint32_t& a_lo, uint32_t& a_hi,
                                             uint32_t& b_lo, uint32_t& b_hi, bool relaxed = false) {
   static_assert(9 + RELAXED <= 63, "the wait count has six bits");
   const f32x16 kZeroTile = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -532,7 +535,7 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][2], bf16x8 (&fa)[2]
   acc[FMI][FNI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[(KK) & 1][FMI], fb[(KK) & 1][FNI], \
                                                           (FRESH && (KK) == 0) ? kZeroTile : acc[FMI][FNI], 0, 0, 0); \
   ADWIN_FENCE
-#define ADWIN_DMA(I) dma_one<I>(r_wr, voffw, addr_of(a_lo, a_hi), addr_of(b_lo, b_hi)); ADWIN_FENCE
+#define ADWIN_DMA(I) dma_one<I>(r_wr, voffa, voffw, addr_of(a_lo, a_hi), addr_of(b_lo, b_hi)); ADWIN_FENCE
   // sub-step KK: 8 MFMAs; reads of the next sub-step's fragments from slot R when READ; H0..H3:
   // bookkeeping in the shadows of the first four MFMAs.  xa, xb: the lane's LDS addresses of its
   // first A and B fragment, formed once (and kept from being re-associated with the fragments'
@@ -558,7 +561,7 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][2], bf16x8 (&fa)[2]
   ADWIN_FENCE
   ADWIN_SUB(0, true, r_rd, 0, 1, 2,
             { r_nx = ring_next<kLogitStage>(r_rd, ring_begin, ring_end); }, { r_wr = ring_next<kLogitStage>(r_nx, ring_begin, ring_end); },
-            { addr_advance<kImgABytes>(a_lo, a_hi); }, { addr_advance<kImgBBytes>(b_lo, b_hi); })
+            { addr_advance<A_STEP>(a_lo, a_hi); }, { addr_advance<kImgBBytes>(b_lo, b_hi); })
   ADWIN_SUB(1, true, r_rd, 3, 4, 5, {}, {}, {}, {})
   ADWIN_SUB(2, true, r_rd, 6, 7, 8, {}, {}, {}, {})
   if constexpr (!LAST) {
@@ -582,7 +585,11 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][2], bf16x8 (&fa)[2]
 #undef ADWIN_FENCE
 }
 
-template <int MODE>
+// DIRECT: the W tiles are staged from the row-major weights instead of their images: wave-load I
+// takes its 8 rows' 128 bytes from 8 rows of W, the lane offsets following the image's row
+// permutation and chunk swizzle, so that the LDS holds the same bytes; rows beyond V repeat the
+// last one (their logits are masked like the image's zero rows).
+template <int MODE, bool DIRECT>
 __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -617,8 +624,40 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   // blocks of this token tile (fixed) and of vocabulary tile vt, teacher and student
   const char* sHt = a.ht_img + (int64_t)tt * nk_t * kImgBBytes;
   const char* sHs = a.hs_img + (int64_t)tt * nk_s * kImgBBytes;
-  auto blocks_wt = [&](int vt) { return a.Wt_img + (int64_t)vt * nk_t * kImgABytes; };
-  auto blocks_ws = [&](int vt) { return a.Ws_img + (int64_t)vt * nk_s * kImgABytes; };
+  constexpr int kAStep = DIRECT ? kRowBytes : kImgABytes;
+  uint32_t voffa[4];
+  // lane offsets of the wave's four A loads for the rows of vocabulary tile vt of a [V, H] operand:
+  // tile row 8 wave + 32 I + lane / 8 holds entry 32 I + e0 (entry_of_tile_row)
+  const int e0 = 16 * (lane >> 5) + 4 * wave + ((lane >> 3) & 3);
+  const uint32_t chunk = (uint32_t)((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) * 16u;
+  const uint32_t row0_t = (uint32_t)e0 * (uint32_t)a.H_t * 2u + chunk, row0_s = (uint32_t)e0 * (uint32_t)a.H_s * 2u + chunk;
+  auto rows_w = [&](int vt, int H, uint32_t row0) __attribute__((always_inline)) {
+    if constexpr (DIRECT) {
+      const int left = a.V - vt * kTileVocab;
+      if (left >= kTileVocab) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) voffa[i] = row0 + (uint32_t)(i * 64 * H);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int v = 32 * i + e0 < left ? 32 * i + e0 : left - 1;
+          voffa[i] = (uint32_t)v * ((uint32_t)H * 2u) + chunk;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(voffa[i]));
+    }
+  };
+  if constexpr (!DIRECT) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) voffa[i] = voffw[i];
+  }
+  auto blocks_wt = [&](int vt) {
+    return DIRECT ? (const char*)a.W_t + (int64_t)vt * kTileVocab * a.H_t * 2 : a.Wt_img + (int64_t)vt * nk_t * kImgABytes;
+  };
+  auto blocks_ws = [&](int vt) {
+    return DIRECT ? (const char*)a.W_s + (int64_t)vt * kTileVocab * a.H_s * 2 : a.Ws_img + (int64_t)vt * nk_s * kImgABytes;
+  };
 
   LaneStats st;
   LaneSums sm;
@@ -660,7 +699,7 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   uint32_t a_lo, a_hi, b_lo, b_hi;
 #define ADWIN_SET_BLOCKS(A, B)                                             \
   {                                                                        \
-    const uint64_t pa = (uint64_t)(A) - kImgABytes, pb = (uint64_t)(B) - kImgBBytes; \
+    const uint64_t pa = (uint64_t)(A) - kAStep, pb = (uint64_t)(B) - kImgBBytes; \
     a_lo = (uint32_t)pa; a_hi = (uint32_t)(pa >> 32);                      \
     b_lo = (uint32_t)pb; b_hi = (uint32_t)(pb >> 32);                      \
   }
@@ -671,27 +710,30 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
       if (!ld_student) {                                                   \
         ld_student = true; ld_lim = nk_s;                                  \
         ADWIN_SET_BLOCKS(blocks_ws(ld_vt), sHs)                            \
+        rows_w(ld_vt, a.H_s, row0_s);                                      \
       } else {                                                             \
         ld_student = false; ld_lim = nk_t;                                 \
         ld_vt = ld_vt + 1 < vt_end ? ld_vt + 1 : vt_begin;                 \
         ADWIN_SET_BLOCKS(blocks_wt(ld_vt), sHt)                            \
+        rows_w(ld_vt, a.H_t, row0_t);                                      \
       }                                                                    \
     }                                                                      \
   }
   ADWIN_SET_BLOCKS(blocks_wt(vt_begin), sHt)
+  rows_w(vt_begin, a.H_t, row0_t);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const uint32_t dst = ring_begin + (uint32_t)i * kLogitStage;
-    addr_advance<kImgABytes>(a_lo, a_hi);
+    addr_advance<kAStep>(a_lo, a_hi);
     addr_advance<kImgBBytes>(b_lo, b_hi);
     const char* ldA = addr_of(a_lo, a_hi);
     const char* ldB = addr_of(b_lo, b_hi);
-    dma_one<0>(dst, voffw, ldA, ldB); dma_one<1>(dst, voffw, ldA, ldB);
-    dma_one<2>(dst, voffw, ldA, ldB); dma_one<3>(dst, voffw, ldA, ldB);
-    dma_one<4>(dst, voffw, ldA, ldB); dma_one<5>(dst, voffw, ldA, ldB);
-    dma_one<6>(dst, voffw, ldA, ldB); dma_one<7>(dst, voffw, ldA, ldB);
-    dma_one<8>(dst, voffw, ldA, ldB); dma_one<9>(dst, voffw, ldA, ldB);
-    dma_one<10>(dst, voffw, ldA, ldB); dma_one<11>(dst, voffw, ldA, ldB);
+    dma_one<0>(dst, voffa, voffw, ldA, ldB); dma_one<1>(dst, voffa, voffw, ldA, ldB);
+    dma_one<2>(dst, voffa, voffw, ldA, ldB); dma_one<3>(dst, voffa, voffw, ldA, ldB);
+    dma_one<4>(dst, voffa, voffw, ldA, ldB); dma_one<5>(dst, voffa, voffw, ldA, ldB);
+    dma_one<6>(dst, voffa, voffw, ldA, ldB); dma_one<7>(dst, voffa, voffw, ldA, ldB);
+    dma_one<8>(dst, voffa, voffw, ldA, ldB); dma_one<9>(dst, voffa, voffw, ldA, ldB);
+    dma_one<10>(dst, voffa, voffw, ldA, ldB); dma_one<11>(dst, voffa, voffw, ldA, ldB);
     ADWIN_COUNT_LOADS()
   }
   // 16-byte stores a wave issues per tile in its epilogue, at the least (see sweep_kstep, RELAXED)
@@ -703,7 +745,7 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
                   __attribute__((always_inline)) {
     constexpr bool kLast = decltype(last_c)::value, kFresh = decltype(fresh_c)::value;
     constexpr int kRelaxed = decltype(relaxed_c)::value;
-    sweep_kstep<kLast, kFresh, kRelaxed>(acc, fa, fb, r_rd, ring_begin, ring_end, swA, swB, voffw,
+    sweep_kstep<kLast, kFresh, kRelaxed, kAStep>(acc, fa, fb, r_rd, ring_begin, ring_end, swA, swB, voffa, voffw,
                                          a_lo, a_hi, b_lo, b_hi, relaxed);
     ADWIN_COUNT_LOADS()
   };
@@ -934,14 +976,22 @@ hipError_t sweep_kernels_opt_in() {
   if (e != hipSuccess) return e;
   ADWIN_OPT_IN(logit_pass_kernel<false>, kLogitLds)
   ADWIN_OPT_IN(logit_pass_kernel<true>, kLogitLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeStats>, kDmaLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeDz>, kDmaLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeSingle>, kDmaLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeSingleDiag>, kDmaLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeSingleE2>, kDmaLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeSingleE2Diag>, kDmaLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeSingleFwd>, kDmaLds)
-  ADWIN_OPT_IN(logit_pass_dma_kernel<kModeSingleFwdDiag>, kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeDz, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeDz, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, false>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, true>), kDmaLds)
 #undef ADWIN_OPT_IN
   return hipSuccess;
 }
@@ -960,14 +1010,20 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStre
     return hipGetLastError();
   }
   switch (mode) {
-    case kModeStats: logit_pass_dma_kernel<kModeStats><<<grid, 256, kDmaLds, st>>>(a); break;
-    case kModeDz: logit_pass_dma_kernel<kModeDz><<<grid, 256, kDmaLds, st>>>(a); break;
-    case kModeSingle: logit_pass_dma_kernel<kModeSingle><<<grid, 256, kDmaLds, st>>>(a); break;
-    case kModeSingleDiag: logit_pass_dma_kernel<kModeSingleDiag><<<grid, 256, kDmaLds, st>>>(a); break;
-    case kModeSingleE2: logit_pass_dma_kernel<kModeSingleE2><<<grid, 256, kDmaLds, st>>>(a); break;
-    case kModeSingleE2Diag: logit_pass_dma_kernel<kModeSingleE2Diag><<<grid, 256, kDmaLds, st>>>(a); break;
-    case kModeSingleFwd: logit_pass_dma_kernel<kModeSingleFwd><<<grid, 256, kDmaLds, st>>>(a); break;
-    case kModeSingleFwdDiag: logit_pass_dma_kernel<kModeSingleFwdDiag><<<grid, 256, kDmaLds, st>>>(a); break;
+#define ADWIN_CASE(M)                                                                       \
+  case M:                                                                                   \
+    if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, kDmaLds, st>>>(a);          \
+    else logit_pass_dma_kernel<M, false><<<grid, 256, kDmaLds, st>>>(a);                    \
+    break;
+    ADWIN_CASE(kModeStats)
+    ADWIN_CASE(kModeDz)
+    ADWIN_CASE(kModeSingle)
+    ADWIN_CASE(kModeSingleDiag)
+    ADWIN_CASE(kModeSingleE2)
+    ADWIN_CASE(kModeSingleE2Diag)
+    ADWIN_CASE(kModeSingleFwd)
+    ADWIN_CASE(kModeSingleFwdDiag)
+#undef ADWIN_CASE
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

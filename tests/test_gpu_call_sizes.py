@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     (16648, 128, 320, [200, 57], [200, 57]),     # one row into the second token tile
     (16616, 320, 128, [700], [513]),             # three token tiles; a last half block that is all padding
     (4104, 256, 192, [900, 390], [900, 390]),    # six token tiles: a group of four and one of two
+    (4104, 128, 192, [2000], [2000]),            # eight token tiles, the most that stage W directly at 320 / 40
+    (4104, 128, 192, [2050], [2050]),            # ... and one more: tile images
     (4096, 128, 128, [2100], [2049]),            # nine token tiles, whole vocabulary tiles
 ])
 def test_few_rows_match_oracle(B, V, H_s, H_t, lens, win, estimator):  # noqa: F811
