@@ -120,7 +120,13 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
 // 35620 / 35884, 128 tiles 70313 / 70595, 256 tiles 140609 / 140325; H = 256 + 384, 16 tiles
 // 2359 / 2387, 64 tiles 9396 / 9357; H = 1024 + 1024 (V = 32,776), 16 tiles 1062 / 1112, 64 tiles
 // 3800 / 3781.
-static bool stage_w_directly(int64_t n_tiles, int H_s, int H_t) { return n_tiles * 40 <= H_s + H_t; }
+// The statistics-only sweep writes no factors, so its loads are a larger share of its time and the
+// images are worth 2.4 % of it (64 tiles, H = 2048 + 4096: 23.3 against 23.9 ms): `loads_bound`
+// moves the line to where that meets the 0.75 ms.  So does the diagnostics sweep that writes both
+// factors, whose direct form has no registers to spare.  134 tiles, statistics: 50.9 -> 50.4 ms.
+static bool stage_w_directly(int64_t n_tiles, int H_s, int H_t, bool loads_bound) {
+  return n_tiles * (loads_bound ? 72 : 40) <= H_s + H_t;
+}
 
 static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) {
   FusedLayout L;
@@ -161,7 +167,9 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   L.o_mu = take(sizeof(float) * (size_t)n_pad);
   L.o_klr = take(sizeof(float) * (size_t)n_pad);
   L.o_rownorm = take(sizeof(float) * (size_t)n_pad);
-  L.direct_w = stage_w_directly(n_pad / kTileTokens, p->H_s, p->H_t);
+  const bool both_factors_diag = (p->t_entropy || p->t_rank) && p->estimator != ADWIN_EST_SAMPLED;
+  L.direct_w = stage_w_directly(n_pad / kTileTokens, p->H_s, p->H_t,
+                                (L.single && !needs_gradient(p)) || both_factors_diag);
   L.o_wt_img = take(L.use_dma && !L.direct_w ? 2 * (size_t)L.Vp * (size_t)p->H_t : 0);
   L.o_ws_img = take(L.use_dma && !L.direct_w ? 2 * (size_t)L.Vp * (size_t)p->H_s : 0);
   L.o_ht_img = take(L.use_dma ? 2 * (size_t)n_pad * (size_t)p->H_t : 0);
