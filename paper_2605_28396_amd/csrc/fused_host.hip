@@ -315,7 +315,6 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
   std::optional<PhaseScope> scope;
   auto phase = [&](int ph) { scope.reset(); scope.emplace(timer, ph); };
   phase(ADWIN_PHASE_SETUP);
-  ADWIN_HIP_TRY(launch_upload(ws + L.o_plan, blob.data(), blob.size(), stream));
   DevicePlan pl = device_plan_at(ws + L.o_plan, p->B, (int32_t*)(ws + L.o_row_idx),
                                  (int32_t*)(ws + L.o_row_seq));
   float* klr = (float*)(ws + L.o_klr);
@@ -324,22 +323,25 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
   double* seg = (double*)(ws + L.o_seg);
   const int64_t n_pad = hp.n_pad;
 
-  ADWIN_HIP_TRY(launch_fill_u32(p->status_dev, 1, 0u, stream));
-  if (!probe) {   // rows outside the windows report zero KL, cost and diagnostics
-    ADWIN_HIP_TRY(launch_fill_f32(p->kl, p->T, 0.f, stream));
-    ADWIN_HIP_TRY(launch_fill_f32(p->c, p->T, 0.f, stream));
-    ADWIN_HIP_TRY(launch_fill_f32(p->t_logp, p->T, 0.f, stream));
-    ADWIN_HIP_TRY(launch_fill_f32(p->t_entropy, p->T, 0.f, stream));
-    ADWIN_HIP_TRY(launch_fill_u32((uint32_t*)p->t_rank, p->T, 0u, stream));
-  } else if (!p->ids) {
-    ADWIN_HIP_TRY(launch_fill_f32(p->c, p->T, 0.f, stream));
-  }
-
   HeavyList heavy;
   heavy.cnt = (int32_t*)(ws + L.o_heavy_cnt); heavy.v = (int32_t*)(ws + L.o_heavy_v);
+  SetupArgs setup(ws + L.o_plan, p->B);
+  setup.n_rows = hp.n_rows; setup.n_pad = n_pad;
+  setup.row_idx = pl.row_idx; setup.row_seq = pl.row_seq;
+  setup.clear(p->status_dev, 1);
+  setup.clear(heavy.cnt, n_pad);
+  if (!probe) {   // rows outside the windows report zero KL, cost and diagnostics
+    setup.clear(p->kl, p->T);
+    setup.clear(p->c, p->T);
+    setup.clear(p->t_logp, p->T);
+    setup.clear(p->t_entropy, p->T);
+    setup.clear(p->t_rank, p->T);
+  } else if (!p->ids) {
+    setup.clear(p->c, p->T);
+  }
+  ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
+
   if (hp.n_rows > 0) {
-    ADWIN_HIP_TRY(launch_build_rows(pl, p->B, hp.n_rows, n_pad, stream));
-    ADWIN_HIP_TRY(launch_fill_u32((uint32_t*)heavy.cnt, n_pad, 0u, stream));
     const int vt_total = (int)(L.Vp / kTileVocab);
     const int n_tiles = (int)(n_pad / kTileTokens);
     const int h_tiles = (p->H_s + kGradTile - 1) / kGradTile;

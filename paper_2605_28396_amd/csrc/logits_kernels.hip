@@ -519,12 +519,13 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
 
   std::vector<unsigned char> blob;
   HostPlan hp = make_host_plan(p->T, p->B, p->offsets, p->window, /*probe=*/0, p->reduction, &blob);
-  ADWIN_HIP_TRY(launch_upload(ws + L.o_plan, blob.data(), blob.size(), stream));
   DevicePlan pl = device_plan_at(ws + L.o_plan, p->B, nullptr, nullptr);
   float* klr = (float*)(ws + L.o_klr);
   double* seg = (double*)(ws + L.o_seg);
 
-  ADWIN_HIP_TRY(launch_fill_u32(p->status_dev, 1, 0u, stream));
+  SetupArgs setup(ws + L.o_plan, p->B);
+  setup.clear(p->status_dev, 1);
+  ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
   if (p->T > 0) {
     LogitsArgs a;
     a.pl = pl; a.B = p->B; a.V = p->V;

@@ -15,13 +15,32 @@ hipError_t logits_kernels_opt_in();
 hipError_t logits_static_setup();
 
 // --- launchers (all asynchronous on `st`) ---------------------------------------------
-hipError_t launch_build_rows(const DevicePlan& pl, int32_t B, int64_t n_rows, int64_t n_pad,
-                             hipStream_t st);
 // copies `bytes` (a multiple of 16) of host memory to `dst`; the host bytes are taken
 // before the call returns
 hipError_t launch_upload(void* dst, const void* src_host, size_t bytes, hipStream_t st);
 hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t st);
-hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
+
+// What a call sets up before its first real kernel, in one launch: the plan in the workspace, the
+// rows of the plan's rollouts (row_idx, row_seq; padding repeats the last computed row) and
+// arrays of 32-bit words that start at zero.
+struct SetupArgs {
+  unsigned char* plan;                  // in the workspace; PlanBlobLayout(B)
+  int32_t B;
+  int64_t o_comp_off;                   // PlanBlobLayout(B).o_comp_off (o_offsets is 0)
+  int64_t n_rows = 0, n_pad = 0;        // 0: no rows wanted
+  int32_t* row_idx = nullptr; int32_t* row_seq = nullptr;
+  static constexpr int kMaxZero = 8;
+  uint32_t* zero[kMaxZero]; int64_t zero_n[kMaxZero];
+  int n_zero = 0;
+  SetupArgs(unsigned char* ws_plan, int32_t rollouts)
+      : plan(ws_plan), B(rollouts), o_comp_off((int64_t)PlanBlobLayout(rollouts).o_comp_off) {}
+  void clear(void* words, int64_t n) {  // NULL: an output that is not wanted
+    if (!words || n <= 0) return;
+    zero[n_zero] = (uint32_t*)words;
+    zero_n[n_zero++] = n;
+  }
+};
+hipError_t launch_setup(const SetupArgs& a, const std::vector<unsigned char>& blob, hipStream_t st);
 
 // Per-rollout sums of KL (and of ||g_t||^2 when `rownorm` is given) over the window and
 // over the whole rollout; writes loss_prefix / loss_full.  seg is double [B][4].
