@@ -330,6 +330,8 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
   setup.row_idx = pl.row_idx; setup.row_seq = pl.row_seq;
   setup.clear(p->status_dev, 1);
   setup.clear(heavy.cnt, n_pad);
+  uint32_t* done = (uint32_t*)(ws + L.o_racc);      // racc is not used when `done` is
+  setup.clear(done, 1);
   if (!probe) {   // rows outside the windows report zero KL, cost and diagnostics
     setup.clear(p->kl, p->T);
     setup.clear(p->c, p->T);
@@ -532,25 +534,21 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     f.dh_prefix = p->dh_prefix; f.dh_full = p->dh_full; f.rownorm = rownorm;
     ADWIN_HIP_TRY(launch_finalize(f, stream));
   }
-  ADWIN_HIP_TRY(launch_segment_sums(pl, p->B, probe, klr, need_g ? rownorm : nullptr, seg, p->loss_prefix,
-                                    p->loss_full, stream));
-  PoolArgs pa;
-  pa.pl = pl; pa.B = p->B; pa.probe = probe; pa.H = p->H_s; pa.g = gws;
+  const bool pooled = probe && need_g;
+  PoolArgs pa{};
+  pa.pl = pl; pa.B = p->B; pa.H = p->H_s; pa.g = gws;
   pa.pp = (float*)(ws + L.o_pp); pa.pf = (float*)(ws + L.o_pf);
   pa.up = (float*)(ws + L.o_up); pa.uf = (float*)(ws + L.o_uf);
-  if (probe && need_g) {
-    if (hp.n_chunks > 0) ADWIN_HIP_TRY(launch_pool_partial(pa, (int)hp.n_chunks, stream));
-    ADWIN_HIP_TRY(launch_pool_final(pa, stream));
-  }
   BatchArgs b{};
   b.pl = pl; b.B = p->B; b.H = need_g ? p->H_s : 0; b.probe = probe;
   b.zero_grad = (p->grad_scale == 0.f) || !need_g;
-  b.seg = seg; b.up = pa.up; b.uf = pa.uf; b.racc = (double*)(ws + L.o_racc);
+  b.klr = klr; b.rownorm = need_g ? rownorm : nullptr;
+  b.loss_prefix = p->loss_prefix; b.loss_full = p->loss_full;
+  b.seg = seg; b.up = pa.up; b.uf = pa.uf; b.racc = (double*)(ws + L.o_racc); b.done = done;
   b.rho_pooled = p->rho_pooled; b.rho_field = p->rho_field; b.batch = p->batch;
   b.n_out = p->n_out; b.n_adm_out = p->n_adm_out; b.n_adm = hp.n_adm;
-  ADWIN_HIP_TRY(launch_alignment_and_batch(b, stream));
-  if (probe && need_g && p->candidates && p->n_candidates > 0) {
-    CandArgs ca{};
+  CandArgs ca{};
+  if (pooled && p->candidates && p->n_candidates > 0) {
     ca.pl = pl; ca.B = p->B; ca.H = p->H_s; ca.K = p->n_candidates;
     ca.reduction = p->reduction; ca.zero_grad = (p->grad_scale == 0.f);
     for (int k = 0; k < ca.K; ++k) {
@@ -562,17 +560,12 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       }
       ca.inv_nadm[k] = nadm > 0 ? 1.0 / (double)nadm : 0.0;
     }
-    ca.g = gws; ca.pf = pa.pf; ca.uf = pa.uf; ca.rownorm = rownorm; ca.seg = seg;
+    ca.uf = pa.uf; ca.rownorm = rownorm; ca.seg = seg;
     ca.uc = (float*)(ws + L.o_uc); ca.cacc = (double*)(ws + L.o_cacc); ca.cS = (double*)(ws + L.o_cS);
     ca.rho_pooled = p->cand_rho_pooled; ca.rho_field = p->cand_rho_field; ca.batch = p->cand_batch;
-    ADWIN_HIP_TRY(launch_candidate_audit(ca, stream));
   }
-  // alignment of the two objectives in the LM-head parameter block: batch[6]
-  if (p->dW_prefix && p->dW_full && p->batch)
-    ADWIN_HIP_TRY(launch_cosine(p->dW_prefix, p->dW_full, (int64_t)p->V * p->H_s,
-                                (double*)(ws + L.o_cosp), p->batch + 6, stream));
+  SummaryArgs sa{};
   if (p->t_first_reject || p->t_logp_mean || p->cand_loss_share) {
-    SummaryArgs sa{};
     sa.pl = pl; sa.B = p->B; sa.probe = probe; sa.topk = p->topk;
     sa.K = p->cand_loss_share ? p->n_candidates : 0;
     for (int k = 0; k < sa.K; ++k) sa.L[k] = p->candidates[k];
@@ -580,8 +573,12 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     sa.kl = klr;             // per computed row = per packed row in the full-rollout mode
     sa.acc = (double*)(ws + L.o_summ);
     sa.first_reject = p->t_first_reject; sa.logp_mean = p->t_logp_mean; sa.loss_share = p->cand_loss_share;
-    ADWIN_HIP_TRY(launch_summaries(sa, stream));
   }
+  ADWIN_HIP_TRY(launch_tail(b, sa, ca, pooled ? &pa : nullptr, hp.n_chunks, stream));
+  // alignment of the two objectives in the LM-head parameter block: batch[6]
+  if (p->dW_prefix && p->dW_full && p->batch)
+    ADWIN_HIP_TRY(launch_cosine(p->dW_prefix, p->dW_full, (int64_t)p->V * p->H_s,
+                                (double*)(ws + L.o_cosp), p->batch + 6, stream));
   return ADWIN_OK;
 }
 

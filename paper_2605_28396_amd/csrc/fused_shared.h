@@ -278,13 +278,6 @@ struct FinalizeArgs {
   float* rownorm;
 };
 
-// Pooled gradients per rollout (see pool_partial_kernel, pool_final_kernel).
-struct PoolArgs {
-  DevicePlan pl; int B; int probe; int H;
-  const float* g; float* pp; float* pf;   // partials [n_chunks][H]
-  float* up; float* uf;                   // [B][H]
-};
-
 // ---------------------------------------------------------------------------------------
 // Launchers (asynchronous on `st`; the return value is that of the launch)
 // ---------------------------------------------------------------------------------------
@@ -304,8 +297,6 @@ hipError_t launch_hs_gather(const HsGatherArgs& a, int64_t rows, hipStream_t st)
 hipError_t launch_combine(bool transposed, bool sampled, const CombineArgs& a, int row_tiles, hipStream_t st);
 hipError_t launch_grad_gemm(const GradArgs& a, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t st);
-hipError_t launch_pool_partial(const PoolArgs& a, int n_chunks, hipStream_t st);
-hipError_t launch_pool_final(const PoolArgs& a, hipStream_t st);
 
 }  // namespace adwin
 

@@ -6,7 +6,6 @@
 //            the head-weight contraction needs.
 // GEMM     : g = dz W_s (and dW_s = (w dz)^T h_s) as bf16 MFMA GEMMs over tile images.
 // Finalize : scale by grad_scale * alpha, scatter to dh_prefix / dh_full, row norms.
-// Pool     : per-rollout column sums of g over the window and over the rollout (Sec. 4.2).
 #include "fused_shared.h"
 #include <utility>
 
@@ -572,44 +571,6 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Pooled gradients: column sums of g over the window and over the rollout, two levels.
-// ---------------------------------------------------------------------------------------
-
-__global__ __launch_bounds__(256) void pool_partial_kernel(PoolArgs a) {
-  const int ch = blockIdx.x;
-  const int h = blockIdx.y * 256 + threadIdx.x;
-  const int i = last_le<int32_t>(a.pl.chunk_off, a.B + 1, ch);
-  const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
-  const int64_t ni = a.pl.n[i];
-  const int64_t hi = a.probe ? len : ni;
-  const int64_t j0 = (int64_t)(ch - a.pl.chunk_off[i]) * kChunkRows;
-  const int64_t j1 = j0 + kChunkRows < hi ? j0 + kChunkRows : hi;
-  if (h >= a.H) return;
-  const float* g = a.g + (a.pl.comp_off[i] + j0) * a.H + h;
-  float sp = 0.f, sf = 0.f;
-  for (int64_t j = j0; j < j1; ++j, g += a.H) {
-    const float v = *g;
-    sf += v;
-    if (j < ni) sp += v;
-  }
-  a.pp[(int64_t)ch * a.H + h] = sp;
-  a.pf[(int64_t)ch * a.H + h] = sf;
-}
-
-__global__ __launch_bounds__(256) void pool_final_kernel(PoolArgs a) {
-  const int i = blockIdx.x;
-  const int h = blockIdx.y * 256 + threadIdx.x;
-  if (h >= a.H) return;
-  float sp = 0.f, sf = 0.f;
-  for (int ch = a.pl.chunk_off[i]; ch < a.pl.chunk_off[i + 1]; ++ch) {
-    sp += a.pp[(int64_t)ch * a.H + h];
-    sf += a.pf[(int64_t)ch * a.H + h];
-  }
-  a.up[(int64_t)i * a.H + h] = sp;
-  a.uf[(int64_t)i * a.H + h] = sf;
-}
-
-// ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
 hipError_t grad_kernels_opt_in() {
@@ -642,16 +603,6 @@ hipError_t launch_grad_gemm(const GradArgs& a, hipStream_t st) {
 
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t st) {
   finalize_kernel<<<(unsigned)((a.T + 3) / 4), 256, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t launch_pool_partial(const PoolArgs& a, int n_chunks, hipStream_t st) {
-  pool_partial_kernel<<<dim3((unsigned)n_chunks, (unsigned)((a.H + 255) / 256)), 256, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t launch_pool_final(const PoolArgs& a, hipStream_t st) {
-  pool_final_kernel<<<dim3((unsigned)a.B, (unsigned)((a.H + 255) / 256)), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -464,13 +464,13 @@ hipError_t logits_kernels_opt_in() {
 }
 
 struct LogitsLayout {
-  size_t o_plan, o_klr, o_seg, o_racc, o_summ, total;
+  size_t o_plan, o_klr, o_seg, o_done, o_summ, total;
   LogitsLayout(int32_t B, int64_t T) {
     size_t o = 0;
     o_plan = o; o += PlanBlobLayout(B).bytes;
     o_klr = o;  o = align_up(o + sizeof(float) * (size_t)(T > 0 ? T : 1), 256);
     o_seg = o;  o = align_up(o + sizeof(double) * 4 * (size_t)B, 256);
-    o_racc = o; o = align_up(o + sizeof(double) * 4 * (size_t)B, 256);
+    o_done = o; o = align_up(o + sizeof(double) * 4 * (size_t)B, 256);   // one word; the size is part of the interface's limit
     o_summ = o; o = align_up(o + sizeof(double) * kSummarySlots * (size_t)B, 256);
     total = o;
   }
@@ -523,7 +523,9 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
   float* klr = (float*)(ws + L.o_klr);
   double* seg = (double*)(ws + L.o_seg);
 
+  uint32_t* done = (uint32_t*)(ws + L.o_done);
   SetupArgs setup(ws + L.o_plan, p->B);
+  setup.clear(done, 1);
   setup.clear(p->status_dev, 1);
   ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
   if (p->T > 0) {
@@ -548,21 +550,19 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
     ADWIN_HIP_TRY(hipGetLastError());
   }
   PhaseScope scope(timer, ADWIN_PHASE_REDUCE);
-  ADWIN_HIP_TRY(launch_segment_sums(pl, p->B, 0, klr, nullptr, seg, p->loss_prefix, nullptr, stream));
   BatchArgs b{};
-  b.pl = pl; b.B = p->B; b.H = 0; b.probe = 0; b.zero_grad = 1; b.seg = seg;
-  b.up = nullptr; b.uf = nullptr; b.racc = (double*)(ws + L.o_racc);
-  b.rho_pooled = nullptr; b.rho_field = nullptr; b.batch = p->batch;
-  b.n_out = p->n_out; b.n_adm_out = p->n_adm_out; b.n_adm = hp.n_adm;
-  ADWIN_HIP_TRY(launch_alignment_and_batch(b, stream));
+  b.pl = pl; b.B = p->B; b.H = 0; b.probe = 0; b.zero_grad = 1;
+  b.klr = klr; b.rownorm = nullptr; b.seg = seg; b.loss_prefix = p->loss_prefix; b.loss_full = nullptr;
+  b.done = done;
+  b.batch = p->batch; b.n_out = p->n_out; b.n_adm_out = p->n_adm_out; b.n_adm = hp.n_adm;
+  SummaryArgs sa{};
   if (p->t_first_reject || p->t_logp_mean) {
-    SummaryArgs sa{};
     sa.pl = pl; sa.B = p->B; sa.probe = 0; sa.topk = p->topk; sa.K = 0;
-    sa.t_rank = p->t_rank; sa.t_logp = p->t_logp; sa.kl = nullptr;
+    sa.t_rank = p->t_rank; sa.t_logp = p->t_logp;
     sa.acc = (double*)(ws + L.o_summ);
-    sa.first_reject = p->t_first_reject; sa.logp_mean = p->t_logp_mean; sa.loss_share = nullptr;
-    ADWIN_HIP_TRY(launch_summaries(sa, stream));
+    sa.first_reject = p->t_first_reject; sa.logp_mean = p->t_logp_mean;
   }
+  ADWIN_HIP_TRY(launch_tail(b, sa, CandArgs{}, nullptr, 0, stream));
   return ADWIN_OK;
 }
 

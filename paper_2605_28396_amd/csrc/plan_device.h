@@ -43,26 +43,24 @@ struct SetupArgs {
 hipError_t launch_setup(const SetupArgs& a, const std::vector<unsigned char>& blob, hipStream_t st);
 
 // Per-rollout sums of KL (and of ||g_t||^2 when `rownorm` is given) over the window and
-// over the whole rollout; writes loss_prefix / loss_full.  seg is double [B][4].
-hipError_t launch_segment_sums(const DevicePlan& pl, int32_t B, int probe, const float* klr,
-                               const float* rownorm, double* seg, float* loss_prefix,
-                               float* loss_full, hipStream_t st);
-
+// over the whole rollout, the window losses and the alignment of the two gradients, then the
+// batch aggregates.
 struct BatchArgs {
   DevicePlan pl;
   int32_t B;
   int32_t H;            // 0: no gradient statistics (logits-given path)
   int probe;
   int zero_grad;        // grad_scale == 0: every alignment is defined as 0
-  const double* seg;    // [B][4]
+  const float* klr; const float* rownorm;   // per computed row; rownorm may be NULL
+  double* seg;          // [B][4] scratch: KL prefix, KL full, ||g||^2 prefix, ||g||^2 full
+  float* loss_prefix; float* loss_full;     // [B], may be NULL
   const float* up;      // [B][H] pooled prefix sums (unweighted)
   const float* uf;      // [B][H] pooled full-rollout sums
-  double* racc;         // [B][4] scratch
+  double* racc;         // [B][4] scratch of the alignment (not used without probe gradients)
+  uint32_t* done;       // a word that is zero when the call starts (not used with probe gradients)
   float* rho_pooled; float* rho_field; float* batch;
   int32_t* n_out; int64_t* n_adm_out; int64_t n_adm;
 };
-hipError_t launch_alignment_and_batch(const BatchArgs& a, hipStream_t st);
-
 // Candidate-window audit (Sec. 4.2): alignment of the shared prefix window L_k, for every
 // candidate k, with the full-rollout gradient, from the per-row gradients of one
 // full-rollout pass.
@@ -73,8 +71,6 @@ struct CandArgs {
   int zero_grad;
   int32_t L[ADWIN_MAX_CANDIDATES];
   double inv_nadm[ADWIN_MAX_CANDIDATES];   // TOKEN_MEAN weight of candidate k: 1 / sum_i min(L_k, len_i)
-  const float* g;        // [rows][H] per-row gradients, computed-row order (every row: probe mode)
-  const float* pf;       // [chunks][H] column sums of g over kChunkRows-row chunks of each rollout
   const float* uf;       // [B][H] pooled full-rollout sums
   const float* rownorm;  // [rows] ||g_t||^2
   const double* seg;     // [B][4]; seg[4 i + 3] = sum of ||g_t||^2 over rollout i
@@ -83,7 +79,6 @@ struct CandArgs {
   double* cS;            // [K][B]   scratch: sum of ||g_t||^2 over the prefix
   float* rho_pooled; float* rho_field; float* batch;   // outputs, may be NULL
 };
-hipError_t launch_candidate_audit(const CandArgs& a, hipStream_t st);
 
 // Rollout-level summaries of per-row outputs (Sec. 3.1 top-k rejection; App. C loss
 // distribution and prefix / suffix teacher log-probability).  Rows are packed positions;
@@ -103,7 +98,17 @@ struct SummaryArgs {
   float* loss_share;         // [K] or NULL (needs kl)
 };
 constexpr int kSummarySlots = ADWIN_MAX_CANDIDATES + 3;   // K candidate sums, total, logp prefix, logp suffix
-hipError_t launch_summaries(const SummaryArgs& a, hipStream_t st);
+
+// The reductions that end a call.  pooled: the probe's pooled gradients (PoolArgs) are wanted
+// too; cand.K may be 0; a summary output that is NULL is not wanted.
+struct PoolArgs {       // pooled gradients per rollout (see pool_partial_kernel, pool_kernel)
+  DevicePlan pl; int B; int H;
+  const float* g; float* pp; float* pf;   // partials [n_chunks][H]
+  float* up; float* uf;                   // [B][H]
+};
+struct TailArgs { BatchArgs b; SummaryArgs s; CandArgs c; int fold, with_summary; };
+hipError_t launch_tail(const BatchArgs& b, const SummaryArgs& s, const CandArgs& c, const PoolArgs* pooled,
+                       int64_t n_chunks, hipStream_t st);
 
 // Cosine of two fp32 arrays of n elements into *out (0 if either norm is 0): fixed partition
 // into kCosineBlocks contiguous pieces, double sums, pieces added in index order.

@@ -46,74 +46,134 @@ __device__ __forceinline__ void block_sum256(double (&v)[K], double* sh /* [K][4
   __syncthreads();
 }
 
-// One workgroup per rollout: sums of KL_t and ||g_t||^2 over the window and the rollout.
-__global__ __launch_bounds__(256) void segment_sums_kernel(DevicePlan pl, int probe,
-                                                           const float* __restrict__ klr,
-                                                           const float* __restrict__ rownorm,
-                                                           double* __restrict__ seg,
-                                                           float* loss_prefix, float* loss_full) {
-  __shared__ double sh[16];
-  const int i = blockIdx.x;
-  const int64_t len = pl.offsets[i + 1] - pl.offsets[i];
-  const int64_t ni = pl.n[i];
-  const int64_t hi = probe ? len : ni;
-  const int64_t r0 = pl.comp_off[i];
+// Column sums of g over the window and over the rollout, in two levels.  Both kernels add rows in
+// index order; the rows of a step are loaded together first (added one by one as they arrived, a
+// chunk of 128 rows was 128 dependent round trips: 37 us of a 400 us call, and now 8).
+constexpr int kPoolStep = 16;
+
+__global__ __launch_bounds__(256) void pool_partial_kernel(PoolArgs a) {
+  const int ch = blockIdx.x;
+  const int h = blockIdx.y * 256 + threadIdx.x;
+  const int i = last_le<int32_t>(a.pl.chunk_off, a.B + 1, ch);
+  const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
+  const int64_t ni = a.pl.n[i];
+  const int64_t j0 = (int64_t)(ch - a.pl.chunk_off[i]) * kChunkRows;
+  const int rows = (int)(j0 + kChunkRows < len ? (int64_t)kChunkRows : len - j0);
+  const int in_window = (int)(ni - j0 < rows ? (ni > j0 ? ni - j0 : 0) : rows);
+  if (h >= a.H) return;
+  const float* g = a.g + (a.pl.comp_off[i] + j0) * a.H + h;
+  float sp = 0.f, sf = 0.f;
+  for (int j = 0; j < rows; j += kPoolStep) {
+    float v[kPoolStep];
+#pragma unroll
+    for (int q = 0; q < kPoolStep; ++q) v[q] = j + q < rows ? g[(int64_t)(j + q) * a.H] : 0.f;
+#pragma unroll
+    for (int q = 0; q < kPoolStep; ++q) {
+      sf += v[q];
+      sp += j + q < in_window ? v[q] : 0.f;
+    }
+  }
+  a.pp[(int64_t)ch * a.H + h] = sp;
+  a.pf[(int64_t)ch * a.H + h] = sf;
+}
+
+// Slot 0: the pooled sums of the call's own windows and of whole rollouts, from the chunk sums.
+// Slot 1 + k: the pooled prefix sum u_i(L_k) of candidate k, whole chunks from the chunk sums,
+// the ragged rest row by row.
+__global__ __launch_bounds__(256) void pool_kernel(PoolArgs a, CandArgs c) {
+  const int slot = blockIdx.x / a.B, i = blockIdx.x % a.B;
+  const int h = blockIdx.y * 256 + threadIdx.x;
+  if (h >= a.H) return;
+  const int64_t c0 = a.pl.chunk_off[i];
+  const float* pf = a.pf + c0 * a.H + h;
+  if (slot == 0) {
+    const int nch = (int)(a.pl.chunk_off[i + 1] - c0);
+    const float* pp = a.pp + c0 * a.H + h;
+    float sp = 0.f, sf = 0.f;
+#pragma unroll 8
+    for (int q = 0; q < nch; ++q) {
+      sp += pp[(int64_t)q * a.H];
+      sf += pf[(int64_t)q * a.H];
+    }
+    a.up[(int64_t)i * a.H + h] = sp;
+    a.uf[(int64_t)i * a.H + h] = sf;
+    return;
+  }
+  const int k = slot - 1;
+  const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
+  const int64_t n = c.L[k] < len ? (int64_t)c.L[k] : len;
+  const int full = (int)(n / kChunkRows), rest = (int)(n - (int64_t)full * kChunkRows);
+  float s = 0.f;
+#pragma unroll 8
+  for (int q = 0; q < full; ++q) s += pf[(int64_t)q * a.H];
+  const float* g = a.g + (a.pl.comp_off[i] + (int64_t)full * kChunkRows) * a.H + h;
+  for (int j = 0; j < rest; j += kPoolStep) {
+    float v[kPoolStep];
+#pragma unroll
+    for (int q = 0; q < kPoolStep; ++q) v[q] = j + q < rest ? g[(int64_t)(j + q) * a.H] : 0.f;
+#pragma unroll
+    for (int q = 0; q < kPoolStep; ++q) s += v[q];
+  }
+  c.uc[((int64_t)k * a.B + i) * a.H + h] = s;
+}
+
+// Rollout i: sums of KL_t and ||g_t||^2 over the window and the rollout, the window losses, and
+// the cosines from the pooled sums and the norm sums.
+__device__ __forceinline__ void rollout_body(const BatchArgs& a, int i, double* sh) {
+  const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
+  const int64_t ni = a.pl.n[i];
+  const int64_t hi = a.probe ? len : ni;
+  const int64_t r0 = a.pl.comp_off[i];
   double v[4] = {0.0, 0.0, 0.0, 0.0};   // kl prefix, kl full, norm prefix, norm full
+#pragma unroll 4
   for (int64_t j = threadIdx.x; j < hi; j += 256) {
-    const double k = klr[r0 + j];
-    const double s = rownorm ? (double)rownorm[r0 + j] : 0.0;
+    const double k = a.klr[r0 + j];
+    const double s = a.rownorm ? (double)a.rownorm[r0 + j] : 0.0;
     v[1] += k;
     v[3] += s;
     if (j < ni) { v[0] += k; v[2] += s; }
   }
   block_sum256<4>(v, sh);
-  if (threadIdx.x == 0) {
-    seg[i * 4 + 0] = v[0];
-    seg[i * 4 + 1] = v[1];
-    seg[i * 4 + 2] = v[2];
-    seg[i * 4 + 3] = v[3];
-    if (loss_prefix) loss_prefix[i] = ni > 0 ? (float)(v[0] / (double)ni) : 0.f;
-    if (loss_full) loss_full[i] = (probe && len > 0) ? (float)(v[1] / (double)len) : 0.f;
-  }
-}
-
-// One workgroup per rollout: cosines from the pooled sums and the norm sums.
-__global__ __launch_bounds__(256) void rollout_alignment_kernel(BatchArgs a) {
-  __shared__ double sh[16];
-  const int i = blockIdx.x;
-  double v[3] = {0.0, 0.0, 0.0};
-  if (a.probe && !a.zero_grad) {
+  const bool align = a.probe && !a.zero_grad;
+  double u[3] = {0.0, 0.0, 0.0};
+  if (align) {
     const float* up = a.up + (size_t)i * a.H;
     const float* uf = a.uf + (size_t)i * a.H;
+#pragma unroll 4
     for (int h = threadIdx.x; h < a.H; h += 256) {
       const double p = up[h], f = uf[h];
-      v[0] += p * f;
-      v[1] += p * p;
-      v[2] += f * f;
+      u[0] += p * f;
+      u[1] += p * p;
+      u[2] += f * f;
     }
+    block_sum256<3>(u, sh);
   }
-  block_sum256<3>(v, sh);
   if (threadIdx.x == 0) {
+    a.seg[i * 4 + 0] = v[0];
+    a.seg[i * 4 + 1] = v[1];
+    a.seg[i * 4 + 2] = v[2];
+    a.seg[i * 4 + 3] = v[3];
+    if (a.loss_prefix) a.loss_prefix[i] = ni > 0 ? (float)(v[0] / (double)ni) : 0.f;
+    if (a.loss_full) a.loss_full[i] = (a.probe && len > 0) ? (float)(v[1] / (double)len) : 0.f;
     double rp = 0.0, rf = 0.0, okp = 0.0, okf = 0.0;
-    if (a.probe && !a.zero_grad) {
-      if (v[1] > 0.0 && v[2] > 0.0) { rp = v[0] / (sqrt(v[1]) * sqrt(v[2])); okp = 1.0; }
-      const double Sp = a.seg[i * 4 + 2], Sf = a.seg[i * 4 + 3];
-      if (Sp > 0.0 && Sf > 0.0) { rf = sqrt(Sp / Sf); okf = 1.0; }
+    if (align) {
+      if (u[1] > 0.0 && u[2] > 0.0) { rp = u[0] / (sqrt(u[1]) * sqrt(u[2])); okp = 1.0; }
+      if (v[2] > 0.0 && v[3] > 0.0) { rf = sqrt(v[2] / v[3]); okf = 1.0; }
+      a.racc[i * 4 + 0] = rp;
+      a.racc[i * 4 + 1] = okp;
+      a.racc[i * 4 + 2] = rf;
+      a.racc[i * 4 + 3] = okf;
     }
-    a.racc[i * 4 + 0] = rp;
-    a.racc[i * 4 + 1] = okp;
-    a.racc[i * 4 + 2] = rf;
-    a.racc[i * 4 + 3] = okf;
     if (a.rho_pooled) a.rho_pooled[i] = (float)rp;
     if (a.rho_field) a.rho_field[i] = (float)rf;
   }
 }
 
-// Single workgroup: batch objectives, micro (after aggregation) and macro (mean of
+// One workgroup: batch objectives, micro (after aggregation) and macro (mean of
 // per-rollout) alignment, integer outputs.
-__global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
-  __shared__ double sh[16];
+__device__ __forceinline__ void batch_body(const BatchArgs& a, double* sh) {
   const int B = a.B;
+  const bool align = a.probe && !a.zero_grad;
   // batch objectives and field sums
   double w[4] = {0.0, 0.0, 0.0, 0.0};   // L^p, L^f, macro pooled sum, macro pooled count
   double f[4] = {0.0, 0.0, 0.0, 0.0};   // field: dot, |p|^2, |f|^2, unused
@@ -121,8 +181,8 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
   for (int i = threadIdx.x; i < B; i += 256) {
     const double ap = a.pl.alpha_p[i], af = a.pl.alpha_f[i];
     w[0] += ap * a.seg[i * 4 + 0];
-    if (a.probe) {
-      w[1] += af * a.seg[i * 4 + 1];
+    if (a.probe) w[1] += af * a.seg[i * 4 + 1];
+    if (align) {
       w[2] += a.racc[i * 4 + 0] * a.racc[i * 4 + 1];
       w[3] += a.racc[i * 4 + 1];
       mf[0] += a.racc[i * 4 + 2] * a.racc[i * 4 + 3];
@@ -134,13 +194,14 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
     }
   }
   block_sum256<4>(w, sh);
-  block_sum256<4>(f, sh);
-  block_sum256<2>(mf, sh);
   // micro pooled: aggregate the weighted pooled gradients over the batch, then one cosine
   double m[3] = {0.0, 0.0, 0.0};
-  if (a.probe && !a.zero_grad) {
+  if (align) {
+    block_sum256<4>(f, sh);
+    block_sum256<2>(mf, sh);
     for (int h = threadIdx.x; h < a.H; h += 256) {
       double sp = 0.0, sf = 0.0;
+#pragma unroll 4
       for (int i = 0; i < B; ++i) {
         sp += (double)a.pl.alpha_p[i] * (double)a.up[(size_t)i * a.H + h];
         sf += (double)a.pl.alpha_f[i] * (double)a.uf[(size_t)i * a.H + h];
@@ -149,8 +210,8 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
       m[1] += sp * sp;
       m[2] += sf * sf;
     }
+    block_sum256<3>(m, sh);
   }
-  block_sum256<3>(m, sh);
   if (a.n_out)
     for (int i = threadIdx.x; i < B; i += 256) a.n_out[i] = a.pl.n[i];
   if (threadIdx.x == 0) {
@@ -158,14 +219,12 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
     if (a.batch) {
       float o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       o[0] = (float)w[0];
-      if (a.probe) {
-        o[1] = (float)w[1];
-        if (!a.zero_grad) {
-          if (m[1] > 0.0 && m[2] > 0.0) o[2] = (float)(m[0] / (sqrt(m[1]) * sqrt(m[2])));
-          if (f[1] > 0.0 && f[2] > 0.0) o[3] = (float)(f[0] / (sqrt(f[1]) * sqrt(f[2])));
-          if (w[3] > 0.0) o[4] = (float)(w[2] / w[3]);
-          if (mf[1] > 0.0) o[5] = (float)(mf[0] / mf[1]);
-        }
+      if (a.probe) o[1] = (float)w[1];
+      if (align) {
+        if (m[1] > 0.0 && m[2] > 0.0) o[2] = (float)(m[0] / (sqrt(m[1]) * sqrt(m[2])));
+        if (f[1] > 0.0 && f[2] > 0.0) o[3] = (float)(f[0] / (sqrt(f[1]) * sqrt(f[2])));
+        if (w[3] > 0.0) o[4] = (float)(w[2] / w[3]);
+        if (mf[1] > 0.0) o[5] = (float)(mf[0] / mf[1]);
       }
       for (int k = 0; k < 8; ++k) a.batch[k] = o[k];
     }
@@ -183,32 +242,16 @@ __device__ __forceinline__ double cand_alpha_p(const CandArgs& a, int k, int64_t
   return a.inv_nadm[k];
 }
 
-// Pooled prefix sum u_i(L_k): whole chunks from the chunk sums, the ragged rest row by row.
-__global__ __launch_bounds__(256) void cand_pool_kernel(CandArgs a) {
-  const int k = blockIdx.x / a.B, i = blockIdx.x % a.B;
-  const int h = blockIdx.y * 256 + threadIdx.x;
-  if (h >= a.H) return;
-  const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
-  const int64_t n = a.L[k] < len ? (int64_t)a.L[k] : len;
-  const int64_t full = n / kChunkRows;
-  float s = 0.f;
-  const float* pf = a.pf + (int64_t)a.pl.chunk_off[i] * a.H + h;
-  for (int64_t c = 0; c < full; ++c) s += pf[c * a.H];
-  const float* g = a.g + (a.pl.comp_off[i] + full * kChunkRows) * a.H + h;
-  for (int64_t j = full * kChunkRows; j < n; ++j, g += a.H) s += *g;
-  a.uc[((int64_t)k * a.B + i) * a.H + h] = s;
-}
-
-// One workgroup per (candidate, rollout): cosines of the pooled and of the field gradients.
-__global__ __launch_bounds__(256) void cand_align_kernel(CandArgs a) {
-  __shared__ double sh[16];
-  const int k = blockIdx.x / a.B, i = blockIdx.x % a.B;
+// Candidate k, rollout i: cosines of the pooled and of the field gradients.
+__device__ __forceinline__ void cand_align_body(const CandArgs& a, int k, int i, double* sh) {
   const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
   const int64_t n = a.L[k] < len ? (int64_t)a.L[k] : len;
   double v[4] = {0.0, 0.0, 0.0, 0.0};   // <u_p,u_f>, |u_p|^2, |u_f|^2, S_i(n)
+  double Sf[1] = {0.0};                 // S_i(len), summed as in rollout_body
   if (!a.zero_grad) {
     const float* up = a.uc + ((int64_t)k * a.B + i) * a.H;
     const float* uf = a.uf + (int64_t)i * a.H;
+#pragma unroll 4
     for (int h = threadIdx.x; h < a.H; h += 256) {
       const double p = up[h], f = uf[h];
       v[0] += p * f;
@@ -216,15 +259,20 @@ __global__ __launch_bounds__(256) void cand_align_kernel(CandArgs a) {
       v[2] += f * f;
     }
     const float* rn = a.rownorm + a.pl.comp_off[i];
-    for (int64_t j = threadIdx.x; j < n; j += 256) v[3] += (double)rn[j];
+#pragma unroll 4
+    for (int64_t j = threadIdx.x; j < len; j += 256) {
+      const double s = (double)rn[j];
+      if (j < n) v[3] += s;
+      Sf[0] += s;
+    }
   }
   block_sum256<4>(v, sh);
+  block_sum256<1>(Sf, sh);
   if (threadIdx.x == 0) {
     double rp = 0.0, rf = 0.0, okp = 0.0, okf = 0.0;
     if (!a.zero_grad) {
       if (v[1] > 0.0 && v[2] > 0.0) { rp = v[0] / (sqrt(v[1]) * sqrt(v[2])); okp = 1.0; }
-      const double Sf = a.seg[i * 4 + 3];
-      if (v[3] > 0.0 && Sf > 0.0) { rf = sqrt(v[3] / Sf); okf = 1.0; }
+      if (v[3] > 0.0 && Sf[0] > 0.0) { rf = sqrt(v[3] / Sf[0]); okf = 1.0; }
     }
     const int64_t o = (int64_t)k * a.B + i;
     a.cacc[o * 4 + 0] = rp;
@@ -237,17 +285,21 @@ __global__ __launch_bounds__(256) void cand_align_kernel(CandArgs a) {
   }
 }
 
-// One workgroup per candidate: micro (after batch aggregation) and macro cosines.
-__global__ __launch_bounds__(256) void cand_batch_kernel(CandArgs a) {
-  __shared__ double sh[16];
-  const int k = blockIdx.x, B = a.B;
+// Candidate k: micro (after batch aggregation) and macro cosines.  The weights of up to kCandLds
+// rollouts are formed once (their divisions, repeated per column, were most of this kernel).
+constexpr int kCandLds = 256;
+__device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double* sh, double* alpha_lds) {
+  const int B = a.B;
   double w[4] = {0.0, 0.0, 0.0, 0.0};   // macro pooled sum, count, macro field sum, count
   double f[3] = {0.0, 0.0, 0.0};        // field: dot, |p|^2, |f|^2
+  auto alpha = [&](int i) {
+    const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
+    return cand_alpha_p(a, k, a.L[k] < len ? (int64_t)a.L[k] : len);
+  };
   for (int i = threadIdx.x; i < B; i += 256) {
     const int64_t o = (int64_t)k * B + i;
-    const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
-    const int64_t n = a.L[k] < len ? (int64_t)a.L[k] : len;
-    const double ap = cand_alpha_p(a, k, n), af = a.pl.alpha_f[i];
+    const double ap = alpha(i), af = a.pl.alpha_f[i];
+    if (i < kCandLds) alpha_lds[i] = ap;
     w[0] += a.cacc[o * 4 + 0] * a.cacc[o * 4 + 1];
     w[1] += a.cacc[o * 4 + 1];
     w[2] += a.cacc[o * 4 + 2] * a.cacc[o * 4 + 3];
@@ -256,16 +308,15 @@ __global__ __launch_bounds__(256) void cand_batch_kernel(CandArgs a) {
     f[1] += ap * ap * a.cS[o];
     f[2] += af * af * a.seg[i * 4 + 3];
   }
-  block_sum256<4>(w, sh);
+  block_sum256<4>(w, sh);               // its barriers also publish alpha_lds
   block_sum256<3>(f, sh);
   double m[3] = {0.0, 0.0, 0.0};
   if (!a.zero_grad) {
     for (int h = threadIdx.x; h < a.H; h += 256) {
       double sp = 0.0, sf = 0.0;
+#pragma unroll 4
       for (int i = 0; i < B; ++i) {
-        const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
-        const int64_t n = a.L[k] < len ? (int64_t)a.L[k] : len;
-        sp += cand_alpha_p(a, k, n) * (double)a.uc[((int64_t)k * B + i) * a.H + h];
+        sp += (i < kCandLds ? alpha_lds[i] : alpha(i)) * (double)a.uc[((int64_t)k * B + i) * a.H + h];
         sf += (double)a.pl.alpha_f[i] * (double)a.uf[(int64_t)i * a.H + h];
       }
       m[0] += sp * sf;
@@ -286,7 +337,6 @@ __global__ __launch_bounds__(256) void cand_batch_kernel(CandArgs a) {
   }
 }
 
-
 // ---------------------------------------------------------------------------------------
 // Rollout-level summaries of the per-row outputs.  One workgroup per rollout; every thread
 // takes positions tid, tid + 256, ... in ascending order with double accumulators, and the
@@ -305,10 +355,9 @@ __device__ __forceinline__ double block_sum_256(double v, double* sh) {
   return r;
 }
 
-__global__ __launch_bounds__(256) void summary_rollout_kernel(SummaryArgs a) {
-  __shared__ double sh[256];
-  __shared__ int sh_first[256];
-  const int i = blockIdx.x, tid = threadIdx.x;
+__device__ __forceinline__ void summary_rollout_body(const SummaryArgs& a, int i, double* sh /* [256] */,
+                                                     int* sh_first /* [256] */) {
+  const int tid = threadIdx.x;
   const int64_t base = a.pl.offsets[i];
   const int64_t len = a.pl.offsets[i + 1] - base;
   const int64_t n = a.pl.n[i];
@@ -367,7 +416,7 @@ __global__ __launch_bounds__(256) void summary_rollout_kernel(SummaryArgs a) {
 }
 
 // Batch rows of the summaries: sums over rollouts in index order.
-__global__ __launch_bounds__(64) void summary_batch_kernel(SummaryArgs a) {
+__device__ __forceinline__ void summary_batch_body(const SummaryArgs& a) {
   const int tid = threadIdx.x;
   if (a.loss_share && tid < a.K) {
     double part = 0.0, tot = 0.0;
@@ -388,6 +437,46 @@ __global__ __launch_bounds__(64) void summary_batch_kernel(SummaryArgs a) {
       cnt += c == 0 ? n : m - n;
     }
     a.logp_mean[2 * a.B + c] = cnt > 0 ? (float)(sum / (double)cnt) : 0.f;
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// The end of a call in one launch (two with probe gradients).  Workgroups [0, B): rollouts; the
+// next B (with_summary): their summaries; the next K B: candidates.  Each of these used to be
+// a launch of about 4.7 us, and so were the batch aggregates, which need all of them: without
+// probe gradients they are a few sums over B and are taken by the workgroup that finishes last
+// (`fold`: it counts the finished ones in `done`, and adds in rollout order, so the result does
+// not depend on which one it is); with them each aggregate runs over all H columns, and a launch
+// of 1 + K workgroups (batch_kernel) takes them side by side.  Logits of 24
+// rollouts with diagnostics: 425 -> 412 us; one rollout of 37 rows 52.6 -> 49.5 us; the probe
+// audit of 9 rollouts with 7 candidates, with the pooling above: 397 -> 333 us.
+// ---------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void tail_kernel(TailArgs a) {
+  __shared__ double sh[256];
+  __shared__ int sh_first[256];
+  const int B = a.b.B, role = blockIdx.x / B, i = blockIdx.x % B;
+  if (role == 0) rollout_body(a.b, i, sh);
+  else if (role == 1 && a.with_summary) summary_rollout_body(a.s, i, sh, sh_first);
+  else cand_align_body(a.c, role - 1 - a.with_summary, i, sh);
+  if (!a.fold) return;
+  __threadfence();                      // this workgroup's sums, before it counts itself
+  __syncthreads();
+  if (threadIdx.x == 0) sh_first[0] = atomicAdd(a.b.done, 1u) + 1u == gridDim.x;
+  __syncthreads();
+  if (!sh_first[0]) return;
+  __threadfence();                      // the other workgroups' sums
+  batch_body(a.b, sh);
+  if (a.with_summary) summary_batch_body(a.s);
+}
+
+__global__ __launch_bounds__(256) void batch_kernel(TailArgs a) {
+  __shared__ double sh[16];
+  __shared__ double alpha[kCandLds];
+  if (blockIdx.x == 0) {
+    batch_body(a.b, sh);
+    if (a.with_summary) summary_batch_body(a.s);
+  } else {
+    cand_batch_body(a.c, blockIdx.x - 1, sh, alpha);
   }
 }
 
@@ -435,26 +524,26 @@ hipError_t launch_cosine(const float* x, const float* y, int64_t n, double* part
   cosine_final_kernel<<<1, 64, 0, st>>>(partials, out);
   return hipGetLastError();
 }
-hipError_t launch_summaries(const SummaryArgs& a, hipStream_t st) {
-  if (!a.first_reject && !a.logp_mean && !a.loss_share) return hipSuccess;
-  summary_rollout_kernel<<<(unsigned)a.B, 256, 0, st>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.logp_mean || a.loss_share) {
-    summary_batch_kernel<<<1, 64, 0, st>>>(a);
-    e = hipGetLastError();
+hipError_t launch_tail(const BatchArgs& b, const SummaryArgs& s, const CandArgs& c, const PoolArgs* pooled,
+                       int64_t n_chunks, hipStream_t st) {
+  TailArgs a;
+  a.b = b; a.s = s; a.c = c;
+  a.fold = pooled == nullptr;
+  a.with_summary = s.first_reject || s.logp_mean || s.loss_share;
+  const unsigned B = (unsigned)b.B, K = pooled ? (unsigned)c.K : 0u;
+  hipError_t e;
+  if (pooled) {
+    const unsigned cols = (unsigned)((pooled->H + 255) / 256);
+    if (n_chunks > 0) {
+      pool_partial_kernel<<<dim3((unsigned)n_chunks, cols), 256, 0, st>>>(*pooled);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    pool_kernel<<<dim3((1 + K) * B, cols), 256, 0, st>>>(*pooled, c);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  return e;
-}
-hipError_t launch_candidate_audit(const CandArgs& a, hipStream_t st) {
-  if (a.K <= 0) return hipSuccess;
-  cand_pool_kernel<<<dim3((unsigned)(a.K * a.B), (unsigned)((a.H + 255) / 256)), 256, 0, st>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  cand_align_kernel<<<(unsigned)(a.K * a.B), 256, 0, st>>>(a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  cand_batch_kernel<<<(unsigned)a.K, 256, 0, st>>>(a);
+  tail_kernel<<<B * (1 + (unsigned)a.with_summary + K), 256, 0, st>>>(a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (pooled) batch_kernel<<<1 + K, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t st) {
@@ -530,20 +619,6 @@ hipError_t launch_setup(const SetupArgs& a, const std::vector<unsigned char>& bl
     if (e != hipSuccess) return e;
     setup_kernel<<<grid, 256, 0, st>>>(a);
   }
-  return hipGetLastError();
-}
-hipError_t launch_segment_sums(const DevicePlan& pl, int32_t B, int probe, const float* klr,
-                               const float* rownorm, double* seg, float* loss_prefix,
-                               float* loss_full, hipStream_t st) {
-  segment_sums_kernel<<<(unsigned)B, 256, 0, st>>>(pl, probe, klr, rownorm, seg, loss_prefix,
-                                                   loss_full);
-  return hipGetLastError();
-}
-hipError_t launch_alignment_and_batch(const BatchArgs& a, hipStream_t st) {
-  rollout_alignment_kernel<<<(unsigned)a.B, 256, 0, st>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  batch_kernel<<<1, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
