@@ -353,17 +353,28 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       // token tiles of 256 computed rows gathered through row_idx
       RowImageArgs ia;
       if (!L.direct_w) {
-        ia.row_idx = nullptr; ia.n_rows = p->V; ia.th = kTileVocab; ia.permute = 1;
+        ia.row_idx = nullptr; ia.n_rows = p->V; ia.permute = 1;
         ia.src = (const uint4*)p->W_t; ia.img = (uint4*)(ws + L.o_wt_img); ia.H = p->H_t; ia.nk = p->H_t / kBK;
         ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
         ia.src = (const uint4*)p->W_s; ia.img = (uint4*)(ws + L.o_ws_img); ia.H = p->H_s; ia.nk = p->H_s / kBK;
         ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
       }
-      ia.row_idx = pl.row_idx; ia.n_rows = n_pad; ia.th = kTileTokens; ia.permute = 0;
+      PrepareArgs pr;
+      ia.row_idx = pl.row_idx; ia.n_rows = n_pad; ia.permute = 0;
       ia.src = (const uint4*)p->h_t; ia.img = (uint4*)(ws + L.o_ht_img); ia.H = p->H_t; ia.nk = p->H_t / kBK;
-      ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)n_tiles, stream));
+      pr.ht = ia;
       ia.src = (const uint4*)p->h_s; ia.img = (uint4*)(ws + L.o_hs_img); ia.H = p->H_s; ia.nk = p->H_s / kBK;
-      ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)n_tiles, stream));
+      pr.hs = ia;
+      // single sweep: the fixed references of every row, from vocabulary tile 0 and the sampled
+      // token (without ids: id -1 on every row, which the diagnostics sweep expects)
+      pr.ref_blocks = L.single ? (int)(n_pad / 32) : 0;
+      pr.r.row_idx = pl.row_idx; pr.r.ids = p->ids;
+      pr.r.h_s = (const __bf16*)p->h_s; pr.r.h_t = (const __bf16*)p->h_t;
+      pr.r.W_s = (const __bf16*)p->W_s; pr.r.W_t = (const __bf16*)p->W_t;
+      pr.r.H_s = p->H_s; pr.r.H_t = p->H_t; pr.r.V = p->V;
+      pr.r.ref_s2 = (float*)(ws + L.o_lse2); pr.r.ref_t2 = (float*)(ws + L.o_ref_t2); pr.r.mu0 = (float*)(ws + L.o_mu);
+      pr.r.zy_s = (float*)(ws + L.o_zy_s); pr.r.zy_t = (float*)(ws + L.o_zy_t); pr.r.yid = (int32_t*)(ws + L.o_yid);
+      ADWIN_HIP_TRY(launch_prepare(pr, n_tiles, stream));
     }
     LogitPassArgs la;
     la.h_s = (const __bf16*)p->h_s; la.h_t = (const __bf16*)p->h_t;
@@ -396,28 +407,9 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     ga.g = gws; ga.H = p->H_s; ga.h_tiles = h_tiles; ga.ksplit = L.ksplit;
     ga.out_rows = (int64_t)1 << 62; ga.accumulate = 0;
     if (L.single) {
-      // Single sweep.  (1) online statistics of vocabulary tile 0 and the sampled token's
-      // logits give each row its fixed references; (2) per row slab: one sweep over the
-      // vocabulary producing the strip sums and the gradient factors, the merge of the
-      // slab's rows, the combine pass over the factors and the GEMM of dz with W_s.
-      la.tile0 = 0; la.n_tiles = n_tiles; la.strips = 1; la.vt_total = 1;
-      {
-        ADWIN_HIP_TRY(launch_logit_pass(kModeStats, true, la, stream));
-        if (p->ids || diag) {      // without ids: id -1 on every row, which the diagnostics sweep expects
-          TokenLogitArgs ta;
-          ta.row_idx = pl.row_idx; ta.ids = p->ids;
-          ta.h_s = la.h_s; ta.W_s = la.W_s; ta.h_t = la.h_t; ta.W_t = la.W_t;
-          ta.H_s = p->H_s; ta.H_t = p->H_t; ta.V = p->V; ta.n_pad = n_pad;
-          ta.zy_s = (float*)(ws + L.o_zy_s); ta.zy_t = (float*)(ws + L.o_zy_t);
-          ta.yid = (int32_t*)(ws + L.o_yid);
-          ADWIN_HIP_TRY(launch_token_logit(ta, stream));
-        }
-        ADWIN_HIP_TRY(launch_make_refs(la.part, n_pad, (const float*)(ws + L.o_zy_s),
-                                       (const float*)(ws + L.o_zy_t),
-                                       p->ids ? (const int32_t*)(ws + L.o_yid) : nullptr,
-                                       (float*)(ws + L.o_lse2), (float*)(ws + L.o_ref_t2),
-                                       (float*)(ws + L.o_mu), stream));
-      }
+      // Single sweep, the references fixed: per row slab one sweep over the vocabulary producing
+      // the strip sums and the gradient factors, the merge of the slab's rows, the combine pass
+      // over the factors and the GEMM of dz with W_s.
       la.vt_total = vt_total;
       la.zy_t = (const float*)(ws + L.o_zy_t); la.yid = (const int32_t*)(ws + L.o_yid);
       ga.g_rows = 2 * n_pad; ga.half_off = n_pad;
@@ -436,6 +428,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         MergeSingleArgs ms;
         ms.m = m; ms.m.strips = la.strips;
         ms.ref_s2 = la.ref_s2; ms.ref_t2 = la.ref_t2;
+        ms.zy_s = (const float*)(ws + L.o_zy_s); ms.zy_t = la.zy_t; ms.yid = la.yid;
         ms.mu_out = (float*)(ws + L.o_delta); ms.inv_z = (float*)(ws + L.o_invz);
         ms.row0 = r0; ms.rows = rows;
         ADWIN_HIP_TRY(launch_merge_single(ms, stream));

@@ -175,7 +175,7 @@ constexpr int kModeSingleFwdDiag = 7; // the same plus the diagnostics
 // Tile images of a row-major [rows, H] operand (see row_image_kernel).
 struct RowImageArgs {
   const uint4* src; uint4* img; const int32_t* row_idx;
-  int64_t n_rows; int H, nk, th;
+  int64_t n_rows; int H, nk;
   int permute;     // rows of every group of 32 in the order the logit kernels' epilogues want (W tiles)
 };
 
@@ -201,18 +201,22 @@ struct MergeArgs {
 struct MergeSingleArgs {
   MergeArgs m;                 // part: [3][strips][n_pad] sums Z_s, A, Z_t
   const float* ref_s2; const float* ref_t2;
+  const float* zy_s; const float* zy_t; const int32_t* yid;   // of prepare_kernel
   float* mu_out; float* inv_z;
   int64_t row0, rows;          // computed rows [row0, row0 + rows) of this launch (one slab)
 };
 
-// Logits of the sampled token under both models (see token_logit_kernel).
-struct TokenLogitArgs {
-  const int32_t* row_idx; const int32_t* ids;
+// References of the single sweep per computed row, and the logits of the sampled token under both
+// models with its id (-1: none, or out of range) (see prepare_kernel).
+struct RefArgs {
+  const int32_t* row_idx; const int32_t* ids;     // ids may be NULL
   const __bf16* h_s; const __bf16* W_s; const __bf16* h_t; const __bf16* W_t;
   int H_s, H_t, V;
-  int64_t n_pad;
+  float* ref_s2; float* ref_t2; float* mu0;
   float* zy_s; float* zy_t; int32_t* yid;
 };
+// ref_blocks: workgroups of 32 rows (0: no references), then those of the two images.
+struct PrepareArgs { RefArgs r; RowImageArgs ht, hs; int ref_blocks, t_blocks; };
 
 // Combine pass over one slab (see combine_kernel).
 struct CombineArgs {
@@ -286,9 +290,7 @@ hipError_t sweep_kernels_opt_in();       // large dynamic LDS of the logit kerne
 hipError_t launch_row_image(const RowImageArgs& a, unsigned tiles, hipStream_t st);
 // mode: one of kMode*; dma false selects the register-staged kernel (kModeStats, kModeDz only)
 hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStream_t st);
-hipError_t launch_token_logit(const TokenLogitArgs& a, hipStream_t st);
-hipError_t launch_make_refs(const float* part, int64_t n_pad, const float* zy_s, const float* zy_t,
-                            const int32_t* yid, float* ref_s2, float* ref_t2, float* mu0, hipStream_t st);
+hipError_t launch_prepare(const PrepareArgs& a, int n_tiles, hipStream_t st);
 hipError_t launch_merge_stats(const MergeArgs& a, hipStream_t st);
 hipError_t launch_merge_single(const MergeSingleArgs& a, hipStream_t st);
 // grad_kernels.hip

@@ -464,20 +464,29 @@ constexpr int kDmaPerWave = (kTileVocab + kTileTokens) / 8 / 4;   // 12 wave-loa
 // consecutive bytes and no operand needs 32-bit lane offsets from its base.  With `permute`
 // (the W operands) tile row r holds source row entry_of_tile_row(r) of the tile.
 
-__global__ __launch_bounds__(256) void row_image_kernel(RowImageArgs a) {
-  const int kt = blockIdx.x;
-  const int64_t tile = blockIdx.y;
-  uint4* blk = a.img + ((tile * a.nk + kt) * a.th) * 8;
-  for (int q = threadIdx.x; q < a.th * 8; q += 256) {
+template <int THREADS, int TH>
+__device__ __forceinline__ void image_block(const RowImageArgs& a, int64_t tile, int kt) {
+  constexpr int N = TH * 8 / THREADS;      // 16-byte chunks per thread, loaded together
+  uint4* blk = a.img + ((tile * a.nk + kt) * TH) * 8;
+  uint4 v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int q = threadIdx.x + i * THREADS;
     const int r = q >> 3, pos = q & 7, c = pos ^ ((r >> 1) & 7);
-    const int64_t row = tile * a.th + (a.permute ? entry_of_tile_row(r) : r);
-    uint4 v = {0u, 0u, 0u, 0u};
+    const int64_t row = tile * TH + (a.permute ? entry_of_tile_row(r) : r);
+    v[i] = make_uint4(0u, 0u, 0u, 0u);
     if (row < a.n_rows) {
       const int64_t src_row = a.row_idx ? (int64_t)a.row_idx[row] : row;
-      v = a.src[src_row * (a.H >> 3) + kt * 8 + c];
+      v[i] = a.src[src_row * (a.H >> 3) + kt * 8 + c];
     }
-    blk[q] = v;
   }
+#pragma unroll
+  for (int i = 0; i < N; ++i) blk[threadIdx.x + i * THREADS] = v[i];
+}
+
+// vocabulary tiles of 128 rows
+__global__ __launch_bounds__(256) void row_image_kernel(RowImageArgs a) {
+  image_block<256, kTileVocab>(a, blockIdx.y, blockIdx.x);
 }
 
 constexpr int kImgABytes = kTileVocab * kRowBytes;    // 16 KiB: one W block
@@ -853,37 +862,203 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(MergeArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Single-sweep mode: per-row references from the online statistics of vocabulary tile 0,
-// and the merge of the fixed-reference strip sums.
+// Single-sweep mode: what a call prepares for its sweep, in one launch.  The first workgroups fix
+// the references of 32 rows each: online statistics of vocabulary tile 0 (128 entries) and the
+// logits of the sampled token under both models, z_s[y_t] = h_s . W_s[y_t] and
+// z_t[y_t] = h_t . W_t[y_t], which the merge and the diagnostics sweep use again.  The others lay
+// the hidden states out as tile images.
+// The references are bound by latency: (H_t + H_s) / 64 staged k-steps per row tile.  As a sweep of
+// one vocabulary tile they took 83 us for any call (one workgroup per 256 rows, loads two k-steps
+// ahead), and 98 with the token logits and the combination of both in launches of their own.
+// Here 32 rows take 8 waves, one per 32 entries and half of every k-step, and the stages are small
+// enough (20 KiB) for loads kRefLead k-steps ahead: 53 us with the images for 256 rows at
+// H = 2048 + 4096 (118 before).  The merge takes the token logits from here (89 -> 22 us per 16,384 rows).  (Operands straight from the row-major rows into
+// registers, no LDS: 132 us, a load of 16 bytes from each of 64 places costs the L1 a line each.)
 // ---------------------------------------------------------------------------------------
-__global__ void make_refs_kernel(const float* __restrict__ part /* [5][1][n_pad] */, int64_t n_pad,
-                                 const float* __restrict__ zy_s, const float* __restrict__ zy_t,
-                                 const int32_t* __restrict__ yid, float* ref_s2, float* ref_t2,
-                                 float* mu0) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n_pad) return;
-  float ms = part[r], Zs = part[n_pad + r], A = part[2 * n_pad + r], mt = part[3 * n_pad + r];
-  if (yid && yid[r] >= 0) {
+constexpr int kRefRows = 32, kRefThreads = 512, kRefLead = 5;
+constexpr int kRefStage = (kTileVocab + kRefRows) * kRowBytes;          // 20 KiB
+constexpr int kRefLds = (kRefLead + 1) * kRefStage;                     // 120 KiB
+
+// As dma16_at, from a 64-bit address per lane.
+__device__ __forceinline__ void dma16_from(uint32_t lds, const char* src) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(src) : "memory");
+}
+
+// x[i] . y[i] for the wave's four tokens, the loads of all four together; sums as in dot_bf16_row.
+__device__ __forceinline__ void ref_dots(const uint4* const (&x)[4], const uint4* const (&y)[4], int H, int lane,
+                                         float (&out)[4]) {
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int q = lane; q < (H >> 3); q += 64) {
+    uint4 a[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { a[i] = x[i][q]; b[i] = y[i][q]; }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc[i] = fmaf(bf16_lo(a[i].x), bf16_lo(b[i].x), acc[i]); acc[i] = fmaf(bf16_hi(a[i].x), bf16_hi(b[i].x), acc[i]);
+      acc[i] = fmaf(bf16_lo(a[i].y), bf16_lo(b[i].y), acc[i]); acc[i] = fmaf(bf16_hi(a[i].y), bf16_hi(b[i].y), acc[i]);
+      acc[i] = fmaf(bf16_lo(a[i].z), bf16_lo(b[i].z), acc[i]); acc[i] = fmaf(bf16_hi(a[i].z), bf16_hi(b[i].z), acc[i]);
+      acc[i] = fmaf(bf16_lo(a[i].w), bf16_lo(b[i].w), acc[i]); acc[i] = fmaf(bf16_hi(a[i].w), bf16_hi(b[i].w), acc[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) out[i] = wave_sum(acc[i]);
+}
+
+__device__ __forceinline__ void refs_block(const RefArgs& a, int64_t row0, char* lds) {
+  __shared__ float token[2][kRefRows];
+  __shared__ int token_id[kRefRows];
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  const int nt = a.H_t / kBK, nk = nt + a.H_s / kBK;      // k-steps: teacher, then student
+  // A stage: 128 rows of W (tile 0; rows beyond V repeat the last, masked below), then 32 of h, row r
+  // at 128 r, chunk c at position c ^ ((r >> 1) & 7).  Wave-load i < 2 of a wave: W rows
+  // 16 wave + 8 i .. + 7; the third, of waves 0 to 3 only: h rows 8 wave .. + 7.
+  const char *pt[3], *ps[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int m = i < 2 ? 2 * wave + i : (wave & 3), r = 8 * m + (lane >> 3);
+    const uint32_t chunk = (uint32_t)((lane & 7) ^ ((r >> 1) & 7)) * 16u;
+    const int64_t row = i < 2 ? (r < a.V ? r : a.V - 1) : a.row_idx[row0 + r];
+    pt[i] = (const char*)((i < 2 ? a.W_t : a.h_t) + row * a.H_t) + chunk;
+    ps[i] = (const char*)((i < 2 ? a.W_s : a.h_s) + row * a.H_s) + chunk;
+  }
+  auto load = [&](int s) __attribute__((always_inline)) {      // past the last k-step: that one again
+    const uint32_t slot = lds0 + (uint32_t)(s % (kRefLead + 1)) * kRefStage;
+    const int k = s < nk ? s : nk - 1;
+    const bool student = k >= nt;
+    const int64_t off = (int64_t)(student ? k - nt : k) * kRowBytes;
+    dma16_from(slot + (uint32_t)(2 * wave) * 1024u, (student ? ps[0] : pt[0]) + off);
+    dma16_from(slot + (uint32_t)(2 * wave + 1) * 1024u, (student ? ps[1] : pt[1]) + off);
+    if (wave < 4) dma16_from(slot + (uint32_t)(16 + wave) * 1024u, (student ? ps[2] : pt[2]) + off);
+  };
+  for (int s = 0; s < kRefLead; ++s) load(s);
+  {                                                // the sampled tokens of rows 4 wave .. 4 wave + 3
+    const uint4 *xs[4], *ys[4], *xt[4], *yt[4];
+    int y[4];
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t t = a.row_idx[row0 + wave * 4 + i];
+      y[i] = a.ids ? a.ids[t] : -1;
+      const bool ok = y[i] >= 0 && y[i] < a.V;
+      if (!ok) y[i] = -1;
+      any |= ok;
+      const int64_t v = ok ? y[i] : 0;
+      xs[i] = (const uint4*)(a.h_s + t * a.H_s); ys[i] = (const uint4*)(a.W_s + v * a.H_s);
+      xt[i] = (const uint4*)(a.h_t + t * a.H_t); yt[i] = (const uint4*)(a.W_t + v * a.H_t);
+    }
+    float ds[4] = {0.f, 0.f, 0.f, 0.f}, dt[4] = {0.f, 0.f, 0.f, 0.f};
+    if (any) {                                     // uniform: the rows are the wave's
+      ref_dots(xt, yt, a.H_t, lane, dt);
+      ref_dots(xs, ys, a.H_s, lane, ds);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (lane == i) {
+        const bool ok = y[i] >= 0;
+        token[0][wave * 4 + i] = ok ? ds[i] : 0.f;
+        token[1][wave * 4 + i] = ok ? dt[i] : 0.f;
+        token_id[wave * 4 + i] = y[i];
+      }
+  }
+  // wave = vocabulary block vb, half kq of every k-step; A = W rows, B = h rows as in the sweep
+  const int vb = wave & 3, kq = wave >> 2;
+  f32x16 zt = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, zs = zt;
+  const uint32_t key = (uint32_t)(lane >> 1) & 7u, frag = (uint32_t)(lane & 31) * kRowBytes;
+  auto step = [&](int s, f32x16& acc) __attribute__((always_inline)) {
+    // stage s has landed once at most the loads of the kRefLead - 1 later ones are outstanding;
+    // past the barrier every wave is done with stage s - 1, whose slot the next load takes
+    if (wave < 4) wait_vm<3 * (kRefLead - 1)>();
+    else wait_vm<2 * (kRefLead - 1)>();
+    __syncthreads();
+    const uint32_t slot = lds0 + (uint32_t)(s % (kRefLead + 1)) * kRefStage + frag;
+    bf16x8 fa[2], fb[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t sw = ((uint32_t)(4 * kq + 2 * j + half) ^ key) << 4;
+      fa[j] = *lds_frag(slot + (uint32_t)(vb * 32 * kRowBytes) + sw);
+      fb[j] = *lds_frag(slot + (uint32_t)(kTileVocab * kRowBytes) + sw);
+    }
+    load(s + kRefLead);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[j], fb[j], acc, 0, 0, 0);
+  };
+  for (int s = 0; s < nt; ++s) step(s, zt);
+  for (int s = nt; s < nk; ++s) step(s, zs);
+  wait_vm<0>();
+  __syncthreads();                                 // the ring is free from here on
+  float(*half_sum)[32][64] = (float(*)[32][64])lds;                      // [4]: of the second halves
+  float(*stat)[4][kRefRows] = (float(*)[4][kRefRows])(lds + 4 * 32 * 64 * 4);   // [4]: m_s, Z_s, A, m_t
+  if (kq) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { half_sum[vb][e][lane] = zs[e]; half_sum[vb][16 + e][lane] = zt[e]; }
+  }
+  __syncthreads();
+  if (!kq) {
+    float ms = kNegBig, mt = kNegBig, Z = 0.f, A = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      zs[e] += half_sum[vb][e][lane]; zt[e] += half_sum[vb][16 + e][lane];
+      const bool ok = vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V;
+      if (ok) { ms = fmaxf(ms, zs[e]); mt = fmaxf(mt, zt[e]); }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const bool ok = vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V;
+      const float es = ok ? fast_exp2((zs[e] - ms) * kLog2e) : 0.f;
+      Z += es;
+      if (ok) A = fmaf(es, zs[e] - zt[e], A);
+    }
+    merge_mza(ms, Z, A, __shfl_xor(ms, 32, 64), __shfl_xor(Z, 32, 64), __shfl_xor(A, 32, 64));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    if (lane < 32) { stat[vb][0][lane] = ms; stat[vb][1][lane] = Z; stat[vb][2][lane] = A; stat[vb][3][lane] = mt; }
+  }
+  __syncthreads();
+  const int r = threadIdx.x;
+  if (r >= kRefRows) return;
+  float ms = stat[0][0][r], Zs = stat[0][1][r], A = stat[0][2][r], mt = stat[0][3][r];
+#pragma unroll
+  for (int q = 1; q < 4; ++q) {
+    merge_mza(ms, Zs, A, stat[q][0][r], stat[q][1][r], stat[q][2][r]);
+    mt = fmaxf(mt, stat[q][3][r]);
+  }
+  const float zys = token[0][r], zyt = token[1][r];
+  const int y = token_id[r];
+  if (y >= 0) {
     // The sampled token joins the first vocabulary tile as a sample of the row: drawn from the
     // student, it sits where the mass is, which the first 128 entries of a peaked row do not.
     // The references rise to its logits (the exponentials of the sweep stay near 1 at the
     // row maximum instead of growing with the gap to the first tile), and mu0 becomes the
     // self-normalised estimate of E_p[z_s - z_t] over the tile's entries and the token.
-    const float zs = zy_s[r], zt = zy_t[r];
-    const float rs = fmaxf(ms, zs);
+    const float rs = fmaxf(ms, zys);
     const float sc = fast_exp2((ms - rs) * kLog2e);
     Zs *= sc; A *= sc;
-    if (yid[r] >= kTileVocab) {           // not already one of the tile's entries
-      const float ey = fast_exp2((zs - rs) * kLog2e);
+    if (y >= kTileVocab) {                // not already one of the tile's entries
+      const float ey = fast_exp2((zys - rs) * kLog2e);
       Zs += ey;
-      A = fmaf(ey, zs - zt, A);
+      A = fmaf(ey, zys - zyt, A);
     }
     ms = rs;
-    mt = fmaxf(mt, zt);
+    mt = fmaxf(mt, zyt);
   }
-  ref_s2[r] = ms * kLog2e;
-  ref_t2[r] = mt * kLog2e;
-  mu0[r] = A / Zs;
+  a.ref_s2[row0 + r] = ms * kLog2e;
+  a.ref_t2[row0 + r] = mt * kLog2e;
+  a.mu0[row0 + r] = A / Zs;
+  a.zy_s[row0 + r] = zys;
+  a.zy_t[row0 + r] = zyt;
+  a.yid[row0 + r] = y;
+}
+
+__global__ __launch_bounds__(kRefThreads) void prepare_kernel(PrepareArgs a) {
+  extern __shared__ __align__(16) char lds[];
+  int b = (int)blockIdx.x;
+  if (b < a.ref_blocks) return refs_block(a.r, (int64_t)b * kRefRows, lds);
+  b -= a.ref_blocks;
+  const RowImageArgs& im = b < a.t_blocks ? a.ht : a.hs;
+  if (b >= a.t_blocks) b -= a.t_blocks;
+  image_block<kRefThreads, kTileTokens>(im, b / im.nk, b % im.nk);
 }
 
 __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
@@ -923,10 +1098,8 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   bool have_y = false;
   uint32_t flag = dead ? ADWIN_DEV_NONFINITE : 0u;
   if (a.ids && (a.c || a.t_logp || a.t_rank || a.cr) && !dead) {
-    const int y = a.ids[t];
-    if (y >= 0 && y < a.V) {
-      const float zy_s = dot_bf16_row(a.h_s + t * a.H_s, a.W_s + (int64_t)y * a.H_s, a.H_s, lane);
-      const float zy_t = dot_bf16_row(a.h_t + t * a.H_t, a.W_t + (int64_t)y * a.H_t, a.H_t, lane);
+    if (b.yid[r] >= 0) {
+      const float zy_s = b.zy_s[r], zy_t = b.zy_t[r];     // taken with the references
       c = (zy_s - lse_s) - (zy_t - lse_t);
       logp_t = zy_t - lse_t;
       have_y = true;
@@ -945,27 +1118,6 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   }
 }
 
-// Logits of the sampled token under both models, z_s[y_t] = h_s . W_s[y_t] and
-// z_t[y_t] = h_t . W_t[y_t], and the token id (-1 when there is none or it is out of range),
-// per computed row.  The references of the single sweep are built from them (make_refs_kernel)
-// and the diagnostics sweep compares against z_t[y_t] to count the entries the teacher ranks
-// above y_t (Sec. 3.1).  One wave per row.
-
-__global__ __launch_bounds__(256) void token_logit_kernel(TokenLogitArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= a.n_pad) return;
-  const int64_t t = a.row_idx[r];
-  const int y = a.ids ? a.ids[t] : -1;
-  float zs = 0.f, zt = 0.f;
-  const bool ok = y >= 0 && y < a.V;
-  if (ok) {
-    zs = dot_bf16_row(a.h_s + t * a.H_s, a.W_s + (int64_t)y * a.H_s, a.H_s, lane);
-    zt = dot_bf16_row(a.h_t + t * a.H_t, a.W_t + (int64_t)y * a.H_t, a.H_t, lane);
-  }
-  if (lane == 0) { a.zy_s[r] = zs; a.zy_t[r] = zt; a.yid[r] = ok ? y : -1; }
-}
-
 // ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
@@ -974,6 +1126,7 @@ hipError_t sweep_kernels_opt_in() {
 #define ADWIN_OPT_IN(KERNEL, BYTES)                                                              \
   e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES); \
   if (e != hipSuccess) return e;
+  ADWIN_OPT_IN(prepare_kernel, kRefLds)
   ADWIN_OPT_IN(logit_pass_kernel<false>, kLogitLds)
   ADWIN_OPT_IN(logit_pass_kernel<true>, kLogitLds)
   ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, false>), kDmaLds)
@@ -1029,15 +1182,18 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_token_logit(const TokenLogitArgs& a, hipStream_t st) {
-  token_logit_kernel<<<(unsigned)((a.n_pad + 3) / 4), 256, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t launch_make_refs(const float* part, int64_t n_pad, const float* zy_s, const float* zy_t,
-                            const int32_t* yid, float* ref_s2, float* ref_t2, float* mu0, hipStream_t st) {
-  make_refs_kernel<<<(unsigned)((n_pad + 255) / 256), 256, 0, st>>>(part, n_pad, zy_s, zy_t, yid, ref_s2,
-                                                                    ref_t2, mu0);
+// One launch up to 32 token tiles.  An image workgroup in a launch with references holds their
+// LDS as well, one workgroup per compute unit, so that the images of a large call, 164 us of
+// copying for 34,000 rows, go by themselves.
+hipError_t launch_prepare(const PrepareArgs& p, int n_tiles, hipStream_t st) {
+  PrepareArgs a = p;
+  a.t_blocks = n_tiles * a.ht.nk;
+  const unsigned images = (unsigned)(a.t_blocks + n_tiles * a.hs.nk);
+  if (a.ref_blocks && n_tiles > 32) {
+    prepare_kernel<<<(unsigned)a.ref_blocks, kRefThreads, kRefLds, st>>>(a);
+    a.ref_blocks = 0;
+  }
+  prepare_kernel<<<(unsigned)a.ref_blocks + images, kRefThreads, a.ref_blocks ? kRefLds : 0, st>>>(a);
   return hipGetLastError();
 }
 
