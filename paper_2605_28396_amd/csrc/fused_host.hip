@@ -511,7 +511,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
   phase(ADWIN_PHASE_REDUCE);
   if (p->T > 0 && need_g) {
     FinalizeArgs f;
-    f.pl = pl; f.B = p->B; f.T = p->T; f.probe = probe;
+    f.pl = pl; f.B = p->B; f.T = p->T; f.probe = probe; f.n_rows = hp.n_rows;
     f.g = gws; f.ksplit = L.ksplit; f.n_pad = n_pad; f.H = p->H_s;
     f.g_rows = L.single ? 2 * n_pad : n_pad;
     f.inv_z = (const float*)(ws + L.o_invz);

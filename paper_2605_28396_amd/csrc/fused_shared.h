@@ -266,7 +266,7 @@ struct GradArgs {
 
 // Scale + scatter of the row gradients (see finalize_kernel).
 struct FinalizeArgs {
-  DevicePlan pl; int B; int64_t T; int probe;
+  DevicePlan pl; int B; int64_t T; int probe; int64_t n_rows;
   float* g; int ksplit; int64_t n_pad; int H;
   int64_t g_rows;                          // rows per k-split plane of g
   const float* inv_z;                      // per computed row: 1 / Z_s (single sweep) or 1 (two sweeps);
