@@ -80,4 +80,20 @@ __device__ __forceinline__ int last_le(const T* a, int n, T x) {
   return lo;
 }
 
+// last_le by one wave, 64 probes a round (every lane gets the answer): one round trip up to 64
+// entries where the binary search takes six.
+__device__ __forceinline__ int wave_last_le(const int64_t* a, int n, int64_t x) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0;
+  while (n > 1) {
+    const int step = (n + 63) >> 6;
+    const int64_t at = (int64_t)lane * step;
+    const int found = __popcll(__ballot(at < n && a[at < n ? lo + at : lo] <= x));   // >= 1: a[lo] <= x
+    const int skip = (found - 1) * step;
+    lo += skip;
+    n = step < n - skip ? step : n - skip;
+  }
+  return lo;
+}
+
 }  // namespace adwin

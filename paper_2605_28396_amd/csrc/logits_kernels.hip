@@ -15,6 +15,7 @@ constexpr int kRowThreads = 512;
 
 struct LogitsArgs {
   DevicePlan pl;
+  int64_t T;
   int32_t B, V;
   const uint4* z_s;
   const uint4* z_t;
@@ -458,6 +459,185 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Rows of up to 80 logits per thread, in registers alone: THREADS threads (64: a wave per row, four
+// rows to a workgroup) load the whole row pair at once and keep it until dz is written, so HBM
+// sees each logit once (6 B per element) and, at 4 waves per SIMD, one workgroup's reduction and
+// stores run under the loads of others.  Memory bound: what counts is bytes in flight.  The
+// kernel for long rows has 75 such vectors per thread, one workgroup per compute unit and most of
+// its iterations empty on a shorter row; the streaming kernel reads the rows twice.
+// Train call, us, long-row kernel / streaming / this one: V = 2,048 (25,600 of 32,768 rows)
+// 942 / 158 / 97; V = 8,192 (16,384 rows) 522 / 166 / 150; V = 32,776 (3,584) 220 / 165 / 132 and
+// with diagnostics - / 172 / 141; V = 65,536 (2,048) 193 / 209 / 172; V = 81,920 (1,536) 173 / 212 / 159.
+// ---------------------------------------------------------------------------------------
+constexpr int kShortIters = 10;
+constexpr int short_row_limit(int threads) { return threads * kShortIters * 8; }
+
+template <int THREADS, bool DIAG>
+__global__ __launch_bounds__(THREADS < 256 ? 256 : THREADS, THREADS < 1024 ? 4 : 1)
+void logits_row_short_kernel(LogitsArgs a) {
+  constexpr int kRows = THREADS == 64 ? 4 : 1, kWaves = THREADS / 64;
+  __shared__ float sh[7][kWaves];
+  const int lid = kRows > 1 ? threadIdx.x & 63 : threadIdx.x, lane = threadIdx.x & 63;
+  const int64_t t = kRows > 1 ? (int64_t)blockIdx.x * kRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                              : (int64_t)blockIdx.x;
+  if (t >= a.T) return;
+  const int nvec = a.V >> 3;
+  const int i = wave_last_le(a.pl.offsets, a.B + 1, t);
+  const int64_t j = t - a.pl.offsets[i];
+  const int row_bytes = nvec * 16, lane_off = lid * 16;
+  const __amdgpu_buffer_rsrc_t bd = row_rsrc(a.dz ? a.dz + t * nvec : nullptr, a.dz ? row_bytes : 0);
+  auto clear_row = [&]() {
+    const uint4 z = {0u, 0u, 0u, 0u};
+    for (int it = 0; it * THREADS < nvec; ++it) row_store16(bd, lane_off, it * THREADS * 16, z);
+  };
+  if (j >= a.pl.n[i]) {   // outside the window: zero gradient row, zero KL
+    if (a.dz) clear_row();
+    if (lid == 0) {
+      if (a.kl) a.kl[t] = 0.f;
+      if (a.c) a.c[t] = 0.f;
+      if (DIAG) {
+        if (a.t_logp) a.t_logp[t] = 0.f;
+        if (a.t_entropy) a.t_entropy[t] = 0.f;
+        if (a.t_rank) a.t_rank[t] = 0;
+      }
+    }
+    return;
+  }
+  const uint4* zs = a.z_s + t * nvec;
+  const uint4* zt = a.z_t + t * nvec;
+  const __amdgpu_buffer_rsrc_t bs = row_rsrc(zs, row_bytes), bt = row_rsrc(zt, row_bytes);
+  uint4 rs[kShortIters], rt[kShortIters];
+  static_for<kShortIters>([&](auto it_c) {
+    constexpr int it = decltype(it_c)::value;
+    rs[it] = row_load16(bs, lane_off, it * THREADS * 16);      // zeros beyond the row
+    rt[it] = row_load16(bt, lane_off, it * THREADS * 16);
+  });
+  int y = a.ids ? a.ids[t] : -1;
+  const bool has_y = y >= 0 && y < a.V;
+  if (!has_y) y = -1;
+  float zy_s = 0.f, zy_t = 0.f;
+  if (has_y) {
+    zy_s = __uint_as_float((uint32_t)((const uint16_t*)zs)[y] << 16);
+    zy_t = __uint_as_float((uint32_t)((const uint16_t*)zt)[y] << 16);
+  }
+  // ---- statistics: the thread's maxima first, then its sums relative to them -------------
+  float ms = kNegBig, mt = kNegBig, Zs = 0.f, A = 0.f, Zt = 0.f, Bt = 0.f;
+  int cnt = 0;            // entries the teacher ranks strictly above y_t
+  static_for<kShortIters>([&](auto it_c) {
+    constexpr int it = decltype(it_c)::value;
+    if (it * THREADS + lid < nvec) {
+      float s[8], u[8];
+      unpack8(rs[it], s);
+      unpack8(rt[it], u);
+      ms = fmaxf(ms, max8(s));
+      mt = fmaxf(mt, max8(u));
+    }
+  });
+  const float ms2 = ms * kLog2e, mt2 = mt * kLog2e;
+  static_for<kShortIters>([&](auto it_c) {
+    constexpr int it = decltype(it_c)::value;
+    if (it * THREADS + lid < nvec) {
+      float s[8], u[8];
+      unpack8(rs[it], s);
+      unpack8(rt[it], u);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float e = fast_exp2(fmaf(s[k], kLog2e, -ms2));
+        Zs += e;
+        A = fmaf(e, s[k] - u[k], A);
+        const float et = fast_exp2(fmaf(u[k], kLog2e, -mt2));
+        Zt += et;
+        if (DIAG) {
+          Bt = fmaf(et, u[k], Bt);
+          cnt += u[k] > zy_t ? 1 : 0;       // y_t itself is not above itself
+        }
+      }
+    }
+  });
+  auto fold = [&](int o) __attribute__((always_inline)) {
+    merge_mza(ms, Zs, A, __shfl_xor(ms, o, 64), __shfl_xor(Zs, o, 64), __shfl_xor(A, o, 64));
+    if (DIAG) {
+      merge_mza(mt, Zt, Bt, __shfl_xor(mt, o, 64), __shfl_xor(Zt, o, 64), __shfl_xor(Bt, o, 64));
+      cnt += __shfl_xor(cnt, o, 64);
+    } else {
+      merge_mz(mt, Zt, __shfl_xor(mt, o, 64), __shfl_xor(Zt, o, 64));
+    }
+  };
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) fold(o);
+  if constexpr (kWaves > 1) {
+    if (lane == 0) {
+      const int w = threadIdx.x >> 6;
+      sh[0][w] = ms; sh[1][w] = Zs; sh[2][w] = A; sh[3][w] = mt; sh[4][w] = Zt;
+      if (DIAG) { sh[5][w] = Bt; sh[6][w] = __int_as_float(cnt); }
+    }
+    __syncthreads();
+    const int w = lane & (kWaves - 1);
+    ms = sh[0][w]; Zs = sh[1][w]; A = sh[2][w]; mt = sh[3][w]; Zt = sh[4][w];
+    if (DIAG) { Bt = sh[5][w]; cnt = __float_as_int(sh[6][w]); }
+#pragma unroll
+    for (int o = kWaves / 2; o > 0; o >>= 1) fold(o);
+  }
+  // every thread has the row's sums
+  const float lse_s = ms + logf(Zs), lse_t = mt + logf(Zt);
+  const float mu = A / Zs;                       // E_{p_s}[z_s - z_t]
+  float kl = kl_from_sums(mu, ms - mt, Zs, Zt);
+  float ent = DIAG ? lse_t - Bt / Zt : 0.f;
+  // a row without finite statistics is excluded: zeros in every output
+  const bool dead = !(fabsf(lse_s) < 3.0e38f) || !(fabsf(lse_t) < 3.0e38f) || !(fabsf(kl) < 3.0e38f) ||
+                    !(fabsf(mu) < 3.0e38f) || !(fabsf(ent) < 3.0e38f);
+  if (dead) { kl = 0.f; ent = 0.f; }
+  const float c = has_y && !dead ? (zy_s - lse_s) - (zy_t - lse_t) : 0.f;
+  if (lid == 0) {
+    const uint32_t flag = dead ? ADWIN_DEV_NONFINITE : (a.ids && !has_y ? ADWIN_DEV_BAD_ID : 0u);
+    if (flag && a.status) atomicOr(a.status, flag);
+    if (a.kl) a.kl[t] = kl;
+    if (a.c) a.c[t] = c;
+    if (DIAG) {
+      if (a.t_entropy) a.t_entropy[t] = ent;
+      if (a.t_logp) a.t_logp[t] = has_y && !dead ? zy_t - lse_t : 0.f;
+      if (a.t_rank) a.t_rank[t] = has_y && !dead ? cnt + 1 : 0;
+    }
+    a.klr[a.pl.comp_off[i] + j] = kl;
+  }
+  if (!a.dz) return;
+  if (dead) return clear_row();
+  // ---- dz from the registers (see logits_row_resident_kernel) ------------------------------
+  const float scale = a.grad_scale * a.pl.alpha_p[i];
+  const float k_s = a.sampled ? scale * c : scale;
+  const float sg = k_s < 0.f ? -1.f : 1.f;
+  const float sgn = a.sampled ? 0.f : sg;
+  const float lse2 = lse_s * kLog2e - log2f(fabsf(k_s)), nmu = a.sampled ? -sg : -sg * mu;
+  const bool onehot = a.sampled && has_y;
+  const uint32_t vy = pack_bf16(k_s * (1.f - __expf(zy_s - lse_s)), 0.f) & 0xffffu;
+  static_for<kShortIters>([&](auto it_c) {
+    constexpr int it = decltype(it_c)::value;
+    if (it * THREADS < nvec) {
+      uint4 o = dz_vector(rs[it], rt[it], lse2, sgn, nmu);
+      if (onehot && it * THREADS + lid == (y >> 3)) {      // the one-hot term: k (1 - p_s(y))
+        const int word = (y >> 1) & 3;
+        auto put = [&](uint32_t x) { return (y & 1) ? (x & 0xffffu) | (vy << 16) : (x & 0xffff0000u) | vy; };
+        o.x = word == 0 ? put(o.x) : o.x;
+        o.y = word == 1 ? put(o.y) : o.y;
+        o.z = word == 2 ? put(o.z) : o.z;
+        o.w = word == 3 ? put(o.w) : o.w;
+      }
+      row_store16(bd, lane_off, it * THREADS * 16, o);
+    }
+  });
+}
+
+template <bool DIAG>
+static hipError_t launch_short_rows(const LogitsArgs& a, hipStream_t st) {
+  const unsigned T = (unsigned)a.T;
+  if (a.V <= short_row_limit(64)) logits_row_short_kernel<64, DIAG><<<(T + 3) / 4, 256, 0, st>>>(a);
+  else if (a.V <= short_row_limit(256)) logits_row_short_kernel<256, DIAG><<<T, 256, 0, st>>>(a);
+  else if (a.V <= short_row_limit(512)) logits_row_short_kernel<512, DIAG><<<T, 512, 0, st>>>(a);
+  else logits_row_short_kernel<1024, DIAG><<<T, 1024, 0, st>>>(a);
+  return hipGetLastError();
+}
+
 hipError_t logits_kernels_opt_in() {
   return hipFuncSetAttribute((const void*)logits_row_resident_kernel,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
@@ -530,7 +710,7 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
   ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
   if (p->T > 0) {
     LogitsArgs a;
-    a.pl = pl; a.B = p->B; a.V = p->V;
+    a.pl = pl; a.T = p->T; a.B = p->B; a.V = p->V;
     a.z_s = (const uint4*)p->z_s; a.z_t = (const uint4*)p->z_t; a.ids = p->ids;
     a.grad_scale = p->grad_scale;
     a.kl = p->kl; a.c = p->c; a.dz = (uint4*)p->dz; a.klr = klr; a.status = p->status_dev;
@@ -538,7 +718,10 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
     a.sampled = p->estimator == ADWIN_EST_SAMPLED;
     PhaseScope scope(timer, ADWIN_PHASE_STATS);
     const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING;
-    if (p->t_logp || p->t_entropy || p->t_rank) {
+    const bool diag = p->t_logp || p->t_entropy || p->t_rank;
+    if (!streaming && p->V <= short_row_limit(1024)) {
+      ADWIN_HIP_TRY(diag ? launch_short_rows<true>(a, stream) : launch_short_rows<false>(a, stream));
+    } else if (diag) {
       // the diagnostics ride on the streaming kernel (the row-resident one has no register to spare)
       logits_row_kernel<true><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
     } else if (streaming) {

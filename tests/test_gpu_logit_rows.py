@@ -1,0 +1,76 @@
+"""Logits-given rows around the sizes where the serving kernel changes: a wave, 256, 512 or 1024
+threads per row (80 logits per thread), then the long-row kernel; against the oracle, and against the
+streaming kernel where rows hold masked or non-finite logits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import adwin_oracle as O
+from paper_2605_28396_amd import synth
+from tests import helpers as Hp
+from tests.test_gpu_parity import B  # noqa: F401  (a fixture)
+
+pytestmark = pytest.mark.gpu
+
+DIAG = ("t_logp", "t_entropy", "t_rank")
+BASE = ("kl", "c", "dz", "loss_prefix", "batch", "n_out", "n_adm_out", "status_dev")
+SIZES = [8, 520, 5120, 5128, 20480, 20488, 40960, 40968, 81920, 81928]
+
+
+def _host(out):
+    torch.cuda.synchronize()
+    return {k: v.float().cpu().numpy() if v.dtype.is_floating_point else v.cpu().numpy() for k, v in out.items()}
+
+
+@pytest.mark.parametrize("V", SIZES)
+def test_row_kernels_match_oracle(B, V):  # noqa: F811
+    w = synth.Workload(f"rows_{V}", V, 0, 0, synth._offsets([3, 0, 1, 4]), np.array([2, 4, 1, 9], np.int32))
+    p = synth.logits_problem(w)
+    f = Hp.oracle_inputs(p)
+    d = {k: v.cuda() for k, v in p.items()}
+    rows = O.plan(w.offsets, w.window)["rows"]
+    for est in (O.EST_EXPECTED, O.EST_SAMPLED):
+        ref = O.supervise_from_logits(f["z_s"], f["z_t"], f["ids"], w.offsets, w.window, reduction=O.RED_SUM,
+                                      grad_scale=-2.0, estimator=est)
+        for want in (BASE, BASE + DIAG):
+            got = _host(B.adwin_opd_from_logits(d["z_s"], d["z_t"], d["ids"], w.offsets, w.window,
+                                                reduction=O.RED_SUM, grad_scale=-2.0, estimator=est, want=want))
+            assert int(got["status_dev"][0]) == 0 and int(got["n_adm_out"][0]) == ref["n_adm"]
+            Hp.assert_kl(got["kl"], ref["kl"])
+            Hp.assert_cost(got["c"], ref["c"])
+            Hp.assert_grad(got["dz"], ref["dz"], "dz", Hp.BF16_ULP, abs_cap=False)
+            Hp.assert_close_rel(got["loss_prefix"], ref["loss_prefix"], Hp.LOSS_REL, "loss_prefix")
+            if "t_rank" in got:
+                for t in rows:
+                    z, y = f["z_t"][t], int(f["ids"][t])
+                    assert got["t_rank"][t] == O.teacher_rank(z, y)
+                    assert abs(got["t_entropy"][t] - O.teacher_entropy(z)) <= 1e-4
+                other = np.setdiff1d(np.arange(w.T), rows)
+                assert not any(got[k][other].any() for k in DIAG)
+
+
+@pytest.mark.parametrize("V", [8, 520, 5128, 20488, 81920])
+def test_masked_and_nonfinite_rows_match_streaming(B, V):  # noqa: F811
+    g = torch.Generator().manual_seed(V)
+    T = 8
+    z = [torch.randn((T, V), generator=g).to(torch.bfloat16) for _ in range(2)]
+    lowest = torch.finfo(torch.bfloat16).min
+    z[0][0, 1::2] = lowest                       # the type's lowest value as a mask, in both
+    z[1][0, 1::2] = lowest
+    z[1][1, ::3] = -float("inf")
+    z[0][2, V // 2] = float("nan")
+    z[1][3, V - 1] = float("inf")
+    z[0][4] = -float("inf")
+    z[0][5, 0] = 300.0                           # one entry holds the row
+    ids = torch.tensor([0, 1, 0, 1, 0, 0, -1, V], dtype=torch.int32)     # two ids out of range
+    d = [x.cuda() for x in (*z, ids)]
+    off, win = np.array([0, T]), np.array([T], np.int32)
+    outs = [_host(B.adwin_opd_from_logits(*d, off, win, want=BASE + DIAG, scheme=s, reduction=B.ADWIN_RED_SUM))
+            for s in (B.ADWIN_LOGITS_AUTO, B.ADWIN_LOGITS_STREAMING)]
+    a, b = outs
+    for k in ("status_dev", "t_rank", "n_out"):
+        assert np.array_equal(a[k], b[k]), k
+    for k in ("kl", "c", "t_logp", "t_entropy"):     # fp32 sums in two orders
+        assert np.allclose(a[k], b[k], rtol=1e-5, atol=1e-5 * max(1.0, np.abs(b[k]).max())), k
+    # each side is a bf16 rounding of fp32 values within 1e-5 of each other: at most one ulp apart
+    assert np.all(np.abs(a["dz"] - b["dz"]) <= 2 * Hp.BF16_ULP * np.abs(b["dz"]) + 1e-6 * np.abs(b["dz"]).max())
