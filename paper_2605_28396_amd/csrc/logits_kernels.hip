@@ -1,7 +1,7 @@
 // Logits-given path: full-vocabulary log-softmax of student and teacher, per-token
 // reverse KL (Eq. 2 at token level), sampled cost c_t (Sec. 2.3) and the logit gradient
 // p_s((z_s - z_t) - mu) (Eq. 4 in expectation, App. A.1) on the admitted rows
-// (Sec. 4.1), streamed from HBM.  One workgroup per packed row; two sweeps over the row.
+// (Sec. 4.1), from HBM.  Which kernel a row takes follows its length and the number of rows.
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -28,6 +28,8 @@ struct LogitsArgs {
   uint32_t* status;
   // teacher-side diagnostics (Sec. 3.1), each may be NULL
   float* t_logp; float* t_entropy; int32_t* t_rank;
+  // few long rows, each cut into `splits` pieces: the pieces' sums [n_adm][splits][8]
+  float* part; int splits; int64_t n_adm;
   int sampled;         // dz = scale c_t (e_y - p_s) (Eq. 4 on the sampled token) instead of scale p_s (Delta - KL_t)
 };
 
@@ -473,20 +475,44 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
 constexpr int kShortIters = 10;
 constexpr int short_row_limit(int threads) { return threads * kShortIters * 8; }
 
-template <int THREADS, bool DIAG>
+// What a launch does with its rows: all of it, or the two halves of a split row.  A row beyond the
+// limit has a whole compute unit in the long-row kernel, 50 us however few rows there are.  A
+// call of few such rows cuts each into pieces (<= 20,480 logits, 256 threads): one launch leaves the
+// sums of every piece, the next combines them in piece order and writes dz, its second read of
+// the logits coming from the caches.
+constexpr int kWhole = 0, kPieceSums = 1, kPieceGrad = 2;
+
+template <int THREADS, bool DIAG, int PHASE = kWhole>
 __global__ __launch_bounds__(THREADS < 256 ? 256 : THREADS, THREADS < 1024 ? 4 : 1)
 void logits_row_short_kernel(LogitsArgs a) {
   constexpr int kRows = THREADS == 64 ? 4 : 1, kWaves = THREADS / 64;
+  static_assert(PHASE == kWhole || kRows == 1, "a piece is a workgroup's");
   __shared__ float sh[7][kWaves];
   const int lid = kRows > 1 ? threadIdx.x & 63 : threadIdx.x, lane = threadIdx.x & 63;
-  const int64_t t = kRows > 1 ? (int64_t)blockIdx.x * kRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
-                              : (int64_t)blockIdx.x;
-  if (t >= a.T) return;
-  const int nvec = a.V >> 3;
-  const int i = wave_last_le(a.pl.offsets, a.B + 1, t);
-  const int64_t j = t - a.pl.offsets[i];
+  // pieces come first, a workgroup each; kPieceSums has the T packed rows behind them, of which
+  // those outside the windows are cleared
+  const int64_t n_pieces = PHASE == kWhole ? 0 : a.n_adm * a.splits;
+  const bool is_piece = PHASE != kWhole && (int64_t)blockIdx.x < n_pieces;
+  int64_t t = kRows > 1 ? (int64_t)blockIdx.x * kRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                        : (int64_t)blockIdx.x - (is_piece ? 0 : n_pieces);
+  if (t >= a.T && !is_piece) return;
+  const int row_vec = a.V >> 3;
+  int i, piece = 0, q0 = 0, nvec = row_vec;       // the vectors [q0, q0 + nvec) of the row
+  int64_t j;
+  if (is_piece) {
+    const int64_t r = t / a.splits;               // the r-th admitted row
+    piece = (int)(t % a.splits);
+    i = wave_last_le(a.pl.comp_off, a.B + 1, r);
+    j = r - a.pl.comp_off[i];
+    t = a.pl.offsets[i] + j;
+    q0 = (int)((int64_t)row_vec * piece / a.splits);
+    nvec = (int)((int64_t)row_vec * (piece + 1) / a.splits) - q0;
+  } else {
+    i = wave_last_le(a.pl.offsets, a.B + 1, t);
+    j = t - a.pl.offsets[i];
+  }
   const int row_bytes = nvec * 16, lane_off = lid * 16;
-  const __amdgpu_buffer_rsrc_t bd = row_rsrc(a.dz ? a.dz + t * nvec : nullptr, a.dz ? row_bytes : 0);
+  const __amdgpu_buffer_rsrc_t bd = row_rsrc(a.dz ? a.dz + t * row_vec + q0 : nullptr, a.dz ? row_bytes : 0);
   auto clear_row = [&]() {
     const uint4 z = {0u, 0u, 0u, 0u};
     for (int it = 0; it * THREADS < nvec; ++it) row_store16(bd, lane_off, it * THREADS * 16, z);
@@ -504,9 +530,10 @@ void logits_row_short_kernel(LogitsArgs a) {
     }
     return;
   }
-  const uint4* zs = a.z_s + t * nvec;
-  const uint4* zt = a.z_t + t * nvec;
-  const __amdgpu_buffer_rsrc_t bs = row_rsrc(zs, row_bytes), bt = row_rsrc(zt, row_bytes);
+  if (PHASE != kWhole && !is_piece) return;
+  const uint4* zs = a.z_s + t * row_vec;
+  const uint4* zt = a.z_t + t * row_vec;
+  const __amdgpu_buffer_rsrc_t bs = row_rsrc(zs + q0, row_bytes), bt = row_rsrc(zt + q0, row_bytes);
   uint4 rs[kShortIters], rt[kShortIters];
   static_for<kShortIters>([&](auto it_c) {
     constexpr int it = decltype(it_c)::value;
@@ -524,7 +551,7 @@ void logits_row_short_kernel(LogitsArgs a) {
   // ---- statistics: the thread's maxima first, then its sums relative to them -------------
   float ms = kNegBig, mt = kNegBig, Zs = 0.f, A = 0.f, Zt = 0.f, Bt = 0.f;
   int cnt = 0;            // entries the teacher ranks strictly above y_t
-  static_for<kShortIters>([&](auto it_c) {
+  if constexpr (PHASE != kPieceGrad) static_for<kShortIters>([&](auto it_c) {
     constexpr int it = decltype(it_c)::value;
     if (it * THREADS + lid < nvec) {
       float s[8], u[8];
@@ -535,7 +562,7 @@ void logits_row_short_kernel(LogitsArgs a) {
     }
   });
   const float ms2 = ms * kLog2e, mt2 = mt * kLog2e;
-  static_for<kShortIters>([&](auto it_c) {
+  if constexpr (PHASE != kPieceGrad) static_for<kShortIters>([&](auto it_c) {
     constexpr int it = decltype(it_c)::value;
     if (it * THREADS + lid < nvec) {
       float s[8], u[8];
@@ -564,9 +591,17 @@ void logits_row_short_kernel(LogitsArgs a) {
       merge_mz(mt, Zt, __shfl_xor(mt, o, 64), __shfl_xor(Zt, o, 64));
     }
   };
+  float* part = PHASE == kWhole ? nullptr : a.part + (a.pl.comp_off[i] + j) * a.splits * 8;   // of the row's pieces
+  if constexpr (PHASE == kPieceGrad) {
+    // up to 64 pieces, one per lane; lanes without one hold the neutral element
+    if (lane < a.splits) {
+      const float4 x = *(const float4*)(part + lane * 8), x2 = *(const float4*)(part + lane * 8 + 4);
+      ms = x.x; Zs = x.y; A = x.z; mt = x.w; Zt = x2.x; Bt = x2.y; cnt = __float_as_int(x2.z);
+    }
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) fold(o);
-  if constexpr (kWaves > 1) {
+  if constexpr (kWaves > 1 && PHASE != kPieceGrad) {
     if (lane == 0) {
       const int w = threadIdx.x >> 6;
       sh[0][w] = ms; sh[1][w] = Zs; sh[2][w] = A; sh[3][w] = mt; sh[4][w] = Zt;
@@ -579,6 +614,13 @@ void logits_row_short_kernel(LogitsArgs a) {
 #pragma unroll
     for (int o = kWaves / 2; o > 0; o >>= 1) fold(o);
   }
+  if constexpr (PHASE == kPieceSums) {
+    if (lid == 0) {
+      *(float4*)(part + piece * 8) = make_float4(ms, Zs, A, mt);
+      *(float4*)(part + piece * 8 + 4) = make_float4(Zt, Bt, __int_as_float(cnt), 0.f);
+    }
+    return;
+  }
   // every thread has the row's sums
   const float lse_s = ms + logf(Zs), lse_t = mt + logf(Zt);
   const float mu = A / Zs;                       // E_{p_s}[z_s - z_t]
@@ -589,7 +631,7 @@ void logits_row_short_kernel(LogitsArgs a) {
                     !(fabsf(mu) < 3.0e38f) || !(fabsf(ent) < 3.0e38f);
   if (dead) { kl = 0.f; ent = 0.f; }
   const float c = has_y && !dead ? (zy_s - lse_s) - (zy_t - lse_t) : 0.f;
-  if (lid == 0) {
+  if (lid == 0 && piece == 0) {
     const uint32_t flag = dead ? ADWIN_DEV_NONFINITE : (a.ids && !has_y ? ADWIN_DEV_BAD_ID : 0u);
     if (flag && a.status) atomicOr(a.status, flag);
     if (a.kl) a.kl[t] = kl;
@@ -615,7 +657,7 @@ void logits_row_short_kernel(LogitsArgs a) {
     constexpr int it = decltype(it_c)::value;
     if (it * THREADS < nvec) {
       uint4 o = dz_vector(rs[it], rt[it], lse2, sgn, nmu);
-      if (onehot && it * THREADS + lid == (y >> 3)) {      // the one-hot term: k (1 - p_s(y))
+      if (onehot && q0 + it * THREADS + lid == (y >> 3)) {      // the one-hot term: k (1 - p_s(y))
         const int word = (y >> 1) & 3;
         auto put = [&](uint32_t x) { return (y & 1) ? (x & 0xffffu) | (vy << 16) : (x & 0xffff0000u) | vy; };
         o.x = word == 0 ? put(o.x) : o.x;
@@ -638,10 +680,40 @@ static hipError_t launch_short_rows(const LogitsArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Pieces per row of a call of few long rows; 0: the long-row (with diagnostics the streaming) kernel
+// serves it.  A piece fits the registers of a workgroup; a call of very few rows takes as many as
+// give every compute unit one.  At V = 151,936 the long-row kernel costs about 47 us per round of 256
+// rows and 15 besides, the split 0.24 us per row and 20; both scale with V.  us, split / whole:
+// 16 rows 23 / 51, 64 rows 35 / 57, 128 rows 48 / 60, 200 rows 67 / 62, 300 rows 89 / 106, 400 rows
+// 118 / 116; V = 90,000: 128 rows 38 / 43, 200 rows 52 / 46, 300 rows 63 / 70; with diagnostics 64 rows
+// 39 / 62, 128 rows 54 / 64, 300 rows 96 / 98.
+static int row_splits(int V, bool diag, int64_t n_adm, int64_t room) {
+  if (n_adm <= 0) return 0;
+  const int64_t rounds = (n_adm + 255) / 256;
+  if (rounds > (diag ? 1 : 2) || n_adm + 40 > 196 * rounds) return 0;
+  int splits = (V + short_row_limit(256) - 1) / short_row_limit(256);
+  const int64_t fill = 256 / n_adm < 16 ? 256 / n_adm : 16;
+  if (splits < fill) splits = (int)fill;
+  return splits <= 64 && n_adm * splits <= room ? splits : 0;
+}
+
+template <bool DIAG>
+static hipError_t launch_split_rows(const LogitsArgs& a, hipStream_t st) {
+  const unsigned pieces = (unsigned)(a.n_adm * a.splits);
+  logits_row_short_kernel<256, DIAG, kPieceSums><<<pieces + (unsigned)a.T, 256, 0, st>>>(a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  logits_row_short_kernel<256, DIAG, kPieceGrad><<<pieces, 256, 0, st>>>(a);
+  return hipGetLastError();
+}
+
 hipError_t logits_kernels_opt_in() {
   return hipFuncSetAttribute((const void*)logits_row_resident_kernel,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
 }
+
+constexpr size_t kPieceBytes = 32;       // the sums of one piece: 8 words
+constexpr size_t kMaxPieces = 4096;
 
 struct LogitsLayout {
   size_t o_plan, o_klr, o_seg, o_done, o_summ, total;
@@ -653,6 +725,15 @@ struct LogitsLayout {
     o_done = o; o = align_up(o + sizeof(double) * 4 * (size_t)B, 256);   // one word; the size is part of the interface's limit
     o_summ = o; o = align_up(o + sizeof(double) * kSummarySlots * (size_t)B, 256);
     total = o;
+  }
+  // Room for the pieces of split rows behind everything else; a call whose workspace lacks it
+  // serves its rows whole.
+  size_t with_pieces() const {
+    const size_t all = total + kPieceBytes * kMaxPieces;
+    // what fits the static scratch without them still does, with what is left of it
+    if (total <= (size_t)ADWIN_STATIC_SCRATCH_BYTES && all > (size_t)ADWIN_STATIC_SCRATCH_BYTES)
+      return (size_t)ADWIN_STATIC_SCRATCH_BYTES;
+    return all;
   }
 };
 
@@ -680,7 +761,7 @@ extern "C" int adwin_opd_logits_workspace_bytes(const adwin_opd_logits_problem* 
   if (!bytes) return ADWIN_E_NULL;
   int st = check_logits_problem(p);
   if (st != ADWIN_OK) return st;
-  *bytes = LogitsLayout(p->B, p->T).total;
+  *bytes = LogitsLayout(p->B, p->T).with_pieces();
   return ADWIN_OK;
 }
 
@@ -718,9 +799,16 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
     a.sampled = p->estimator == ADWIN_EST_SAMPLED;
     PhaseScope scope(timer, ADWIN_PHASE_STATS);
     const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING;
+    a.part = (float*)(ws + L.total);
+    a.n_adm = hp.n_adm;
+    const size_t room = (workspace_bytes - L.total) / kPieceBytes;
     const bool diag = p->t_logp || p->t_entropy || p->t_rank;
+    a.splits = p->scheme == ADWIN_LOGITS_AUTO && p->V > short_row_limit(1024)
+                   ? row_splits(p->V, diag, hp.n_adm, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
     if (!streaming && p->V <= short_row_limit(1024)) {
       ADWIN_HIP_TRY(diag ? launch_short_rows<true>(a, stream) : launch_short_rows<false>(a, stream));
+    } else if (a.splits > 0) {
+      ADWIN_HIP_TRY(diag ? launch_split_rows<true>(a, stream) : launch_split_rows<false>(a, stream));
     } else if (diag) {
       // the diagnostics ride on the streaming kernel (the row-resident one has no register to spare)
       logits_row_kernel<true><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);

@@ -1,5 +1,5 @@
 """Logits-given rows around the sizes where the serving kernel changes: a wave, 256, 512 or 1024
-threads per row (80 logits per thread), then the long-row kernel; against the oracle, and against the
+threads per row (80 logits per thread), beyond that pieces of a row or the long-row kernel; against the oracle, and against the
 streaming kernel where rows hold masked or non-finite logits."""
 import numpy as np
 import pytest
@@ -74,3 +74,31 @@ def test_masked_and_nonfinite_rows_match_streaming(B, V):  # noqa: F811
         assert np.allclose(a[k], b[k], rtol=1e-5, atol=1e-5 * max(1.0, np.abs(b[k]).max())), k
     # each side is a bf16 rounding of fp32 values within 1e-5 of each other: at most one ulp apart
     assert np.all(np.abs(a["dz"] - b["dz"]) <= 2 * Hp.BF16_ULP * np.abs(b["dz"]) + 1e-6 * np.abs(b["dz"]).max())
+
+
+@pytest.mark.parametrize("V,n_adm", [(81928, 1), (81928, 15), (102408, 156), (81928, 157), (163848, 31), (81928, 257)])
+def test_split_rows_match_whole_rows(B, V, n_adm):  # noqa: F811
+    """Few long rows are cut into pieces (up to 156 rows, and where a second round of the compute
+    units would be nearly empty); the same rows served whole differ by the order of fp32 sums."""
+    g = torch.Generator().manual_seed(n_adm)
+    off = np.array([0, 2, 2, 2 + n_adm, 5 + n_adm], np.int64)
+    win = np.array([0, 7, n_adm, 0], np.int32)           # rows outside the windows on both sides
+    T = int(off[-1])
+    z = [(2 * torch.randn((T, V), generator=g)).to(torch.bfloat16) for _ in range(2)]
+    z[1][2, 5] = float("nan")
+    ids = torch.randint(0, V, (T,), generator=g, dtype=torch.int32)
+    if n_adm > 2:
+        ids[3], ids[4] = -1, V - 1
+    d = [x.cuda() for x in (*z, ids)]
+    for est in (O.EST_EXPECTED, O.EST_SAMPLED):
+        for want in (BASE, BASE + DIAG):
+            kw = dict(want=want, estimator=est, reduction=B.ADWIN_RED_SUM, grad_scale=-2.0)
+            a = _host(B.adwin_opd_from_logits(*d, off, win, scheme=B.ADWIN_LOGITS_AUTO, **kw))
+            b = _host(B.adwin_opd_from_logits(*d, off, win, scheme=B.ADWIN_LOGITS_STREAMING, **kw))
+            for k in a:
+                if a[k].dtype.kind == "i" or k == "t_rank":
+                    assert np.array_equal(a[k], b[k]), k
+                elif k == "dz":
+                    assert np.all(np.abs(a[k] - b[k]) <= 2 * Hp.BF16_ULP * np.abs(b[k]) + 1e-6 * np.abs(b[k]).max())
+                else:
+                    assert np.allclose(a[k], b[k], rtol=2e-5, atol=1e-5 * max(1.0, np.abs(b[k]).max())), k
