@@ -86,9 +86,12 @@ static int sweep_strips(int n_tiles, int vt_total) {
 // pieces, one workgroup each, whose partial planes of g finalize_kernel adds in index order.
 // Cost in k-steps (1.6 us): rounds x (k-steps of a piece + 20 for the start and the epilogue of a
 // tile, from 256-step and 2374-step launches), and per piece the partial plane written and read
-// once at 4 TB/s plus 0.4 for finalize_kernel's turn around one more load.  Slabs are multiples of 8 token tiles between 4,096 and 16,384 rows; ties go to the
-// larger slab (fewer launches, each of which ends in a partly idle round) and to fewer pieces.
-// One row tile of V = 151,936, H_s = 2048 ran on 128 compute units with the split bounded by 16.
+// once at 4 TB/s plus 0.2 for the load of one more plane in finalize_kernel.  Slabs are
+// multiples of 8 token tiles between 4,096 and 16,384 rows; ties go to the larger slab (fewer
+// launches, each of which ends in a partly idle round) and to fewer pieces.  Up to 128 pieces: one
+// output tile of 2374 k-steps (256 rows, H_s = 256) takes 95, call 250 -> 214 us against
+// 32; two tiles 489 -> 458 us; 3,100 rows of 188 k-steps and H_s = 512 take 9, 302 -> 290 us.
+constexpr int kMaxSplit = 128;
 struct GradGeometry { int64_t slab_rows; int ksplit; };
 static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
   GradGeometry best{0, 1};
@@ -98,9 +101,9 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
   for (int64_t r = first; r >= (forced ? first : 4096); r -= 2048) {
     const int64_t slab = r < n_pad ? r : n_pad;
     // pieces only where one slab holds every row: the partial planes cover all rows of the call
-    const int most = slab == n_pad ? (nk < 32 ? nk : 32) : 1;
+    const int most = slab == n_pad ? (nk < kMaxSplit ? nk : kMaxSplit) : 1;
     for (int ks = 1; ks <= most; ++ks) {
-      double cost = ks > 1 ? (double)ks * ((double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 + 0.4) : 0.0;
+      double cost = ks > 1 ? (double)ks * ((double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 + 0.2) : 0.0;
       for (int64_t r0 = 0; r0 < n_pad; r0 += slab) {
         const int64_t rows = n_pad - r0 < slab ? n_pad - r0 : slab;
         const int64_t rounds = ((rows / kGradTile) * h_tiles * ks + 255) / 256;
