@@ -340,23 +340,16 @@ __device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double
 // ---------------------------------------------------------------------------------------
 // Rollout-level summaries of the per-row outputs.  One workgroup per rollout; every thread
 // takes positions tid, tid + 256, ... in ascending order with double accumulators, and the
-// 256 partials are folded by a fixed tree, so the results do not depend on scheduling.
+// 256 partials are folded in a fixed order, so the results do not depend on scheduling.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ double block_sum_256(double v, double* sh) {
-  const int tid = threadIdx.x;
-  sh[tid] = v;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) sh[tid] += sh[tid + s];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
+  double x[1] = {v};
+  block_sum256<1>(x, sh);
+  return x[0];
 }
 
-__device__ __forceinline__ void summary_rollout_body(const SummaryArgs& a, int i, double* sh /* [256] */,
-                                                     int* sh_first /* [256] */) {
+__device__ __forceinline__ void summary_rollout_body(const SummaryArgs& a, int i, double* sh /* [4 (ADWIN_MAX_CANDIDATES + 1)] */,
+                                                     int* sh_first /* [4] */) {
   const int tid = threadIdx.x;
   const int64_t base = a.pl.offsets[i];
   const int64_t len = a.pl.offsets[i + 1] - base;
@@ -367,14 +360,12 @@ __device__ __forceinline__ void summary_rollout_body(const SummaryArgs& a, int i
     int64_t first = m;
     for (int64_t j = tid; j < m; j += 256)
       if (a.t_rank[base + j] > a.topk) { first = j; break; }
-    sh_first[tid] = (int)first;
+    int lowest = (int)first;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) lowest = min(lowest, __shfl_xor(lowest, o, 64));
+    if ((tid & 63) == 0) sh_first[tid >> 6] = lowest;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (tid < s) sh_first[tid] = min(sh_first[tid], sh_first[tid + s]);
-      __syncthreads();
-    }
-    if (tid == 0) a.first_reject[i] = sh_first[0];
-    __syncthreads();
+    if (tid == 0) a.first_reject[i] = min(min(sh_first[0], sh_first[1]), min(sh_first[2], sh_first[3]));
   }
   if (a.logp_mean) {
     double sp = 0.0, ss = 0.0;
@@ -382,8 +373,9 @@ __device__ __forceinline__ void summary_rollout_body(const SummaryArgs& a, int i
       const double v = (double)a.t_logp[base + j];
       if (j < n) sp += v; else ss += v;
     }
-    sp = block_sum_256(sp, sh);
-    ss = block_sum_256(ss, sh);
+    double both[2] = {sp, ss};
+    block_sum256<2>(both, sh);
+    sp = both[0]; ss = both[1];
     if (tid == 0) {
       acc[ADWIN_MAX_CANDIDATES + 1] = sp;
       acc[ADWIN_MAX_CANDIDATES + 2] = ss;
@@ -392,25 +384,22 @@ __device__ __forceinline__ void summary_rollout_body(const SummaryArgs& a, int i
     }
   }
   if (a.loss_share) {
-    double part[ADWIN_MAX_CANDIDATES];
+    double part[ADWIN_MAX_CANDIDATES + 1];       // per candidate, then the total
 #pragma unroll
-    for (int k = 0; k < ADWIN_MAX_CANDIDATES; ++k) part[k] = 0.0;
-    double tot = 0.0;
+    for (int k = 0; k <= ADWIN_MAX_CANDIDATES; ++k) part[k] = 0.0;
     for (int64_t j = tid; j < m; j += 256) {
       const double v = (double)a.kl[base + j];
-      tot += v;
+      part[ADWIN_MAX_CANDIDATES] += v;
 #pragma unroll
       for (int k = 0; k < ADWIN_MAX_CANDIDATES; ++k)
         if (k < a.K && j < a.L[k]) part[k] += v;
     }
-    tot = block_sum_256(tot, sh);
-    if (tid == 0) acc[ADWIN_MAX_CANDIDATES] = tot;
+    block_sum256<ADWIN_MAX_CANDIDATES + 1>(part, sh);     // together: two barriers in all
+    if (tid == 0) {
+      acc[ADWIN_MAX_CANDIDATES] = part[ADWIN_MAX_CANDIDATES];
 #pragma unroll
-    for (int k = 0; k < ADWIN_MAX_CANDIDATES; ++k) {
-      if (k < a.K) {                              // uniform across the workgroup
-        const double r = block_sum_256(part[k], sh);
-        if (tid == 0) acc[k] = r;
-      }
+      for (int k = 0; k < ADWIN_MAX_CANDIDATES; ++k)
+        if (k < a.K) acc[k] = part[k];
     }
   }
 }
@@ -452,8 +441,8 @@ __device__ __forceinline__ void summary_batch_body(const SummaryArgs& a) {
 // audit of 9 rollouts with 7 candidates, with the pooling above: 397 -> 333 us.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void tail_kernel(TailArgs a) {
-  __shared__ double sh[256];
-  __shared__ int sh_first[256];
+  __shared__ double sh[4 * (ADWIN_MAX_CANDIDATES + 1)];
+  __shared__ int sh_first[4];
   const int B = a.b.B, role = blockIdx.x / B, i = blockIdx.x % B;
   if (role == 0) rollout_body(a.b, i, sh);
   else if (role == 1 && a.with_summary) summary_rollout_body(a.s, i, sh, sh_first);
@@ -485,7 +474,7 @@ __global__ __launch_bounds__(256) void batch_kernel(TailArgs a) {
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void cosine_partial_kernel(const float* x, const float* y, int64_t n,
                                                              double* partials) {
-  __shared__ double sh[256];
+  __shared__ double sh[4];
   const int64_t per = (n + kCosineBlocks - 1) / kCosineBlocks;
   const int64_t lo = (int64_t)blockIdx.x * per;
   const int64_t hi = lo + per < n ? lo + per : n;
