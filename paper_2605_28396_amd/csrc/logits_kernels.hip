@@ -271,13 +271,15 @@ __device__ __forceinline__ void row_store16(__amdgpu_buffer_rsrc_t r, int lane_o
   __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off, iter_off, 0);
 }
 
-struct RowStats { float ms, Zs, A, mt, Zt; };
+// Bt = sum e^{z_t - m_t} z_t and cnt = entries above zy, the teacher's logit of y_t: diagnostics only.
+struct RowStats { float ms, Zs, A, mt, Zt, Bt; int cnt; };
 
 __device__ __forceinline__ float max8(const float (&v)[8]) {
   return fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7])));
 }
 
-__device__ __forceinline__ void stats_update(RowStats& r, const uint4& qs, const uint4& qt) {
+template <bool DIAG>
+__device__ __forceinline__ void stats_update(RowStats& r, const uint4& qs, const uint4& qt, float zy, bool in) {
   float s[8], u[8];
   unpack8(qs, s);
   unpack8(qt, u);
@@ -286,15 +288,27 @@ __device__ __forceinline__ void stats_update(RowStats& r, const uint4& qs, const
     const float sc = fast_exp2((r.ms - mx) * kLog2e);
     r.Zs *= sc; r.A *= sc; r.ms = mx;
   }
-  if (mxt > r.mt) { r.Zt *= fast_exp2((r.mt - mxt) * kLog2e); r.mt = mxt; }
+  if (mxt > r.mt) {
+    const float sc = fast_exp2((r.mt - mxt) * kLog2e);
+    r.Zt *= sc;
+    if (DIAG) r.Bt *= sc;
+    r.mt = mxt;
+  }
   const float ms2 = r.ms * kLog2e, mt2 = r.mt * kLog2e;
+  int above = 0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const float e = fast_exp2(fmaf(s[k], kLog2e, -ms2));
     r.Zs += e;
     r.A = fmaf(e, s[k] - u[k], r.A);
-    r.Zt += fast_exp2(fmaf(u[k], kLog2e, -mt2));
+    const float et = fast_exp2(fmaf(u[k], kLog2e, -mt2));
+    r.Zt += et;
+    if (DIAG) {
+      r.Bt = fmaf(et, u[k], r.Bt);
+      above += u[k] > zy ? 1 : 0;           // y_t itself is not above itself
+    }
   }
+  if (DIAG) r.cnt += in ? above : 0;
 }
 
 // dz = sgn * 2^(z_s*log2e - lse2s) * ((z_s - z_t) - mu), with |scale| folded into lse2s
@@ -314,10 +328,11 @@ __device__ __forceinline__ uint4 dz_vector(const uint4& qs, const uint4& qt, flo
   return o;
 }
 
+template <bool DIAG>
 __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(LogitsArgs a) {
   extern __shared__ __align__(16) char lds_raw[];
   uint4* lds_t = (uint4*)lds_raw;
-  float* sh = (float*)(lds_raw + kResTLds * kResThreads * 16);   // [5][4] + broadcast [5]
+  float* sh = (float*)(lds_raw + kResTLds * kResThreads * 16);   // [7][4] + broadcast [5]
   const int64_t t = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int nvec = a.V >> 3;
@@ -332,6 +347,11 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
     if (tid == 0) {
       if (a.kl) a.kl[t] = 0.f;
       if (a.c) a.c[t] = 0.f;
+      if (DIAG) {
+        if (a.t_logp) a.t_logp[t] = 0.f;
+        if (a.t_entropy) a.t_entropy[t] = 0.f;
+        if (a.t_rank) a.t_rank[t] = 0;
+      }
     }
     return;
   }
@@ -342,7 +362,12 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
 
   uint4 rs[kResIters];
   uint4 rt[kResTReg];
-  RowStats st = {kNegBig, 0.f, 0.f, kNegBig, 0.f};
+  RowStats st = {kNegBig, 0.f, 0.f, kNegBig, 0.f, 0.f, 0};
+  float zy_rank = 0.f;            // teacher logit of the sampled token, for the rank
+  if (DIAG && a.ids) {
+    const int y = a.ids[t];
+    if (y >= 0 && y < a.V) zy_rank = __uint_as_float((uint32_t)((const uint16_t*)zt)[y] << 16);
+  }
   // ---- sweep 1: load the row pair once, keep it, accumulate the statistics ------------
   // Loads are issued kResDepth batches (of kResBatch iterations) ahead of the arithmetic, so
   // that the single wave per SIMD always has 2 * kResBatch 16-byte loads in flight per lane.
@@ -377,40 +402,57 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
         if constexpr (it < kResTLds) qt = tb[b % (kResDepth + 1)][g]; else qt = rt[it - kResTLds];
         if (!in) { qs = neutral; qt = neutral; }
         if constexpr (it < kResTLds) lds_t[it * kResThreads + tid] = qt;
-        stats_update(st, qs, qt);
+        stats_update<DIAG>(st, qs, qt, zy_rank, in);
       });
     }
   });
-  for (int q = kResVec + tid; q < nvec; q += kResThreads) stats_update(st, zs[q], zt[q]);
+  for (int q = kResVec + tid; q < nvec; q += kResThreads) stats_update<DIAG>(st, zs[q], zt[q], zy_rank, true);
   float Zs = st.Zs, As = st.A, Zt = st.Zt;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     merge_mza(st.ms, Zs, As, __shfl_xor(st.ms, o, 64), __shfl_xor(Zs, o, 64), __shfl_xor(As, o, 64));
-    merge_mz(st.mt, Zt, __shfl_xor(st.mt, o, 64), __shfl_xor(Zt, o, 64));
+    if (DIAG) {
+      merge_mza(st.mt, Zt, st.Bt, __shfl_xor(st.mt, o, 64), __shfl_xor(Zt, o, 64), __shfl_xor(st.Bt, o, 64));
+      st.cnt += __shfl_xor(st.cnt, o, 64);
+    } else {
+      merge_mz(st.mt, Zt, __shfl_xor(st.mt, o, 64), __shfl_xor(Zt, o, 64));
+    }
   }
   if (lane == 0) { sh[0 + w] = st.ms; sh[4 + w] = Zs; sh[8 + w] = As; sh[12 + w] = st.mt; sh[16 + w] = Zt; }
+  if (DIAG && lane == 0) { sh[20 + w] = st.Bt; sh[24 + w] = __int_as_float(st.cnt); }
   __syncthreads();
   if (tid == 0) {
     float m = sh[0], Z = sh[4], Aa = sh[8], m2 = sh[12], Z2 = sh[16];
+    float B2 = DIAG ? sh[20] : 0.f;
+    int rank = DIAG ? __float_as_int(sh[24]) : 0;
     for (int k = 1; k < kResThreads / 64; ++k) {
       merge_mza(m, Z, Aa, sh[k], sh[4 + k], sh[8 + k]);
-      merge_mz(m2, Z2, sh[12 + k], sh[16 + k]);
+      if (DIAG) {
+        merge_mza(m2, Z2, B2, sh[12 + k], sh[16 + k], sh[20 + k]);
+        rank += __float_as_int(sh[24 + k]);
+      } else {
+        merge_mz(m2, Z2, sh[12 + k], sh[16 + k]);
+      }
     }
     const float lse_s = m + logf(Z), lse_t = m2 + logf(Z2);
     const float mu = Aa / Z;                       // E_{p_s}[z_s - z_t]
     float kl = kl_from_sums(mu, m - m2, Z, Z2);
+    float ent = DIAG ? lse_t - B2 / Z2 : 0.f;
     // a row without finite statistics is excluded: zeros in every output
     const bool dead = !(fabsf(lse_s) < 3.0e38f) || !(fabsf(lse_t) < 3.0e38f) || !(fabsf(kl) < 3.0e38f) ||
-                      !(fabsf(mu) < 3.0e38f);
-    float c = 0.f;
+                      !(fabsf(mu) < 3.0e38f) || !(fabsf(ent) < 3.0e38f);
+    float c = 0.f, logp_t = 0.f;
+    bool have_y = false;
     uint32_t flag = dead ? ADWIN_DEV_NONFINITE : 0u;
-    if (dead) kl = 0.f;
+    if (dead) { kl = 0.f; ent = 0.f; }
     if (a.ids && !dead) {
       const int y = a.ids[t];
       if (y >= 0 && y < a.V) {
         const float zy_s = __uint_as_float((uint32_t)((const uint16_t*)zs)[y] << 16);
         const float zy_t = __uint_as_float((uint32_t)((const uint16_t*)zt)[y] << 16);
         c = (zy_s - lse_s) - (zy_t - lse_t);
+        logp_t = zy_t - lse_t;
+        have_y = true;
       } else {
         flag |= ADWIN_DEV_BAD_ID;
       }
@@ -418,16 +460,21 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
     if (flag && a.status) atomicOr(a.status, flag);
     if (a.kl) a.kl[t] = kl;
     if (a.c) a.c[t] = c;
+    if (DIAG) {
+      if (a.t_entropy) a.t_entropy[t] = ent;
+      if (a.t_logp) a.t_logp[t] = logp_t;
+      if (a.t_rank) a.t_rank[t] = have_y ? rank + 1 : 0;
+    }
     a.klr[a.pl.comp_off[i] + j] = kl;
-    sh[20] = lse_s * kLog2e;
-    sh[21] = mu;
-    sh[22] = c;
-    sh[23] = lse_s;
-    sh[24] = dead ? 1.f : 0.f;
+    sh[28] = lse_s * kLog2e;
+    sh[29] = mu;
+    sh[30] = c;
+    sh[31] = lse_s;
+    sh[32] = dead ? 1.f : 0.f;
   }
   __syncthreads();
   if (!dzr) return;
-  if (sh[24] != 0.f) {
+  if (sh[32] != 0.f) {
     const uint4 z = {0u, 0u, 0u, 0u};
     for (int q = tid; q < nvec; q += kResThreads) store16(dzr + q, z);
     return;
@@ -436,10 +483,10 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
   // expected: scale p_s ((z_s - z_t) - mu); sampled: -k p_s with k = scale c_t (the one-hot
   // term follows); |scale| resp. |k| is folded into the exponent, the sign into the factor
   const float scale = a.grad_scale * a.pl.alpha_p[i];
-  const float k_s = a.sampled ? scale * sh[22] : scale;
+  const float k_s = a.sampled ? scale * sh[30] : scale;
   const float sg = k_s < 0.f ? -1.f : 1.f;
   const float sgn = a.sampled ? 0.f : sg;
-  const float lse2 = sh[20] - log2f(fabsf(k_s)), nmu = a.sampled ? -sg : -sg * sh[21];
+  const float lse2 = sh[28] - log2f(fabsf(k_s)), nmu = a.sampled ? -sg : -sg * sh[29];
   const __amdgpu_buffer_rsrc_t bd = row_rsrc(dzr, row_bytes);
   static_for<kResIters>([&](auto it_c) {
     constexpr int it = decltype(it_c)::value;
@@ -456,7 +503,7 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
     if (tid == 0 && a.ids) {
       const int yy = a.ids[t];
       if (yy >= 0 && yy < a.V)
-        store_onehot(dzr, yy, k_s, __uint_as_float((uint32_t)((const uint16_t*)zs)[yy] << 16), sh[23]);
+        store_onehot(dzr, yy, k_s, __uint_as_float((uint32_t)((const uint16_t*)zs)[yy] << 16), sh[31]);
     }
   }
 }
@@ -680,17 +727,16 @@ static hipError_t launch_short_rows(const LogitsArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Pieces per row of a call of few long rows; 0: the long-row (with diagnostics the streaming) kernel
-// serves it.  A piece fits the registers of a workgroup; a call of very few rows takes as many as
+// Pieces per row of a call of few long rows; 0: the long-row kernel serves it.  A piece fits the registers of a workgroup; a call of very few rows takes as many as
 // give every compute unit one.  At V = 151,936 the long-row kernel costs about 47 us per round of 256
 // rows and 15 besides, the split 0.24 us per row and 20; both scale with V.  us, split / whole:
 // 16 rows 23 / 51, 64 rows 35 / 57, 128 rows 48 / 60, 200 rows 67 / 62, 300 rows 89 / 106, 400 rows
 // 118 / 116; V = 90,000: 128 rows 38 / 43, 200 rows 52 / 46, 300 rows 63 / 70; with diagnostics 64 rows
 // 39 / 62, 128 rows 54 / 64, 300 rows 96 / 98.
-static int row_splits(int V, bool diag, int64_t n_adm, int64_t room) {
+static int row_splits(int V, int64_t n_adm, int64_t room) {
   if (n_adm <= 0) return 0;
   const int64_t rounds = (n_adm + 255) / 256;
-  if (rounds > (diag ? 1 : 2) || n_adm + 40 > 196 * rounds) return 0;
+  if (rounds > 2 || n_adm + 40 > 196 * rounds) return 0;
   int splits = (V + short_row_limit(256) - 1) / short_row_limit(256);
   const int64_t fill = 256 / n_adm < 16 ? 256 / n_adm : 16;
   if (splits < fill) splits = (int)fill;
@@ -708,7 +754,10 @@ static hipError_t launch_split_rows(const LogitsArgs& a, hipStream_t st) {
 }
 
 hipError_t logits_kernels_opt_in() {
-  return hipFuncSetAttribute((const void*)logits_row_resident_kernel,
+  hipError_t e = hipFuncSetAttribute((const void*)logits_row_resident_kernel<false>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute((const void*)logits_row_resident_kernel<true>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
 }
 
@@ -804,19 +853,21 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
     const size_t room = (workspace_bytes - L.total) / kPieceBytes;
     const bool diag = p->t_logp || p->t_entropy || p->t_rank;
     a.splits = p->scheme == ADWIN_LOGITS_AUTO && p->V > short_row_limit(1024)
-                   ? row_splits(p->V, diag, hp.n_adm, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
+                   ? row_splits(p->V, hp.n_adm, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
     if (!streaming && p->V <= short_row_limit(1024)) {
       ADWIN_HIP_TRY(diag ? launch_short_rows<true>(a, stream) : launch_short_rows<false>(a, stream));
     } else if (a.splits > 0) {
       ADWIN_HIP_TRY(diag ? launch_split_rows<true>(a, stream) : launch_split_rows<false>(a, stream));
-    } else if (diag) {
-      // the diagnostics ride on the streaming kernel (the row-resident one has no register to spare)
-      logits_row_kernel<true><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
-    } else if (streaming) {
-      logits_row_kernel<false><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
+    } else if (streaming || (diag && hp.n_adm > 352 && hp.n_adm <= 440)) {
+      // diagnostics: a little over one round of the compute units is where the two workgroups that
+      // the streaming kernel has on each make up for reading twice (400 rows of V = 151,936:
+      // 118 us against 128; 1,352 rows 448 / 370, 12,226 rows 4162 / 3168)
+      if (diag) logits_row_kernel<true><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
+      else logits_row_kernel<false><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
     } else {
       if (first_use_on_device(1)) ADWIN_HIP_TRY(logits_kernels_opt_in());
-      logits_row_resident_kernel<<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
+      if (diag) logits_row_resident_kernel<true><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
+      else logits_row_resident_kernel<false><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
     }
     ADWIN_HIP_TRY(hipGetLastError());
   }

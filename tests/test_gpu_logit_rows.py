@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 DIAG = ("t_logp", "t_entropy", "t_rank")
 BASE = ("kl", "c", "dz", "loss_prefix", "batch", "n_out", "n_adm_out", "status_dev")
 SIZES = [8, 520, 5120, 5128, 20480, 20488, 40960, 40968, 81920, 81928]
+LONG = [81928, 153600, 153608]
 
 
 def _host(out):
@@ -74,6 +75,27 @@ def test_masked_and_nonfinite_rows_match_streaming(B, V):  # noqa: F811
         assert np.allclose(a[k], b[k], rtol=1e-5, atol=1e-5 * max(1.0, np.abs(b[k]).max())), k
     # each side is a bf16 rounding of fp32 values within 1e-5 of each other: at most one ulp apart
     assert np.all(np.abs(a["dz"] - b["dz"]) <= 2 * Hp.BF16_ULP * np.abs(b["dz"]) + 1e-6 * np.abs(b["dz"]).max())
+
+
+@pytest.mark.parametrize("V", LONG)
+def test_long_rows_with_diagnostics_match_oracle(B, V):  # noqa: F811
+    """The long-row kernel itself (the scheme that never cuts rows), up to and beyond its capacity."""
+    w = synth.Workload(f"long_{V}", V, 0, 0, synth._offsets([2, 3]), np.array([1, 9], np.int32))
+    p = synth.logits_problem(w)
+    f = Hp.oracle_inputs(p)
+    d = {k: v.cuda() for k, v in p.items()}
+    ref = O.supervise_from_logits(f["z_s"], f["z_t"], f["ids"], w.offsets, w.window, reduction=O.RED_SUM)
+    got = _host(B.adwin_opd_from_logits(d["z_s"], d["z_t"], d["ids"], w.offsets, w.window, reduction=O.RED_SUM,
+                                        scheme=B.ADWIN_LOGITS_RESIDENT, want=BASE + DIAG))
+    Hp.assert_kl(got["kl"], ref["kl"])
+    Hp.assert_cost(got["c"], ref["c"])
+    Hp.assert_grad(got["dz"], ref["dz"], "dz", Hp.BF16_ULP)
+    for t in O.plan(w.offsets, w.window)["rows"]:
+        z, y = f["z_t"][t], int(f["ids"][t])
+        assert got["t_rank"][t] == O.teacher_rank(z, y)
+        assert abs(got["t_entropy"][t] - O.teacher_entropy(z)) <= 1e-4
+        assert abs(got["t_logp"][t] - O.teacher_logp(z, y)) <= 1e-4 * max(1.0, abs(O.teacher_logp(z, y)))
+    assert got["t_rank"][1] == 0 and not got["t_entropy"][1]
 
 
 @pytest.mark.parametrize("V,n_adm", [(81928, 1), (81928, 15), (102408, 156), (81928, 157), (163848, 31), (81928, 257)])
