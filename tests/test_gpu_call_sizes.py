@@ -31,3 +31,19 @@ def test_few_rows_match_oracle(B, V, H_s, H_t, lens, win, estimator):  # noqa: F
                           reduction=O.RED_SEQ_MEAN, mode=mode, estimator=estimator)
         got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator)
         _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+
+
+def test_wide_rows_of_one_plane_match_oracle(B, monkeypatch):  # noqa: F811
+    """Rows of more than 512 columns whose gradient GEMM is not split (several slabs): a wave
+    each.  V is that of the other cases: at a hundred entries a gradient element is a handful of terms
+    with up to three roundings of 2^-9 each, 5.9e-3 against the bound of 2e-3."""
+    monkeypatch.setenv("ADWIN_SLAB_ROWS", "256")
+    w = synth.Workload("wide_rows", 4104, 576, 192, synth._offsets([300, 41]), np.array([289, 41], np.int32),
+                       synth.MODE_PREFIX_AND_FULL)
+    p = synth.hidden_problem(w)
+    f = Hp.oracle_inputs(p)
+    for estimator in (O.EST_EXPECTED, O.EST_SAMPLED):
+        ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                          reduction=O.RED_SEQ_MEAN, mode=w.mode, estimator=estimator)
+        got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator)
+        _check_fused(w, got, ref, O.RED_SEQ_MEAN)
