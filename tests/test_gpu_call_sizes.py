@@ -47,3 +47,44 @@ def test_wide_rows_of_one_plane_match_oracle(B, monkeypatch):  # noqa: F811
                           reduction=O.RED_SEQ_MEAN, mode=w.mode, estimator=estimator)
         got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator)
         _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+
+
+def _kl_in_64_bits(d, V):
+    """KL_t of every row, c_t of its token, from the bf16 inputs in fp64."""
+    kl, c = [], []
+    step = max(1, (1 << 25) // V)
+    W_s, W_t = d["W_s"].double(), d["W_t"].double()
+    for r in range(0, d["h_s"].shape[0], step):
+        ls = torch.log_softmax(d["h_s"][r:r + step].double() @ W_s.t(), 1)
+        lt = torch.log_softmax(d["h_t"][r:r + step].double() @ W_t.t(), 1)
+        kl.append((ls.exp() * (ls - lt)).sum(1))
+        c.append((ls - lt).gather(1, d["ids"][r:r + step].long()[:, None])[:, 0])
+    return {"kl": torch.cat(kl), "c": torch.cat(c)}
+
+
+@pytest.mark.parametrize("V,H_s,H_t,rows", [
+    (50000, 128, 256, 7000),      # 28 token tiles, which 18 strips fill exactly twice
+    (8000, 512, 512, 4900),       # 20 token tiles
+    (11912, 192, 256, 2305),      # 10 token tiles
+    (50000, 128, 256, 300),       # 2 token tiles: a strip per compute unit
+])
+def test_strips_cost_no_accuracy(B, monkeypatch, V, H_s, H_t, rows):  # noqa: F811
+    """A strip's sums are fp32 chains as long as the strip: whatever number of strips fills the
+    chip, KL_t and c_t are as close to 64 bits as with the 32 strips of a large call (2-norm over the
+    rows; 5 % for the scatter of the roundings over a few hundred rows)."""
+    w = synth.Workload(f"strips_{V}_{rows}", V, H_s, H_t, synth._offsets([rows]), np.array([rows], np.int32),
+                       synth.MODE_PREFIX_ONLY)
+    d = {k: v.cuda() for k, v in synth.hidden_problem(w).items()}
+    ref = _kl_in_64_bits(d, V)
+
+    def errors():
+        out = B.adwin_opd_fused(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window,
+                                want=("kl", "c", "status_dev"))
+        torch.cuda.synchronize()
+        return {k: float((out[k].double() - ref[k]).norm()) for k in ref}
+
+    got = errors()
+    monkeypatch.setenv("ADWIN_STRIPS2", "32")
+    base = errors()
+    for k in ref:
+        assert got[k] <= 1.05 * base[k], (k, got[k], base[k])
