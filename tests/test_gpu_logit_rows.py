@@ -124,3 +124,29 @@ def test_split_rows_match_whole_rows(B, V, n_adm):  # noqa: F811
                     assert np.all(np.abs(a[k] - b[k]) <= 2 * Hp.BF16_ULP * np.abs(b[k]) + 1e-6 * np.abs(b[k]).max())
                 else:
                     assert np.allclose(a[k], b[k], rtol=2e-5, atol=1e-5 * max(1.0, np.abs(b[k]).max())), k
+
+
+@pytest.mark.parametrize("V,rows", [(3256, 400), (8832, 400), (20480, 300), (81920, 200), (90000, 400), (151936, 500)])
+def test_diagnostics_are_as_accurate_as_the_streaming_kernel(B, V, rows):  # noqa: F811
+    """The sums over a row are fp32: however many logits one thread adds up, KL_t and the teacher
+    entropy are as close to 64 bits as the streaming kernel's, whose 512 threads share a row (2-norm over
+    the rows; 10 % for the scatter of the roundings over a few hundred rows)."""
+    g = torch.Generator("cuda").manual_seed(V)
+    z = [torch.randn((rows, V), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2)]
+    ids = torch.randint(0, V, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    ref = {"kl": [], "t_entropy": []}
+    for r in range(0, rows, 50):
+        ls, lt = (torch.log_softmax(x[r:r + 50].double(), 1) for x in z)
+        ref["kl"].append((ls.exp() * (ls - lt)).sum(1))
+        ref["t_entropy"].append(-(lt.exp() * lt).sum(1))
+    off, win = np.array([0, rows]), np.array([rows], np.int32)
+
+    def errors(scheme):
+        out = B.adwin_opd_from_logits(*z, ids, off, win, scheme=scheme, want=("kl",) + DIAG)
+        return {k: float((out[k].double() - torch.cat(v)).norm()) for k, v in ref.items()}
+
+    base = errors(B.ADWIN_LOGITS_STREAMING)
+    for scheme in (B.ADWIN_LOGITS_AUTO, B.ADWIN_LOGITS_RESIDENT):
+        got = errors(scheme)
+        for k in ref:
+            assert got[k] <= 1.1 * base[k], (scheme, k, got[k], base[k])
