@@ -259,6 +259,7 @@ typedef struct adwin_opd_logits_problem {
   float* c;                  /* [T]                                                            */
   void*  dz;                 /* device bf16 [T, V]: grad_scale*alpha^p_i*p_s*((z_s-z_t)-mu_t)   */
                              /* on admitted rows, 0 elsewhere                                  */
+                             /* May be z_s or z_t itself (with the sampled estimator: z_t only) */
   float* loss_prefix;        /* [B]                                                            */
   float* batch;              /* [8] L^p then zeros                                             */
   int32_t* n_out;            /* [B]                                                            */

@@ -601,7 +601,7 @@ void logits_row_short_kernel(LogitsArgs a) {
   const bool has_y = y >= 0 && y < a.V;
   if (!has_y) y = -1;
   float zy_s = 0.f, zy_t = 0.f;
-  if (has_y) {
+  if (PHASE != kPieceGrad && has_y) {
     zy_s = __uint_as_float((uint32_t)((const uint16_t*)zs)[y] << 16);
     zy_t = __uint_as_float((uint32_t)((const uint16_t*)zt)[y] << 16);
   }
@@ -651,10 +651,14 @@ void logits_row_short_kernel(LogitsArgs a) {
   float* part = PHASE == kWhole ? nullptr : a.part + (a.pl.comp_off[i] + j) * a.splits * 8;   // of the row's pieces
   if constexpr (PHASE == kPieceGrad) {
     // up to 64 pieces, one per lane; lanes without one hold the neutral element
+    uint32_t zy = 0u;
     if (lane < a.splits) {
       const float4 x = *(const float4*)(part + lane * 8), x2 = *(const float4*)(part + lane * 8 + 4);
       ms = x.x; Zs = x.y; A = x.z; mt = x.w; Zt = x2.x; Bt = x2.y; cnt = __float_as_int(x2.z);
+      zy = __float_as_uint(x2.w);
     }
+    zy = (uint32_t)__shfl((int)zy, 0, 64);        // the token's logits, from piece 0
+    zy_s = bf16_lo(zy); zy_t = bf16_hi(zy);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) fold(o);
@@ -674,7 +678,10 @@ void logits_row_short_kernel(LogitsArgs a) {
   if constexpr (PHASE == kPieceSums) {
     if (lid == 0) {
       *(float4*)(part + piece * 8) = make_float4(ms, Zs, A, mt);
-      *(float4*)(part + piece * 8 + 4) = make_float4(Zt, Bt, __int_as_float(cnt), 0.f);
+      // the token's two logits go along (exact: they are bf16): the launch that writes dz must not
+      // read them from the rows, of which another piece's workgroup may hold dz by then (dz in place)
+      const uint32_t zy = (__float_as_uint(zy_s) >> 16) | (__float_as_uint(zy_t) & 0xffff0000u);
+      *(float4*)(part + piece * 8 + 4) = make_float4(Zt, Bt, __int_as_float(cnt), __uint_as_float(zy));
     }
     return;
   }

@@ -150,3 +150,35 @@ def test_diagnostics_are_as_accurate_as_the_streaming_kernel(B, V, rows):  # noq
         got = errors(scheme)
         for k in ref:
             assert got[k] <= 1.1 * base[k], (scheme, k, got[k], base[k])
+
+
+@pytest.mark.parametrize("V,n_adm,scheme", [
+    (5120, 20, "AUTO"), (20480, 20, "AUTO"), (81920, 5, "AUTO"),      # a row's logits in registers
+    (81928, 15, "AUTO"), (151936, 29, "AUTO"), (102408, 156, "AUTO"),  # rows cut into pieces
+    (151936, 9, "RESIDENT"), (163848, 9, "RESIDENT"), (81928, 9, "STREAMING"),
+])
+def test_gradient_in_place(B, V, n_adm, scheme):  # noqa: F811
+    """dz may be the storage of z_s or of z_t: the same bits as in an array of its own.  The sampled
+    token's logits, which every workgroup of a row wants, lie anywhere in the row."""
+    g = torch.Generator("cuda").manual_seed(V + n_adm)
+    T = n_adm + 3
+    off, win = np.array([0, 2, T]), np.array([0, n_adm], np.int32)     # rows outside the windows on both sides
+    z = [torch.randn((T, V), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2)]
+    ids = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    ids[2], ids[3] = 0, V - 1
+    for est in (B.ADWIN_EST_EXPECTED, B.ADWIN_EST_SAMPLED):
+        # with the sampled estimator the whole-row kernels of long rows read z_s[y] after dz is stored
+        whole = V > 153600 or scheme != "AUTO"
+        for which in ((0, 1) if est == B.ADWIN_EST_EXPECTED or not whole else (1,)):
+            outs = []
+            for in_place in (False, True):
+                x = [q.clone() for q in z]
+                call = B.LogitsCall(*x, ids, off, win, estimator=est, scheme=getattr(B, "ADWIN_LOGITS_" + scheme),
+                                    reduction=B.ADWIN_RED_SUM, want=BASE + DIAG)
+                if in_place:
+                    call.out["dz"] = x[which]
+                    call.p.dz = x[which].data_ptr()
+                assert call.run() == B.ADWIN_OK
+                outs.append({k: v.clone() for k, v in call.out.items()})
+            for k in outs[0]:
+                assert torch.equal(outs[0][k].view(torch.uint8), outs[1][k].view(torch.uint8)), (k, est, which)
