@@ -154,8 +154,11 @@ __global__ __launch_bounds__(256) void hs_gather_kernel(HsGatherArgs a) {
   const bool alive = a.alive[r] != 0.f;
   const uint4* src = a.h_s + (int64_t)a.row_idx[r] * (a.H >> 3);
   uint4* dst = a.out + k * (a.H >> 3);
-  const uint4 zero = {0u, 0u, 0u, 0u};
-  for (int q = lane; q < (a.H >> 3); q += 64) dst[q] = alive ? src[q] : zero;
+  for (int q = lane; q < (a.H >> 3); q += 64) {
+    uint4 v = src[q];                      // (a choice between src[q] and a zero vector puts that vector into scratch memory)
+    if (!alive) v = make_uint4(0u, 0u, 0u, 0u);
+    dst[q] = v;
+  }
 }
 
 // ---------------------------------------------------------------------------------------
