@@ -131,9 +131,10 @@ extern "C" {
 
 /* scheme of the logits-given path: which kernel streams the rows
  *   AUTO / RESIDENT  one workgroup per row keeps the row pair on chip between its two sweeps, so
- *                    memory sees each logit once; AUTO cuts rows of more than 81,920 logits into
- *                    pieces, read twice through the caches, where a call has too few of them to
- *                    fill the GPU
+ *                    memory sees each logit once (beyond 153,600 logits, the excess twice).  AUTO
+ *                    takes what is faster: few rows of more than 81,920 logits are cut into
+ *                    pieces, read twice through the caches, and some sizes of calls with
+ *                    diagnostics (t_*) and more than 40,960 logits a row go to STREAMING
  *   STREAMING        reads the row pair twice; no limit on what stays resident */
 #define ADWIN_LOGITS_AUTO       0
 #define ADWIN_LOGITS_RESIDENT   1

@@ -744,16 +744,45 @@ static hipError_t launch_short_rows(const LogitsArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Pieces per row of a call of few long rows; 0: the long-row kernel serves it.  A piece fits the registers of a workgroup; a call of very few rows takes as many as
-// give every compute unit one.  At V = 151,936 the long-row kernel costs about 47 us per round of 256
-// rows and 15 besides, the split 0.24 us per row and 20; both scale with V.  us, split / whole:
-// 16 rows 23 / 51, 64 rows 35 / 57, 128 rows 48 / 60, 200 rows 67 / 62, 300 rows 89 / 106, 400 rows
-// 118 / 116; V = 90,000: 128 rows 38 / 43, 200 rows 52 / 46, 300 rows 63 / 70; with diagnostics 64 rows
-// 39 / 62, 128 rows 54 / 64, 300 rows 96 / 98.
-static int row_splits(int V, int64_t n_adm, int64_t room) {
-  if (n_adm <= 0) return 0;
-  const int64_t rounds = (n_adm + 255) / 256;
-  if (rounds > 2 || n_adm + 40 > 196 * rounds) return 0;
+// Whether a call with diagnostics takes the streaming kernel under ADWIN_LOGITS_AUTO.
+// Diagnostics add arithmetic, which a workgroup that holds a row of more than 40,960 logits and has its
+// compute unit to itself (1024 threads, or the long-row kernel's 256) hides less well than the streaming
+// kernel's two workgroups; what that costs in return is the second read of the rows, which comes from
+// the last-level cache while the row pairs of the call fit its 256 MiB.  us, row on chip / streaming, on
+// both sides of that line: V = 90,000: 700 rows 131 / 121, 768 rows 131 / 144; V = 102,400: 600 rows
+// 135 / 118, 700 rows 140 / 147; V = 136,000: 480 rows 128 / 125, 512 rows 132 / 143; V = 151,936: 400 rows
+// 130 / 121, 480 rows 139 / 157.  The line of the 1024-thread kernel lies a
+// little lower, and the two draw level as a row fills its registers: V = 60,000: 600 rows 77 / 68, 1,024
+// rows 112 / 112; V = 65,536: 513 rows 72 / 65, 1,024 rows 122 / 130; V = 73,728: 512 rows 67 / 68.  Up to 256 rows
+// each has a compute unit either way: V = 50,000: 256 rows 36 / 38; V = 122,880: 200 rows 61 / 59, 256 rows
+// 65 / 66; V = 151,936: 200 rows 70 / 70, 256 rows 73 / 77.  A few rows more than two rounds cost a row on
+// chip a third: V = 73,728: 513 rows 76 / 70; V = 131,072: 169 / 147; V = 176,000: 541 rows 238 / 227;
+// V = 151,936: 520 rows 186 / 193.
+// A kernel whose registers are half empty loses whatever the number of rows (V = 42,000: 16,384 rows
+// 1066 / 988; V = 50,000: 700 rows 76 / 66, 2,048 rows 184 / 187, 8,192 rows 623 / 619; V = 81,928: 1,352 rows
+// 230 / 227), and so does the long-row kernel far beyond the 153,600 logits that stay on chip, where it
+// reads twice as well (V = 176,000: 1,024 rows 327 / 367; V = 200,000: 447 / 415; V = 262,144: 682 / 531).
+static bool streaming_suits_diagnostics(int V, int64_t n_adm) {
+  const int64_t mib = 4 * n_adm * V >> 20;
+  const bool third_round = n_adm > 512 && n_adm <= 560;
+  if (V <= short_row_limit(1024))
+    return V > short_row_limit(512) && n_adm > 256 && (V <= 51200 || third_round || (V <= 69632 && mib < 240));
+  if (V <= 86016 || V > 180224) return true;
+  return n_adm <= 256 ? n_adm <= 216 : mib < 256 || third_round;
+}
+
+// Pieces per row of a call of few rows of more than 81,920 logits; 0: not split.  A piece fits the
+// registers of a workgroup; a call of very few rows takes as many as give every compute unit one.  At
+// V = 151,936 the pieces cost 20 us and 0.24 us per row, the long-row kernel 47 us per round of 256
+// rows and 15 besides (all scale with V), so that pieces also serve a few rows more than one round.  us,
+// pieces / long-row: V = 151,936: 32 rows 28 / 54, 128 rows 52 / 61, 156 rows 59 / 62, 200 rows 72 / 65,
+// 257 rows 84 / 105, 352 rows 106 / 113, 400 rows 124 / 120; V = 102,400: 128 rows 45 / 48, 156 rows 51 / 48;
+// V = 81,928: 128 rows 42 / 44, 156 rows 47 / 44.  With diagnostics the second window is the streaming
+// kernel's on shorter rows, pieces / streaming: V = 136,000: 300 rows 90 / 87; V = 151,936: 352 rows 110 / 113.
+static int row_splits(int V, int64_t n_adm, bool diag, int64_t room) {
+  if (n_adm <= 0 || V <= short_row_limit(1024)) return 0;
+  const bool few = n_adm <= (V < 122880 ? 140 : 156), one_round_more = n_adm > 256 && n_adm <= 352;
+  if (!few && !(one_round_more && (!diag || V > 144000))) return 0;
   int splits = (V + short_row_limit(256) - 1) / short_row_limit(256);
   const int64_t fill = 256 / n_adm < 16 ? 256 / n_adm : 16;
   if (splits < fill) splits = (int)fill;
@@ -864,21 +893,19 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
     a.t_logp = p->t_logp; a.t_entropy = p->t_entropy; a.t_rank = p->t_rank;
     a.sampled = p->estimator == ADWIN_EST_SAMPLED;
     PhaseScope scope(timer, ADWIN_PHASE_STATS);
-    const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING;
     a.part = (float*)(ws + L.total);
     a.n_adm = hp.n_adm;
     const size_t room = (workspace_bytes - L.total) / kPieceBytes;
     const bool diag = p->t_logp || p->t_entropy || p->t_rank;
-    a.splits = p->scheme == ADWIN_LOGITS_AUTO && p->V > short_row_limit(1024)
-                   ? row_splits(p->V, hp.n_adm, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
+    const bool automatic = p->scheme == ADWIN_LOGITS_AUTO;
+    a.splits = automatic ? row_splits(p->V, hp.n_adm, diag, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
+    const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING ||
+                           (automatic && diag && a.splits == 0 && streaming_suits_diagnostics(p->V, hp.n_adm));
     if (!streaming && p->V <= short_row_limit(1024)) {
       ADWIN_HIP_TRY(diag ? launch_short_rows<true>(a, stream) : launch_short_rows<false>(a, stream));
     } else if (a.splits > 0) {
       ADWIN_HIP_TRY(diag ? launch_split_rows<true>(a, stream) : launch_split_rows<false>(a, stream));
-    } else if (streaming || (diag && hp.n_adm > 352 && hp.n_adm <= 440)) {
-      // diagnostics: a little over one round of the compute units is where the two workgroups that
-      // the streaming kernel has on each make up for reading twice (400 rows of V = 151,936:
-      // 118 us against 128; 1,352 rows 448 / 370, 12,226 rows 4162 / 3168)
+    } else if (streaming) {
       if (diag) logits_row_kernel<true><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
       else logits_row_kernel<false><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
     } else {

@@ -98,9 +98,9 @@ def test_long_rows_with_diagnostics_match_oracle(B, V):  # noqa: F811
     assert got["t_rank"][1] == 0 and not got["t_entropy"][1]
 
 
-@pytest.mark.parametrize("V,n_adm", [(81928, 1), (81928, 15), (102408, 156), (81928, 157), (163848, 31), (81928, 257)])
+@pytest.mark.parametrize("V,n_adm", [(81928, 1), (81928, 15), (102408, 156), (122880, 156), (81928, 157), (163848, 31), (81928, 257)])
 def test_split_rows_match_whole_rows(B, V, n_adm):  # noqa: F811
-    """Few long rows are cut into pieces (up to 156 rows, and where a second round of the compute
+    """Few long rows are cut into pieces (up to 140 or 156 rows, and where a second round of the compute
     units would be nearly empty); the same rows served whole differ by the order of fp32 sums."""
     g = torch.Generator().manual_seed(n_adm)
     off = np.array([0, 2, 2, 2 + n_adm, 5 + n_adm], np.int64)
@@ -154,7 +154,7 @@ def test_diagnostics_are_as_accurate_as_the_streaming_kernel(B, V, rows):  # noq
 
 @pytest.mark.parametrize("V,n_adm,scheme", [
     (5120, 20, "AUTO"), (20480, 20, "AUTO"), (81920, 5, "AUTO"),      # a row's logits in registers
-    (81928, 15, "AUTO"), (151936, 29, "AUTO"), (102408, 156, "AUTO"),  # rows cut into pieces
+    (81928, 15, "AUTO"), (151936, 29, "AUTO"), (122880, 156, "AUTO"),  # rows cut into pieces
     (151936, 9, "RESIDENT"), (163848, 9, "RESIDENT"), (81928, 9, "STREAMING"),
 ])
 def test_gradient_in_place(B, V, n_adm, scheme):  # noqa: F811
@@ -182,3 +182,47 @@ def test_gradient_in_place(B, V, n_adm, scheme):  # noqa: F811
                 outs.append({k: v.clone() for k, v in call.out.items()})
             for k in outs[0]:
                 assert torch.equal(outs[0][k].view(torch.uint8), outs[1][k].view(torch.uint8)), (k, est, which)
+
+
+def _long_rows(V, n, seed):
+    g = torch.Generator("cuda").manual_seed(seed)
+    z = [torch.randn((n, V), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2)]
+    return z, torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+
+
+def test_resident_scheme_holds_for_any_number_of_rows(B):  # noqa: F811
+    """An explicit scheme is the caller's choice: the long-row kernel's bits for 400 rows with
+    diagnostics are those of the same rows in a call of 500, and AUTO, which takes the faster kernel for
+    either, stays with the streaming kernel for the 400."""
+    z, ids = _long_rows(151936, 500, 7)
+
+    def run(n, scheme):
+        out = B.adwin_opd_from_logits(z[0][:n], z[1][:n], ids[:n], np.array([0, n]), np.array([n], np.int32),
+                                      reduction=O.RED_SUM, scheme=scheme, want=BASE + DIAG)
+        return {k: out[k][:400] for k in ("kl", "c", "dz") + DIAG}
+
+    few, many = run(400, B.ADWIN_LOGITS_RESIDENT), run(500, B.ADWIN_LOGITS_RESIDENT)
+    auto, streaming = run(400, B.ADWIN_LOGITS_AUTO), run(400, B.ADWIN_LOGITS_STREAMING)
+    for k in few:
+        assert torch.equal(few[k].view(torch.uint8), many[k].view(torch.uint8)), k
+        assert torch.equal(auto[k].view(torch.uint8), streaming[k].view(torch.uint8)), k
+
+
+@pytest.mark.parametrize("V,n", [
+    (40968, 256), (40968, 257), (51200, 300), (51208, 300), (69632, 257), (69640, 257), (69632, 903), (69632, 904),
+    (69640, 512), (81920, 513), (81920, 561),
+    (81928, 140), (81928, 141), (86016, 256), (86024, 216), (86024, 217), (86024, 257), (86024, 780), (86024, 781),
+    (144000, 352), (144008, 352), (144008, 353), (151936, 156), (151936, 157), (180224, 256), (180232, 256),
+    (131072, 513), (131072, 561),
+])
+def test_automatic_route_with_diagnostics(B, V, n):  # noqa: F811
+    """On both sides of each line of the rule, AUTO gives the row outputs of the streaming kernel."""
+    z, ids = _long_rows(V, n, V + n)
+    off, win = np.array([0, n]), np.array([n], np.int32)
+    auto, ref = (B.adwin_opd_from_logits(*z, ids, off, win, reduction=O.RED_SUM, scheme=s, want=BASE + DIAG)
+                 for s in (B.ADWIN_LOGITS_AUTO, B.ADWIN_LOGITS_STREAMING))
+    assert torch.equal(auto["t_rank"], ref["t_rank"])
+    # fp32 sums in another order: KL and entropy of unit-variance logits lie near 1 and ln V
+    for k in ("kl", "c", "t_entropy", "t_logp"):
+        assert torch.allclose(auto[k], ref[k], rtol=2e-6, atol=1e-5), k
+    assert torch.allclose(auto["dz"].float(), ref["dz"].float(), rtol=2 * Hp.BF16_ULP, atol=1e-6 * float(ref["dz"].float().abs().max()))
