@@ -170,7 +170,10 @@ __device__ __forceinline__ void rollout_body(const BatchArgs& a, int i, double* 
 }
 
 // One workgroup: batch objectives, micro (after aggregation) and macro (mean of
-// per-rollout) alignment, integer outputs.
+// per-rollout) alignment, integer outputs.  The sums over the rollouts run in index order, their
+// terms loaded kBatchStep rollouts ahead: one round trip per rollout made the aggregates of 200
+// rollouts at H = 1536 635 us.
+constexpr int kBatchStep = 16;
 __device__ __forceinline__ void batch_body(const BatchArgs& a, double* sh) {
   const int B = a.B;
   const bool align = a.probe && !a.zero_grad;
@@ -201,10 +204,20 @@ __device__ __forceinline__ void batch_body(const BatchArgs& a, double* sh) {
     block_sum256<2>(mf, sh);
     for (int h = threadIdx.x; h < a.H; h += 256) {
       double sp = 0.0, sf = 0.0;
-#pragma unroll 4
-      for (int i = 0; i < B; ++i) {
-        sp += (double)a.pl.alpha_p[i] * (double)a.up[(size_t)i * a.H + h];
-        sf += (double)a.pl.alpha_f[i] * (double)a.uf[(size_t)i * a.H + h];
+      for (int i0 = 0; i0 < B; i0 += kBatchStep) {
+        float p[kBatchStep], f[kBatchStep];
+#pragma unroll
+        for (int q = 0; q < kBatchStep; ++q) {
+          const int i = i0 + q < B ? i0 + q : B - 1;
+          p[q] = a.up[(size_t)i * a.H + h];
+          f[q] = a.uf[(size_t)i * a.H + h];
+        }
+#pragma unroll
+        for (int q = 0; q < kBatchStep; ++q)
+          if (i0 + q < B) {
+            sp += (double)a.pl.alpha_p[i0 + q] * (double)p[q];
+            sf += (double)a.pl.alpha_f[i0 + q] * (double)f[q];
+          }
       }
       m[0] += sp * sf;
       m[1] += sp * sp;
@@ -314,10 +327,21 @@ __device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double
   if (!a.zero_grad) {
     for (int h = threadIdx.x; h < a.H; h += 256) {
       double sp = 0.0, sf = 0.0;
-#pragma unroll 4
-      for (int i = 0; i < B; ++i) {
-        sp += (i < kCandLds ? alpha_lds[i] : alpha(i)) * (double)a.uc[((int64_t)k * B + i) * a.H + h];
-        sf += (double)a.pl.alpha_f[i] * (double)a.uf[(int64_t)i * a.H + h];
+      for (int i0 = 0; i0 < B; i0 += kBatchStep) {
+        float p[kBatchStep], f[kBatchStep];
+#pragma unroll
+        for (int q = 0; q < kBatchStep; ++q) {
+          const int i = i0 + q < B ? i0 + q : B - 1;
+          p[q] = a.uc[((int64_t)k * B + i) * a.H + h];
+          f[q] = a.uf[(int64_t)i * a.H + h];
+        }
+#pragma unroll
+        for (int q = 0; q < kBatchStep; ++q)
+          if (i0 + q < B) {
+            const int i = i0 + q;
+            sp += (i < kCandLds ? alpha_lds[i] : alpha(i)) * (double)p[q];
+            sf += (double)a.pl.alpha_f[i] * (double)f[q];
+          }
       }
       m[0] += sp * sf;
       m[1] += sp * sp;
@@ -409,9 +433,17 @@ __device__ __forceinline__ void summary_batch_body(const SummaryArgs& a) {
   const int tid = threadIdx.x;
   if (a.loss_share && tid < a.K) {
     double part = 0.0, tot = 0.0;
-    for (int i = 0; i < a.B; ++i) {
-      part += a.acc[(size_t)i * kSummarySlots + tid];
-      tot += a.acc[(size_t)i * kSummarySlots + ADWIN_MAX_CANDIDATES];
+    for (int i0 = 0; i0 < a.B; i0 += kBatchStep) {
+      double p[kBatchStep], t[kBatchStep];
+#pragma unroll
+      for (int q = 0; q < kBatchStep; ++q) {
+        const double* acc = a.acc + (size_t)(i0 + q < a.B ? i0 + q : a.B - 1) * kSummarySlots;
+        p[q] = acc[tid];
+        t[q] = acc[ADWIN_MAX_CANDIDATES];
+      }
+#pragma unroll
+      for (int q = 0; q < kBatchStep; ++q)
+        if (i0 + q < a.B) { part += p[q]; tot += t[q]; }
     }
     a.loss_share[tid] = tot != 0.0 ? (float)(part / tot) : 0.f;
   }
@@ -419,11 +451,20 @@ __device__ __forceinline__ void summary_batch_body(const SummaryArgs& a) {
     const int c = tid - 32;
     double sum = 0.0;
     int64_t cnt = 0;
-    for (int i = 0; i < a.B; ++i) {
-      const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
-      const int64_t n = a.pl.n[i], m = a.probe ? len : n;
-      sum += a.acc[(size_t)i * kSummarySlots + ADWIN_MAX_CANDIDATES + 1 + c];
-      cnt += c == 0 ? n : m - n;
+    for (int i0 = 0; i0 < a.B; i0 += kBatchStep) {
+      double v[kBatchStep];
+      int64_t k[kBatchStep];
+#pragma unroll
+      for (int q = 0; q < kBatchStep; ++q) {
+        const int i = i0 + q < a.B ? i0 + q : a.B - 1;
+        const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
+        const int64_t n = a.pl.n[i], m = a.probe ? len : n;
+        v[q] = a.acc[(size_t)i * kSummarySlots + ADWIN_MAX_CANDIDATES + 1 + c];
+        k[q] = c == 0 ? n : m - n;
+      }
+#pragma unroll
+      for (int q = 0; q < kBatchStep; ++q)
+        if (i0 + q < a.B) { sum += v[q]; cnt += k[q]; }
     }
     a.logp_mean[2 * a.B + c] = cnt > 0 ? (float)(sum / (double)cnt) : 0.f;
   }
