@@ -106,8 +106,12 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
   while (!forced && first > 4096 && first - 2048 >= n_pad) first -= 2048;
   for (int64_t r = first; r >= (forced ? first : 4096); r -= 2048) {
     const int64_t slab = r < n_pad ? r : n_pad;
-    // pieces only where one slab holds every row: the partial planes cover all rows of the call
-    const int most = slab == n_pad ? (nk < kMaxSplit ? nk : kMaxSplit) : 1;
+    // the partial planes hold all rows of the call, so a call of several slabs takes no more pieces than
+    // fill one round.  us per call, whole tiles / pieces: 18,000 rows, H_s = 128, V = 50,000 4585 / 3376;
+    // 20,000 rows, H_s = 256, V = 151,936 18582 / 14667; H_s = 512, V = 11,912 1553 / 1259
+    const int64_t fill = 256 / ((slab / kGradTile) * h_tiles);
+    const int64_t limit = slab == n_pad ? kMaxSplit : forced ? 1 : fill;
+    const int most = (int)(limit > nk ? nk : limit > 1 ? limit : 1);
     for (int ks = 1; ks <= most; ++ks) {
       double cost = ks > 1 ? (double)ks * ((double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 + 0.2) : 0.0;
       for (int64_t r0 = 0; r0 < n_pad; r0 += slab) {

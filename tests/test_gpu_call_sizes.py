@@ -88,3 +88,33 @@ def test_strips_cost_no_accuracy(B, monkeypatch, V, H_s, H_t, rows):  # noqa: F8
     base = errors()
     for k in ref:
         assert got[k] <= 1.05 * base[k], (k, got[k], base[k])
+
+
+@pytest.mark.parametrize("estimator", [O.EST_EXPECTED, O.EST_SAMPLED])
+@pytest.mark.parametrize("H_s,rows", [(128, 16385), (256, 20000), (512, 16640)])
+def test_pieces_in_calls_of_several_slabs(B, monkeypatch, H_s, rows, estimator):  # noqa: F811
+    """A call of several slabs whose output tiles leave compute units idle cuts the contraction into
+    pieces as well; whole tiles (a forced slab size) give the same gradient up to the order of fp32 sums,
+    4,104 terms of which the partial sums are exact to 2^-24 each."""
+    w = synth.Workload(f"slabs_{H_s}_{rows}", 4104, H_s, 128, synth._offsets([rows - 300, 300]),
+                       np.array([rows, 300], np.int32), synth.MODE_PREFIX_AND_FULL)
+    d = synth.hidden_problem(w, "cuda")
+
+    def call():
+        c = B.FusedCall(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window, mode=w.mode,
+                        estimator=estimator, reduction=O.RED_SUM)
+        assert c.run() == 0
+        torch.cuda.synchronize()
+        return c
+
+    got = call()
+    info = B.adwin_opd_fused_launch_info(got.p)
+    assert info["slabs"] > 1
+    monkeypatch.setenv("ADWIN_SLAB_ROWS", str(info["slab_rows"]))
+    whole = call()
+    assert got.workspace_bytes > whole.workspace_bytes          # planes of partial sums
+    for k in ("dh_prefix", "dh_full"):
+        a, b = got.out[k], whole.out[k]
+        assert (a - b).abs().max() <= 4104 ** 0.5 * 2.0 ** -24 * 8 * b.abs().max()
+    for k in ("rho_pooled", "rho_field"):
+        assert torch.allclose(got.out[k], whole.out[k], rtol=1e-5, atol=1e-6)
