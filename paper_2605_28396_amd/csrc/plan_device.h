@@ -36,8 +36,11 @@ struct SetupArgs {
       : plan(ws_plan), B(rollouts), o_comp_off((int64_t)PlanBlobLayout(rollouts).o_comp_off) {}
   void clear(void* words, int64_t n) {  // NULL: an output that is not wanted
     if (!words || n <= 0) return;
-    zero[n_zero] = (uint32_t*)words;
-    zero_n[n_zero++] = n;
+    if (n_zero < kMaxZero) {            // one too many is counted, and refused by launch_setup
+      zero[n_zero] = (uint32_t*)words;
+      zero_n[n_zero] = n;
+    }
+    ++n_zero;
   }
 };
 hipError_t launch_setup(const SetupArgs& a, const std::vector<unsigned char>& blob, hipStream_t st);

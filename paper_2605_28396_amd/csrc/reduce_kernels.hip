@@ -635,6 +635,7 @@ __global__ __launch_bounds__(256) void setup_kernel(const SetupArgs a) { setup_b
 
 hipError_t launch_setup(const SetupArgs& a, const std::vector<unsigned char>& blob, hipStream_t st) {
   static_assert(sizeof(SetupArgs) + sizeof(SetupBlob) < 4096, "kernel arguments");
+  if (a.n_zero > SetupArgs::kMaxZero) return hipErrorInvalidValue;
   int64_t most = a.n_pad > 1 ? a.n_pad : 1;
   for (int z = 0; z < a.n_zero; ++z) most = a.zero_n[z] > most ? a.zero_n[z] : most;
   const int64_t blocks = (most + 255) / 256;
