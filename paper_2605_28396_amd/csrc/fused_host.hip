@@ -135,8 +135,10 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
 // 3800 / 3781.
 // The statistics-only sweep writes no factors, so its loads are a larger share of its time and the
 // images are worth 2.4 % of it (64 tiles, H = 2048 + 4096: 23.3 against 23.9 ms): `loads_bound`
-// moves the line to where that meets the 0.75 ms.  So does the diagnostics sweep that writes both
-// factors, whose direct form has no registers to spare.  134 tiles, statistics: 50.9 -> 50.4 ms.
+// moves the line to where that meets the 0.75 ms.  134 tiles, statistics: 50.9 -> 50.4 ms.  The
+// diagnostics sweep that writes both factors shares it, direct against images, ms: H = 2048 + 4096, 64
+// tiles 36.44 / 36.53, 85 tiles 49.31 / 49.15, 128 tiles 73.03 / 72.58; H = 1024 + 1024 (V = 32,776), 28
+// tiles 1.785 / 1.826; H = 256 + 384, 9 tiles 1.508 / 1.559, 32 tiles 5.140 / 5.134.
 static bool stage_w_directly(int64_t n_tiles, int H_s, int H_t, bool loads_bound) {
   return n_tiles * (loads_bound ? 72 : 40) <= H_s + H_t;
 }

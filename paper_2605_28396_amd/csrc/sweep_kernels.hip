@@ -643,7 +643,22 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   auto rows_w = [&](int vt, int H, uint32_t row0) __attribute__((always_inline)) {
     if constexpr (DIRECT) {
       const int left = a.V - vt * kTileVocab;
-      if (left >= kTileVocab) {
+      if constexpr (MODE == kModeSingleDiag) {
+        // The sweep with the most state: e0, the chunk and both row0 are formed from the lane number
+        // again for each head of a tile (the asm hides that they could be kept).  Kept, they were the
+        // registers that made it spill 13: V = 32,776, H = 1024 + 1024, 28 token tiles 1842 -> 1808 us
+        // per call, H = 512 + 640 (V = 11,912, 13 tiles) 287 -> 278.  The others have the registers
+        // and lose up to 1 % this way.
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int e = 16 * (l >> 5) + 4 * wave + ((l >> 3) & 3);
+        const uint32_t c = (uint32_t)((l & 7) ^ ((4 * wave + (l >> 4)) & 7)) * 16u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int v = 32 * i + e < left ? 32 * i + e : left - 1;
+          voffa[i] = (uint32_t)v * ((uint32_t)H * 2u) + c;
+        }
+      } else if (left >= kTileVocab) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) voffa[i] = row0 + (uint32_t)(i * 64 * H);
       } else {

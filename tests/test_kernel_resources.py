@@ -14,7 +14,6 @@ LLVM = "/opt/rocm/llvm/bin"
 ALLOWED = {
     # 75 + 36 vectors of a row held in registers: four of them do not fit
     "logits_row_resident_kernelILb0EE": 20,
-    "logit_pass_dma_kernelILi3ELb1EE": 36,
 }
 
 
