@@ -133,6 +133,9 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
 // 35620 / 35884, 128 tiles 70313 / 70595, 256 tiles 140609 / 140325; H = 256 + 384, 16 tiles
 // 2359 / 2387, 64 tiles 9396 / 9357; H = 1024 + 1024 (V = 32,776), 16 tiles 1062 / 1112, 64 tiles
 // 3800 / 3781.
+// The two-sweep scheme walks W twice and stages the same tiles: 54628 / 54634 at 64 tiles, 109372 /
+// 110366 at 128 and 136430 / 138157 at 160 of H = 2048 + 4096; 3376 / 3358 at 16 and 4119 / 4130 at 24 of
+// H = 256 + 384: within 1 % of each other on both sides of the line.
 // The statistics-only sweep writes no factors, so its loads are a larger share of its time and the
 // images are worth 2.4 % of it (64 tiles, H = 2048 + 4096: 23.3 against 23.9 ms): `loads_bound`
 // moves the line to where that meets the 0.75 ms.  134 tiles, statistics: 50.9 -> 50.4 ms.  The

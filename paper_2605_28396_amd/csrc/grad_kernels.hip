@@ -450,9 +450,8 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
 // it wrote 8 bytes per lane (291,000 rows cleared at 3.4 TB/s, 350 us).  A row of more than 512
 // columns with several planes takes 256 threads, its planes are loaded eight at a time and the
 // dot products of its heavy entries are split over all of them.  Narrower rows take a wave, and so do
-// rows of one plane, which the GEMM has only where there are thousands: 256 threads for two 16-byte
-// loads each spend their time at the barriers (65,536 rows, H = 2048, with 212,000 cleared: the
-// reductions of the call 882 -> 735 us on one GPU).
+// rows of one plane: 256 threads for two 16-byte loads each spend their time at the barriers
+// (65,536 rows, H = 2048, with 212,000 cleared: the reductions of the call 882 -> 735 us on one GPU).
 // 337 rows of 32 planes: 98 -> 19 us; 4,096 computed and 291,000 cleared rows: 350 -> 209 us.
 // ---------------------------------------------------------------------------------------
 constexpr int kZeroRows = 32;
@@ -629,7 +628,8 @@ hipError_t launch_grad_gemm(const GradArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t st) {
-  const bool wide = a.H > 512 && a.ksplit > 1;     // one plane: there are rows enough for a wave each
+  // one plane: thousands of rows, or a vocabulary so small that a row has nothing to add up; a wave each
+  const bool wide = a.H > 512 && a.ksplit > 1;
   const int64_t row_blocks = wide ? a.n_rows : (a.n_rows + 3) / 4;
   const int64_t zero_blocks = !a.probe && a.dh_prefix ? (a.T + kZeroRows - 1) / kZeroRows : 0;
   const unsigned grid = (unsigned)(row_blocks + zero_blocks);

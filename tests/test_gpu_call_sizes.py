@@ -1,5 +1,7 @@
 """Calls of few rows: the launch geometry, the operand staging and the split of the work follow
 the number of token tiles, so the sizes on both sides of each rule are compared with the oracle."""
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -7,7 +9,7 @@ import torch
 from oracle import adwin_oracle as O
 from paper_2605_28396_amd import synth
 from tests import helpers as Hp
-from tests.test_gpu_parity import B, _check_fused, _run_fused  # noqa: F401  (B is a fixture)
+from tests.test_gpu_parity import B, _check_fused, _grad_l2, _run_fused, _teacher_reference  # noqa: F401  (B is a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -33,12 +35,13 @@ def test_few_rows_match_oracle(B, V, H_s, H_t, lens, win, estimator):  # noqa: F
         _check_fused(w, got, ref, O.RED_SEQ_MEAN)
 
 
-def test_wide_rows_of_one_plane_match_oracle(B, monkeypatch):  # noqa: F811
+@pytest.mark.parametrize("V", [104, 4104])
+def test_wide_rows_of_one_plane_match_oracle(B, monkeypatch, V):  # noqa: F811
     """Rows of more than 512 columns whose gradient GEMM is not split (several slabs): a wave
-    each.  V is that of the other cases: at a hundred entries a gradient element is a handful of terms
-    with up to three roundings of 2^-9 each, 5.9e-3 against the bound of 2e-3."""
+    each.  Held to the bound of their own summands, which is the one that knows that at a hundred
+    entries a gradient element is a handful of terms with up to three roundings of 2^-9 each."""
     monkeypatch.setenv("ADWIN_SLAB_ROWS", "256")
-    w = synth.Workload("wide_rows", 4104, 576, 192, synth._offsets([300, 41]), np.array([289, 41], np.int32),
+    w = synth.Workload("wide_rows", V, 576, 192, synth._offsets([300, 41]), np.array([289, 41], np.int32),
                        synth.MODE_PREFIX_AND_FULL)
     p = synth.hidden_problem(w)
     f = Hp.oracle_inputs(p)
@@ -46,7 +49,7 @@ def test_wide_rows_of_one_plane_match_oracle(B, monkeypatch):  # noqa: F811
         ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
                           reduction=O.RED_SEQ_MEAN, mode=w.mode, estimator=estimator)
         got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator)
-        _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+        _check_fused(w, got, ref, O.RED_SEQ_MEAN, grad_l2=_grad_l2(f, w, ref, O.RED_SEQ_MEAN, estimator=estimator))
 
 
 def _kl_in_64_bits(d, V):
@@ -118,3 +121,46 @@ def test_pieces_in_calls_of_several_slabs(B, monkeypatch, H_s, rows, estimator):
         assert (a - b).abs().max() <= 4104 ** 0.5 * 2.0 ** -24 * 8 * b.abs().max()
     for k in ("rho_pooled", "rho_field"):
         assert torch.allclose(got.out[k], whole.out[k], rtol=1e-5, atol=1e-6)
+
+
+STATS = ("kl", "c", "loss_prefix", "n_out", "n_adm_out", "status_dev")
+DIAGNOSTICS = ("t_logp", "t_entropy", "t_rank")
+H_SUM = 128 + 192
+
+
+@functools.lru_cache(maxsize=2)
+def _staging_problem(rows, estimator):
+    w = synth.Workload(f"staging_{rows}", 4104, 128, 192, synth._offsets([rows - 100, 100]),
+                       np.array([rows, 100], np.int32), synth.MODE_PREFIX_ONLY)
+    p = synth.hidden_problem(w)
+    f = Hp.oracle_inputs(p)
+    ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                      reduction=O.RED_SEQ_MEAN, mode=w.mode, estimator=estimator)
+    return w, p, ref, _teacher_reference(f["h_t"] @ f["W_t"].T, f["ids"], list(ref["rows"]), 1e-4)
+
+
+@pytest.mark.parametrize("images", [False, True])
+@pytest.mark.parametrize("what,line", [("train", 40), ("train_diag", 72), ("stats", 72), ("stats_diag", 72),
+                                       ("sampled", 40), ("sampled_diag", 40), ("two_sweep", 40)])
+def test_both_stagings_of_every_sweep_mode(B, what, line, images):  # noqa: F811
+    """The most token tiles whose W tiles come from the row-major weights, (H_s + H_t) / line, and one
+    more, which takes tile images: every mode of the sweep in both forms against the oracle."""
+    rows = H_SUM // line * 256 + (1 if images else 0)
+    estimator = O.EST_SAMPLED if what.startswith("sampled") else O.EST_EXPECTED
+    w, p, ref, (ent, logp, lo, hi) = _staging_problem(rows, estimator)
+    stats, diag = what.startswith("stats"), what.endswith("diag")
+    want = (STATS if stats else B.FusedCall.DEFAULT_OUTPUTS) + (DIAGNOSTICS if diag else ())
+    got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator, want=want,
+                     scheme=B.ADWIN_SCHEME_TWO_SWEEP if what == "two_sweep" else B.ADWIN_SCHEME_AUTO)
+    if stats:
+        assert int(got["status_dev"][0]) == 0 and int(got["n_adm_out"][0]) == ref["n_adm"]
+        Hp.assert_kl(got["kl"], ref["kl"])
+        Hp.assert_cost(got["c"], ref["c"])
+        Hp.assert_close_rel(got["loss_prefix"], ref["loss_prefix"], Hp.LOSS_REL, "loss_prefix")
+    else:
+        _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+    if diag:
+        for t in ref["rows"]:
+            assert abs(got["t_entropy"][t] - ent[t]) <= 1e-3
+            assert abs(got["t_logp"][t] - logp[t]) <= 1e-3 * max(1.0, abs(logp[t]))
+            assert lo[t] <= got["t_rank"][t] <= hi[t], (t, got["t_rank"][t], lo[t], hi[t])
