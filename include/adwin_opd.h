@@ -326,7 +326,10 @@ int adwin_opd_probe_staleness(int32_t* age, const uint8_t* pending, int32_t n_pr
                               uint8_t* force, int32_t* n_forced);
 
 /* Bytes of device workspace adwin_opd_fused needs for this problem.  Pure host; reads
- * shapes, mode, offsets and window only. */
+ * shapes, mode, scheme, estimator, offsets, window and which outputs are wanted.  Never less for a
+ * problem of more computed rows and otherwise the same numbers, and the same with or without kl, c,
+ * t_logp, t_entropy and t_rank beside an output that needs gradients: a workspace for the largest call
+ * of a program serves the others. */
 int adwin_opd_workspace_bytes(const adwin_opd_problem* p, size_t* bytes);
 
 /* Launch geometry adwin_opd_fused will use for this problem (pure host; for benchmarks that

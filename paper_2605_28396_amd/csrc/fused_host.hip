@@ -2,6 +2,7 @@
 // that makes one call (Sec. 4.1: supervision on the admitted prefix; Sec. 4.2: the probe
 // audit against the full-rollout gradient).  The kernels are in sweep_kernels.hip,
 // grad_kernels.hip and reduce_kernels.hip; nothing here touches device memory itself.
+#include <cmath>
 #include <optional>
 #include <utility>
 #include <vector>
@@ -95,12 +96,34 @@ static int sweep_strips(int n_tiles, int vt_total) {
 // output tile of 2374 k-steps (256 rows, H_s = 256) takes 95, call 250 -> 214 us against
 // 32; two tiles 489 -> 458 us; 3,100 rows of 188 k-steps and H_s = 512 take 9, 302 -> 290 us.
 constexpr int kMaxSplit = 128;
+constexpr int64_t kMaxSlab = 16384;
+
+// What bounds the pieces and sizes the workspace for them: pieces times token tiles, for a call of up
+// to `n_tiles` tiles.  It grows with n_tiles, which the number of pieces that suits a call does not (64
+// tiles of H_s = 2048 take 2, 36 tiles 8), so that a workspace for the largest call of a program holds
+// every smaller one.  The optimum lies below 1.9 sqrt(nk) pieces (the cost of a piece is at least 0.28
+// k-steps), below one round of output tiles, or, where a few rounds are filled, below 12 pieces;
+// calls of several slabs take what fills a round.
+static int64_t most_split_tiles(int64_t n_tiles, int h_tiles, int nk) {
+  const int root = 2 + (int)(2.0 * sqrt((double)nk));
+  int64_t pieces = root < kMaxSplit ? root : kMaxSplit;
+  if (pieces > nk) pieces = nk;
+  const int64_t slab_tiles = n_tiles < kMaxSlab / kTileTokens ? n_tiles : kMaxSlab / kTileTokens;
+  int64_t most = 256 / h_tiles > 12 * slab_tiles ? 256 / h_tiles : 12 * slab_tiles;
+  if (most > pieces * slab_tiles) most = pieces * slab_tiles;
+  int64_t fill = 16 / h_tiles < 12 ? 16 / h_tiles : 12;          // slabs of 4,096 rows: 16 tiles
+  if (fill > pieces) fill = pieces;
+  const int64_t several = n_tiles * (fill > 1 ? fill : 1);
+  return several > most ? several : most;
+}
+
 struct GradGeometry { int64_t slab_rows; int ksplit; };
 static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
   GradGeometry best{0, 1};
   double least = -1.0;
   const bool forced = getenv("ADWIN_SLAB_ROWS") != nullptr;
-  int64_t first = forced ? (int64_t)align_up((size_t)env_int("ADWIN_SLAB_ROWS", 8192), kTileTokens) : 16384;
+  const int64_t room = most_split_tiles(n_pad / kTileTokens, h_tiles, nk) / (n_pad / kTileTokens);
+  int64_t first = forced ? (int64_t)align_up((size_t)env_int("ADWIN_SLAB_ROWS", 8192), kTileTokens) : kMaxSlab;
   // one size that holds every row is enough: the larger ones are the same slab (seven searches of up
   // to 128 pieces each made a layout of 256 rows 4.7 us of host time, of which one leaves 1.9)
   while (!forced && first > 4096 && first - 2048 >= n_pad) first -= 2048;
@@ -110,7 +133,8 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
     // fill one round.  us per call, whole tiles / pieces: 18,000 rows, H_s = 128, V = 50,000 4585 / 3376;
     // 20,000 rows, H_s = 256, V = 151,936 18582 / 14667; H_s = 512, V = 11,912 1553 / 1259
     const int64_t fill = 256 / ((slab / kGradTile) * h_tiles);
-    const int64_t limit = slab == n_pad ? kMaxSplit : forced ? 1 : fill;
+    int64_t limit = slab == n_pad ? kMaxSplit : forced ? 1 : fill;
+    if (limit > room) limit = room;
     const int most = (int)(limit > nk ? nk : limit > 1 ? limit : 1);
     for (int ks = 1; ks <= most; ++ks) {
       double cost = ks > 1 ? (double)ks * ((double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 + 0.2) : 0.0;
@@ -157,7 +181,6 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   L.strips = strips;
   (void)resolve_scheme(p, &L.use_dma, &L.single);     // validity was checked with the problem
   const int halves = L.single ? 2 : 1;     // the single sweep stores two factors per logit
-  // (the gradient GEMM contracts one: the combined logit gradient, or E2 with the sampled estimator)
   const int h_tiles = (p->H_s + kGradTile - 1) / kGradTile;
   const GradGeometry gg = grad_geometry(n_pad, h_tiles, (int)(L.Vp / kBK));
   const int64_t slab = gg.slab_rows;
@@ -169,17 +192,18 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   L.o_plan = take(PlanBlobLayout(p->B).bytes);
   L.o_row_idx = take(sizeof(int32_t) * (size_t)n_pad);
   L.o_row_seq = take(sizeof(int32_t) * (size_t)n_pad);
-  // strip partials of the widest launch: the slabs are swept one after the other
-  int part_strips = strips;
-  for (int64_t r0 = 0; r0 < n_pad; r0 += slab) {
-    const int s = sweep_strips((int)((n_pad - r0 < slab ? n_pad - r0 : slab) / kTileTokens), vt_total);
-    if (s > part_strips) part_strips = s;
-  }
-  L.o_part = take(sizeof(float) * 5 * (size_t)part_strips * (size_t)n_pad);
+  // A program that sizes its workspace for its largest call, or with other outputs than the diagnostics,
+  // uses it for the others: no part may be larger in a smaller call.  The slab, the strips and the
+  // pieces that suit a call are not monotone in its rows, so their arrays are sized by bounds that are.
+  const int64_t bound_slab = n_pad < kMaxSlab ? n_pad : slab > kMaxSlab ? slab : kMaxSlab;
+  // strip partials: of one slab after the other (single sweep), or of all rows (two sweeps)
+  const int most_strips = vt_total < kMaxSweepStrips ? vt_total : kMaxSweepStrips;
+  L.o_part = take(sizeof(float) * 5 * (L.single ? (size_t)most_strips * (size_t)bound_slab
+                                                : (size_t)strips * (size_t)n_pad));
   L.o_ref_t2 = take(sizeof(float) * (size_t)n_pad);
   L.o_delta = take(sizeof(float) * (size_t)n_pad);
   L.o_mu0t = take((L.single && p->estimator != ADWIN_EST_SAMPLED)
-                      ? sizeof(float) * (size_t)vt_total * (size_t)slab : 0);
+                      ? sizeof(float) * (size_t)vt_total * (size_t)bound_slab : 0);
   L.o_invz = take(sizeof(float) * (size_t)n_pad);
   L.o_lse2 = take(sizeof(float) * (size_t)n_pad);
   L.o_mu = take(sizeof(float) * (size_t)n_pad);
@@ -188,14 +212,21 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   const bool both_factors_diag = (p->t_entropy || p->t_rank) && p->estimator != ADWIN_EST_SAMPLED;
   L.direct_w = stage_w_directly(n_pad / kTileTokens, p->H_s, p->H_t,
                                 (L.single && !needs_gradient(p)) || both_factors_diag);
-  L.o_wt_img = take(L.use_dma && !L.direct_w ? 2 * (size_t)L.Vp * (size_t)p->H_t : 0);
-  L.o_ws_img = take(L.use_dma && !L.direct_w ? 2 * (size_t)L.Vp * (size_t)p->H_s : 0);
+  // room for the images from the lower of the two lines on, whichever this call goes by
+  const bool w_images = L.use_dma && !stage_w_directly(n_pad / kTileTokens, p->H_s, p->H_t, true);
+  L.o_wt_img = take(w_images ? 2 * (size_t)L.Vp * (size_t)p->H_t : 0);
+  L.o_ws_img = take(w_images ? 2 * (size_t)L.Vp * (size_t)p->H_s : 0);
   L.o_ht_img = take(L.use_dma ? 2 * (size_t)n_pad * (size_t)p->H_t : 0);
   L.o_hs_img = take(L.use_dma ? 2 * (size_t)n_pad * (size_t)p->H_s : 0);
   // statistics-only calls (no output depends on the gradients) need neither the slab nor g
   const bool need_g = needs_gradient(p) || !L.single;
-  L.o_slab = take(need_g ? 2 * (size_t)halves * (size_t)slab * (size_t)L.Vp : 0);
-  L.o_g = take(need_g ? sizeof(float) * (size_t)ks * (size_t)halves * (size_t)n_pad * (size_t)p->H_s : 0);
+  L.o_slab = take(need_g ? 2 * (size_t)halves * (size_t)bound_slab * (size_t)L.Vp : 0);
+  // the planes of the pieces; with the sampled estimator behind n_pad rows for g itself, which
+  // finalize_kernel forms from the contracted E2
+  const bool sampled = L.single && p->estimator == ADWIN_EST_SAMPLED;
+  int64_t g_tiles = most_split_tiles(n_pad / kTileTokens, h_tiles, (int)(L.Vp / kBK));
+  if (g_tiles < ks * (n_pad / kTileTokens)) g_tiles = ks * (n_pad / kTileTokens);
+  L.o_g = take(need_g ? sizeof(float) * ((size_t)g_tiles * kTileTokens + (sampled ? (size_t)n_pad : 0)) * (size_t)p->H_s : 0);
   const size_t nch = (size_t)(hp.n_chunks > 0 ? hp.n_chunks : 1);
   L.o_pp = take(sizeof(float) * nch * (size_t)p->H_s);
   L.o_pf = take(sizeof(float) * nch * (size_t)p->H_s);
@@ -215,9 +246,9 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   // vocabulary tiles of 256 image rows: the last one may be half used (its upper rows are
   // never written, and their output rows do not exist)
   const size_t v_img = align_up((size_t)L.Vp, (size_t)kGradTile);
-  L.o_dzT_p = take(p->dW_prefix ? 2 * (size_t)slab * v_img : 0);
-  L.o_dzT_f = take(p->dW_full ? 2 * (size_t)slab * v_img : 0);
-  L.o_hsg = take(head ? 2 * (size_t)slab * (size_t)p->H_s : 0);
+  L.o_dzT_p = take(p->dW_prefix ? 2 * (size_t)bound_slab * v_img : 0);
+  L.o_dzT_f = take(p->dW_full ? 2 * (size_t)bound_slab * v_img : 0);
+  L.o_hsg = take(head ? 2 * (size_t)bound_slab * (size_t)p->H_s : 0);
   L.o_cosp = take((p->dW_prefix && p->dW_full) ? sizeof(double) * 3 * kCosineBlocks : 0);
   L.o_summ = take((p->t_first_reject || p->t_logp_mean || p->cand_loss_share)
                       ? sizeof(double) * (size_t)p->B * kSummarySlots : 0);
@@ -430,12 +461,13 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       // over the factors and the GEMM of dz with W_s.
       la.vt_total = vt_total;
       la.zy_t = (const float*)(ws + L.o_zy_t); la.yid = (const int32_t*)(ws + L.o_yid);
-      ga.g_rows = 2 * n_pad; ga.half_off = n_pad;
+      ga.g_rows = n_pad; ga.half_off = n_pad;
       for (int64_t r0 = 0; r0 < n_pad; r0 += L.slab_rows) {
         const int64_t rows = (n_pad - r0 < L.slab_rows) ? n_pad - r0 : L.slab_rows;
         la.tile0 = (int)(r0 / kTileTokens); la.n_tiles = (int)(rows / kTileTokens);
         la.e2_off = rows * L.Vp;
         la.strips = sweep_strips(la.n_tiles, vt_total);
+        la.part = (float*)(ws + L.o_part) - r0; la.n_pad = rows;       // partials of this slab's rows
         phase(ADWIN_PHASE_STATS);
         const int sweep_mode = !need_g ? (diag ? kModeSingleFwdDiag : kModeSingleFwd)
                                : sampled ? (diag ? kModeSingleE2Diag : kModeSingleE2)
@@ -444,7 +476,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         // this slab's rows are complete: KL_t, c_t, mu; then the logit gradient proper
         phase(ADWIN_PHASE_MERGE);
         MergeSingleArgs ms;
-        ms.m = m; ms.m.strips = la.strips;
+        ms.m = m; ms.m.strips = la.strips; ms.m.part = la.part; ms.m.n_pad = la.n_pad;
         ms.ref_s2 = la.ref_s2; ms.ref_t2 = la.ref_t2;
         ms.zy_s = (const float*)(ws + L.o_zy_s); ms.zy_t = la.zy_t; ms.yid = la.yid;
         ms.mu_out = (float*)(ws + L.o_delta); ms.inv_z = (float*)(ws + L.o_invz);
@@ -464,7 +496,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         ca.heavy = heavy;
         if (sampled) {       // contract the E2 factor; c_t and W_s[y_t] enter in finalize_kernel
           ga.slab = la.slab + la.e2_off;
-          ga.half_tiles = 0;                       // output rows in the second half of g
+          ga.half_tiles = 0;                       // output rows behind the n_pad of g
           if (head) {        // the transposed operand of the head-weight GEMMs; the slab stays as it is
             phase(ADWIN_PHASE_DZ);
             ADWIN_HIP_TRY(launch_combine(true, true, ca, ga.row_tiles, stream));
@@ -472,7 +504,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         } else {
           phase(ADWIN_PHASE_DZ);
           ADWIN_HIP_TRY(launch_combine(head, false, ca, ga.row_tiles, stream));
-          ga.half_tiles = ga.row_tiles;            // output rows in the first half of g
+          ga.half_tiles = ga.row_tiles;            // output rows are those of g
         }
         phase(ADWIN_PHASE_GRAD);
         ADWIN_HIP_TRY(launch_grad_gemm(ga, stream));
@@ -531,7 +563,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     FinalizeArgs f;
     f.pl = pl; f.B = p->B; f.T = p->T; f.probe = probe; f.n_rows = hp.n_rows;
     f.g = gws; f.ksplit = L.ksplit; f.n_pad = n_pad; f.H = p->H_s;
-    f.g_rows = L.single ? 2 * n_pad : n_pad;
+    f.g_rows = n_pad;
     f.inv_z = (const float*)(ws + L.o_invz);
     // the fp32 part of g; the sampled estimator contracts E2 as stored and lists nothing
     f.heavy = heavy;

@@ -274,8 +274,8 @@ struct FinalizeArgs {
   // heavy entries: fp32 part of g, from the row's lse_s and mu and fresh dot products
   HeavyList heavy; const float* lse_s; const float* mu;
   const __bf16* h_s; const __bf16* h_t; const __bf16* W_t; int H_t;
-  // sampled estimator (Eq. 4): g = c_t (W_s[y_t] - G2 inv_z), G2 = E2 W_s in the second half of
-  // g; cr NULL: g is the contraction of the logit gradient itself, in the first half
+  // sampled estimator (Eq. 4): g = c_t (W_s[y_t] - G2 inv_z), G2 = E2 W_s behind the n_pad rows of
+  // g; cr NULL: g is the contraction of the logit gradient itself (plane 0 once summed)
   const float* cr; const int32_t* ids; const __bf16* W_s; int V;
   float grad_scale; int dh_bf16;
   void* dh_prefix; void* dh_full;

@@ -542,7 +542,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
   __syncthreads();
   const float sp = admitted ? a.grad_scale * a.pl.alpha_p[i] : 0.f;
   const float sf = a.grad_scale * a.pl.alpha_f[i];
-  // sampled estimator: g = c (W_s[y] - G2 / Z_s), G2 in the second half of the planes
+  // sampled estimator: g = c (W_s[y] - G2 / Z_s), G2 in the planes, which lie behind the n_pad rows of g
   const float c = a.cr && have ? a.cr[r] : 0.f;
   const int64_t src = (a.cr ? a.n_pad + r : r) * a.H;
   int64_t y = 0;

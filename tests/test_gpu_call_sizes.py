@@ -115,7 +115,7 @@ def test_pieces_in_calls_of_several_slabs(B, monkeypatch, H_s, rows, estimator):
     assert info["slabs"] > 1
     monkeypatch.setenv("ADWIN_SLAB_ROWS", str(info["slab_rows"]))
     whole = call()
-    assert got.workspace_bytes > whole.workspace_bytes          # planes of partial sums
+    assert any(not torch.equal(got.out[k], whole.out[k]) for k in ("dh_prefix", "dh_full"))    # there are pieces
     for k in ("dh_prefix", "dh_full"):
         a, b = got.out[k], whole.out[k]
         assert (a - b).abs().max() <= 4104 ** 0.5 * 2.0 ** -24 * 8 * b.abs().max()

@@ -98,6 +98,35 @@ def _problem(mod, **over):
     return p
 
 
+GRADIENTS = dict(kl=4096, c=4096, dh_prefix=4096, batch=4096, status_dev=4096)
+
+
+@pytest.mark.parametrize("V,H_s,H_t", [(151936, 2048, 4096), (32776, 1024, 1024), (50000, 128, 256), (11912, 512, 640),
+                                       (4104, 128, 192), (104, 64, 64), (8000, 3584, 1024)])
+@pytest.mark.parametrize("outputs", [
+    GRADIENTS, dict(GRADIENTS, estimator=1), dict(GRADIENTS, dW_prefix=4096), dict(kl=4096, status_dev=4096),
+    dict(GRADIENTS, scheme=2), dict(GRADIENTS, scheme=3)], ids=["train", "sampled", "head", "stats", "two_sweep", "two_sweep_reg"])
+def test_workspace_of_the_largest_call_serves_the_others(B, V, H_s, H_t, outputs):
+    """A program lays its workspace out once, for the most rows that it will compute: no call of fewer
+    rows may need more, nor may one that wants the diagnostics as well (slabs, strips and pieces that
+    suit a call are not monotone in its rows)."""
+    if H_s < 128 and outputs.get("scheme") == 2:
+        pytest.skip("not offered for this shape")
+
+    def need(rows, **more):
+        off, win = np.array([0, rows], np.int64), np.array([rows], np.int32)
+        return B.adwin_opd_workspace_bytes(_problem(B, T=rows, B=1, V=V, H_s=H_s, H_t=H_t, offsets=off.ctypes.data,
+                                                    window=win.ctypes.data, **outputs, **more))
+
+    last = 0
+    for tiles in [*range(1, 135), *range(135, 520, 7)]:
+        n = need(256 * tiles)
+        assert n >= last, tiles
+        last = n
+        if outputs.get("scheme", 0) == 0 and H_s >= 128:
+            assert need(256 * tiles, t_entropy=4096, t_rank=4096, t_logp=4096) <= n, tiles
+
+
 def test_workspace_bytes_and_argument_errors_without_gpu(B):
     p = _problem(B)
     n = B.adwin_opd_workspace_bytes(p)
