@@ -118,7 +118,7 @@ static int64_t most_split_tiles(int64_t n_tiles, int h_tiles, int nk) {
 }
 
 struct GradGeometry { int64_t slab_rows; int ksplit; };
-static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
+static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk, double head_steps) {
   GradGeometry best{0, 1};
   double least = -1.0;
   const bool forced = getenv("ADWIN_SLAB_ROWS") != nullptr;
@@ -136,8 +136,12 @@ static GradGeometry grad_geometry(int64_t n_pad, int h_tiles, int nk) {
     int64_t limit = slab == n_pad ? kMaxSplit : forced ? 1 : fill;
     if (limit > room) limit = room;
     const int most = (int)(limit > nk ? nk : limit > 1 ? limit : 1);
+    // with the head gradient each slab beyond those that whole tiles need is one more pass over it.  V = 32,776,
+    // H = 1024 + 1024, us without / with this term: 16,640 rows 6012 / 5887, 51,200 rows 16745 / 16605
+    const double more_slabs = (double)((n_pad + slab - 1) / slab - (n_pad + kMaxSlab - 1) / kMaxSlab);
     for (int ks = 1; ks <= most; ++ks) {
-      double cost = ks > 1 ? (double)ks * ((double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 + 0.2) : 0.0;
+      double cost = ks > 1 ? (double)ks * ((double)n_pad * h_tiles * kGradTile * 8.0 / 6.4e6 + 0.2) +
+                                 more_slabs * head_steps : 0.0;
       for (int64_t r0 = 0; r0 < n_pad; r0 += slab) {
         const int64_t rows = n_pad - r0 < slab ? n_pad - r0 : slab;
         const int64_t rounds = ((rows / kGradTile) * h_tiles * ks + 255) / 256;
@@ -182,7 +186,9 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   (void)resolve_scheme(p, &L.use_dma, &L.single);     // validity was checked with the problem
   const int halves = L.single ? 2 : 1;     // the single sweep stores two factors per logit
   const int h_tiles = (p->H_s + kGradTile - 1) / kGradTile;
-  const GradGeometry gg = grad_geometry(n_pad, h_tiles, (int)(L.Vp / kBK));
+  // the head gradients of a slab after the first are read and written once more; k-steps of 1.6 us at 4 TB/s
+  const double head_steps = ((p->dW_prefix ? 1 : 0) + (p->dW_full ? 1 : 0)) * (double)p->V * p->H_s * 8.0 / 6.4e6;
+  const GradGeometry gg = grad_geometry(n_pad, h_tiles, (int)(L.Vp / kBK), head_steps);
   const int64_t slab = gg.slab_rows;
   const int ks = gg.ksplit;
   L.slab_rows = slab;
