@@ -9,7 +9,8 @@ import torch
 from oracle import adwin_oracle as O
 from paper_2605_28396_amd import synth
 from tests import helpers as Hp
-from tests.test_gpu_parity import B, _check_fused, _grad_l2, _run_fused, _teacher_reference  # noqa: F401  (B is a fixture)
+from tests.test_gpu_parity import (B, WANT_HEAD, _check_fused, _grad_l2, _run_fused,  # noqa: F401  (B is a fixture)
+                                   _teacher_reference)
 
 pytestmark = pytest.mark.gpu
 
@@ -164,3 +165,29 @@ def test_both_stagings_of_every_sweep_mode(B, what, line, images):  # noqa: F811
             assert abs(got["t_entropy"][t] - ent[t]) <= 1e-3
             assert abs(got["t_logp"][t] - logp[t]) <= 1e-3 * max(1.0, abs(logp[t]))
             assert lo[t] <= got["t_rank"][t] <= hi[t], (t, got["t_rank"][t], lo[t], hi[t])
+
+
+@pytest.mark.parametrize("V,H_s", [(8, 128), (104, 192), (264, 320), (376, 576), (512, 256)])
+def test_head_gradient_ends_on_partial_tiles(B, monkeypatch, V, H_s):  # noqa: F811
+    """The 256 x 256 output tiles of dW at the last rows and columns of the array: whole groups of 8
+    rows and 32 columns are stored, added to by the second slab, and nothing behind them is touched."""
+    monkeypatch.setenv("ADWIN_SLAB_ROWS", "256")
+    w = synth.Workload("dw_edges", V, H_s, 192, synth._offsets([300, 41]), np.array([289, 41], np.int32),
+                       synth.MODE_PREFIX_ONLY)
+    p = synth.hidden_problem(w)
+    f = Hp.oracle_inputs(p)
+    ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                      reduction=O.RED_SEQ_MEAN, mode=w.mode, head_gradient=True)
+    d = {k: v.cuda() for k, v in p.items()}
+    call = B.FusedCall(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window, mode=w.mode,
+                       reduction=O.RED_SEQ_MEAN, want=WANT_HEAD)
+    assert B.adwin_opd_fused_launch_info(call.p)["slabs"] == 2
+    room = torch.full((V * H_s + 256 * H_s,), 7.0, device="cuda")
+    call.p.dW_prefix = room.data_ptr()
+    assert call.run() == 0
+    torch.cuda.synchronize()
+    assert bool((room[V * H_s:] == 7.0).all())
+    got = room[:V * H_s].reshape(V, H_s).cpu().numpy()
+    nrm = Hp.summand_norms(f, w, ref["rows"], O.RED_SEQ_MEAN, head=True)["dW_prefix_l2"]
+    tol = Hp.DW_SIGMAS * Hp.DW_SIGMA * nrm + 1e-6 * np.abs(ref["dW_prefix"]).max()
+    assert (np.abs(got - ref["dW_prefix"]) <= tol).all()
