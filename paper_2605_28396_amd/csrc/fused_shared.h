@@ -24,6 +24,15 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nb) {
   return xcd * base + (xcd < rem ? xcd : rem) + loc;
 }
 
+// `total` things in `parts` contiguous shares that differ by at most one: the first of share i.  Quotient
+// and remainder are taken on the host: on the device the division, with 64-bit operands, was 100
+// instructions in front of the first load of every workgroup.
+struct Shares {
+  int each, longer;                // longer shares hold one more
+  void split(int total, int parts) { each = total / parts; longer = total % parts; }
+  __device__ __forceinline__ int first(int i) const { return i * each + (i < longer ? i : longer); }
+};
+
 // Workgroup `vid` of a logit pass -> (strip, token tile): groups of `tg` token tiles, inside a
 // group strip-major, so that consecutive ids share a strip's W tiles and a group's h tiles.  The
 // last group holds the tiles that remain: every workgroup of the grid (n_tiles x strips) has
@@ -142,6 +151,7 @@ struct LogitPassArgs {
   int tile0;                   // first token tile of this launch
   int n_tiles;                 // token tiles in this launch
   int strips;                  // vocabulary strips
+  Shares strip_tiles;          // vocabulary tiles of each (set by launch_logit_pass)
   int tg;                      // token tiles per workgroup group (share W tiles in one L2)
   int vt_total;                // vocabulary tiles (of 128)
   // pass 1 out: [5][strips][n_pad]
@@ -258,6 +268,7 @@ struct GradArgs {
   int64_t g_rows; int H;
   int64_t slab_row0;        // computed-row index of slab row 0
   int row_tiles, h_tiles, ksplit;
+  Shares split_steps;       // k-steps of each piece that hold rows of B (set by launch_grad_gemm)
   int half_tiles;           // slab row tiles >= half_tiles hold the E2 factor: output rows
   int64_t half_off;         // half_off + slab_row0 + ... (single-sweep mode; else half_tiles = row_tiles)
   int64_t out_rows;         // rows of g that exist (rows at or beyond are not stored)

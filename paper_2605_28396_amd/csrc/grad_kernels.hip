@@ -311,9 +311,7 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
   const int rt = vid / a.h_tiles, ht = vid % a.h_tiles;
   // k-steps that hold rows of B: the A blocks are padded to whole vocabulary tiles, of which the
   // last k-step may lie beyond k_rows altogether (its A entries are exact zeros)
-  const int nk_rows = (int)((a.k_rows + kBK - 1) / kBK);
-  const int k_begin = (int)((int64_t)nk_rows * split / a.ksplit);
-  const int k_end = (int)((int64_t)nk_rows * (split + 1) / a.ksplit);
+  const int k_begin = a.split_steps.first(split), k_end = a.split_steps.first(split + 1);
   const int nk = k_end - k_begin;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
@@ -640,7 +638,9 @@ hipError_t launch_combine(bool transposed, bool sampled, const CombineArgs& a, i
   return hipGetLastError();
 }
 
-hipError_t launch_grad_gemm(const GradArgs& a, hipStream_t st) {
+hipError_t launch_grad_gemm(const GradArgs& p, hipStream_t st) {
+  GradArgs a = p;
+  a.split_steps.split((int)((a.k_rows + kBK - 1) / kBK), a.ksplit);
   grad_gemm_kernel<<<(unsigned)(a.row_tiles * a.h_tiles * a.ksplit), 256, kGradLds, st>>>(a);
   return hipGetLastError();
 }

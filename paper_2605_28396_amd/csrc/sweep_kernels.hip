@@ -375,8 +375,7 @@ __global__ __launch_bounds__(256) void logit_pass_kernel(LogitPassArgs a) {
   int strip, tt_local;
   strip_and_tile(xcd_contiguous_id(blockIdx.x, gridDim.x), a.tg, a.strips, a.n_tiles, &strip, &tt_local);
   const int tt = a.tile0 + tt_local;
-  const int vt_begin = (int)((int64_t)a.vt_total * strip / a.strips);
-  const int vt_end = (int)((int64_t)a.vt_total * (strip + 1) / a.strips);
+  const int vt_begin = a.strip_tiles.first(strip), vt_end = a.strip_tiles.first(strip + 1);
 
   // token-row stagers (rows fixed for the whole vocabulary walk)
   RowStager<kTileTokens> hs, ht;
@@ -606,8 +605,7 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   int strip, tt_local;
   strip_and_tile(xcd_contiguous_id(blockIdx.x, gridDim.x), a.tg, a.strips, a.n_tiles, &strip, &tt_local);
   const int tt = a.tile0 + tt_local;
-  const int vt_begin = (int)((int64_t)a.vt_total * strip / a.strips);
-  const int vt_end = (int)((int64_t)a.vt_total * (strip + 1) / a.strips);
+  const int vt_begin = a.strip_tiles.first(strip), vt_end = a.strip_tiles.first(strip + 1);
   if (vt_begin >= vt_end) return;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
@@ -1169,7 +1167,9 @@ hipError_t launch_row_image(const RowImageArgs& a, unsigned tiles, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStream_t st) {
+hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStream_t st) {
+  LogitPassArgs a = p;
+  a.strip_tiles.split(a.vt_total, a.strips);
   const unsigned grid = (unsigned)a.n_tiles * (unsigned)a.strips;
   if (!dma) {
     if (mode == kModeStats) logit_pass_kernel<false><<<grid, 256, kLogitLds, st>>>(a);
