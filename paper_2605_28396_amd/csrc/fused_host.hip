@@ -19,7 +19,7 @@ struct FusedLayout {
   bool single;       // single-sweep scheme (needs use_dma)
   bool direct_w;     // ... whose W tiles come from the row-major weights, not from images
   size_t o_wt_img, o_ws_img, o_ht_img, o_hs_img;   // tile images of the logit operands (use_dma)
-  size_t o_ref_t2, o_delta, o_invz, o_mu0t;
+  size_t o_ref, o_delta, o_invz, o_mu0t;
   int strips, ksplit;
   int64_t slab_rows, Vp;
   size_t o_plan, o_row_idx, o_row_seq, o_part, o_lse2, o_mu, o_klr, o_rownorm, o_slab, o_g,
@@ -207,7 +207,7 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   const int most_strips = vt_total < kMaxSweepStrips ? vt_total : kMaxSweepStrips;
   L.o_part = take(sizeof(float) * 5 * (L.single ? (size_t)most_strips * (size_t)bound_slab
                                                 : (size_t)strips * (size_t)n_pad));
-  L.o_ref_t2 = take(sizeof(float) * (size_t)n_pad);
+  L.o_ref = take(L.single ? sizeof(float) * 2 * kMaxRefParts * (size_t)n_pad : 0);
   L.o_delta = take(sizeof(float) * (size_t)n_pad);
   L.o_mu0t = take((L.single && p->estimator != ADWIN_EST_SAMPLED)
                       ? sizeof(float) * (size_t)vt_total * (size_t)bound_slab : 0);
@@ -404,6 +404,10 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     const int n_tiles = (int)(n_pad / kTileTokens);
     const int h_tiles = (p->H_s + kGradTile - 1) / kGradTile;
     const bool use_dma = L.use_dma;
+    References ref;
+    ref.n_pad = n_pad; ref.parts = n_tiles <= kFineRefTiles ? kMaxRefParts : 1; ref.yid = (int32_t*)(ws + L.o_yid);
+    for (int m = 0; m < 2; ++m) ref.max[m] = (float*)(ws + L.o_ref) + (int64_t)m * kMaxRefParts * n_pad;
+    ref.zy[0] = (float*)(ws + L.o_zy_s); ref.zy[1] = (float*)(ws + L.o_zy_t);
     if (use_dma) {
       // tile images of the logit operands: vocabulary tiles of 128 rows (zero beyond V),
       // token tiles of 256 computed rows gathered through row_idx
@@ -415,22 +419,19 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         ia.src = (const uint4*)p->W_s; ia.img = (uint4*)(ws + L.o_ws_img); ia.H = p->H_s; ia.nk = p->H_s / kBK;
         ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
       }
-      PrepareArgs pr;
+      PrepareArgs pr{};
+      pr.row_idx = pl.row_idx; pr.ids = p->ids; pr.V = p->V; pr.ref = ref;
+      pr.h[0] = (const __bf16*)p->h_s; pr.W[0] = (const __bf16*)p->W_s; pr.H[0] = p->H_s;
+      pr.h[1] = (const __bf16*)p->h_t; pr.W[1] = (const __bf16*)p->W_t; pr.H[1] = p->H_t;
       ia.row_idx = pl.row_idx; ia.n_rows = n_pad; ia.permute = 0;
-      ia.src = (const uint4*)p->h_t; ia.img = (uint4*)(ws + L.o_ht_img); ia.H = p->H_t; ia.nk = p->H_t / kBK;
-      pr.ht = ia;
-      ia.src = (const uint4*)p->h_s; ia.img = (uint4*)(ws + L.o_hs_img); ia.H = p->H_s; ia.nk = p->H_s / kBK;
-      pr.hs = ia;
+      for (int m = 0; m < 2; ++m) {
+        ia.src = (const uint4*)pr.h[m]; ia.img = (uint4*)(ws + (m ? L.o_ht_img : L.o_hs_img));
+        ia.H = pr.H[m]; ia.nk = pr.H[m] / kBK;
+        pr.img[m] = ia;
+      }
       // single sweep: the fixed references of every row, from vocabulary tile 0 and the sampled
       // token (without ids: id -1 on every row, which the diagnostics sweep expects)
-      pr.ref_blocks = L.single ? (int)(n_pad / 32) : 0;
-      pr.r.row_idx = pl.row_idx; pr.r.ids = p->ids;
-      pr.r.h_s = (const __bf16*)p->h_s; pr.r.h_t = (const __bf16*)p->h_t;
-      pr.r.W_s = (const __bf16*)p->W_s; pr.r.W_t = (const __bf16*)p->W_t;
-      pr.r.H_s = p->H_s; pr.r.H_t = p->H_t; pr.r.V = p->V;
-      pr.r.ref_s2 = (float*)(ws + L.o_lse2); pr.r.ref_t2 = (float*)(ws + L.o_ref_t2); pr.r.mu0 = (float*)(ws + L.o_mu);
-      pr.r.zy_s = (float*)(ws + L.o_zy_s); pr.r.zy_t = (float*)(ws + L.o_zy_t); pr.r.yid = (int32_t*)(ws + L.o_yid);
-      ADWIN_HIP_TRY(launch_prepare(pr, n_tiles, stream));
+      ADWIN_HIP_TRY(launch_prepare(pr, L.single, n_tiles, stream));
     }
     LogitPassArgs la;
     la.h_s = (const __bf16*)p->h_s; la.h_t = (const __bf16*)p->h_t;
@@ -441,8 +442,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     la.part = (float*)(ws + L.o_part);
     la.lse2 = (const float*)(ws + L.o_lse2); la.mu = (const float*)(ws + L.o_mu);
     la.slab = (__bf16*)(ws + L.o_slab); la.Vp = L.Vp;
-    la.ref_s2 = (const float*)(ws + L.o_lse2); la.ref_t2 = (const float*)(ws + L.o_ref_t2);
-    la.mu0 = (const float*)(ws + L.o_mu); la.e2_off = 0;
+    la.ref = ref; la.e2_off = 0;
     la.mu0t = (L.single && !sampled && need_g) ? (float*)(ws + L.o_mu0t) : nullptr; la.mu0t_stride = L.slab_rows;
     la.tg = env_int("ADWIN_TG", 4);      // tuning override
     la.Wt_img = (const char*)(ws + L.o_wt_img); la.Ws_img = (const char*)(ws + L.o_ws_img);
@@ -467,7 +467,6 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       // the strip sums and the gradient factors, the merge of the slab's rows, the combine pass
       // over the factors and the GEMM of dz with W_s.
       la.vt_total = vt_total;
-      la.zy_t = (const float*)(ws + L.o_zy_t); la.yid = (const int32_t*)(ws + L.o_yid);
       ga.g_rows = n_pad; ga.half_off = n_pad;
       for (int64_t r0 = 0; r0 < n_pad; r0 += L.slab_rows) {
         const int64_t rows = (n_pad - r0 < L.slab_rows) ? n_pad - r0 : L.slab_rows;
@@ -484,8 +483,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         phase(ADWIN_PHASE_MERGE);
         MergeSingleArgs ms;
         ms.m = m; ms.m.strips = la.strips; ms.m.part = la.part; ms.m.n_pad = la.n_pad;
-        ms.ref_s2 = la.ref_s2; ms.ref_t2 = la.ref_t2;
-        ms.zy_s = (const float*)(ws + L.o_zy_s); ms.zy_t = la.zy_t; ms.yid = la.yid;
+        ms.ref = ref;
         ms.mu_out = (float*)(ws + L.o_delta); ms.inv_z = (float*)(ws + L.o_invz);
         ms.row0 = r0; ms.rows = rows;
         ADWIN_HIP_TRY(launch_merge_single(ms, stream));

@@ -87,6 +87,13 @@ __device__ __forceinline__ const char* addr_of(uint32_t lo, uint32_t hi) {
 typedef const __attribute__((address_space(3))) bf16x8* LdsFragPtr;
 __device__ __forceinline__ LdsFragPtr lds_frag(uint32_t addr) { return (LdsFragPtr)(uintptr_t)addr; }
 
+// The same, 4 bytes per lane.
+template <int IMM>
+__device__ __forceinline__ void dma4_at(uint32_t lds_base, uint32_t voff, const char* sbase) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :: "s"(lds_base), "v"(voff), "s"(sbase), "n"(IMM) : "memory", "scc");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
@@ -140,6 +147,29 @@ __device__ __forceinline__ float dot_bf16_row(const __bf16* x, const __bf16* y, 
   return wave_sum(acc);
 }
 
+// References of the single sweep per computed row (see prepare_kernel): the larger of the maximum
+// over vocabulary tile 0 and the logit of the sampled token, as the maximum over `parts` planes: one, or,
+// in calls of few token tiles, the four blocks of 32 entries and the token (kMaxRefParts).
+constexpr int kRefBlocks = kTileVocab / 32;
+constexpr int kMaxRefParts = kRefBlocks + 1;
+constexpr int kFineRefTiles = 8;           // see launch_prepare
+struct References {
+  float* max[2];            // [parts][n_pad] student, teacher; kNegBig: nothing to take the maximum of
+  float* zy[2];             // [n_pad] logit of the sampled token (0: none)
+  int32_t* yid;             // [n_pad] its id; -1: none, or out of range
+  int64_t n_pad;
+  int parts;
+  __device__ __forceinline__ float of(int head, int64_t r) const {
+    if (parts == 1) return max[head][r];
+    float v[kMaxRefParts];                  // loaded together
+#pragma unroll
+    for (int k = 0; k < kMaxRefParts; ++k) v[k] = max[head][(k < parts ? k : 0) * n_pad + r];
+#pragma unroll
+    for (int k = 1; k < kMaxRefParts; ++k) v[0] = fmaxf(v[0], v[k]);
+    return v[0];
+  }
+};
+
 // ---------------------------------------------------------------------------------------
 // Argument blocks
 // ---------------------------------------------------------------------------------------
@@ -160,12 +190,10 @@ struct LogitPassArgs {
   const float* lse2; const float* mu;
   __bf16* slab; int64_t Vp;    // slab blocks of the launch's token tiles, tile0 first
   // single-sweep mode: fixed per-row references and the offset of the second slab half
-  const float* ref_s2; const float* ref_t2; const float* mu0;
+  References ref;
   int64_t e2_off;
   // per-(vocabulary tile, slab row) reference mu0 of the D factor, written by the sweep
   float* mu0t; int64_t mu0t_stride;
-  // diagnostics mode: teacher logit of the sampled token and the token id (-1: none) per row
-  const float* zy_t; const int32_t* yid;
   // direct-to-LDS kernel: tile images of the four operands (see row_image_kernel)
   const char* Wt_img; const char* Ws_img; const char* ht_img; const char* hs_img;
   bool direct_w;               // stage W from W_s / W_t themselves; there are no W images
@@ -210,23 +238,21 @@ struct MergeArgs {
 
 struct MergeSingleArgs {
   MergeArgs m;                 // part: [3][strips][n_pad] sums Z_s, A, Z_t
-  const float* ref_s2; const float* ref_t2;
-  const float* zy_s; const float* zy_t; const int32_t* yid;   // of prepare_kernel
+  References ref;
   float* mu_out; float* inv_z;
   int64_t row0, rows;          // computed rows [row0, row0 + rows) of this launch (one slab)
 };
 
-// References of the single sweep per computed row, and the logits of the sampled token under both
-// models with its id (-1: none, or out of range) (see prepare_kernel).
-struct RefArgs {
+// What a call prepares for its sweep (see prepare_kernel).
+struct PrepareArgs {
   const int32_t* row_idx; const int32_t* ids;     // ids may be NULL
-  const __bf16* h_s; const __bf16* W_s; const __bf16* h_t; const __bf16* W_t;
-  int H_s, H_t, V;
-  float* ref_s2; float* ref_t2; float* mu0;
-  float* zy_s; float* zy_t; int32_t* yid;
+  const __bf16* h[2]; const __bf16* W[2];         // student, teacher
+  int H[2]; int V;
+  References ref;
+  RowImageArgs img[2];                            // of the hidden states
+  // workgroups: references (0: none wanted), logits of the sampled tokens, images of h_s, of h_t
+  int ref_blocks, dot_blocks, img_blocks[2];
 };
-// ref_blocks: workgroups of 32 rows (0: no references), then those of the two images.
-struct PrepareArgs { RefArgs r; RowImageArgs ht, hs; int ref_blocks, t_blocks; };
 
 // Combine pass over one slab (see combine_kernel).
 struct CombineArgs {
@@ -301,7 +327,8 @@ hipError_t sweep_kernels_opt_in();       // large dynamic LDS of the logit kerne
 hipError_t launch_row_image(const RowImageArgs& a, unsigned tiles, hipStream_t st);
 // mode: one of kMode*; dma false selects the register-staged kernel (kModeStats, kModeDz only)
 hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStream_t st);
-hipError_t launch_prepare(const PrepareArgs& a, int n_tiles, hipStream_t st);
+// `refs`: with the references of the single sweep
+hipError_t launch_prepare(const PrepareArgs& a, bool refs, int n_tiles, hipStream_t st);
 hipError_t launch_merge_stats(const MergeArgs& a, hipStream_t st);
 hipError_t launch_merge_single(const MergeSingleArgs& a, hipStream_t st);
 // grad_kernels.hip

@@ -453,6 +453,7 @@ __global__ __launch_bounds__(256) void logit_pass_kernel(LogitPassArgs a) {
 // ---------------------------------------------------------------------------------------
 constexpr int kDmaStages = 3;
 constexpr int kDmaLds = kDmaStages * kLogitStage;           // 144 KiB
+constexpr int kDmaRefLds = kDmaLds + 4 * 2 * kMaxRefParts * 256;  // ... and the references of the single sweep
 constexpr int kDmaPerWave = (kTileVocab + kTileTokens) / 8 / 4;   // 12 wave-loads per stage
 
 // Row images.  The direct-to-LDS logit kernel reads all four operands as LDS images of its
@@ -700,10 +701,18 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
       lse2[fn] = a.lse2[r];
       mu[fn] = a.mu[r];
     } else if (kSingle) {
-      rs2[fn] = a.ref_s2[r];
-      rt2[fn] = a.ref_t2[r];
-      mu[fn] = a.mu0[r];
-      if (kDiag) { zyt[fn] = a.zy_t[r]; yid[fn] = a.yid[r]; }
+      if (kDiag) { zyt[fn] = a.ref.zy[1][r]; yid[fn] = a.ref.yid[r]; }
+    }
+  }
+  // The references go into the LDS behind the ring, ahead of the first stages: loaded into registers they
+  // made every workgroup wait for one more round trip before it asked for its first stage.
+  const uint32_t ref_lds = lds0 + kDmaLds + (uint32_t)wave * (2 * kMaxRefParts * 256);
+  if (kSingle) {
+    const uint32_t row = (uint32_t)lane * 4u;
+    for (int k = 0; k < 2 * a.ref.parts; ++k) {
+      const int head = k >= a.ref.parts, plane = head ? k - a.ref.parts : k;
+      dma4_at<0>(ref_lds + (uint32_t)k * 256u, row,
+                 (const char*)(a.ref.max[head] + plane * a.ref.n_pad + (int64_t)tt * kTileTokens + wave * 64));
     }
   }
 
@@ -757,6 +766,18 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     dma_one<8>(dst, voffa, voffw, ldA, ldB); dma_one<9>(dst, voffa, voffw, ldA, ldB);
     dma_one<10>(dst, voffa, voffw, ldA, ldB); dma_one<11>(dst, voffa, voffw, ldA, ldB);
     ADWIN_COUNT_LOADS()
+  }
+  if (kSingle) {
+    typedef const __attribute__((address_space(3))) float* LdsFloat;
+    wait_vm<2 * kDmaPerWave>();                // all but the two stages
+#pragma unroll
+    for (int fn = 0; fn < 2; ++fn) {
+      const LdsFloat p = (LdsFloat)(uintptr_t)(ref_lds + (uint32_t)(fn * 32 + (lane & 31)) * 4u);
+      float m[2] = {p[0], p[a.ref.parts * 64]};
+      for (int k = 1; k < a.ref.parts; ++k) { m[0] = fmaxf(m[0], p[k * 64]); m[1] = fmaxf(m[1], p[(a.ref.parts + k) * 64]); }
+      rs2[fn] = m[0] * kLog2e;
+      rt2[fn] = m[1] * kLog2e;
+    }
   }
   // 16-byte stores a wave issues per tile in its epilogue, at the least (see sweep_kstep, RELAXED)
   constexpr int kEpilogueStores = MODE == kModeDz ? 16 : (kWriteE2 && kSingle ? 16 : 0) + (kWriteD ? 16 : 0);
@@ -875,56 +896,101 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(MergeArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Single-sweep mode: what a call prepares for its sweep, in one launch.  The first workgroups fix
-// the references of 32 rows each: online statistics of vocabulary tile 0 (128 entries) and the
-// logits of the sampled token under both models, z_s[y_t] = h_s . W_s[y_t] and
-// z_t[y_t] = h_t . W_t[y_t], which the merge and the diagnostics sweep use again.  The others lay
-// the hidden states out as tile images.
-// The references are bound by latency: (H_t + H_s) / 64 staged k-steps per row tile.  As a sweep of
-// one vocabulary tile they took 83 us for any call (one workgroup per 256 rows, loads two k-steps
-// ahead), and 98 with the token logits and the combination of both in launches of their own.
-// Here 32 rows take 8 waves, one per 32 entries and half of every k-step, and the stages are small
-// enough (20 KiB) for loads kRefLead k-steps ahead: 53 us with the images for 256 rows at
-// H = 2048 + 4096 (118 before).  The merge takes the token logits from here (89 -> 22 us per 16,384 rows).  (Operands straight from the row-major rows into
-// registers, no LDS: 132 us, a load of 16 bytes from each of 64 places costs the L1 a line each.)
+// Single-sweep mode: what a call prepares for its sweep, in one launch: the references of every row
+// (maxima over vocabulary tile 0, 128 entries, under both models), the logits of its sampled token,
+// z_s[y_t] = h_s . W_s[y_t] and z_t[y_t] = h_t . W_t[y_t], which the merge and the diagnostics sweep
+// use again, and the hidden states as tile images.
+// The references are bound by latency, in two forms (see launch_prepare).
+//
+// Calls of few token tiles: cut as finely as the maxima allow.  A workgroup takes 32 rows, one model and
+// one block of 32 entries, its waves an eighth of the k-blocks each, straight from the row-major operands
+// into the fragments: no staging, no barrier before the partial sums meet.  The order of k is free, so
+// a lane takes 64 consecutive bytes of its row per k-block of 64 (lane / 32 picks the half), four
+// fragments of either operand.  (A lane's 16 bytes of a fragment in its place, k = 8 (lane / 32) .. + 7
+// of 16, costs the L1 a line each, in kilobyte strides.)  256 rows at H = 2048 + 4096, with the images: 48 us
+// as eight workgroups of the other form, 17 as these 64; 800 rows at H = 2048 + 3072 32.5 -> 18.5.
+//
+// Others: 32 rows and all four blocks to a workgroup of 8 waves, one per block and half of every k-step;
+// the stages are small enough (20 KiB) for loads kRefLead k-steps ahead.  Every operand line is
+// moved into the LDS once; read into registers by the waves that use it, it goes through the L1 up
+// to five times, which is what bounds the form above (13 token tiles at H = 512 + 640: 20.6 us
+// against 15.8).
 // ---------------------------------------------------------------------------------------
-constexpr int kRefRows = 32, kRefThreads = 512, kRefLead = 5;
+constexpr int kPrepThreads = 512, kPrepWaves = kPrepThreads / 64;
+constexpr int kRefRows = 32, kRefLead = 5;
 constexpr int kRefStage = (kTileVocab + kRefRows) * kRowBytes;          // 20 KiB
 constexpr int kRefLds = (kRefLead + 1) * kRefStage;                     // 120 KiB
+constexpr int kRefFineLds = kPrepWaves * 17 * 64 * 4;                   // 34 KiB
 
 // As dma16_at, from a 64-bit address per lane.
 __device__ __forceinline__ void dma16_from(uint32_t lds, const char* src) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(src) : "memory");
 }
 
-// x[i] . y[i] for the wave's four tokens, the loads of all four together; sums as in dot_bf16_row.
-__device__ __forceinline__ void ref_dots(const uint4* const (&x)[4], const uint4* const (&y)[4], int H, int lane,
-                                         float (&out)[4]) {
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+// Four computed rows of a wave: their packed positions and sampled tokens (-1: none, or out of range).
+constexpr int kTokenRows = 4;
+struct TokenRows {
+  int64_t row0, t[kTokenRows];
+  int y[kTokenRows];
+  bool any;
+  __device__ __forceinline__ TokenRows(const PrepareArgs& a, int64_t first) : row0(first), any(false) {
+#pragma unroll
+    for (int i = 0; i < kTokenRows; ++i) t[i] = a.row_idx[row0 + i];
+#pragma unroll
+    for (int i = 0; i < kTokenRows; ++i) {
+      y[i] = a.ids ? a.ids[t[i]] : -1;
+      if (y[i] < 0 || y[i] >= a.V) y[i] = -1;
+      any |= y[i] >= 0;
+    }
+  }
+};
+
+// The sampled tokens' logits under one model, by one wave, the loads of all four rows together.  Lane i < 4
+// returns that of row i, kNegBig without a token.
+__device__ __forceinline__ float token_logits(const PrepareArgs& a, const TokenRows& r, int head, int lane) {
+  const int H = a.H[head];
+  const uint4 *x[kTokenRows], *w[kTokenRows];
+  float z[kTokenRows], mine = kNegBig;
+#pragma unroll
+  for (int i = 0; i < kTokenRows; ++i) {
+    x[i] = (const uint4*)(a.h[head] + r.t[i] * H);
+    w[i] = (const uint4*)(a.W[head] + (int64_t)(r.y[i] >= 0 ? r.y[i] : 0) * H);
+    z[i] = 0.f;
+  }
+  if (r.any) {                                      // uniform: the rows are the wave's
 #pragma unroll 2
-  for (int q = lane; q < (H >> 3); q += 64) {
-    uint4 a[4], b[4];
+    for (int q = lane; q < (H >> 3); q += 64) {
+      uint4 p[kTokenRows], o[kTokenRows];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { a[i] = x[i][q]; b[i] = y[i][q]; }
+      for (int i = 0; i < kTokenRows; ++i) { p[i] = x[i][q]; o[i] = w[i][q]; }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      acc[i] = fmaf(bf16_lo(a[i].x), bf16_lo(b[i].x), acc[i]); acc[i] = fmaf(bf16_hi(a[i].x), bf16_hi(b[i].x), acc[i]);
-      acc[i] = fmaf(bf16_lo(a[i].y), bf16_lo(b[i].y), acc[i]); acc[i] = fmaf(bf16_hi(a[i].y), bf16_hi(b[i].y), acc[i]);
-      acc[i] = fmaf(bf16_lo(a[i].z), bf16_lo(b[i].z), acc[i]); acc[i] = fmaf(bf16_hi(a[i].z), bf16_hi(b[i].z), acc[i]);
-      acc[i] = fmaf(bf16_lo(a[i].w), bf16_lo(b[i].w), acc[i]); acc[i] = fmaf(bf16_hi(a[i].w), bf16_hi(b[i].w), acc[i]);
+      for (int i = 0; i < kTokenRows; ++i) {        // as in dot_bf16_row
+        z[i] = fmaf(bf16_lo(p[i].x), bf16_lo(o[i].x), z[i]); z[i] = fmaf(bf16_hi(p[i].x), bf16_hi(o[i].x), z[i]);
+        z[i] = fmaf(bf16_lo(p[i].y), bf16_lo(o[i].y), z[i]); z[i] = fmaf(bf16_hi(p[i].y), bf16_hi(o[i].y), z[i]);
+        z[i] = fmaf(bf16_lo(p[i].z), bf16_lo(o[i].z), z[i]); z[i] = fmaf(bf16_hi(p[i].z), bf16_hi(o[i].z), z[i]);
+        z[i] = fmaf(bf16_lo(p[i].w), bf16_lo(o[i].w), z[i]); z[i] = fmaf(bf16_hi(p[i].w), bf16_hi(o[i].w), z[i]);
+      }
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) out[i] = wave_sum(acc[i]);
+  for (int i = 0; i < kTokenRows; ++i) {
+    z[i] = wave_sum(z[i]);
+    if (lane == i) {
+      a.ref.zy[head][r.row0 + i] = r.y[i] >= 0 ? z[i] : 0.f;
+      if (head == 0) a.ref.yid[r.row0 + i] = r.y[i];
+      if (r.y[i] >= 0) mine = z[i];
+    }
+  }
+  return mine;
 }
 
-__device__ __forceinline__ void refs_block(const RefArgs& a, int64_t row0, char* lds) {
+// References of 32 rows, both models, the tokens of four of them by each wave.
+__device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, int64_t row0, char* lds) {
   __shared__ float token[2][kRefRows];
-  __shared__ int token_id[kRefRows];
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  const int nt = a.H_t / kBK, nk = nt + a.H_s / kBK;      // k-steps: teacher, then student
+  const int nt = a.H[1] / kBK, nk = nt + a.H[0] / kBK;      // k-steps: teacher, then student
   // A stage: 128 rows of W (tile 0; rows beyond V repeat the last, masked below), then 32 of h, row r
   // at 128 r, chunk c at position c ^ ((r >> 1) & 7).  Wave-load i < 2 of a wave: W rows
   // 16 wave + 8 i .. + 7; the third, of waves 0 to 3 only: h rows 8 wave .. + 7.
@@ -934,8 +1000,8 @@ __device__ __forceinline__ void refs_block(const RefArgs& a, int64_t row0, char*
     const int m = i < 2 ? 2 * wave + i : (wave & 3), r = 8 * m + (lane >> 3);
     const uint32_t chunk = (uint32_t)((lane & 7) ^ ((r >> 1) & 7)) * 16u;
     const int64_t row = i < 2 ? (r < a.V ? r : a.V - 1) : a.row_idx[row0 + r];
-    pt[i] = (const char*)((i < 2 ? a.W_t : a.h_t) + row * a.H_t) + chunk;
-    ps[i] = (const char*)((i < 2 ? a.W_s : a.h_s) + row * a.H_s) + chunk;
+    pt[i] = (const char*)((i < 2 ? a.W[1] : a.h[1]) + row * a.H[1]) + chunk;
+    ps[i] = (const char*)((i < 2 ? a.W[0] : a.h[0]) + row * a.H[0]) + chunk;
   }
   auto load = [&](int s) __attribute__((always_inline)) {      // past the last k-step: that one again
     const uint32_t slot = lds0 + (uint32_t)(s % (kRefLead + 1)) * kRefStage;
@@ -947,34 +1013,10 @@ __device__ __forceinline__ void refs_block(const RefArgs& a, int64_t row0, char*
     if (wave < 4) dma16_from(slot + (uint32_t)(16 + wave) * 1024u, (student ? ps[2] : pt[2]) + off);
   };
   for (int s = 0; s < kRefLead; ++s) load(s);
-  {                                                // the sampled tokens of rows 4 wave .. 4 wave + 3
-    const uint4 *xs[4], *ys[4], *xt[4], *yt[4];
-    int y[4];
-    bool any = false;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t t = a.row_idx[row0 + wave * 4 + i];
-      y[i] = a.ids ? a.ids[t] : -1;
-      const bool ok = y[i] >= 0 && y[i] < a.V;
-      if (!ok) y[i] = -1;
-      any |= ok;
-      const int64_t v = ok ? y[i] : 0;
-      xs[i] = (const uint4*)(a.h_s + t * a.H_s); ys[i] = (const uint4*)(a.W_s + v * a.H_s);
-      xt[i] = (const uint4*)(a.h_t + t * a.H_t); yt[i] = (const uint4*)(a.W_t + v * a.H_t);
-    }
-    float ds[4] = {0.f, 0.f, 0.f, 0.f}, dt[4] = {0.f, 0.f, 0.f, 0.f};
-    if (any) {                                     // uniform: the rows are the wave's
-      ref_dots(xt, yt, a.H_t, lane, dt);
-      ref_dots(xs, ys, a.H_s, lane, ds);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (lane == i) {
-        const bool ok = y[i] >= 0;
-        token[0][wave * 4 + i] = ok ? ds[i] : 0.f;
-        token[1][wave * 4 + i] = ok ? dt[i] : 0.f;
-        token_id[wave * 4 + i] = y[i];
-      }
+  {
+    const TokenRows rows(a, row0 + wave * kTokenRows);
+    const float yt = token_logits(a, rows, 1, lane), ys = token_logits(a, rows, 0, lane);
+    if (lane < kTokenRows) { token[0][wave * kTokenRows + lane] = ys; token[1][wave * kTokenRows + lane] = yt; }
   }
   // wave = vocabulary block vb, half kq of every k-step; A = W rows, B = h rows as in the sweep
   const int vb = wave & 3, kq = wave >> 2;
@@ -1003,75 +1045,103 @@ __device__ __forceinline__ void refs_block(const RefArgs& a, int64_t row0, char*
   wait_vm<0>();
   __syncthreads();                                 // the ring is free from here on
   float(*half_sum)[32][64] = (float(*)[32][64])lds;                      // [4]: of the second halves
-  float(*stat)[4][kRefRows] = (float(*)[4][kRefRows])(lds + 4 * 32 * 64 * 4);   // [4]: m_s, Z_s, A, m_t
+  float(*stat)[2][kRefRows] = (float(*)[2][kRefRows])(lds + 4 * 32 * 64 * 4);   // [4]: maxima
   if (kq) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) { half_sum[vb][e][lane] = zs[e]; half_sum[vb][16 + e][lane] = zt[e]; }
   }
   __syncthreads();
   if (!kq) {
-    float ms = kNegBig, mt = kNegBig, Z = 0.f, A = 0.f;
+    float ms = kNegBig, mt = kNegBig;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       zs[e] += half_sum[vb][e][lane]; zt[e] += half_sum[vb][16 + e][lane];
-      const bool ok = vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V;
-      if (ok) { ms = fmaxf(ms, zs[e]); mt = fmaxf(mt, zt[e]); }
+      if (vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V) { ms = fmaxf(ms, zs[e]); mt = fmaxf(mt, zt[e]); }
     }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const bool ok = vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V;
-      const float es = ok ? fast_exp2((zs[e] - ms) * kLog2e) : 0.f;
-      Z += es;
-      if (ok) A = fmaf(es, zs[e] - zt[e], A);
-    }
-    merge_mza(ms, Z, A, __shfl_xor(ms, 32, 64), __shfl_xor(Z, 32, 64), __shfl_xor(A, 32, 64));
+    ms = fmaxf(ms, __shfl_xor(ms, 32, 64));
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    if (lane < 32) { stat[vb][0][lane] = ms; stat[vb][1][lane] = Z; stat[vb][2][lane] = A; stat[vb][3][lane] = mt; }
+    if (lane < 32) { stat[vb][0][lane] = ms; stat[vb][1][lane] = mt; }
   }
   __syncthreads();
-  const int r = threadIdx.x;
-  if (r >= kRefRows) return;
-  float ms = stat[0][0][r], Zs = stat[0][1][r], A = stat[0][2][r], mt = stat[0][3][r];
-#pragma unroll
-  for (int q = 1; q < 4; ++q) {
-    merge_mza(ms, Zs, A, stat[q][0][r], stat[q][1][r], stat[q][2][r]);
-    mt = fmaxf(mt, stat[q][3][r]);
-  }
-  const float zys = token[0][r], zyt = token[1][r];
-  const int y = token_id[r];
-  if (y >= 0) {
-    // The sampled token joins the first vocabulary tile as a sample of the row: drawn from the
-    // student, it sits where the mass is, which the first 128 entries of a peaked row do not.
-    // The references rise to its logits (the exponentials of the sweep stay near 1 at the
-    // row maximum instead of growing with the gap to the first tile), and mu0 becomes the
-    // self-normalised estimate of E_p[z_s - z_t] over the tile's entries and the token.
-    const float rs = fmaxf(ms, zys);
-    const float sc = fast_exp2((ms - rs) * kLog2e);
-    Zs *= sc; A *= sc;
-    if (y >= kTileVocab) {                // not already one of the tile's entries
-      const float ey = fast_exp2((zys - rs) * kLog2e);
-      Zs += ey;
-      A = fmaf(ey, zys - zyt, A);
-    }
-    ms = rs;
-    mt = fmaxf(mt, zyt);
-  }
-  a.ref_s2[row0 + r] = ms * kLog2e;
-  a.ref_t2[row0 + r] = mt * kLog2e;
-  a.mu0[row0 + r] = A / Zs;
-  a.zy_s[row0 + r] = zys;
-  a.zy_t[row0 + r] = zyt;
-  a.yid[row0 + r] = y;
+  const int head = threadIdx.x >> 5, r = threadIdx.x & 31;
+  if (head < 2)
+    a.ref.max[head][row0 + r] = fmaxf(fmaxf(fmaxf(stat[0][head][r], stat[1][head][r]), fmaxf(stat[2][head][r], stat[3][head][r])),
+                                      token[head][r]);
 }
 
-__global__ __launch_bounds__(kRefThreads) void prepare_kernel(PrepareArgs a) {
+// References of 32 rows, one model, one vocabulary block.
+__device__ __forceinline__ void refs_fine_block(const PrepareArgs& a, int blk, char* lds) {
+  float(*part)[16][64] = (float(*)[16][64])lds;     // [kPrepWaves] a wave's partial logits
+  float(*top)[64] = (float(*)[64])(lds + kPrepWaves * 16 * 64 * 4);   // [kPrepWaves]
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int head = blk & 1, vb = (blk >> 1) % kRefBlocks;
+  const int64_t row0 = (int64_t)((blk >> 1) / kRefBlocks) * kRefRows;
+  const int H = a.H[head], nb = H / kBK;
+  const int v = vb * 32 + (lane & 31);
+  const uint4* ph = (const uint4*)(a.h[head] + (int64_t)a.row_idx[row0 + (lane & 31)] * H) + half * 4;
+  const uint4* pw = (const uint4*)(a.W[head] + (int64_t)(v < a.V ? v : a.V - 1) * H) + half * 4;   // masked below
+  f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 2;                              // k-blocks loaded together
+  for (int b = wave; b < nb; b += U * kPrepWaves) {
+    uint4 x[U][4], w[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = (b + u * kPrepWaves < nb ? b + u * kPrepWaves : b) * (kBK / 8);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) { x[u][c] = ph[k + c]; w[u][c] = pw[k + c]; }
+    }
+    __builtin_amdgcn_sched_barrier(0);              // the loads stay together
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (b + u * kPrepWaves >= nb) break;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[u][c]), __builtin_bit_cast(bf16x8, x[u][c]),
+                                                    z, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) part[wave][e][lane] = z[e];
+  __syncthreads();
+  // wave w adds up elements 2 w and 2 w + 1 of every lane: entries 8 (e / 4) + 4 half + e % 4 of the block
+  float m = kNegBig;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = 2 * wave + q;
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < kPrepWaves; ++k) s += part[k][e][lane];
+    if (vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V) m = fmaxf(m, s);
+  }
+  top[wave][lane] = m;
+  __syncthreads();
+  if (threadIdx.x >= kRefRows) return;
+#pragma unroll
+  for (int k = 0; k < kPrepWaves; ++k) m = fmaxf(m, fmaxf(top[k][threadIdx.x], top[k][threadIdx.x + 32]));
+  a.ref.max[head][(int64_t)vb * a.ref.n_pad + row0 + threadIdx.x] = m;
+}
+
+__device__ __forceinline__ void token_block(const PrepareArgs& a, int blk) {
+  const int64_t unit = (int64_t)blk * kPrepWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, head = (int)(unit & 1);
+  const TokenRows rows(a, (unit >> 1) * kTokenRows);               // n_pad is a multiple of 256
+  const float z = token_logits(a, rows, head, lane);
+  if (lane < kTokenRows) a.ref.max[head][kRefBlocks * a.ref.n_pad + rows.row0 + lane] = z;
+}
+
+template <bool FINE>
+__global__ __launch_bounds__(kPrepThreads) void prepare_kernel(PrepareArgs a) {
   extern __shared__ __align__(16) char lds[];
   int b = (int)blockIdx.x;
-  if (b < a.ref_blocks) return refs_block(a.r, (int64_t)b * kRefRows, lds);
+  if (b < a.ref_blocks) return FINE ? refs_fine_block(a, b, lds) : refs_staged_block(a, (int64_t)b * kRefRows, lds);
   b -= a.ref_blocks;
-  const RowImageArgs& im = b < a.t_blocks ? a.ht : a.hs;
-  if (b >= a.t_blocks) b -= a.t_blocks;
-  image_block<kRefThreads, kTileTokens>(im, b / im.nk, b % im.nk);
+  if (b < a.dot_blocks) return token_block(a, b);
+  b -= a.dot_blocks;
+  const int head = b < a.img_blocks[0] ? 0 : 1;
+  if (head) b -= a.img_blocks[0];
+  const RowImageArgs& im = a.img[head];
+  image_block<kPrepThreads, kTileTokens>(im, b / im.nk, b % im.nk);
 }
 
 __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
@@ -1080,6 +1150,7 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   const int64_t r = b.row0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= b.row0 + b.rows) return;
   const int64_t plane = (int64_t)a.strips * a.n_pad;
+  const float ref_s = b.ref.of(0, r), ref_t = b.ref.of(1, r);
   float Zs = 0.f, A = 0.f, Zt = 0.f, Bt = 0.f, cnt = 0.f;
   for (int s = lane; s < a.strips; s += 64) {
     const float* p = a.part + (int64_t)s * a.n_pad + r;
@@ -1088,9 +1159,9 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   }
   Zs = wave_sum(Zs); A = wave_sum(A); Zt = wave_sum(Zt);
   if (a.diag) { Bt = wave_sum(Bt); cnt = wave_sum(cnt); }
-  const float lse_s = b.ref_s2[r] * kLn2 + logf(Zs), lse_t = b.ref_t2[r] * kLn2 + logf(Zt);
+  const float lse_s = ref_s + logf(Zs), lse_t = ref_t + logf(Zt);
   const float mu = A / Zs;                  // E_{p_s}[z_s - z_t]
-  float kl = kl_from_sums(mu, (b.ref_s2[r] - b.ref_t2[r]) * kLn2, Zs, Zt);
+  float kl = kl_from_sums(mu, ref_s - ref_t, Zs, Zt);
   const float iz = 1.f / Zs;
   float ent = lse_t - Bt / Zt;              // H[p_t] = lse_t - E_{p_t}[z_t]; both sums share the reference
   // a row without a finite log-sum-exp, mean or KL (logits beyond the range the fixed
@@ -1111,8 +1182,8 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   bool have_y = false;
   uint32_t flag = dead ? ADWIN_DEV_NONFINITE : 0u;
   if (a.ids && (a.c || a.t_logp || a.t_rank || a.cr) && !dead) {
-    if (b.yid[r] >= 0) {
-      const float zy_s = b.zy_s[r], zy_t = b.zy_t[r];     // taken with the references
+    if (b.ref.yid[r] >= 0) {
+      const float zy_s = b.ref.zy[0][r], zy_t = b.ref.zy[1][r];     // taken with the references
       c = (zy_s - lse_s) - (zy_t - lse_t);
       logp_t = zy_t - lse_t;
       have_y = true;
@@ -1139,25 +1210,25 @@ hipError_t sweep_kernels_opt_in() {
 #define ADWIN_OPT_IN(KERNEL, BYTES)                                                              \
   e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES); \
   if (e != hipSuccess) return e;
-  ADWIN_OPT_IN(prepare_kernel, kRefLds)
+  ADWIN_OPT_IN(prepare_kernel<false>, kRefLds)
   ADWIN_OPT_IN(logit_pass_kernel<false>, kLogitLds)
   ADWIN_OPT_IN(logit_pass_kernel<true>, kLogitLds)
   ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, false>), kDmaLds)
   ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, true>), kDmaLds)
   ADWIN_OPT_IN((logit_pass_dma_kernel<kModeDz, false>), kDmaLds)
   ADWIN_OPT_IN((logit_pass_dma_kernel<kModeDz, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, true>), kDmaLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, false>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, true>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, false>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, true>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, false>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, true>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, false>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, true>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, false>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, true>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, false>), kDmaRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, true>), kDmaRefLds)
 #undef ADWIN_OPT_IN
   return hipSuccess;
 }
@@ -1180,8 +1251,8 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStre
   switch (mode) {
 #define ADWIN_CASE(M)                                                                       \
   case M:                                                                                   \
-    if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, kDmaLds, st>>>(a);          \
-    else logit_pass_dma_kernel<M, false><<<grid, 256, kDmaLds, st>>>(a);                    \
+    if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, M < kModeSingle ? kDmaLds : kDmaRefLds, st>>>(a);  \
+    else logit_pass_dma_kernel<M, false><<<grid, 256, M < kModeSingle ? kDmaLds : kDmaRefLds, st>>>(a);            \
     break;
     ADWIN_CASE(kModeStats)
     ADWIN_CASE(kModeDz)
@@ -1197,18 +1268,28 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStre
   return hipGetLastError();
 }
 
-// One launch up to 32 token tiles.  An image workgroup in a launch with references holds their
-// LDS as well, one workgroup per compute unit, so that the images of a large call, 164 us of
-// copying for 34,000 rows, go by themselves.
-hipError_t launch_prepare(const PrepareArgs& p, int n_tiles, hipStream_t st) {
+// The finely cut references serve calls of up to kFineRefTiles token tiles (References::parts is set by the
+// same rule): at five tiles of H = 1024 + 2048 they take 18 us against 25.5 staged, at 13 tiles of H = 512 + 640
+// 20.6 against 15.8.
+hipError_t launch_prepare(const PrepareArgs& p, bool refs, int n_tiles, hipStream_t st) {
   PrepareArgs a = p;
-  a.t_blocks = n_tiles * a.ht.nk;
-  const unsigned images = (unsigned)(a.t_blocks + n_tiles * a.hs.nk);
+  const int rows = n_tiles * kTileTokens;
+  const bool fine = a.ref.parts > 1;
+  a.ref_blocks = !refs ? 0 : fine ? rows / kRefRows * kRefBlocks * 2 : rows / kRefRows;
+  a.dot_blocks = refs && fine ? rows * 2 / (kPrepWaves * kTokenRows) : 0;
+  for (int m = 0; m < 2; ++m) a.img_blocks[m] = n_tiles * a.img[m].nk;
+  const int rest = a.dot_blocks + a.img_blocks[0] + a.img_blocks[1];
+  if (fine) {
+    prepare_kernel<true><<<(unsigned)(a.ref_blocks + rest), kPrepThreads, kRefFineLds, st>>>(a);
+    return hipGetLastError();
+  }
+  // a workgroup of a launch with staged references holds their LDS as well, one workgroup per compute
+  // unit, so that the others of a large call, 164 us of copying for 34,000 rows, go by themselves
   if (a.ref_blocks && n_tiles > 32) {
-    prepare_kernel<<<(unsigned)a.ref_blocks, kRefThreads, kRefLds, st>>>(a);
+    prepare_kernel<false><<<(unsigned)a.ref_blocks, kPrepThreads, kRefLds, st>>>(a);
     a.ref_blocks = 0;
   }
-  prepare_kernel<<<(unsigned)a.ref_blocks + images, kRefThreads, a.ref_blocks ? kRefLds : 0, st>>>(a);
+  prepare_kernel<false><<<(unsigned)(a.ref_blocks + rest), kPrepThreads, a.ref_blocks ? kRefLds : 0, st>>>(a);
   return hipGetLastError();
 }
 
