@@ -562,26 +562,6 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     ADWIN_HIP_TRY(launch_fill_f32(p->dW_prefix, (int64_t)p->V * p->H_s, 0.f, stream));
     ADWIN_HIP_TRY(launch_fill_f32(p->dW_full, (int64_t)p->V * p->H_s, 0.f, stream));
   }
-  // finalize over every packed row (also zero-fills rows outside the windows)
-  phase(ADWIN_PHASE_REDUCE);
-  if (p->T > 0 && need_g) {
-    FinalizeArgs f;
-    f.pl = pl; f.B = p->B; f.T = p->T; f.probe = probe; f.n_rows = hp.n_rows;
-    f.g = gws; f.ksplit = L.ksplit; f.n_pad = n_pad; f.H = p->H_s;
-    f.g_rows = n_pad;
-    f.inv_z = (const float*)(ws + L.o_invz);
-    // the fp32 part of g; the sampled estimator contracts E2 as stored and lists nothing
-    f.heavy = heavy;
-    if (p->estimator == ADWIN_EST_SAMPLED) f.heavy.cnt = nullptr;
-    f.lse_s = (const float*)(ws + L.o_lse_s);
-    f.mu = (const float*)(ws + (L.single ? L.o_delta : L.o_mu));
-    f.h_s = (const __bf16*)p->h_s; f.h_t = (const __bf16*)p->h_t; f.W_t = (const __bf16*)p->W_t; f.H_t = p->H_t;
-    f.cr = (L.single && p->estimator == ADWIN_EST_SAMPLED) ? (const float*)(ws + L.o_cr) : nullptr;
-    f.ids = p->ids; f.W_s = (const __bf16*)p->W_s; f.V = p->V;
-    f.grad_scale = p->grad_scale; f.dh_bf16 = p->dh_dtype == ADWIN_DT_BF16;
-    f.dh_prefix = p->dh_prefix; f.dh_full = p->dh_full; f.rownorm = rownorm;
-    ADWIN_HIP_TRY(launch_finalize(f, stream));
-  }
   const bool pooled = probe && need_g;
   PoolArgs pa{};
   pa.pl = pl; pa.B = p->B; pa.H = p->H_s; pa.g = gws;
@@ -590,7 +570,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
   BatchArgs b{};
   b.pl = pl; b.B = p->B; b.H = need_g ? p->H_s : 0; b.probe = probe;
   b.zero_grad = (p->grad_scale == 0.f) || !need_g;
-  b.klr = klr; b.rownorm = need_g ? rownorm : nullptr;
+  b.klr = klr; b.rownorm = pooled ? rownorm : nullptr;     // only the alignment reads their sums
   b.loss_prefix = p->loss_prefix; b.loss_full = p->loss_full;
   b.seg = seg; b.up = pa.up; b.uf = pa.uf; b.racc = (double*)(ws + L.o_racc); b.done = done;
   b.rho_pooled = p->rho_pooled; b.rho_field = p->rho_field; b.batch = p->batch;
@@ -622,7 +602,31 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     sa.acc = (double*)(ws + L.o_summ);
     sa.first_reject = p->t_first_reject; sa.logp_mean = p->t_logp_mean; sa.loss_share = p->cand_loss_share;
   }
-  ADWIN_HIP_TRY(launch_tail(b, sa, ca, pooled ? &pa : nullptr, hp.n_chunks, stream));
+  // finalize over every packed row (also zero-fills rows outside the windows).  Without probe gradients the
+  // reductions that end the call need nothing of it and share its launch (but for the rollout summaries,
+  // whose registers would cost it waves).
+  phase(ADWIN_PHASE_REDUCE);
+  const TailArgs tail = make_tail(b, sa);
+  const bool finalize = p->T > 0 && need_g, together = finalize && !pooled && !tail.with_summary;
+  if (finalize) {
+    FinalizeArgs f;
+    f.pl = pl; f.B = p->B; f.T = p->T; f.probe = probe; f.n_rows = hp.n_rows;
+    f.g = gws; f.ksplit = L.ksplit; f.n_pad = n_pad; f.H = p->H_s;
+    f.g_rows = n_pad;
+    f.inv_z = (const float*)(ws + L.o_invz);
+    // the fp32 part of g; the sampled estimator contracts E2 as stored and lists nothing
+    f.heavy = heavy;
+    if (p->estimator == ADWIN_EST_SAMPLED) f.heavy.cnt = nullptr;
+    f.lse_s = (const float*)(ws + L.o_lse_s);
+    f.mu = (const float*)(ws + (L.single ? L.o_delta : L.o_mu));
+    f.h_s = (const __bf16*)p->h_s; f.h_t = (const __bf16*)p->h_t; f.W_t = (const __bf16*)p->W_t; f.H_t = p->H_t;
+    f.cr = (L.single && p->estimator == ADWIN_EST_SAMPLED) ? (const float*)(ws + L.o_cr) : nullptr;
+    f.ids = p->ids; f.W_s = (const __bf16*)p->W_s; f.V = p->V;
+    f.grad_scale = p->grad_scale; f.dh_bf16 = p->dh_dtype == ADWIN_DT_BF16;
+    f.dh_prefix = p->dh_prefix; f.dh_full = p->dh_full; f.rownorm = rownorm;
+    ADWIN_HIP_TRY(launch_finalize(f, together ? &tail : nullptr, stream));
+  }
+  if (!together) ADWIN_HIP_TRY(launch_tail(b, sa, ca, pooled ? &pa : nullptr, hp.n_chunks, stream));
   // alignment of the two objectives in the LM-head parameter block: batch[6]
   if (p->dW_prefix && p->dW_full && p->batch)
     ADWIN_HIP_TRY(launch_cosine(p->dW_prefix, p->dW_full, (int64_t)p->V * p->H_s,

@@ -336,7 +336,8 @@ hipError_t grad_kernels_opt_in();
 hipError_t launch_hs_gather(const HsGatherArgs& a, int64_t rows, hipStream_t st);
 hipError_t launch_combine(bool transposed, bool sampled, const CombineArgs& a, int row_tiles, hipStream_t st);
 hipError_t launch_grad_gemm(const GradArgs& a, hipStream_t st);
-hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t st);
+// `tail`: the reductions that end a call without probe gradients, in the same launch (or NULL)
+hipError_t launch_finalize(const FinalizeArgs& a, const TailArgs* tail, hipStream_t st);
 
 }  // namespace adwin
 

@@ -7,6 +7,7 @@
 // GEMM     : g = dz W_s (and dW_s = (w dz)^T h_s) as bf16 MFMA GEMMs over tile images.
 // Finalize : scale by grad_scale * alpha, scatter to dh_prefix / dh_full, row norms.
 #include "fused_shared.h"
+#include "tail_device.h"
 #include <utility>
 
 namespace adwin {
@@ -460,7 +461,8 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
 // ---------------------------------------------------------------------------------------
 // Finalize.  TPR threads per computed row sum the k-split planes, add the heavy entries, write
 // the row norm, scale by grad_scale*alpha and scatter to dh_prefix / dh_full; the workgroups
-// behind those clear the rows outside the windows, kZeroRows packed rows each.
+// behind those clear the rows outside the windows, kZeroRows packed rows each, and the first
+// tail.blocks take the reductions that end the call, which need nothing of the rest.
 // Memory bound, if enough is in flight: a wave per row added up to 32 planes of 8 KB one load
 // after the other (97 us for 337 rows, H = 2048) and looked every packed row up for itself before
 // it wrote 8 bytes per lane (291,000 rows cleared at 3.4 TB/s, 350 us).  A row of more than 512
@@ -497,18 +499,22 @@ __device__ __forceinline__ void clear_rows(const FinalizeArgs& a, int64_t t0, in
 }
 
 template <int TPR>
-__global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
+__global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, TailArgs tail) {
   constexpr int kRows = 256 / TPR, kWaves = TPR / 64;
   __shared__ int heavy_v[kRows][kHeavySlots];
   __shared__ float heavy_d[kRows][kHeavySlots];
   __shared__ float part[kRows][kHeavySlots][kWaves][2];
+  __shared__ double sh[16];
+  __shared__ int sh_first[4];
+  if ((int)blockIdx.x < tail.blocks) return tail_body<false>(tail, blockIdx.x, sh, sh_first);
+  const int64_t block = (int64_t)blockIdx.x - tail.blocks;
   const int64_t row_blocks = (a.n_rows + kRows - 1) / kRows;
-  if ((int64_t)blockIdx.x >= row_blocks) {
-    const int64_t t0 = ((int64_t)blockIdx.x - row_blocks) * kZeroRows;
+  if (block >= row_blocks) {
+    const int64_t t0 = (block - row_blocks) * kZeroRows;
     return clear_rows(a, t0, t0 + kZeroRows < a.T ? t0 + kZeroRows : a.T);
   }
   const int sub = threadIdx.x / TPR, lid = threadIdx.x % TPR, lane = threadIdx.x & 63, w = lid >> 6;
-  const int64_t r = (int64_t)blockIdx.x * kRows + sub;
+  const int64_t r = block * kRows + sub;
   const bool have = r < a.n_rows;
   const int i = have ? a.pl.row_seq[r] : 0;
   const int64_t t = have ? a.pl.row_idx[r] : 0;
@@ -645,15 +651,17 @@ hipError_t launch_grad_gemm(const GradArgs& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t st) {
+hipError_t launch_finalize(const FinalizeArgs& a, const TailArgs* end, hipStream_t st) {
   // one plane: thousands of rows, or a vocabulary so small that a row has nothing to add up; a wave each
   const bool wide = a.H > 512 && a.ksplit > 1;
   const int64_t row_blocks = wide ? a.n_rows : (a.n_rows + 3) / 4;
   const int64_t zero_blocks = !a.probe && a.dh_prefix ? (a.T + kZeroRows - 1) / kZeroRows : 0;
-  const unsigned grid = (unsigned)(row_blocks + zero_blocks);
+  TailArgs tail{};
+  if (end) tail = *end;
+  const unsigned grid = (unsigned)(row_blocks + zero_blocks + tail.blocks);
   if (grid == 0) return hipSuccess;
-  if (wide) finalize_kernel<256><<<grid, 256, 0, st>>>(a);
-  else finalize_kernel<64><<<grid, 256, 0, st>>>(a);
+  if (wide) finalize_kernel<256><<<grid, 256, 0, st>>>(a, tail);
+  else finalize_kernel<64><<<grid, 256, 0, st>>>(a, tail);
   return hipGetLastError();
 }
 

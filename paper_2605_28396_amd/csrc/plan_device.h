@@ -109,7 +109,9 @@ struct PoolArgs {       // pooled gradients per rollout (see pool_partial_kernel
   const float* g; float* pp; float* pf;   // partials [n_chunks][H]
   float* up; float* uf;                   // [B][H]
 };
-struct TailArgs { BatchArgs b; SummaryArgs s; CandArgs c; int fold, with_summary; };
+struct TailArgs { BatchArgs b; SummaryArgs s; CandArgs c; int fold, with_summary, blocks; };
+// a tail without probe gradients: `blocks` workgroups (see tail_device.h)
+TailArgs make_tail(const BatchArgs& b, const SummaryArgs& s);
 hipError_t launch_tail(const BatchArgs& b, const SummaryArgs& s, const CandArgs& c, const PoolArgs* pooled,
                        int64_t n_chunks, hipStream_t st);
 

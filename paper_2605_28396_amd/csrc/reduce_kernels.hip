@@ -6,6 +6,7 @@
 
 #include "device_utils.h"
 #include "plan_device.h"
+#include "tail_device.h"
 
 namespace adwin {
 
@@ -29,21 +30,6 @@ DevicePlan device_plan_at(unsigned char* ws_plan, int32_t B, int32_t* row_idx, i
 __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
-}
-
-// Fixed-order block sum of up to 4 doubles per thread (256 threads).
-template <int K>
-__device__ __forceinline__ void block_sum256(double (&v)[K], double* sh /* [K][4] */) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    v[k] = wave_sum(v[k]);
-    if (lane == 0) sh[k * 4 + w] = v[k];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = (sh[k * 4 + 0] + sh[k * 4 + 1]) + (sh[k * 4 + 2] + sh[k * 4 + 3]);
-  __syncthreads();
 }
 
 // Column sums of g over the window and over the rollout, in two levels.  Both kernels add rows in
@@ -115,133 +101,6 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a, CandArgs c) {
     for (int q = 0; q < kPoolStep; ++q) s += v[q];
   }
   c.uc[((int64_t)k * a.B + i) * a.H + h] = s;
-}
-
-// Rollout i: sums of KL_t and ||g_t||^2 over the window and the rollout, the window losses, and
-// the cosines from the pooled sums and the norm sums.
-__device__ __forceinline__ void rollout_body(const BatchArgs& a, int i, double* sh) {
-  const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
-  const int64_t ni = a.pl.n[i];
-  const int64_t hi = a.probe ? len : ni;
-  const int64_t r0 = a.pl.comp_off[i];
-  double v[4] = {0.0, 0.0, 0.0, 0.0};   // kl prefix, kl full, norm prefix, norm full
-#pragma unroll 4
-  for (int64_t j = threadIdx.x; j < hi; j += 256) {
-    const double k = a.klr[r0 + j];
-    const double s = a.rownorm ? (double)a.rownorm[r0 + j] : 0.0;
-    v[1] += k;
-    v[3] += s;
-    if (j < ni) { v[0] += k; v[2] += s; }
-  }
-  block_sum256<4>(v, sh);
-  const bool align = a.probe && !a.zero_grad;
-  double u[3] = {0.0, 0.0, 0.0};
-  if (align) {
-    const float* up = a.up + (size_t)i * a.H;
-    const float* uf = a.uf + (size_t)i * a.H;
-#pragma unroll 4
-    for (int h = threadIdx.x; h < a.H; h += 256) {
-      const double p = up[h], f = uf[h];
-      u[0] += p * f;
-      u[1] += p * p;
-      u[2] += f * f;
-    }
-    block_sum256<3>(u, sh);
-  }
-  if (threadIdx.x == 0) {
-    a.seg[i * 4 + 0] = v[0];
-    a.seg[i * 4 + 1] = v[1];
-    a.seg[i * 4 + 2] = v[2];
-    a.seg[i * 4 + 3] = v[3];
-    if (a.loss_prefix) a.loss_prefix[i] = ni > 0 ? (float)(v[0] / (double)ni) : 0.f;
-    if (a.loss_full) a.loss_full[i] = (a.probe && len > 0) ? (float)(v[1] / (double)len) : 0.f;
-    double rp = 0.0, rf = 0.0, okp = 0.0, okf = 0.0;
-    if (align) {
-      if (u[1] > 0.0 && u[2] > 0.0) { rp = u[0] / (sqrt(u[1]) * sqrt(u[2])); okp = 1.0; }
-      if (v[2] > 0.0 && v[3] > 0.0) { rf = sqrt(v[2] / v[3]); okf = 1.0; }
-      a.racc[i * 4 + 0] = rp;
-      a.racc[i * 4 + 1] = okp;
-      a.racc[i * 4 + 2] = rf;
-      a.racc[i * 4 + 3] = okf;
-    }
-    if (a.rho_pooled) a.rho_pooled[i] = (float)rp;
-    if (a.rho_field) a.rho_field[i] = (float)rf;
-  }
-}
-
-// One workgroup: batch objectives, micro (after aggregation) and macro (mean of
-// per-rollout) alignment, integer outputs.  The sums over the rollouts run in index order, their
-// terms loaded kBatchStep rollouts ahead: one round trip per rollout made the aggregates of 200
-// rollouts at H = 1536 635 us.
-constexpr int kBatchStep = 16;
-__device__ __forceinline__ void batch_body(const BatchArgs& a, double* sh) {
-  const int B = a.B;
-  const bool align = a.probe && !a.zero_grad;
-  // batch objectives and field sums
-  double w[4] = {0.0, 0.0, 0.0, 0.0};   // L^p, L^f, macro pooled sum, macro pooled count
-  double f[4] = {0.0, 0.0, 0.0, 0.0};   // field: dot, |p|^2, |f|^2, unused
-  double mf[2] = {0.0, 0.0};            // macro field sum, count
-  for (int i = threadIdx.x; i < B; i += 256) {
-    const double ap = a.pl.alpha_p[i], af = a.pl.alpha_f[i];
-    w[0] += ap * a.seg[i * 4 + 0];
-    if (a.probe) w[1] += af * a.seg[i * 4 + 1];
-    if (align) {
-      w[2] += a.racc[i * 4 + 0] * a.racc[i * 4 + 1];
-      w[3] += a.racc[i * 4 + 1];
-      mf[0] += a.racc[i * 4 + 2] * a.racc[i * 4 + 3];
-      mf[1] += a.racc[i * 4 + 3];
-      const double Sp = a.seg[i * 4 + 2], Sf = a.seg[i * 4 + 3];
-      f[0] += ap * af * Sp;
-      f[1] += ap * ap * Sp;
-      f[2] += af * af * Sf;
-    }
-  }
-  block_sum256<4>(w, sh);
-  // micro pooled: aggregate the weighted pooled gradients over the batch, then one cosine
-  double m[3] = {0.0, 0.0, 0.0};
-  if (align) {
-    block_sum256<4>(f, sh);
-    block_sum256<2>(mf, sh);
-    for (int h = threadIdx.x; h < a.H; h += 256) {
-      double sp = 0.0, sf = 0.0;
-      for (int i0 = 0; i0 < B; i0 += kBatchStep) {
-        float p[kBatchStep], f[kBatchStep];
-#pragma unroll
-        for (int q = 0; q < kBatchStep; ++q) {
-          const int i = i0 + q < B ? i0 + q : B - 1;
-          p[q] = a.up[(size_t)i * a.H + h];
-          f[q] = a.uf[(size_t)i * a.H + h];
-        }
-#pragma unroll
-        for (int q = 0; q < kBatchStep; ++q)
-          if (i0 + q < B) {
-            sp += (double)a.pl.alpha_p[i0 + q] * (double)p[q];
-            sf += (double)a.pl.alpha_f[i0 + q] * (double)f[q];
-          }
-      }
-      m[0] += sp * sf;
-      m[1] += sp * sp;
-      m[2] += sf * sf;
-    }
-    block_sum256<3>(m, sh);
-  }
-  if (a.n_out)
-    for (int i = threadIdx.x; i < B; i += 256) a.n_out[i] = a.pl.n[i];
-  if (threadIdx.x == 0) {
-    if (a.n_adm_out) *a.n_adm_out = a.n_adm;
-    if (a.batch) {
-      float o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      o[0] = (float)w[0];
-      if (a.probe) o[1] = (float)w[1];
-      if (align) {
-        if (m[1] > 0.0 && m[2] > 0.0) o[2] = (float)(m[0] / (sqrt(m[1]) * sqrt(m[2])));
-        if (f[1] > 0.0 && f[2] > 0.0) o[3] = (float)(f[0] / (sqrt(f[1]) * sqrt(f[2])));
-        if (w[3] > 0.0) o[4] = (float)(w[2] / w[3]);
-        if (mf[1] > 0.0) o[5] = (float)(mf[0] / mf[1]);
-      }
-      for (int k = 0; k < 8; ++k) a.batch[k] = o[k];
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -362,148 +221,30 @@ __device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double
 }
 
 // ---------------------------------------------------------------------------------------
-// Rollout-level summaries of the per-row outputs.  One workgroup per rollout; every thread
-// takes positions tid, tid + 256, ... in ascending order with double accumulators, and the
-// 256 partials are folded in a fixed order, so the results do not depend on scheduling.
-// ---------------------------------------------------------------------------------------
-__device__ __forceinline__ double block_sum_256(double v, double* sh) {
-  double x[1] = {v};
-  block_sum256<1>(x, sh);
-  return x[0];
-}
-
-__device__ __forceinline__ void summary_rollout_body(const SummaryArgs& a, int i, double* sh /* [4 (ADWIN_MAX_CANDIDATES + 1)] */,
-                                                     int* sh_first /* [4] */) {
-  const int tid = threadIdx.x;
-  const int64_t base = a.pl.offsets[i];
-  const int64_t len = a.pl.offsets[i + 1] - base;
-  const int64_t n = a.pl.n[i];
-  const int64_t m = a.probe ? len : n;          // computed positions of this rollout
-  double* acc = a.acc + (size_t)i * kSummarySlots;
-  if (a.first_reject) {
-    int64_t first = m;
-    for (int64_t j = tid; j < m; j += 256)
-      if (a.t_rank[base + j] > a.topk) { first = j; break; }
-    int lowest = (int)first;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lowest = min(lowest, __shfl_xor(lowest, o, 64));
-    if ((tid & 63) == 0) sh_first[tid >> 6] = lowest;
-    __syncthreads();
-    if (tid == 0) a.first_reject[i] = min(min(sh_first[0], sh_first[1]), min(sh_first[2], sh_first[3]));
-  }
-  if (a.logp_mean) {
-    double sp = 0.0, ss = 0.0;
-    for (int64_t j = tid; j < m; j += 256) {
-      const double v = (double)a.t_logp[base + j];
-      if (j < n) sp += v; else ss += v;
-    }
-    double both[2] = {sp, ss};
-    block_sum256<2>(both, sh);
-    sp = both[0]; ss = both[1];
-    if (tid == 0) {
-      acc[ADWIN_MAX_CANDIDATES + 1] = sp;
-      acc[ADWIN_MAX_CANDIDATES + 2] = ss;
-      a.logp_mean[2 * i + 0] = n > 0 ? (float)(sp / (double)n) : 0.f;
-      a.logp_mean[2 * i + 1] = m > n ? (float)(ss / (double)(m - n)) : 0.f;
-    }
-  }
-  if (a.loss_share) {
-    double part[ADWIN_MAX_CANDIDATES + 1];       // per candidate, then the total
-#pragma unroll
-    for (int k = 0; k <= ADWIN_MAX_CANDIDATES; ++k) part[k] = 0.0;
-    for (int64_t j = tid; j < m; j += 256) {
-      const double v = (double)a.kl[base + j];
-      part[ADWIN_MAX_CANDIDATES] += v;
-#pragma unroll
-      for (int k = 0; k < ADWIN_MAX_CANDIDATES; ++k)
-        if (k < a.K && j < a.L[k]) part[k] += v;
-    }
-    block_sum256<ADWIN_MAX_CANDIDATES + 1>(part, sh);     // together: two barriers in all
-    if (tid == 0) {
-      acc[ADWIN_MAX_CANDIDATES] = part[ADWIN_MAX_CANDIDATES];
-#pragma unroll
-      for (int k = 0; k < ADWIN_MAX_CANDIDATES; ++k)
-        if (k < a.K) acc[k] = part[k];
-    }
-  }
-}
-
-// Batch rows of the summaries: sums over rollouts in index order.
-__device__ __forceinline__ void summary_batch_body(const SummaryArgs& a) {
-  const int tid = threadIdx.x;
-  if (a.loss_share && tid < a.K) {
-    double part = 0.0, tot = 0.0;
-    for (int i0 = 0; i0 < a.B; i0 += kBatchStep) {
-      double p[kBatchStep], t[kBatchStep];
-#pragma unroll
-      for (int q = 0; q < kBatchStep; ++q) {
-        const double* acc = a.acc + (size_t)(i0 + q < a.B ? i0 + q : a.B - 1) * kSummarySlots;
-        p[q] = acc[tid];
-        t[q] = acc[ADWIN_MAX_CANDIDATES];
-      }
-#pragma unroll
-      for (int q = 0; q < kBatchStep; ++q)
-        if (i0 + q < a.B) { part += p[q]; tot += t[q]; }
-    }
-    a.loss_share[tid] = tot != 0.0 ? (float)(part / tot) : 0.f;
-  }
-  if (a.logp_mean && tid >= 32 && tid < 34) {
-    const int c = tid - 32;
-    double sum = 0.0;
-    int64_t cnt = 0;
-    for (int i0 = 0; i0 < a.B; i0 += kBatchStep) {
-      double v[kBatchStep];
-      int64_t k[kBatchStep];
-#pragma unroll
-      for (int q = 0; q < kBatchStep; ++q) {
-        const int i = i0 + q < a.B ? i0 + q : a.B - 1;
-        const int64_t len = a.pl.offsets[i + 1] - a.pl.offsets[i];
-        const int64_t n = a.pl.n[i], m = a.probe ? len : n;
-        v[q] = a.acc[(size_t)i * kSummarySlots + ADWIN_MAX_CANDIDATES + 1 + c];
-        k[q] = c == 0 ? n : m - n;
-      }
-#pragma unroll
-      for (int q = 0; q < kBatchStep; ++q)
-        if (i0 + q < a.B) { sum += v[q]; cnt += k[q]; }
-    }
-    a.logp_mean[2 * a.B + c] = cnt > 0 ? (float)(sum / (double)cnt) : 0.f;
-  }
-}
-
-// ---------------------------------------------------------------------------------------
-// The end of a call in one launch (two with probe gradients).  Workgroups [0, B): rollouts; the
-// next B (with_summary): their summaries; the next K B: candidates.  Each of these used to be
-// a launch of about 4.7 us, and so were the batch aggregates, which need all of them: without
-// probe gradients they are a few sums over B and are taken by the workgroup that finishes last
-// (`fold`: it counts the finished ones in `done`, and adds in rollout order, so the result does
-// not depend on which one it is); with them each aggregate runs over all H columns, and a launch
-// of 1 + K workgroups (batch_kernel) takes them side by side.  Logits of 24
+// The end of a call in one launch (two with probe gradients), or in that of finalize_kernel
+// (tail_device.h).  Workgroups [0, B): rollouts; the next B (with_summary): their summaries; the next
+// K B: candidates.  Each of these used to be a launch of about 4.7 us, and so were the batch
+// aggregates, which need all of them: without probe gradients (`fold`) the workgroup that finishes last
+// takes them; with them each aggregate runs over all H columns, and a launch of 1 + K workgroups
+// (batch_kernel) takes them side by side.  Logits of 24
 // rollouts with diagnostics: 425 -> 412 us; one rollout of 37 rows 52.6 -> 49.5 us; the probe
 // audit of 9 rollouts with 7 candidates, with the pooling above: 397 -> 333 us.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void tail_kernel(TailArgs a) {
   __shared__ double sh[4 * (ADWIN_MAX_CANDIDATES + 1)];
   __shared__ int sh_first[4];
+  if (a.fold) return tail_body<true>(a, blockIdx.x, sh, sh_first);
   const int B = a.b.B, role = blockIdx.x / B, i = blockIdx.x % B;
-  if (role == 0) rollout_body(a.b, i, sh);
+  if (role == 0) rollout_body<true>(a.b, i, sh);
   else if (role == 1 && a.with_summary) summary_rollout_body(a.s, i, sh, sh_first);
   else cand_align_body(a.c, role - 1 - a.with_summary, i, sh);
-  if (!a.fold) return;
-  __threadfence();                      // this workgroup's sums, before it counts itself
-  __syncthreads();
-  if (threadIdx.x == 0) sh_first[0] = atomicAdd(a.b.done, 1u) + 1u == gridDim.x;
-  __syncthreads();
-  if (!sh_first[0]) return;
-  __threadfence();                      // the other workgroups' sums
-  batch_body(a.b, sh);
-  if (a.with_summary) summary_batch_body(a.s);
 }
 
 __global__ __launch_bounds__(256) void batch_kernel(TailArgs a) {
   __shared__ double sh[16];
   __shared__ double alpha[kCandLds];
   if (blockIdx.x == 0) {
-    batch_body(a.b, sh);
+    batch_body<true>(a.b, sh);
     if (a.with_summary) summary_batch_body(a.s);
   } else {
     cand_batch_body(a.c, blockIdx.x - 1, sh, alpha);
@@ -554,26 +295,34 @@ hipError_t launch_cosine(const float* x, const float* y, int64_t n, double* part
   cosine_final_kernel<<<1, 64, 0, st>>>(partials, out);
   return hipGetLastError();
 }
+TailArgs make_tail(const BatchArgs& b, const SummaryArgs& s) {
+  TailArgs a;
+  a.b = b; a.s = s; a.c = CandArgs{};
+  a.fold = 1;
+  a.with_summary = s.first_reject || s.logp_mean || s.loss_share;
+  a.blocks = b.B * (1 + a.with_summary);
+  return a;
+}
 hipError_t launch_tail(const BatchArgs& b, const SummaryArgs& s, const CandArgs& c, const PoolArgs* pooled,
                        int64_t n_chunks, hipStream_t st) {
-  TailArgs a;
-  a.b = b; a.s = s; a.c = c;
-  a.fold = pooled == nullptr;
-  a.with_summary = s.first_reject || s.logp_mean || s.loss_share;
-  const unsigned B = (unsigned)b.B, K = pooled ? (unsigned)c.K : 0u;
+  TailArgs a = make_tail(b, s);
   hipError_t e;
-  if (pooled) {
-    const unsigned cols = (unsigned)((pooled->H + 255) / 256);
-    if (n_chunks > 0) {
-      pool_partial_kernel<<<dim3((unsigned)n_chunks, cols), 256, 0, st>>>(*pooled);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    pool_kernel<<<dim3((1 + K) * B, cols), 256, 0, st>>>(*pooled, c);
+  if (!pooled) {
+    tail_kernel<<<(unsigned)a.blocks, 256, 0, st>>>(a);
+    return hipGetLastError();
+  }
+  a.c = c;
+  a.fold = 0;
+  const unsigned B = (unsigned)b.B, K = (unsigned)c.K, cols = (unsigned)((pooled->H + 255) / 256);
+  if (n_chunks > 0) {
+    pool_partial_kernel<<<dim3((unsigned)n_chunks, cols), 256, 0, st>>>(*pooled);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
+  pool_kernel<<<dim3((1 + K) * B, cols), 256, 0, st>>>(*pooled, c);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   tail_kernel<<<B * (1 + (unsigned)a.with_summary + K), 256, 0, st>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (pooled) batch_kernel<<<1 + K, 256, 0, st>>>(a);
+  batch_kernel<<<1 + K, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t st) {
