@@ -397,7 +397,8 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
   } else if (!p->ids) {
     setup.clear(p->c, p->T);
   }
-  ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
+  const bool prepares = hp.n_rows > 0 && L.use_dma;       // launch_prepare does the setup too
+  if (!prepares) ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
 
   if (hp.n_rows > 0) {
     const int vt_total = (int)(L.Vp / kTileVocab);
@@ -413,7 +414,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       // token tiles of 256 computed rows gathered through row_idx
       RowImageArgs ia;
       if (!L.direct_w) {
-        ia.row_idx = nullptr; ia.n_rows = p->V; ia.permute = 1;
+        ia.n_rows = p->V; ia.permute = 1;
         ia.src = (const uint4*)p->W_t; ia.img = (uint4*)(ws + L.o_wt_img); ia.H = p->H_t; ia.nk = p->H_t / kBK;
         ADWIN_HIP_TRY(launch_row_image(ia, (unsigned)vt_total, stream));
         ia.src = (const uint4*)p->W_s; ia.img = (uint4*)(ws + L.o_ws_img); ia.H = p->H_s; ia.nk = p->H_s / kBK;
@@ -423,7 +424,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       pr.row_idx = pl.row_idx; pr.ids = p->ids; pr.V = p->V; pr.ref = ref;
       pr.h[0] = (const __bf16*)p->h_s; pr.W[0] = (const __bf16*)p->W_s; pr.H[0] = p->H_s;
       pr.h[1] = (const __bf16*)p->h_t; pr.W[1] = (const __bf16*)p->W_t; pr.H[1] = p->H_t;
-      ia.row_idx = pl.row_idx; ia.n_rows = n_pad; ia.permute = 0;
+      ia.n_rows = n_pad; ia.permute = 0;
       for (int m = 0; m < 2; ++m) {
         ia.src = (const uint4*)pr.h[m]; ia.img = (uint4*)(ws + (m ? L.o_ht_img : L.o_hs_img));
         ia.H = pr.H[m]; ia.nk = pr.H[m] / kBK;
@@ -431,7 +432,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       }
       // single sweep: the fixed references of every row, from vocabulary tile 0 and the sampled
       // token (without ids: id -1 on every row, which the diagnostics sweep expects)
-      ADWIN_HIP_TRY(launch_prepare(pr, L.single, n_tiles, stream));
+      ADWIN_HIP_TRY(launch_prepare(pr, L.single, n_tiles, setup, blob, stream));
     }
     LogitPassArgs la;
     la.h_s = (const __bf16*)p->h_s; la.h_t = (const __bf16*)p->h_t;

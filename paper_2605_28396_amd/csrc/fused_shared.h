@@ -212,7 +212,7 @@ constexpr int kModeSingleFwdDiag = 7; // the same plus the diagnostics
 
 // Tile images of a row-major [rows, H] operand (see row_image_kernel).
 struct RowImageArgs {
-  const uint4* src; uint4* img; const int32_t* row_idx;
+  const uint4* src; uint4* img;
   int64_t n_rows; int H, nk;
   int permute;     // rows of every group of 32 in the order the logit kernels' epilogues want (W tiles)
 };
@@ -251,7 +251,7 @@ struct PrepareArgs {
   References ref;
   RowImageArgs img[2];                            // of the hidden states
   // workgroups: references (0: none wanted), logits of the sampled tokens, images of h_s, of h_t
-  int ref_blocks, dot_blocks, img_blocks[2];
+  int ref_blocks, dot_blocks, img_blocks[2], setup_blocks;
 };
 
 // Combine pass over one slab (see combine_kernel).
@@ -327,8 +327,9 @@ hipError_t sweep_kernels_opt_in();       // large dynamic LDS of the logit kerne
 hipError_t launch_row_image(const RowImageArgs& a, unsigned tiles, hipStream_t st);
 // mode: one of kMode*; dma false selects the register-staged kernel (kModeStats, kModeDz only)
 hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& a, hipStream_t st);
-// `refs`: with the references of the single sweep
-hipError_t launch_prepare(const PrepareArgs& a, bool refs, int n_tiles, hipStream_t st);
+// the call's setup and what its sweep needs prepared; `refs`: with the references of the single sweep
+hipError_t launch_prepare(const PrepareArgs& a, bool refs, int n_tiles, const SetupArgs& setup,
+                          const std::vector<unsigned char>& plan, hipStream_t st);
 hipError_t launch_merge_stats(const MergeArgs& a, hipStream_t st);
 hipError_t launch_merge_single(const MergeSingleArgs& a, hipStream_t st);
 // grad_kernels.hip

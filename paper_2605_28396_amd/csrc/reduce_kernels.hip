@@ -6,6 +6,7 @@
 
 #include "device_utils.h"
 #include "plan_device.h"
+#include "setup_device.h"
 #include "tail_device.h"
 
 namespace adwin {
@@ -334,7 +335,6 @@ hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t st) {
 // of the bytes before it returns, so the host buffer may be pageable and may be freed or
 // reused at once, whatever the stream still has to do, and the launch is an ordinary kernel
 // node for a caller who captures the stream.
-constexpr int kUploadChunk = 3072;   // bytes per launch (the argument block stays below 4 KiB)
 struct UploadArgs { uint4* dst; int n16; uint4 data[kUploadChunk / 16]; };
 __global__ __launch_bounds__(256) void upload_kernel(const UploadArgs a) {
   const int q = threadIdx.x;
@@ -357,42 +357,20 @@ hipError_t launch_upload(void* dst, const void* src_host, size_t bytes, hipStrea
   return hipSuccess;
 }
 
-// Setup in one launch.  Every launch costs about 4.7 us however little it does, and as separate
-// launches the upload, the fills and the row expansion were 6 of the 19 launches of a small
-// fused call (two rollouts of 128 rows, V = 4,096: 112 -> 105 us).  A plan that fits the
-// argument block (up to about 90 rollouts) is read by every workgroup from there, block 0
-// writing it to the workspace; a larger one is uploaded first and read from the workspace.
-__device__ __forceinline__ void setup_body(const SetupArgs& a, const unsigned char* plan) {
-  const int64_t* offsets = (const int64_t*)plan;
-  const int64_t* comp_off = (const int64_t*)(plan + a.o_comp_off);
-  const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
-  for (int64_t r = first; r < a.n_pad; r += step) {
-    const int64_t rr = r < a.n_rows ? r : a.n_rows - 1;
-    const int i = last_le<int64_t>(comp_off, a.B + 1, rr);
-    a.row_idx[r] = (int32_t)(offsets[i] + (rr - comp_off[i]));
-    a.row_seq[r] = i;
-  }
-  for (int z = 0; z < a.n_zero; ++z)
-    for (int64_t q = first; q < a.zero_n[z]; q += step) a.zero[z][q] = 0u;
-}
-struct SetupBlob { int n16; uint4 data[kUploadChunk / 16]; };
+// Setup in a launch of its own: calls whose plan does not fit a kernel's arguments, and the logits path.
 __global__ __launch_bounds__(256) void setup_inline_kernel(const SetupArgs a, const SetupBlob b) {
-  if (blockIdx.x == 0 && (int)threadIdx.x < b.n16) ((uint4*)a.plan)[threadIdx.x] = b.data[threadIdx.x];
-  setup_body(a, (const unsigned char*)b.data);
+  setup_body(a, &b, (const unsigned char*)b.data, blockIdx.x, gridDim.x, 256);
 }
-__global__ __launch_bounds__(256) void setup_kernel(const SetupArgs a) { setup_body(a, a.plan); }
+__global__ __launch_bounds__(256) void setup_kernel(const SetupArgs a) {
+  setup_body(a, nullptr, a.plan, blockIdx.x, gridDim.x, 256);
+}
 
 hipError_t launch_setup(const SetupArgs& a, const std::vector<unsigned char>& blob, hipStream_t st) {
   static_assert(sizeof(SetupArgs) + sizeof(SetupBlob) < 4096, "kernel arguments");
   if (a.n_zero > SetupArgs::kMaxZero) return hipErrorInvalidValue;
-  int64_t most = a.n_pad > 1 ? a.n_pad : 1;
-  for (int z = 0; z < a.n_zero; ++z) most = a.zero_n[z] > most ? a.zero_n[z] : most;
-  const int64_t blocks = (most + 255) / 256;
-  const unsigned grid = (unsigned)(blocks < 1024 ? blocks : 1024);
-  if (blob.size() <= (size_t)kUploadChunk) {
-    SetupBlob b;
-    b.n16 = (int)(blob.size() / 16);
-    memcpy(b.data, blob.data(), blob.size());
+  const unsigned grid = setup_blocks(a, 256);
+  SetupBlob b;
+  if (b.take(blob)) {
     setup_inline_kernel<<<grid, 256, 0, st>>>(a, b);
   } else {
     hipError_t e = launch_upload(a.plan, blob.data(), blob.size(), st);

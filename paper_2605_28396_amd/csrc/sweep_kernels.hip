@@ -23,6 +23,7 @@
 // consecutive bytes of a slab row per block and writes them with two 16-byte stores, where the
 // natural order gives it four separate 8-byte pieces.
 #include "fused_shared.h"
+#include "setup_device.h"
 
 namespace adwin {
 
@@ -464,8 +465,9 @@ constexpr int kDmaPerWave = (kTileVocab + kTileTokens) / 8 / 4;   // 12 wave-loa
 // consecutive bytes and no operand needs 32-bit lane offsets from its base.  With `permute`
 // (the W operands) tile row r holds source row entry_of_tile_row(r) of the tile.
 
+// `rows`: source rows of the tile (NULL: tile rows are source rows).
 template <int THREADS, int TH>
-__device__ __forceinline__ void image_block(const RowImageArgs& a, int64_t tile, int kt) {
+__device__ __forceinline__ void image_block(const RowImageArgs& a, const int32_t* rows, int64_t tile, int kt) {
   constexpr int N = TH * 8 / THREADS;      // 16-byte chunks per thread, loaded together
   uint4* blk = a.img + ((tile * a.nk + kt) * TH) * 8;
   uint4 v[N];
@@ -476,7 +478,7 @@ __device__ __forceinline__ void image_block(const RowImageArgs& a, int64_t tile,
     const int64_t row = tile * TH + (a.permute ? entry_of_tile_row(r) : r);
     v[i] = make_uint4(0u, 0u, 0u, 0u);
     if (row < a.n_rows) {
-      const int64_t src_row = a.row_idx ? (int64_t)a.row_idx[row] : row;
+      const int64_t src_row = rows ? (int64_t)rows[r] : row;
       v[i] = a.src[src_row * (a.H >> 3) + kt * 8 + c];
     }
   }
@@ -486,7 +488,7 @@ __device__ __forceinline__ void image_block(const RowImageArgs& a, int64_t tile,
 
 // vocabulary tiles of 128 rows
 __global__ __launch_bounds__(256) void row_image_kernel(RowImageArgs a) {
-  image_block<256, kTileVocab>(a, blockIdx.y, blockIdx.x);
+  image_block<256, kTileVocab>(a, nullptr, blockIdx.y, blockIdx.x);
 }
 
 constexpr int kImgABytes = kTileVocab * kRowBytes;    // 16 KiB: one W block
@@ -920,6 +922,7 @@ constexpr int kPrepThreads = 512, kPrepWaves = kPrepThreads / 64;
 constexpr int kRefRows = 32, kRefLead = 5;
 constexpr int kRefStage = (kTileVocab + kRefRows) * kRowBytes;          // 20 KiB
 constexpr int kRefLds = (kRefLead + 1) * kRefStage;                     // 120 KiB
+constexpr int kOneLaunchTiles = 32;
 constexpr int kRefFineLds = kPrepWaves * 17 * 64 * 4;                   // 34 KiB
 
 // As dma16_at, from a 64-bit address per lane.
@@ -933,9 +936,9 @@ struct TokenRows {
   int64_t row0, t[kTokenRows];
   int y[kTokenRows];
   bool any;
-  __device__ __forceinline__ TokenRows(const PrepareArgs& a, int64_t first) : row0(first), any(false) {
+  __device__ __forceinline__ TokenRows(const PrepareArgs& a, const int32_t* rows, int64_t first) : row0(first), any(false) {
 #pragma unroll
-    for (int i = 0; i < kTokenRows; ++i) t[i] = a.row_idx[row0 + i];
+    for (int i = 0; i < kTokenRows; ++i) t[i] = rows[i];
 #pragma unroll
     for (int i = 0; i < kTokenRows; ++i) {
       y[i] = a.ids ? a.ids[t[i]] : -1;
@@ -985,7 +988,7 @@ __device__ __forceinline__ float token_logits(const PrepareArgs& a, const TokenR
 }
 
 // References of 32 rows, both models, the tokens of four of them by each wave.
-__device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, int64_t row0, char* lds) {
+__device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, const int32_t* rows, int64_t row0, char* lds) {
   __shared__ float token[2][kRefRows];
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -999,7 +1002,7 @@ __device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, int64_t 
   for (int i = 0; i < 3; ++i) {
     const int m = i < 2 ? 2 * wave + i : (wave & 3), r = 8 * m + (lane >> 3);
     const uint32_t chunk = (uint32_t)((lane & 7) ^ ((r >> 1) & 7)) * 16u;
-    const int64_t row = i < 2 ? (r < a.V ? r : a.V - 1) : a.row_idx[row0 + r];
+    const int64_t row = i < 2 ? (r < a.V ? r : a.V - 1) : rows[r];
     pt[i] = (const char*)((i < 2 ? a.W[1] : a.h[1]) + row * a.H[1]) + chunk;
     ps[i] = (const char*)((i < 2 ? a.W[0] : a.h[0]) + row * a.H[0]) + chunk;
   }
@@ -1014,8 +1017,8 @@ __device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, int64_t 
   };
   for (int s = 0; s < kRefLead; ++s) load(s);
   {
-    const TokenRows rows(a, row0 + wave * kTokenRows);
-    const float yt = token_logits(a, rows, 1, lane), ys = token_logits(a, rows, 0, lane);
+    const TokenRows four(a, rows + wave * kTokenRows, row0 + wave * kTokenRows);
+    const float yt = token_logits(a, four, 1, lane), ys = token_logits(a, four, 0, lane);
     if (lane < kTokenRows) { token[0][wave * kTokenRows + lane] = ys; token[1][wave * kTokenRows + lane] = yt; }
   }
   // wave = vocabulary block vb, half kq of every k-step; A = W rows, B = h rows as in the sweep
@@ -1070,7 +1073,7 @@ __device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, int64_t 
 }
 
 // References of 32 rows, one model, one vocabulary block.
-__device__ __forceinline__ void refs_fine_block(const PrepareArgs& a, int blk, char* lds) {
+__device__ __forceinline__ void refs_fine_block(const PrepareArgs& a, const int32_t* rows, int blk, char* lds) {
   float(*part)[16][64] = (float(*)[16][64])lds;     // [kPrepWaves] a wave's partial logits
   float(*top)[64] = (float(*)[64])(lds + kPrepWaves * 16 * 64 * 4);   // [kPrepWaves]
   const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -1079,7 +1082,7 @@ __device__ __forceinline__ void refs_fine_block(const PrepareArgs& a, int blk, c
   const int64_t row0 = (int64_t)((blk >> 1) / kRefBlocks) * kRefRows;
   const int H = a.H[head], nb = H / kBK;
   const int v = vb * 32 + (lane & 31);
-  const uint4* ph = (const uint4*)(a.h[head] + (int64_t)a.row_idx[row0 + (lane & 31)] * H) + half * 4;
+  const uint4* ph = (const uint4*)(a.h[head] + (int64_t)rows[lane & 31] * H) + half * 4;
   const uint4* pw = (const uint4*)(a.W[head] + (int64_t)(v < a.V ? v : a.V - 1) * H) + half * 4;   // masked below
   f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   constexpr int U = 2;                              // k-blocks loaded together
@@ -1122,26 +1125,54 @@ __device__ __forceinline__ void refs_fine_block(const PrepareArgs& a, int blk, c
   a.ref.max[head][(int64_t)vb * a.ref.n_pad + row0 + threadIdx.x] = m;
 }
 
-__device__ __forceinline__ void token_block(const PrepareArgs& a, int blk) {
-  const int64_t unit = (int64_t)blk * kPrepWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, head = (int)(unit & 1);
-  const TokenRows rows(a, (unit >> 1) * kTokenRows);               // n_pad is a multiple of 256
-  const float z = token_logits(a, rows, head, lane);
-  if (lane < kTokenRows) a.ref.max[head][kRefBlocks * a.ref.n_pad + rows.row0 + lane] = z;
+constexpr int kTokenBlockRows = kPrepWaves / 2 * kTokenRows;
+__device__ __forceinline__ void token_block(const PrepareArgs& a, const int32_t* rows, int blk) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int head = wave & 1, first = (wave >> 1) * kTokenRows;
+  const TokenRows four(a, rows + first, (int64_t)blk * kTokenBlockRows + first);
+  const float z = token_logits(a, four, head, lane);
+  if (lane < kTokenRows) a.ref.max[head][kRefBlocks * a.ref.n_pad + four.row0 + lane] = z;
 }
 
+// Without INLINE a.row_idx is there already; with it, `setup` is done by the last workgroups of this launch and the
+// others take their rows from the plan in the arguments.
+template <bool FINE, bool INLINE>
+__device__ __forceinline__ void prepare_body(const PrepareArgs& a, const SetupArgs* setup, const SetupBlob* blob, char* lds) {
+  __shared__ int32_t table[INLINE ? kTileTokens : 1];
+  int b = (int)blockIdx.x, role = 0;
+  const int blocks[4] = {a.ref_blocks, a.dot_blocks, a.img_blocks[0], a.img_blocks[1]};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (role == k && b >= blocks[k]) { b -= blocks[k]; ++role; }
+  if (role == 4) {
+    if constexpr (INLINE)
+      setup_body(*setup, blob, (const unsigned char*)blob->data, b, a.setup_blocks, kPrepThreads);
+    return;
+  }
+  const int n = role == 0 ? kRefRows : role == 1 ? kTokenBlockRows : kTileTokens;
+  const int unit = role == 0 ? (FINE ? b / (2 * kRefBlocks) : b) : role == 1 ? b : b / a.img[role - 2].nk;
+  const int64_t row0 = (int64_t)unit * n;
+  const int32_t* rows;
+  if constexpr (INLINE) {
+    plan_rows(*setup, (const unsigned char*)blob->data, row0, n, table);
+    rows = table;
+  } else {
+    rows = a.row_idx + row0;
+  }
+  if (role == 0) return FINE ? refs_fine_block(a, rows, b, lds) : refs_staged_block(a, rows, row0, lds);
+  if (role == 1) return token_block(a, rows, b);
+  const RowImageArgs& im = a.img[role - 2];
+  image_block<kPrepThreads, kTileTokens>(im, rows, unit, b % im.nk);
+}
 template <bool FINE>
 __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(PrepareArgs a) {
   extern __shared__ __align__(16) char lds[];
-  int b = (int)blockIdx.x;
-  if (b < a.ref_blocks) return FINE ? refs_fine_block(a, b, lds) : refs_staged_block(a, (int64_t)b * kRefRows, lds);
-  b -= a.ref_blocks;
-  if (b < a.dot_blocks) return token_block(a, b);
-  b -= a.dot_blocks;
-  const int head = b < a.img_blocks[0] ? 0 : 1;
-  if (head) b -= a.img_blocks[0];
-  const RowImageArgs& im = a.img[head];
-  image_block<kPrepThreads, kTileTokens>(im, b / im.nk, b % im.nk);
+  prepare_body<FINE, false>(a, nullptr, nullptr, lds);
+}
+template <bool FINE>
+__global__ __launch_bounds__(kPrepThreads) void prepare_inline_kernel(PrepareArgs a, const SetupArgs setup, const SetupBlob blob) {
+  extern __shared__ __align__(16) char lds[];
+  prepare_body<FINE, true>(a, &setup, &blob, lds);
 }
 
 __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
@@ -1211,6 +1242,7 @@ hipError_t sweep_kernels_opt_in() {
   e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES); \
   if (e != hipSuccess) return e;
   ADWIN_OPT_IN(prepare_kernel<false>, kRefLds)
+  ADWIN_OPT_IN(prepare_inline_kernel<false>, kRefLds)
   ADWIN_OPT_IN(logit_pass_kernel<false>, kLogitLds)
   ADWIN_OPT_IN(logit_pass_kernel<true>, kLogitLds)
   ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, false>), kDmaLds)
@@ -1271,25 +1303,41 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStre
 // The finely cut references serve calls of up to kFineRefTiles token tiles (References::parts is set by the
 // same rule): at five tiles of H = 1024 + 2048 they take 18 us against 25.5 staged, at 13 tiles of H = 512 + 640
 // 20.6 against 15.8.
-hipError_t launch_prepare(const PrepareArgs& p, bool refs, int n_tiles, hipStream_t st) {
+// A plan that fits the arguments is expanded here too, in calls whose preparation is one launch.
+hipError_t launch_prepare(const PrepareArgs& p, bool refs, int n_tiles, const SetupArgs& setup,
+                          const std::vector<unsigned char>& plan, hipStream_t st) {
+  static_assert(sizeof(PrepareArgs) + sizeof(SetupArgs) + sizeof(SetupBlob) < 4096, "kernel arguments");
   PrepareArgs a = p;
   const int rows = n_tiles * kTileTokens;
   const bool fine = a.ref.parts > 1;
   a.ref_blocks = !refs ? 0 : fine ? rows / kRefRows * kRefBlocks * 2 : rows / kRefRows;
-  a.dot_blocks = refs && fine ? rows * 2 / (kPrepWaves * kTokenRows) : 0;
+  a.dot_blocks = refs && fine ? rows / kTokenBlockRows : 0;
   for (int m = 0; m < 2; ++m) a.img_blocks[m] = n_tiles * a.img[m].nk;
   const int rest = a.dot_blocks + a.img_blocks[0] + a.img_blocks[1];
+  const unsigned lds = fine ? kRefFineLds : a.ref_blocks ? kRefLds : 0;
+  SetupBlob blob;
+  hipError_t e;
+  if (n_tiles <= kOneLaunchTiles && blob.take(plan)) {
+    if (setup.n_zero > SetupArgs::kMaxZero) return hipErrorInvalidValue;
+    a.setup_blocks = (int)setup_blocks(setup, kPrepThreads);
+    const unsigned grid = (unsigned)(a.ref_blocks + rest + a.setup_blocks);
+    if (fine) prepare_inline_kernel<true><<<grid, kPrepThreads, lds, st>>>(a, setup, blob);
+    else prepare_inline_kernel<false><<<grid, kPrepThreads, lds, st>>>(a, setup, blob);
+    return hipGetLastError();
+  }
+  if ((e = launch_setup(setup, plan, st)) != hipSuccess) return e;
   if (fine) {
-    prepare_kernel<true><<<(unsigned)(a.ref_blocks + rest), kPrepThreads, kRefFineLds, st>>>(a);
+    prepare_kernel<true><<<(unsigned)(a.ref_blocks + rest), kPrepThreads, lds, st>>>(a);
     return hipGetLastError();
   }
   // a workgroup of a launch with staged references holds their LDS as well, one workgroup per compute
   // unit, so that the others of a large call, 164 us of copying for 34,000 rows, go by themselves
-  if (a.ref_blocks && n_tiles > 32) {
-    prepare_kernel<false><<<(unsigned)a.ref_blocks, kPrepThreads, kRefLds, st>>>(a);
+  if (a.ref_blocks && n_tiles > kOneLaunchTiles) {
+    prepare_kernel<false><<<(unsigned)a.ref_blocks, kPrepThreads, lds, st>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     a.ref_blocks = 0;
   }
-  prepare_kernel<false><<<(unsigned)(a.ref_blocks + rest), kPrepThreads, a.ref_blocks ? kRefLds : 0, st>>>(a);
+  prepare_kernel<false><<<(unsigned)(a.ref_blocks + rest), kPrepThreads, a.ref_blocks ? lds : 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -191,3 +191,24 @@ def test_head_gradient_ends_on_partial_tiles(B, monkeypatch, V, H_s):  # noqa: F
     nrm = Hp.summand_norms(f, w, ref["rows"], O.RED_SEQ_MEAN, head=True)["dW_prefix_l2"]
     tol = Hp.DW_SIGMAS * Hp.DW_SIGMA * nrm + 1e-6 * np.abs(ref["dW_prefix"]).max()
     assert (np.abs(got - ref["dW_prefix"]) <= tol).all()
+
+
+@pytest.mark.parametrize("nb", [1, 63, 64, 65, 90, 100])
+def test_rows_of_many_rollouts(B, nb):  # noqa: F811
+    """The rows of a call of few token tiles are looked up in the plan that comes with the launch, a wave
+    at a time (64 rollouts a probe), for up to about 90 rollouts; with more, in the uploaded plan.
+    Rollouts of no rows in between, and tiles that one rollout fills."""
+    g = np.random.default_rng(nb)
+    lens = g.integers(0, 9, size=nb, endpoint=True)
+    lens[nb // 2] = 700
+    lens[-1] = 0 if nb > 1 else 700
+    win = np.minimum(g.integers(0, 12, size=nb, endpoint=True), lens).astype(np.int32)
+    win[nb // 2] = 690
+    for mode in (synth.MODE_PREFIX_ONLY, synth.MODE_PREFIX_AND_FULL):
+        w = synth.Workload(f"rollouts_{nb}", 4104, 128, 192, synth._offsets(lens), win, mode)
+        p = synth.hidden_problem(w)
+        f = Hp.oracle_inputs(p)
+        ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                          reduction=O.RED_SEQ_MEAN, mode=mode)
+        got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32)
+        _check_fused(w, got, ref, O.RED_SEQ_MEAN)
