@@ -175,6 +175,17 @@ static bool stage_w_directly(int64_t n_tiles, int H_s, int H_t, bool loads_bound
   return n_tiles * (loads_bound ? 72 : 40) <= H_s + H_t;
 }
 
+// Whether the strips of a sweep begin the contraction at different k-steps.  With one token tile every
+// strip streams its own rows of W from memory, 128 bytes of each row per k-step, and rows of 4 KiB and more put
+// the same 128 bytes of all rows into a few of the memory channels: a read-only copy of this pattern
+// reaches 4.05 TB/s in step and 4.75 with the strips spread over the rows (V = 151,936, H = 4096).  256 rows,
+// H = 2048 + 4096: 774 -> 747 us per call; 16 rows, H = 3584 + 4608: 995 -> 978; H = 1024 + 1024: the same, 355.
+// With several token tiles the strips share their blocks of h in the L2 because they run in step:
+// 512 rows 1243 -> 1289, 2,000 rows 4498 -> 4780 (spread by 5 k-steps a strip).
+static bool rotate_k(int64_t n_tiles, int H_s, int H_t) {
+  return n_tiles == 1 && (H_s > H_t ? H_s : H_t) >= 2048;
+}
+
 static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) {
   FusedLayout L;
   const int64_t n_pad = hp.n_pad > 0 ? hp.n_pad : kTileTokens;
@@ -448,7 +459,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     la.tg = env_int("ADWIN_TG", 4);      // tuning override
     la.Wt_img = (const char*)(ws + L.o_wt_img); la.Ws_img = (const char*)(ws + L.o_ws_img);
     la.ht_img = (const char*)(ws + L.o_ht_img); la.hs_img = (const char*)(ws + L.o_hs_img);
-    la.heavy = heavy; la.direct_w = L.direct_w;
+    la.heavy = heavy; la.direct_w = L.direct_w; la.rotate = rotate_k(n_tiles, p->H_s, p->H_t);
     MergeArgs m;
     m.part = la.part; m.strips = L.strips; m.n_pad = n_pad; m.n_rows = hp.n_rows;
     m.row_idx = pl.row_idx;

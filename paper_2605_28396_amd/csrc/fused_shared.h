@@ -197,6 +197,7 @@ struct LogitPassArgs {
   // direct-to-LDS kernel: tile images of the four operands (see row_image_kernel)
   const char* Wt_img; const char* Ws_img; const char* ht_img; const char* hs_img;
   bool direct_w;               // stage W from W_s / W_t themselves; there are no W images
+  bool rotate;                 // ... the heads of strip s from k-step s on, the first ones last (see rotate_k)
   HeavyList heavy;             // second sweep of the two-sweep scheme: entries taken out of dz
 };
 

@@ -725,14 +725,19 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   // whose loads were issued last; past the strip's last step the walk wraps to the strip's first
   // tile, so that every k-step loads (those last blocks land in slots nobody reads any more).
   // (a, b) = the blocks of that step; a k-step moves them on by one block before it loads, so
-  // at the start of a head they are set one block in front of it.
+  // at the start of a head they are set one block in front of it.  A head that begins at k-step k0
+  // comes back to 0 after its last: ld_lim steps, then the ld_rest others.
   uint32_t r_rd = ring_begin;  // ring slot (address) of the next step to consume
-  int ld_vt = vt_begin, ld_k = 0, ld_lim = nk_t;
+  // the k-step a head of a tile begins with: its own for every strip if there is one token tile (see
+  // LogitPassArgs::rotate), else 0
+  const int k0_t = DIRECT && a.rotate ? strip % nk_t : 0, k0_s = DIRECT && a.rotate ? strip % nk_s : 0;
+  int ld_vt = vt_begin, ld_k = 0, ld_lim = nk_t - k0_t, ld_rest = k0_t;
   bool ld_student = false;
   uint32_t a_lo, a_hi, b_lo, b_hi;
-#define ADWIN_SET_BLOCKS(A, B)                                             \
+#define ADWIN_SET_BLOCKS(A, B, K0)                                         \
   {                                                                        \
-    const uint64_t pa = (uint64_t)(A) - kAStep, pb = (uint64_t)(B) - kImgBBytes; \
+    const uint64_t pa = (uint64_t)(A) + (int64_t)((K0) - 1) * kAStep;      \
+    const uint64_t pb = (uint64_t)(B) + (int64_t)((K0) - 1) * kImgBBytes;  \
     a_lo = (uint32_t)pa; a_hi = (uint32_t)(pa >> 32);                      \
     b_lo = (uint32_t)pb; b_hi = (uint32_t)(pb >> 32);                      \
   }
@@ -740,19 +745,23 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   {                                                                        \
     if (++ld_k == ld_lim) {                                                \
       ld_k = 0;                                                            \
-      if (!ld_student) {                                                   \
-        ld_student = true; ld_lim = nk_s;                                  \
-        ADWIN_SET_BLOCKS(blocks_ws(ld_vt), sHs)                            \
+      if (DIRECT && ld_rest) {          /* the head's first k-steps, which come last */ \
+        ld_lim = ld_rest; ld_rest = 0;                                     \
+        if (ld_student) ADWIN_SET_BLOCKS(blocks_ws(ld_vt), sHs, 0)         \
+        else ADWIN_SET_BLOCKS(blocks_wt(ld_vt), sHt, 0)                    \
+      } else if (!ld_student) {                                            \
+        ld_student = true; ld_lim = nk_s - k0_s; ld_rest = k0_s;           \
+        ADWIN_SET_BLOCKS(blocks_ws(ld_vt), sHs, k0_s)                      \
         rows_w(ld_vt, a.H_s, row0_s);                                      \
       } else {                                                             \
-        ld_student = false; ld_lim = nk_t;                                 \
+        ld_student = false; ld_lim = nk_t - k0_t; ld_rest = k0_t;          \
         ld_vt = ld_vt + 1 < vt_end ? ld_vt + 1 : vt_begin;                 \
-        ADWIN_SET_BLOCKS(blocks_wt(ld_vt), sHt)                            \
+        ADWIN_SET_BLOCKS(blocks_wt(ld_vt), sHt, k0_t)                      \
         rows_w(ld_vt, a.H_t, row0_t);                                      \
       }                                                                    \
     }                                                                      \
   }
-  ADWIN_SET_BLOCKS(blocks_wt(vt_begin), sHt)
+  ADWIN_SET_BLOCKS(blocks_wt(vt_begin), sHt, k0_t)
   rows_w(vt_begin, a.H_t, row0_t);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {

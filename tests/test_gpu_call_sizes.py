@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (16648, 192, 256, [17], [16]),               # one token tile, 131 vocabulary tiles of which the last holds 8
     (16648, 128, 320, [200, 57], [200, 57]),     # one row into the second token tile
     (16616, 320, 128, [700], [513]),             # three token tiles; a last half block that is all padding
+    (4616, 2048, 192, [17], [16]),               # strips that begin the contraction at different k-steps, of 32
+    (4616, 192, 2048, [230], [201]),             # ... and of 3
     (4104, 256, 192, [900, 390], [900, 390]),    # six token tiles: a group of four and one of two
     (4104, 128, 192, [2000], [2000]),            # eight token tiles, the most that stage W directly at 320 / 40
     (4104, 128, 192, [2050], [2050]),            # ... and one more: tile images
