@@ -459,7 +459,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     la.tg = env_int("ADWIN_TG", 4);      // tuning override
     la.Wt_img = (const char*)(ws + L.o_wt_img); la.Ws_img = (const char*)(ws + L.o_ws_img);
     la.ht_img = (const char*)(ws + L.o_ht_img); la.hs_img = (const char*)(ws + L.o_hs_img);
-    la.heavy = heavy; la.direct_w = L.direct_w; la.rotate = rotate_k(n_tiles, p->H_s, p->H_t);
+    la.heavy = heavy; la.narrow = false; la.direct_w = L.direct_w; la.rotate = rotate_k(n_tiles, p->H_s, p->H_t);
     MergeArgs m;
     m.part = la.part; m.strips = L.strips; m.n_pad = n_pad; m.n_rows = hp.n_rows;
     m.row_idx = pl.row_idx;
@@ -486,6 +486,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         la.e2_off = rows * L.Vp;
         la.strips = sweep_strips(la.n_tiles, vt_total);
         la.part = (float*)(ws + L.o_part) - r0; la.n_pad = rows;       // partials of this slab's rows
+        la.narrow = L.direct_w && la.n_tiles == 1 && hp.n_rows - r0 <= kNarrowRows;
         phase(ADWIN_PHASE_STATS);
         const int sweep_mode = !need_g ? (diag ? kModeSingleFwdDiag : kModeSingleFwd)
                                : sampled ? (diag ? kModeSingleE2Diag : kModeSingleE2)

@@ -180,6 +180,7 @@ struct LogitPassArgs {
   int64_t n_pad;
   int tile0;                   // first token tile of this launch
   int n_tiles;                 // token tiles in this launch
+  bool narrow;                 // one token tile, of which only the first 128 rows are wanted (see DmaTile)
   int strips;                  // vocabulary strips
   Shares strip_tiles;          // vocabulary tiles of each (set by launch_logit_pass)
   int tg;                      // token tiles per workgroup group (share W tiles in one L2)
@@ -200,6 +201,8 @@ struct LogitPassArgs {
   bool rotate;                 // ... the heads of strip s from k-step s on, the first ones last (see rotate_k)
   HeavyList heavy;             // second sweep of the two-sweep scheme: entries taken out of dz
 };
+
+constexpr int kNarrowRows = kTileTokens / 2;
 
 // Modes of the direct-to-LDS logit kernel.
 constexpr int kModeStats = 0;   // online (running-max) statistics only

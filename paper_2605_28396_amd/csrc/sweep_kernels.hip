@@ -231,8 +231,8 @@ __device__ __forceinline__ void slab_store16(__amdgpu_buffer_rsrc_t r, int lane_
   __builtin_amdgcn_raw_buffer_store_b128(o, r, lane_off, block_off, 0);
 }
 
-template <bool TAIL, bool DIAG, bool WRITE_D, bool WRITE_E2>
-__device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][2], const f32x16 (&zt)[4][2],
+template <bool TAIL, bool DIAG, bool WRITE_D, bool WRITE_E2, int FN>
+__device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const f32x16 (&zt)[4][FN],
                                                 LaneSums& sm, const float (&rs2)[2],
                                                 const float (&rt2)[2], float (&mu0)[2],
                                                 const float (&zyt)[2], const int (&yid)[2],
@@ -246,7 +246,7 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][2], const 
   float Zs[2], As[2], Zt[2], Bt[2];
   int cnt[2], vy[2];
 #pragma unroll
-  for (int fn = 0; fn < 2; ++fn) {
+  for (int fn = 0; fn < FN; ++fn) {
     Zs[fn] = sm.Z_s[fn]; As[fn] = sm.A_s[fn]; Zt[fn] = sm.Z_t[fn]; Bt[fn] = sm.B_t[fn];
     cnt[fn] = sm.cnt[fn];
     vy[fn] = yid[fn] - vlane;              // position of the sampled token among this lane's entries
@@ -301,32 +301,34 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][2], const 
     for (int p = 0; p < 2; ++p) sums8(0, fm, p);
   float m0 = 0.f;
   if (WRITE_D) m0 = mean_of(0);
-#pragma unroll
-  for (int fm = 0; fm < 4; ++fm)
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      sums8(1, fm, p);
-      if (WRITE_D) factor8(0, fm, p, m0);
-    }
-  if (WRITE_D) {
-    m0 = mean_of(1);
+  if constexpr (FN == 2) {
 #pragma unroll
     for (int fm = 0; fm < 4; ++fm)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) factor8(1, fm, p, m0);
+      for (int p = 0; p < 2; ++p) {
+        sums8(1, fm, p);
+        if (WRITE_D) factor8(0, fm, p, m0);
+      }
+    if (WRITE_D) m0 = mean_of(1);
+  }
+  if (WRITE_D) {
+#pragma unroll
+    for (int fm = 0; fm < 4; ++fm)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) factor8(FN - 1, fm, p, m0);
   }
 #pragma unroll
-  for (int fn = 0; fn < 2; ++fn) {
+  for (int fn = 0; fn < FN; ++fn) {
     sm.Z_s[fn] = Zs[fn]; sm.A_s[fn] = As[fn]; sm.Z_t[fn] = Zt[fn];
     if (DIAG) { sm.B_t[fn] = Bt[fn]; sm.cnt[fn] = cnt[fn]; }
   }
 }
 
-template <bool DIAG>
+template <bool DIAG, int FN>
 __device__ __forceinline__ void write_sums(LaneSums& sm, float* part, int strips, int strip,
                                            int64_t n_pad, int64_t row0, int lane) {
 #pragma unroll
-  for (int fn = 0; fn < 2; ++fn) {
+  for (int fn = 0; fn < FN; ++fn) {
     const float Zs = sm.Z_s[fn] + __shfl_xor(sm.Z_s[fn], 32, 64);
     const float As = sm.A_s[fn] + __shfl_xor(sm.A_s[fn], 32, 64);
     const float Zt = sm.Z_t[fn] + __shfl_xor(sm.Z_t[fn], 32, 64);
@@ -452,10 +454,22 @@ __global__ __launch_bounds__(256) void logit_pass_kernel(LogitPassArgs a) {
 // outstanding" means this stage has landed.  Compiler-issued loads in between only make the
 // count larger, i.e. the wait longer.
 // ---------------------------------------------------------------------------------------
-constexpr int kDmaStages = 3;
-constexpr int kDmaLds = kDmaStages * kLogitStage;           // 144 KiB
-constexpr int kDmaRefLds = kDmaLds + 4 * 2 * kMaxRefParts * 256;  // ... and the references of the single sweep
-constexpr int kDmaPerWave = (kTileVocab + kTileTokens) / 8 / 4;   // 12 wave-loads per stage
+// FN = 2: tiles of 256 tokens, 64 to a wave, and a ring of three stages.  FN = 1, for calls of up to 128 rows:
+// the first half of the one token tile, 32 tokens to a wave, and a ring of four.  With one token tile the
+// sweep streams W from memory, and what bounds it is the bytes of W that are in flight per compute unit
+// (16 KiB per stage and 1.5 us a round trip); the matrix work of the other half, all padding, is left out.
+// 128 rows, V = 151,936, H = 2048 + 4096: sweep 497 -> 414 us (W at 4.5 TB/s), call 741 -> 648; 16 rows,
+// H = 3584 + 4608: 986 -> 856; 100 rows, H = 1024 + 1024: 359 -> 318.  256 rows as two such tiles: 500 -> 650 us (the two
+// workgroups that share W do not stay in step and fetch it twice).
+template <int FN>
+struct DmaTile {
+  static constexpr int kTokens = 128 * FN, kStages = FN == 2 ? 3 : 4;
+  static constexpr int kStage = (kTileVocab + kTokens) * kRowBytes;     // 48 KiB, 32 KiB
+  static constexpr int kRing = kStages * kStage;                        // 144 KiB, 128 KiB
+  static constexpr int kRefLds = kRing + 4 * 2 * kMaxRefParts * 256;    // ... and the references of the single sweep
+  static constexpr int kPerWave = (kTileVocab + kTokens) / 8 / 4;       // wave-loads per stage: 12, 8
+  static constexpr int kAhead = kStages - 1;                            // k-steps from a load to its use
+};
 
 // Row images.  The direct-to-LDS logit kernel reads all four operands as LDS images of its
 // k-steps: [rows, H] row-major (optionally gathered through row_idx) is re-laid as tiles of
@@ -499,7 +513,7 @@ constexpr int kImgBBytes = kTileTokens * kRowBytes;   // 32 KiB: one h block
 // address + 1024 wave; voffw[j] = 16 lane + 1024 (wave + 4 j): the wave's part of both addresses
 // is folded into operands that are set up once, the rest is a literal.  voffa: the same for the
 // A block, or the lane's offsets in the row-major W (direct staging).
-template <int I>
+template <int I>       // I < DmaTile::kPerWave
 __device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voffa)[4], const uint32_t (&voffw)[8],
                                         const char* sA, const char* sB) {
   if constexpr (I < kTileVocab / 32)
@@ -529,14 +543,17 @@ __device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voff
 // per sub-step; (a_lo, a_hi), (b_lo, b_hi) = the blocks that the previous k-step loaded, on
 // return those that this one loaded.
 // A_STEP: bytes from one A block to the next (a W image's block, or a row-major W's 64 entries).
-template <bool LAST, bool FRESH, int RELAXED, int A_STEP>
-__device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][2], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][2],
+template <bool LAST, bool FRESH, int RELAXED, int A_STEP, int FN>
+__device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][FN], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][FN],
                                             uint32_t& r_rd, uint32_t ring_begin, uint32_t ring_end,
                                             const uint32_t (&swA)[4], const uint32_t (&swB)[4],
                                             const uint32_t (&voffa)[4], const uint32_t (&voffw)[8],
                                             uint32_t& a_lo, uint32_t& a_hi,
                                             uint32_t& b_lo, uint32_t& b_hi, bool relaxed = false) {
-  static_assert(9 + RELAXED <= 63, "the wait count has six bits");
+  typedef DmaTile<FN> Tile;
+  // loads issued after those of the next stage, up to the wait: whole stages, and three quarters of one
+  constexpr int kYounger = (Tile::kAhead - 2) * Tile::kPerWave + Tile::kPerWave / 4 * 3;
+  static_assert(kYounger + RELAXED <= 63, "the wait count has six bits");
   const f32x16 kZeroTile = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   uint32_t r_nx, r_wr;
 #define ADWIN_FENCE __builtin_amdgcn_sched_barrier(0);
@@ -569,25 +586,53 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][2], bf16x8 (&fa)[2]
     ADWIN_MM(KK, 3, 0) ADWIN_DMA(D1)                                    \
     ADWIN_MM(KK, 3, 1) ADWIN_DMA(D2)                                    \
   }
+  // 4 MFMAs a sub-step with one token column
+#define ADWIN_SUB1(KK, READ, R, D0, D1, H0, H1, H2, H3)                       \
+  {                                                                     \
+    uint32_t xa = 0, xb = 0;                                            \
+    ADWIN_MM(KK, 0, 0)                                                  \
+    if constexpr (READ) {                                               \
+      xa = (R) + swA[((KK) + 1) & 3]; xb = (R) + swB[((KK) + 1) & 3];   \
+      asm volatile("" : "+v"(xa), "+v"(xb));                            \
+      ADWIN_RA(KK, 0) ADWIN_RB(KK, 0)                                   \
+    }                                                                   \
+    H0 ADWIN_FENCE                                                      \
+    ADWIN_MM(KK, 1, 0) if constexpr (READ) { ADWIN_RA(KK, 1) } H1 ADWIN_FENCE \
+    ADWIN_MM(KK, 2, 0) if constexpr (READ) { ADWIN_RA(KK, 2) } H2 ADWIN_FENCE ADWIN_DMA(D0) \
+    ADWIN_MM(KK, 3, 0) if constexpr (READ) { ADWIN_RA(KK, 3) } H3 ADWIN_FENCE ADWIN_DMA(D1) \
+  }
+#define ADWIN_NEXT(X) ring_next<Tile::kStage>(X, ring_begin, ring_end)
   ADWIN_FENCE
+  if constexpr (FN == 1) {
+    ADWIN_SUB1(0, true, r_rd, 0, 1, { r_nx = ADWIN_NEXT(r_rd); }, { r_wr = ADWIN_NEXT(ADWIN_NEXT(r_nx)); addr_advance<A_STEP>(a_lo, a_hi); },
+               { addr_advance<kImgBBytes>(b_lo, b_hi); }, {})
+    ADWIN_SUB1(1, true, r_rd, 2, 3, {}, {}, {}, {})
+    ADWIN_SUB1(2, true, r_rd, 4, 5, {}, {}, {}, {})
+  } else {
   ADWIN_SUB(0, true, r_rd, 0, 1, 2,
-            { r_nx = ring_next<kLogitStage>(r_rd, ring_begin, ring_end); }, { r_wr = ring_next<kLogitStage>(r_nx, ring_begin, ring_end); },
+            { r_nx = ADWIN_NEXT(r_rd); }, { r_wr = ADWIN_NEXT(r_nx); },
             { addr_advance<A_STEP>(a_lo, a_hi); }, { addr_advance<kImgBBytes>(b_lo, b_hi); })
   ADWIN_SUB(1, true, r_rd, 3, 4, 5, {}, {}, {}, {})
   ADWIN_SUB(2, true, r_rd, 6, 7, 8, {}, {}, {}, {})
+  }
   if constexpr (!LAST) {
-    // loads issued after those of the next stage: the 9 above
     if constexpr (RELAXED > 0) {
-      if (relaxed) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(9 + RELAXED) : "memory");
-      else asm volatile("s_waitcnt vmcnt(9) lgkmcnt(0)" ::: "memory");
+      if (relaxed) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kYounger + RELAXED) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kYounger) : "memory");
     } else {
-      asm volatile("s_waitcnt vmcnt(9) lgkmcnt(0)" ::: "memory");
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kYounger) : "memory");
     }
     __syncthreads();
   }
   ADWIN_FENCE
+  if constexpr (FN == 1) {
+    ADWIN_SUB1(3, !LAST, r_nx, 6, 7, {}, {}, {}, {})
+  } else {
   ADWIN_SUB(3, !LAST, r_nx, 9, 10, 11, {}, {}, {}, {})
+  }
   r_rd = r_nx;
+#undef ADWIN_NEXT
+#undef ADWIN_SUB1
 #undef ADWIN_SUB
 #undef ADWIN_DMA
 #undef ADWIN_MM
@@ -600,14 +645,16 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][2], bf16x8 (&fa)[2]
 // takes its 8 rows' 128 bytes from 8 rows of W, the lane offsets following the image's row
 // permutation and chunk swizzle, so that the LDS holds the same bytes; rows beyond V repeat the
 // last one (their logits are masked like the image's zero rows).
-template <int MODE, bool DIRECT>
+template <int MODE, bool DIRECT, int FN = 2>
 __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   extern __shared__ __align__(16) char lds[];
+  typedef DmaTile<FN> Tile;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int strip, tt_local;
   strip_and_tile(xcd_contiguous_id(blockIdx.x, gridDim.x), a.tg, a.strips, a.n_tiles, &strip, &tt_local);
   const int tt = a.tile0 + tt_local;
+  const int64_t row_tile = (int64_t)tt * kTileTokens;
   const int vt_begin = a.strip_tiles.first(strip), vt_end = a.strip_tiles.first(strip + 1);
   if (vt_begin >= vt_end) return;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
@@ -619,7 +666,7 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     asm volatile("" : "+v"(voffw[j]));   // kept in registers, not recomputed at every load
   }
   // ring slot addresses carry the wave's KiB (for the loads); the fragment offsets take it out again
-  const uint32_t ring_begin = lds0 + (uint32_t)wave * 1024u, ring_end = ring_begin + kDmaStages * kLogitStage;
+  const uint32_t ring_begin = lds0 + (uint32_t)wave * 1024u, ring_end = ring_begin + Tile::kRing;
   uint32_t swA[4], swB[4];
   {
     const int key = (lane >> 1) & 7, half = lane >> 5;
@@ -627,7 +674,7 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       swA[kk] = rowoff + (uint32_t)(((kk * 2 + half) ^ key) << 4);
-      swB[kk] = swA[kk] + (uint32_t)(kTileVocab * kRowBytes + wave * 64 * kRowBytes);
+      swB[kk] = swA[kk] + (uint32_t)(kTileVocab * kRowBytes + wave * 32 * FN * kRowBytes);
     }
   }
   const int nk_t = a.H_t / kBK, nk_s = a.H_s / kBK, nk = nk_t + nk_s;   // each >= 2 on this path
@@ -694,11 +741,11 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   float zyt[2];
   int yid[2];
 #pragma unroll
-  for (int fn = 0; fn < 2; ++fn) {
+  for (int fn = 0; fn < FN; ++fn) {
     st.m_s[fn] = kNegBig; st.Z_s[fn] = 0.f; st.A_s[fn] = 0.f; st.m_t[fn] = kNegBig; st.Z_t[fn] = 0.f;
     sm.Z_s[fn] = 0.f; sm.A_s[fn] = 0.f; sm.Z_t[fn] = 0.f; sm.B_t[fn] = 0.f; sm.cnt[fn] = 0;
     lse2[fn] = 0.f; mu[fn] = 0.f; rs2[fn] = 0.f; rt2[fn] = 0.f; zyt[fn] = 0.f; yid[fn] = -1;
-    const int64_t r = (int64_t)tt * kTileTokens + wave * 64 + fn * 32 + (lane & 31);
+    const int64_t r = row_tile + wave * (32 * FN) + fn * 32 + (lane & 31);
     if (MODE == kModeDz) {
       lse2[fn] = a.lse2[r];
       mu[fn] = a.mu[r];
@@ -708,13 +755,13 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   }
   // The references go into the LDS behind the ring, ahead of the first stages: loaded into registers they
   // made every workgroup wait for one more round trip before it asked for its first stage.
-  const uint32_t ref_lds = lds0 + kDmaLds + (uint32_t)wave * (2 * kMaxRefParts * 256);
+  const uint32_t ref_lds = lds0 + Tile::kRing + (uint32_t)wave * (2 * kMaxRefParts * 256);
   if (kSingle) {
-    const uint32_t row = (uint32_t)lane * 4u;
+    const uint32_t row = (uint32_t)(lane & (32 * FN - 1)) * 4u;
     for (int k = 0; k < 2 * a.ref.parts; ++k) {
       const int head = k >= a.ref.parts, plane = head ? k - a.ref.parts : k;
       dma4_at<0>(ref_lds + (uint32_t)k * 256u, row,
-                 (const char*)(a.ref.max[head] + plane * a.ref.n_pad + (int64_t)tt * kTileTokens + wave * 64));
+                 (const char*)(a.ref.max[head] + plane * a.ref.n_pad + row_tile + wave * (32 * FN)));
     }
   }
 
@@ -764,8 +811,8 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   ADWIN_SET_BLOCKS(blocks_wt(vt_begin), sHt, k0_t)
   rows_w(vt_begin, a.H_t, row0_t);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const uint32_t dst = ring_begin + (uint32_t)i * kLogitStage;
+  for (int i = 0; i < Tile::kAhead; ++i) {
+    const uint32_t dst = ring_begin + (uint32_t)i * Tile::kStage;
     addr_advance<kAStep>(a_lo, a_hi);
     addr_advance<kImgBBytes>(b_lo, b_hi);
     const char* ldA = addr_of(a_lo, a_hi);
@@ -774,15 +821,17 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     dma_one<2>(dst, voffa, voffw, ldA, ldB); dma_one<3>(dst, voffa, voffw, ldA, ldB);
     dma_one<4>(dst, voffa, voffw, ldA, ldB); dma_one<5>(dst, voffa, voffw, ldA, ldB);
     dma_one<6>(dst, voffa, voffw, ldA, ldB); dma_one<7>(dst, voffa, voffw, ldA, ldB);
-    dma_one<8>(dst, voffa, voffw, ldA, ldB); dma_one<9>(dst, voffa, voffw, ldA, ldB);
-    dma_one<10>(dst, voffa, voffw, ldA, ldB); dma_one<11>(dst, voffa, voffw, ldA, ldB);
+    if constexpr (FN == 2) {
+      dma_one<8>(dst, voffa, voffw, ldA, ldB); dma_one<9>(dst, voffa, voffw, ldA, ldB);
+      dma_one<10>(dst, voffa, voffw, ldA, ldB); dma_one<11>(dst, voffa, voffw, ldA, ldB);
+    }
     ADWIN_COUNT_LOADS()
   }
   if (kSingle) {
     typedef const __attribute__((address_space(3))) float* LdsFloat;
-    wait_vm<2 * kDmaPerWave>();                // all but the two stages
+    wait_vm<Tile::kAhead * Tile::kPerWave>();  // all but the stages
 #pragma unroll
-    for (int fn = 0; fn < 2; ++fn) {
+    for (int fn = 0; fn < FN; ++fn) {
       const LdsFloat p = (LdsFloat)(uintptr_t)(ref_lds + (uint32_t)(fn * 32 + (lane & 31)) * 4u);
       float m[2] = {p[0], p[a.ref.parts * 64]};
       for (int k = 1; k < a.ref.parts; ++k) { m[0] = fmaxf(m[0], p[k * 64]); m[1] = fmaxf(m[1], p[(a.ref.parts + k) * 64]); }
@@ -791,15 +840,15 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     }
   }
   // 16-byte stores a wave issues per tile in its epilogue, at the least (see sweep_kstep, RELAXED)
-  constexpr int kEpilogueStores = MODE == kModeDz ? 16 : (kWriteE2 && kSingle ? 16 : 0) + (kWriteD ? 16 : 0);
-  f32x16 zt[4][2], zs[4][2];
-  bf16x8 fa[2][4], fb[2][2];
+  constexpr int kEpilogueStores = MODE == kModeDz ? 16 : (kWriteE2 && kSingle ? 8 * FN : 0) + (kWriteD ? 8 * FN : 0);
+  f32x16 zt[4][FN], zs[4][FN];
+  bf16x8 fa[2][4], fb[2][FN];
   // one k-step: consume slot r_rd, prefetch fragments from the following slot, load into the one after
-  auto step = [&](auto last_c, auto fresh_c, auto relaxed_c, f32x16 (&acc)[4][2], bool relaxed)
+  auto step = [&](auto last_c, auto fresh_c, auto relaxed_c, f32x16 (&acc)[4][FN], bool relaxed)
                   __attribute__((always_inline)) {
     constexpr bool kLast = decltype(last_c)::value, kFresh = decltype(fresh_c)::value;
     constexpr int kRelaxed = decltype(relaxed_c)::value;
-    sweep_kstep<kLast, kFresh, kRelaxed, kAStep>(acc, fa, fb, r_rd, ring_begin, ring_end, swA, swB, voffa, voffw,
+    sweep_kstep<kLast, kFresh, kRelaxed, kAStep, FN>(acc, fa, fb, r_rd, ring_begin, ring_end, swA, swB, voffa, voffw,
                                          a_lo, a_hi, b_lo, b_hi, relaxed);
     ADWIN_COUNT_LOADS()
   };
@@ -809,16 +858,16 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   const std::integral_constant<int, kEpilogueStores> after_epilogue{};
   for (int vt = vt_begin; vt < vt_end; ++vt) {
     const int v0 = vt * kTileVocab;
-    // Step 0 of this tile has landed once at most the 12 loads of step 1 are outstanding.  For
+    // Step 0 of this tile has landed once at most the loads of the steps after it are outstanding.  For
     // the strip's first tile that is waited for here; for every later tile it was waited for
     // before the previous tile's epilogue (below): the counter takes loads and stores in order,
     // so a wait placed here would also wait for nearly all of that epilogue's stores.
-    if (vt == vt_begin) wait_vm<kDmaPerWave>();
+    if (vt == vt_begin) wait_vm<(Tile::kAhead - 1) * Tile::kPerWave>();
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; ++i) fa[0][i] = lds_frag(r_rd + swA[0])[i * 32 * kRowBytes / 16];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) fb[0][i] = lds_frag(r_rd + swB[0])[i * 32 * kRowBytes / 16];
+    for (int i = 0; i < FN; ++i) fb[0][i] = lds_frag(r_rd + swB[0])[i * 32 * kRowBytes / 16];
     // teacher: nk_t k-steps (the first on a zero addend; after an epilogue its wait leaves that
     // epilogue's stores in flight), then student: nk_s k-steps, the last without a barrier
     step(no, yes, after_epilogue, zt, vt != vt_begin);
@@ -826,30 +875,29 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     step(no, yes, strict, zs, false);
     for (int s = 1; s + 1 < nk_s; ++s) step(no, no, strict, zs, false);
     step(yes, no, strict, zs, false);
-    wait_vm<kDmaPerWave>();                    // the next tile's step 0 (see the top of the loop)
+    wait_vm<(Tile::kAhead - 1) * Tile::kPerWave>();      // the next tile's step 0 (see the top of the loop)
     const bool tail = v0 + kTileVocab > a.V;
-    if (MODE == kModeStats) {
+    const int wave_row = wave * (32 * FN);                // of the 256-row image
+    __bf16* blk = a.slab + ((int64_t)(tt - a.tile0) * (a.Vp / kBK) + 2 * vt) * kSlabBlock;
+    if constexpr (MODE == kModeStats) {
       stats_epilogue(zs, zt, st, v0, a.V, tail, lane);
+    } else if constexpr (MODE == kModeDz) {
+      dz_epilogue(zs, zt, lse2, mu, blk, wave_row, v0, a.V, tail, lane, a.heavy, row_tile + wave * (32 * FN));
     } else {
-      __bf16* blk = a.slab + ((int64_t)tt_local * (a.Vp / kBK) + 2 * vt) * kSlabBlock;
-      float* m0t = a.mu0t ? a.mu0t + (int64_t)vt * a.mu0t_stride + (int64_t)tt_local * kTileTokens + wave * 64
-                          : nullptr;
-      if (MODE == kModeDz) {
-        dz_epilogue(zs, zt, lse2, mu, blk, wave * 64, v0, a.V, tail, lane, a.heavy,
-                    (int64_t)tt * kTileTokens + wave * 64);
-      } else if (tail) {
-        single_epilogue<true, kDiag, kWriteD, kWriteE2>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave * 64, v0, a.V, lane, m0t);
+      float* m0t = a.mu0t ? a.mu0t + (int64_t)vt * a.mu0t_stride + (int64_t)(tt - a.tile0) * kTileTokens + wave_row : nullptr;
+      if (tail) {
+        single_epilogue<true, kDiag, kWriteD, kWriteE2, FN>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave_row, v0, a.V, lane, m0t);
       } else {
-        single_epilogue<false, kDiag, kWriteD, kWriteE2>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave * 64, v0, a.V, lane, m0t);
+        single_epilogue<false, kDiag, kWriteD, kWriteE2, FN>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave_row, v0, a.V, lane, m0t);
       }
     }
   }
 #undef ADWIN_COUNT_LOADS
 #undef ADWIN_SET_BLOCKS
   wait_vm<0>();      // the strip's last two k-steps loaded blocks nobody reads: landed before the LDS is released
-  const int64_t row0 = (int64_t)tt * kTileTokens + wave * 64;
+  const int64_t row0 = row_tile + wave * (32 * FN);
   if (MODE == kModeStats) write_partials(st, a.part, a.strips, strip, a.n_pad, row0, lane);
-  else if (kSingle) write_sums<kDiag>(sm, a.part, a.strips, strip, a.n_pad, row0, lane);
+  else if (kSingle) write_sums<kDiag, FN>(sm, a.part, a.strips, strip, a.n_pad, row0, lane);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1206,9 +1254,12 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   float ent = lse_t - Bt / Zt;              // H[p_t] = lse_t - E_{p_t}[z_t]; both sums share the reference
   // a row without a finite log-sum-exp, mean or KL (logits beyond the range the fixed
   // references cover, or non-finite inputs) is excluded: zeros in every output
-  const bool dead = !(fabsf(lse_s) < 3.0e38f) || !(fabsf(lse_t) < 3.0e38f) || !(fabsf(kl) < 3.0e38f) ||
+  const bool bad = !(fabsf(lse_s) < 3.0e38f) || !(fabsf(lse_t) < 3.0e38f) || !(fabsf(kl) < 3.0e38f) ||
                     !(fabsf(A) < 3.0e38f) || !(fabsf(mu) < 3.0e38f) || !(iz > 0.f) || !(iz < 3.0e38f) ||
                     (a.diag && !(fabsf(ent) < 3.0e38f));
+  // padding rows are excluded too: the sweep of a narrow tile leaves them out, and what their slab rows hold
+  // must not reach the lists of heavy entries
+  const bool dead = bad || r >= a.n_rows;
   if (dead) { kl = 0.f; ent = 0.f; }
   if (lane == 0) {
     b.mu_out[r] = dead ? 0.f : mu;
@@ -1254,22 +1305,23 @@ hipError_t sweep_kernels_opt_in() {
   ADWIN_OPT_IN(prepare_inline_kernel<false>, kRefLds)
   ADWIN_OPT_IN(logit_pass_kernel<false>, kLogitLds)
   ADWIN_OPT_IN(logit_pass_kernel<true>, kLogitLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeStats, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeDz, false>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeDz, true>), kDmaLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, false>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingle, true>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, false>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleDiag, true>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, false>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2, true>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, false>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleE2Diag, true>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, false>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwd, true>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, false>), kDmaRefLds)
-  ADWIN_OPT_IN((logit_pass_dma_kernel<kModeSingleFwdDiag, true>), kDmaRefLds)
+#define ADWIN_OPT_IN_MODE(M)                                                  \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, false>), DmaTile<2>::kRefLds)        \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true>), DmaTile<2>::kRefLds)
+  ADWIN_OPT_IN_MODE(kModeStats)
+  ADWIN_OPT_IN_MODE(kModeDz)
+#undef ADWIN_OPT_IN_MODE
+#define ADWIN_OPT_IN_MODE(M)                                                  \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, false>), DmaTile<2>::kRefLds)        \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true>), DmaTile<2>::kRefLds)         \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true, 1>), DmaTile<1>::kRefLds)
+  ADWIN_OPT_IN_MODE(kModeSingle)
+  ADWIN_OPT_IN_MODE(kModeSingleDiag)
+  ADWIN_OPT_IN_MODE(kModeSingleE2)
+  ADWIN_OPT_IN_MODE(kModeSingleE2Diag)
+  ADWIN_OPT_IN_MODE(kModeSingleFwd)
+  ADWIN_OPT_IN_MODE(kModeSingleFwdDiag)
+#undef ADWIN_OPT_IN_MODE
 #undef ADWIN_OPT_IN
   return hipSuccess;
 }
@@ -1289,11 +1341,26 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStre
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
+  if (a.narrow) {
+    if (!a.direct_w || a.n_tiles != 1) return hipErrorInvalidValue;
+    switch (mode) {
+#define ADWIN_CASE(M) case M: logit_pass_dma_kernel<M, true, 1><<<grid, 256, DmaTile<1>::kRefLds, st>>>(a); break;
+      ADWIN_CASE(kModeSingle)
+      ADWIN_CASE(kModeSingleDiag)
+      ADWIN_CASE(kModeSingleE2)
+      ADWIN_CASE(kModeSingleE2Diag)
+      ADWIN_CASE(kModeSingleFwd)
+      ADWIN_CASE(kModeSingleFwdDiag)
+#undef ADWIN_CASE
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   switch (mode) {
 #define ADWIN_CASE(M)                                                                       \
   case M:                                                                                   \
-    if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, M < kModeSingle ? kDmaLds : kDmaRefLds, st>>>(a);  \
-    else logit_pass_dma_kernel<M, false><<<grid, 256, M < kModeSingle ? kDmaLds : kDmaRefLds, st>>>(a);            \
+    if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
+    else logit_pass_dma_kernel<M, false><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);            \
     break;
     ADWIN_CASE(kModeStats)
     ADWIN_CASE(kModeDz)

@@ -149,7 +149,7 @@ H_SUM = 128 + 192
 
 @functools.lru_cache(maxsize=2)
 def _staging_problem(rows, estimator):
-    w = synth.Workload(f"staging_{rows}", 4104, 128, 192, synth._offsets([rows - 100, 100]),
+    w = synth.Workload(f"staging_{rows}", 4104, 128, 192, synth._offsets([rows - min(rows, 100), min(rows, 100)]),
                        np.array([rows, 100], np.int32), synth.MODE_PREFIX_ONLY)
     p = synth.hidden_problem(w)
     f = Hp.oracle_inputs(p)
@@ -164,7 +164,18 @@ def _staging_problem(rows, estimator):
 def test_both_stagings_of_every_sweep_mode(B, what, line, images):  # noqa: F811
     """The most token tiles whose W tiles come from the row-major weights, (H_s + H_t) / line, and one
     more, which takes tile images: every mode of the sweep in both forms against the oracle."""
-    rows = H_SUM // line * 256 + (1 if images else 0)
+    _check_sweep_mode(B, what, H_SUM // line * 256 + (1 if images else 0))
+
+
+@pytest.mark.parametrize("rows", [1, 33, 128, 129])
+@pytest.mark.parametrize("what", ["train", "train_diag", "stats", "stats_diag", "sampled", "sampled_diag"])
+def test_narrow_token_tile_in_every_sweep_mode(B, what, rows):  # noqa: F811
+    """Up to 128 rows the sweep computes half a token tile; the rows of the other half, which its kernels
+    share, hold nothing."""
+    _check_sweep_mode(B, what, rows)
+
+
+def _check_sweep_mode(B, what, rows):  # noqa: F811
     estimator = O.EST_SAMPLED if what.startswith("sampled") else O.EST_EXPECTED
     w, p, ref, (ent, logp, lo, hi) = _staging_problem(rows, estimator)
     stats, diag = what.startswith("stats"), what.endswith("diag")
@@ -185,12 +196,14 @@ def test_both_stagings_of_every_sweep_mode(B, what, line, images):  # noqa: F811
             assert lo[t] <= got["t_rank"][t] <= hi[t], (t, got["t_rank"][t], lo[t], hi[t])
 
 
+@pytest.mark.parametrize("lens,win,slabs", [([300, 41], [289, 41], 2), ([90, 8], [77, 8], 1)])
 @pytest.mark.parametrize("V,H_s", [(8, 128), (104, 192), (264, 320), (376, 576), (512, 256)])
-def test_head_gradient_ends_on_partial_tiles(B, monkeypatch, V, H_s):  # noqa: F811
+def test_head_gradient_ends_on_partial_tiles(B, monkeypatch, V, H_s, lens, win, slabs):  # noqa: F811
     """The 256 x 256 output tiles of dW at the last rows and columns of the array: whole groups of 8
-    rows and 32 columns are stored, added to by the second slab, and nothing behind them is touched."""
+    rows and 32 columns are stored, added to by the second slab, and nothing behind them is touched.
+    85 rows: half of the slab's rows are never written."""
     monkeypatch.setenv("ADWIN_SLAB_ROWS", "256")
-    w = synth.Workload("dw_edges", V, H_s, 192, synth._offsets([300, 41]), np.array([289, 41], np.int32),
+    w = synth.Workload("dw_edges", V, H_s, 192, synth._offsets(lens), np.array(win, np.int32),
                        synth.MODE_PREFIX_ONLY)
     p = synth.hidden_problem(w)
     f = Hp.oracle_inputs(p)
@@ -199,7 +212,8 @@ def test_head_gradient_ends_on_partial_tiles(B, monkeypatch, V, H_s):  # noqa: F
     d = {k: v.cuda() for k, v in p.items()}
     call = B.FusedCall(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window, mode=w.mode,
                        reduction=O.RED_SEQ_MEAN, want=WANT_HEAD)
-    assert B.adwin_opd_fused_launch_info(call.p)["slabs"] == 2
+    assert B.adwin_opd_fused_launch_info(call.p)["slabs"] == slabs
+    call.workspace.fill_(0xff)                   # NaN wherever nothing is written
     room = torch.full((V * H_s + 256 * H_s,), 7.0, device="cuda")
     call.p.dW_prefix = room.data_ptr()
     assert call.run() == 0
