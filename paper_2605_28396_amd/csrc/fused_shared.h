@@ -152,7 +152,7 @@ __device__ __forceinline__ float dot_bf16_row(const __bf16* x, const __bf16* y, 
 // in calls of few token tiles, the four blocks of 32 entries and the token (kMaxRefParts).
 constexpr int kRefBlocks = kTileVocab / 32;
 constexpr int kMaxRefParts = kRefBlocks + 1;
-constexpr int kFineRefTiles = 8;           // see launch_prepare
+constexpr int kFineRefTiles = 5;           // see launch_prepare
 struct References {
   float* max[2];            // [parts][n_pad] student, teacher; kNegBig: nothing to take the maximum of
   float* zy[2];             // [n_pad] logit of the sampled token (0: none)

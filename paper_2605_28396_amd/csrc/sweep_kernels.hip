@@ -959,7 +959,7 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(MergeArgs a) {
 // (maxima over vocabulary tile 0, 128 entries, under both models), the logits of its sampled token,
 // z_s[y_t] = h_s . W_s[y_t] and z_t[y_t] = h_t . W_t[y_t], which the merge and the diagnostics sweep
 // use again, and the hidden states as tile images.
-// The references are bound by latency, in two forms (see launch_prepare).
+// The references are bound by latency, in two forms (the line between them: see launch_prepare).
 //
 // Calls of few token tiles: cut as finely as the maxima allow.  A workgroup takes 32 rows, one model and
 // one block of 32 entries, its waves an eighth of the k-blocks each, straight from the row-major operands
@@ -969,16 +969,18 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(MergeArgs a) {
 // of 16, costs the L1 a line each, in kilobyte strides.)  256 rows at H = 2048 + 4096, with the images: 48 us
 // as eight workgroups of the other form, 17 as these 64; 800 rows at H = 2048 + 3072 32.5 -> 18.5.
 //
-// Others: 32 rows and all four blocks to a workgroup of 8 waves, one per block and half of every k-step;
-// the stages are small enough (20 KiB) for loads kRefLead k-steps ahead.  Every operand line is
-// moved into the LDS once; read into registers by the waves that use it, it goes through the L1 up
-// to five times, which is what bounds the form above (13 token tiles at H = 512 + 640: 20.6 us
-// against 15.8).
+// Others: 32 rows, one model and all four blocks to a workgroup of 8 waves, one per block and half of every
+// k-step, loads kRefLead k-steps ahead.  Stages of 20 KiB: 60 KiB of LDS, so that a compute unit holds two
+// workgroups, which hide each other's barriers: with one of six stages and both models 13 token tiles at H = 512 + 640
+// took 17.0 us against 13.2, 30 tiles at H = 1536 + 2048 54.9 against 46.5 (both with the images), 134 tiles at
+// H = 2048 + 4096 330 against 304.  Every operand line is moved into the LDS once; read into registers by the
+// waves that use it, it goes through the L1 up to five times, which is what bounds the form above (13
+// token tiles: 20.6 us).
 // ---------------------------------------------------------------------------------------
 constexpr int kPrepThreads = 512, kPrepWaves = kPrepThreads / 64;
-constexpr int kRefRows = 32, kRefLead = 5;
+constexpr int kRefRows = 32, kRefLead = 2;
 constexpr int kRefStage = (kTileVocab + kRefRows) * kRowBytes;          // 20 KiB
-constexpr int kRefLds = (kRefLead + 1) * kRefStage;                     // 120 KiB
+constexpr int kRefLds = (kRefLead + 1) * kRefStage;                     // 60 KiB
 constexpr int kOneLaunchTiles = 32;
 constexpr int kRefFineLds = kPrepWaves * 17 * 64 * 4;                   // 34 KiB
 
@@ -1044,45 +1046,42 @@ __device__ __forceinline__ float token_logits(const PrepareArgs& a, const TokenR
   return mine;
 }
 
-// References of 32 rows, both models, the tokens of four of them by each wave.
-__device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, const int32_t* rows, int64_t row0, char* lds) {
-  __shared__ float token[2][kRefRows];
+// References of 32 rows under one model, the tokens of four of them by each wave.
+__device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, const int32_t* rows, int64_t row0, int head, char* lds) {
+  __shared__ float token[kRefRows];
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  const int nt = a.H[1] / kBK, nk = nt + a.H[0] / kBK;      // k-steps: teacher, then student
+  const int H = a.H[head], nk = H / kBK;
   // A stage: 128 rows of W (tile 0; rows beyond V repeat the last, masked below), then 32 of h, row r
   // at 128 r, chunk c at position c ^ ((r >> 1) & 7).  Wave-load i < 2 of a wave: W rows
   // 16 wave + 8 i .. + 7; the third, of waves 0 to 3 only: h rows 8 wave .. + 7.
-  const char *pt[3], *ps[3];
+  const char* src[3];
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int m = i < 2 ? 2 * wave + i : (wave & 3), r = 8 * m + (lane >> 3);
     const uint32_t chunk = (uint32_t)((lane & 7) ^ ((r >> 1) & 7)) * 16u;
     const int64_t row = i < 2 ? (r < a.V ? r : a.V - 1) : rows[r];
-    pt[i] = (const char*)((i < 2 ? a.W[1] : a.h[1]) + row * a.H[1]) + chunk;
-    ps[i] = (const char*)((i < 2 ? a.W[0] : a.h[0]) + row * a.H[0]) + chunk;
+    src[i] = (const char*)((i < 2 ? a.W[head] : a.h[head]) + row * H) + chunk;
   }
   auto load = [&](int s) __attribute__((always_inline)) {      // past the last k-step: that one again
     const uint32_t slot = lds0 + (uint32_t)(s % (kRefLead + 1)) * kRefStage;
-    const int k = s < nk ? s : nk - 1;
-    const bool student = k >= nt;
-    const int64_t off = (int64_t)(student ? k - nt : k) * kRowBytes;
-    dma16_from(slot + (uint32_t)(2 * wave) * 1024u, (student ? ps[0] : pt[0]) + off);
-    dma16_from(slot + (uint32_t)(2 * wave + 1) * 1024u, (student ? ps[1] : pt[1]) + off);
-    if (wave < 4) dma16_from(slot + (uint32_t)(16 + wave) * 1024u, (student ? ps[2] : pt[2]) + off);
+    const int64_t off = (int64_t)(s < nk ? s : nk - 1) * kRowBytes;
+    dma16_from(slot + (uint32_t)(2 * wave) * 1024u, src[0] + off);
+    dma16_from(slot + (uint32_t)(2 * wave + 1) * 1024u, src[1] + off);
+    if (wave < 4) dma16_from(slot + (uint32_t)(16 + wave) * 1024u, src[2] + off);
   };
   for (int s = 0; s < kRefLead; ++s) load(s);
   {
     const TokenRows four(a, rows + wave * kTokenRows, row0 + wave * kTokenRows);
-    const float yt = token_logits(a, four, 1, lane), ys = token_logits(a, four, 0, lane);
-    if (lane < kTokenRows) { token[0][wave * kTokenRows + lane] = ys; token[1][wave * kTokenRows + lane] = yt; }
+    const float y = token_logits(a, four, head, lane);
+    if (lane < kTokenRows) token[wave * kTokenRows + lane] = y;
   }
   // wave = vocabulary block vb, half kq of every k-step; A = W rows, B = h rows as in the sweep
   const int vb = wave & 3, kq = wave >> 2;
-  f32x16 zt = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, zs = zt;
+  f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const uint32_t key = (uint32_t)(lane >> 1) & 7u, frag = (uint32_t)(lane & 31) * kRowBytes;
-  auto step = [&](int s, f32x16& acc) __attribute__((always_inline)) {
+  for (int s = 0; s < nk; ++s) {
     // stage s has landed once at most the loads of the kRefLead - 1 later ones are outstanding;
     // past the barrier every wave is done with stage s - 1, whose slot the next load takes
     if (wave < 4) wait_vm<3 * (kRefLead - 1)>();
@@ -1098,35 +1097,30 @@ __device__ __forceinline__ void refs_staged_block(const PrepareArgs& a, const in
     }
     load(s + kRefLead);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[j], fb[j], acc, 0, 0, 0);
-  };
-  for (int s = 0; s < nt; ++s) step(s, zt);
-  for (int s = nt; s < nk; ++s) step(s, zs);
+    for (int j = 0; j < 2; ++j) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[j], fb[j], z, 0, 0, 0);
+  }
   wait_vm<0>();
   __syncthreads();                                 // the ring is free from here on
-  float(*half_sum)[32][64] = (float(*)[32][64])lds;                      // [4]: of the second halves
-  float(*stat)[2][kRefRows] = (float(*)[2][kRefRows])(lds + 4 * 32 * 64 * 4);   // [4]: maxima
+  float(*half_sum)[16][64] = (float(*)[16][64])lds;                // [4]: of the second halves
+  float(*top)[kRefRows] = (float(*)[kRefRows])(lds + 4 * 16 * 64 * 4);    // [4]: maxima
   if (kq) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { half_sum[vb][e][lane] = zs[e]; half_sum[vb][16 + e][lane] = zt[e]; }
+    for (int e = 0; e < 16; ++e) half_sum[vb][e][lane] = z[e];
   }
   __syncthreads();
   if (!kq) {
-    float ms = kNegBig, mt = kNegBig;
+    float m = kNegBig;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      zs[e] += half_sum[vb][e][lane]; zt[e] += half_sum[vb][16 + e][lane];
-      if (vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V) { ms = fmaxf(ms, zs[e]); mt = fmaxf(mt, zt[e]); }
+      z[e] += half_sum[vb][e][lane];
+      if (vb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) < a.V) m = fmaxf(m, z[e]);
     }
-    ms = fmaxf(ms, __shfl_xor(ms, 32, 64));
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    if (lane < 32) { stat[vb][0][lane] = ms; stat[vb][1][lane] = mt; }
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if (lane < 32) top[vb][lane] = m;
   }
   __syncthreads();
-  const int head = threadIdx.x >> 5, r = threadIdx.x & 31;
-  if (head < 2)
-    a.ref.max[head][row0 + r] = fmaxf(fmaxf(fmaxf(stat[0][head][r], stat[1][head][r]), fmaxf(stat[2][head][r], stat[3][head][r])),
-                                      token[head][r]);
+  const int r = threadIdx.x;
+  if (r < kRefRows) a.ref.max[head][row0 + r] = fmaxf(fmaxf(fmaxf(top[0][r], top[1][r]), fmaxf(top[2][r], top[3][r])), token[r]);
 }
 
 // References of 32 rows, one model, one vocabulary block.
@@ -1207,7 +1201,7 @@ __device__ __forceinline__ void prepare_body(const PrepareArgs& a, const SetupAr
     return;
   }
   const int n = role == 0 ? kRefRows : role == 1 ? kTokenBlockRows : kTileTokens;
-  const int unit = role == 0 ? (FINE ? b / (2 * kRefBlocks) : b) : role == 1 ? b : b / a.img[role - 2].nk;
+  const int unit = role == 0 ? (FINE ? b / (2 * kRefBlocks) : b >> 1) : role == 1 ? b : b / a.img[role - 2].nk;
   const int64_t row0 = (int64_t)unit * n;
   const int32_t* rows;
   if constexpr (INLINE) {
@@ -1216,7 +1210,7 @@ __device__ __forceinline__ void prepare_body(const PrepareArgs& a, const SetupAr
   } else {
     rows = a.row_idx + row0;
   }
-  if (role == 0) return FINE ? refs_fine_block(a, rows, b, lds) : refs_staged_block(a, rows, row0, lds);
+  if (role == 0) return FINE ? refs_fine_block(a, rows, b, lds) : refs_staged_block(a, rows, row0, b & 1, lds);
   if (role == 1) return token_block(a, rows, b);
   const RowImageArgs& im = a.img[role - 2];
   image_block<kPrepThreads, kTileTokens>(im, rows, unit, b % im.nk);
@@ -1377,8 +1371,8 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStre
 }
 
 // The finely cut references serve calls of up to kFineRefTiles token tiles (References::parts is set by the
-// same rule): at five tiles of H = 1024 + 2048 they take 18 us against 25.5 staged, at 13 tiles of H = 512 + 640
-// 20.6 against 15.8.
+// same rule).  us per call, fine / staged: three tiles at H = 1024 + 2048 169.4 / 174.3, five 598.9 / 603.2
+// (V = 50,000); five at H = 1024 + 1024 441.0 / 441.2, seven at H = 512 + 768 130.9 / 127.5.
 // A plan that fits the arguments is expanded here too, in calls whose preparation is one launch.
 hipError_t launch_prepare(const PrepareArgs& p, bool refs, int n_tiles, const SetupArgs& setup,
                           const std::vector<unsigned char>& plan, hipStream_t st) {
@@ -1386,7 +1380,7 @@ hipError_t launch_prepare(const PrepareArgs& p, bool refs, int n_tiles, const Se
   PrepareArgs a = p;
   const int rows = n_tiles * kTileTokens;
   const bool fine = a.ref.parts > 1;
-  a.ref_blocks = !refs ? 0 : fine ? rows / kRefRows * kRefBlocks * 2 : rows / kRefRows;
+  a.ref_blocks = !refs ? 0 : rows / kRefRows * 2 * (fine ? kRefBlocks : 1);
   a.dot_blocks = refs && fine ? rows / kTokenBlockRows : 0;
   for (int m = 0; m < 2; ++m) a.img_blocks[m] = n_tiles * a.img[m].nk;
   const int rest = a.dot_blocks + a.img_blocks[0] + a.img_blocks[1];
@@ -1406,8 +1400,8 @@ hipError_t launch_prepare(const PrepareArgs& p, bool refs, int n_tiles, const Se
     prepare_kernel<true><<<(unsigned)(a.ref_blocks + rest), kPrepThreads, lds, st>>>(a);
     return hipGetLastError();
   }
-  // a workgroup of a launch with staged references holds their LDS as well, one workgroup per compute
-  // unit, so that the others of a large call, 164 us of copying for 34,000 rows, go by themselves
+  // a workgroup of a launch with staged references holds their LDS as well, two workgroups per compute
+  // unit, so that the others of a large call, 155 us of copying for 34,000 rows, go by themselves
   if (a.ref_blocks && n_tiles > kOneLaunchTiles) {
     prepare_kernel<false><<<(unsigned)a.ref_blocks, kPrepThreads, lds, st>>>(a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
