@@ -52,56 +52,82 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
     __syncthreads();
   }
   float dz[TR ? 8 : 1][8];
+  // kTogether vectors of each factor and what belongs to their rows are loaded before the first is looked at:
+  // in a call of few rows nothing else covers the round trips (118 rows of V = 4,096: 44.1 -> 42.6 us per
+  // call; large calls, where waves are many: the same within 0.3 %)
+  constexpr int kTogether = TR ? 2 : 4;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int q = i * 256 + threadIdx.x;
-    const int64_t r = rbase + (q >> 3);
-    const float iz = a.inv_z[r];
-    const uint4 y = p2[q];
-    float d[8];
-    if (SAMPLED) {
-      const float c = a.cr[r], ciz = -c * iz;
-      d[0] = bf16_lo(y.x) * ciz; d[1] = bf16_hi(y.x) * ciz; d[2] = bf16_lo(y.y) * ciz; d[3] = bf16_hi(y.y) * ciz;
-      d[4] = bf16_lo(y.z) * ciz; d[5] = bf16_hi(y.z) * ciz; d[6] = bf16_lo(y.w) * ciz; d[7] = bf16_hi(y.w) * ciz;
-      // entries of this vector: 64 kt + 8 (logical chunk) + e
-      const int rl = q >> 3, v0 = kt * kBK + (((q & 7) ^ ((rl >> 1) & 7)) << 3);
-      const int e_y = a.yid[r] - v0;
+  for (int i0 = 0; i0 < 8; i0 += kTogether) {
+    uint4 xs[kTogether], ys[kTogether];
+    float izs[kTogether], ms[kTogether], m0s[kTogether];
+    int ids[kTogether];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) d[e] += (e == e_y) ? c : 0.f;
-      if (TR) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dz[i][e] = d[e];
+    for (int j = 0; j < kTogether; ++j) {
+      const int q = (i0 + j) * 256 + threadIdx.x;
+      const int64_t r = rbase + (q >> 3);
+      ys[j] = p2[q];
+      izs[j] = a.inv_z[r];
+      if (SAMPLED) {
+        ms[j] = a.cr[r];
+        ids[j] = a.yid[r];
+      } else {
+        xs[j] = p1[q];
+        ms[j] = a.mu[r];
+        m0s[j] = a.mu0t[(int64_t)(kt >> 1) * a.mu0t_stride + rt * kTileTokens + (q >> 3)];
       }
-    } else {
-      const float dl = a.mu[r] - a.mu0t[(int64_t)(kt >> 1) * a.mu0t_stride + rt * kTileTokens + (q >> 3)];
-      const uint4 x = p1[q];
-      float pv[8], xv[8];                      // p_s and the stored D of the vector's 8 entries
-      pv[0] = bf16_lo(y.x) * iz; pv[1] = bf16_hi(y.x) * iz; pv[2] = bf16_lo(y.y) * iz; pv[3] = bf16_hi(y.y) * iz;
-      pv[4] = bf16_lo(y.z) * iz; pv[5] = bf16_hi(y.z) * iz; pv[6] = bf16_lo(y.w) * iz; pv[7] = bf16_hi(y.w) * iz;
-      xv[0] = bf16_lo(x.x); xv[1] = bf16_hi(x.x); xv[2] = bf16_lo(x.y); xv[3] = bf16_hi(x.y);
-      xv[4] = bf16_lo(x.z); xv[5] = bf16_hi(x.z); xv[6] = bf16_lo(x.w); xv[7] = bf16_hi(x.w);
-      const bool dead = iz == 0.f;             // excluded row: its factors may hold inf / NaN
-      float pmax = 0.f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        d[e] = dead ? 0.f : (xv[e] - dl) * pv[e];
-        pmax = fmaxf(pmax, pv[e]);
-      }
-      if (TR) {                                // the head-weight operand keeps every entry in bf16
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dz[i][e] = d[e];
-      }
-      if (__builtin_expect(pmax >= kHeavyP && !dead, 0)) {
+    for (int j = 0; j < kTogether; ++j) {
+      const int i = i0 + j, q = i * 256 + threadIdx.x;
+      const int64_t r = rbase + (q >> 3);
+      const float iz = izs[j];
+      const uint4 y = ys[j];
+      float d[8];
+      if (SAMPLED) {
+        const float c = ms[j], ciz = -c * iz;
+        d[0] = bf16_lo(y.x) * ciz; d[1] = bf16_hi(y.x) * ciz; d[2] = bf16_lo(y.y) * ciz; d[3] = bf16_hi(y.y) * ciz;
+        d[4] = bf16_lo(y.z) * ciz; d[5] = bf16_hi(y.z) * ciz; d[6] = bf16_lo(y.w) * ciz; d[7] = bf16_hi(y.w) * ciz;
         // entries of this vector: 64 kt + 8 (logical chunk) + e
         const int rl = q >> 3, v0 = kt * kBK + (((q & 7) ^ ((rl >> 1) & 7)) << 3);
+        const int e_y = ids[j] - v0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (pv[e] >= kHeavyP && heavy_push(a.heavy, r, v0 + e)) d[e] = 0.f;
+        for (int e = 0; e < 8; ++e) d[e] += (e == e_y) ? c : 0.f;
+        if (TR) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) dz[i][e] = d[e];
+        }
+      } else {
+        const float dl = ms[j] - m0s[j];
+        const uint4 x = xs[j];
+        float pv[8], xv[8];                      // p_s and the stored D of the vector's 8 entries
+        pv[0] = bf16_lo(y.x) * iz; pv[1] = bf16_hi(y.x) * iz; pv[2] = bf16_lo(y.y) * iz; pv[3] = bf16_hi(y.y) * iz;
+        pv[4] = bf16_lo(y.z) * iz; pv[5] = bf16_hi(y.z) * iz; pv[6] = bf16_lo(y.w) * iz; pv[7] = bf16_hi(y.w) * iz;
+        xv[0] = bf16_lo(x.x); xv[1] = bf16_hi(x.x); xv[2] = bf16_lo(x.y); xv[3] = bf16_hi(x.y);
+        xv[4] = bf16_lo(x.z); xv[5] = bf16_hi(x.z); xv[6] = bf16_lo(x.w); xv[7] = bf16_hi(x.w);
+        const bool dead = iz == 0.f;             // excluded row: its factors may hold inf / NaN
+        float pmax = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          d[e] = dead ? 0.f : (xv[e] - dl) * pv[e];
+          pmax = fmaxf(pmax, pv[e]);
+        }
+        if (TR) {                                // the head-weight operand keeps every entry in bf16
+#pragma unroll
+          for (int e = 0; e < 8; ++e) dz[i][e] = d[e];
+        }
+        if (__builtin_expect(pmax >= kHeavyP && !dead, 0)) {
+          // entries of this vector: 64 kt + 8 (logical chunk) + e
+          const int rl = q >> 3, v0 = kt * kBK + (((q & 7) ^ ((rl >> 1) & 7)) << 3);
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (pv[e] >= kHeavyP && heavy_push(a.heavy, r, v0 + e)) d[e] = 0.f;
+        }
+        uint4 o;
+        o.x = pack_bf16(d[0], d[1]); o.y = pack_bf16(d[2], d[3]);
+        o.z = pack_bf16(d[4], d[5]); o.w = pack_bf16(d[6], d[7]);
+        p1[q] = o;
       }
-      uint4 o;
-      o.x = pack_bf16(d[0], d[1]); o.y = pack_bf16(d[2], d[3]);
-      o.z = pack_bf16(d[4], d[5]); o.w = pack_bf16(d[6], d[7]);
-      p1[q] = o;
     }
   }
   if (TR) {
