@@ -8,6 +8,8 @@
 
 #include "device_utils.h"
 #include "plan_device.h"
+#include "setup_device.h"
+#include "tail_device.h"
 
 namespace adwin {
 
@@ -31,7 +33,32 @@ struct LogitsArgs {
   // few long rows, each cut into `splits` pieces: the pieces' sums [n_adm][splits][8]
   float* part; int splits; int64_t n_adm;
   int sampled;         // dz = scale c_t (e_y - p_s) (Eq. 4 on the sampled token) instead of scale p_s (Delta - KL_t)
+  int tail_has_kl;     // split rows: the tail's workgroups, in the same launch as dz, write klr
+  int mark;            // an excluded row leaves kExcludedRow in klr, for the tail to report (BatchArgs::status)
 };
+
+// The arguments of a launch that also sets up.  A launch costs about 2 us on the device and 4 on the host however
+// little it does, and a call of few or short rows is little else: where the plan fits the arguments (up to about
+// 90 rollouts) workgroup 0 of the rows' own launch writes it to the workspace, and the others read it
+// from the arguments.  us per call, with a launch of its own / this: 60 rows of 1,000 logits 14.0 / 11.5, 416 rows
+// of 8,000 17.8 / 15.2, 3,100 rows of 2,048 23.0 / 20.7, 12,000 rows of 16,000 150.1 / 147.7.
+struct RowsLaunch {
+  LogitsArgs a;
+  SetupArgs setup;
+  SetupBlob blob;
+};
+static_assert(sizeof(RowsLaunch) < 4096, "kernel arguments");
+__device__ __forceinline__ DevicePlan plan_of(const RowsLaunch& l) {
+  DevicePlan pl = l.a.pl;
+  auto here = [&](const auto* q) {
+    return (decltype(q))((const unsigned char*)l.blob.data + ((const unsigned char*)q - l.setup.plan));
+  };
+  pl.offsets = here(pl.offsets);
+  pl.comp_off = here(pl.comp_off);
+  pl.n = here(pl.n);
+  pl.alpha_p = here(pl.alpha_p);
+  return pl;
+}
 
 // The one-hot part of the sampled estimator: dz[y] = k (1 - p_s(y)), k = scale c_t, written
 // over the -k p_s(y) the vector sweep stored there.
@@ -539,9 +566,36 @@ constexpr int short_row_limit(int threads) { return threads * kShortIters * 8; }
 // the logits coming from the caches.
 constexpr int kWhole = 0, kPieceSums = 1, kPieceGrad = 2;
 
-template <int THREADS, bool DIAG, int PHASE = kWhole>
-__global__ __launch_bounds__(THREADS < 256 ? 256 : THREADS, THREADS < 1024 ? 4 : 1)
-void logits_row_short_kernel(LogitsArgs a) {
+// A row's results from its sums.
+struct RowResult { float lse_s, lse_t, mu, kl, ent; bool dead; };
+template <bool DIAG>
+__device__ __forceinline__ RowResult row_result(float ms, float Zs, float A, float mt, float Zt, float Bt) {
+  RowResult r;
+  r.lse_s = ms + logf(Zs);
+  r.lse_t = mt + logf(Zt);
+  r.mu = A / Zs;                       // E_{p_s}[z_s - z_t]
+  r.kl = kl_from_sums(r.mu, ms - mt, Zs, Zt);
+  r.ent = DIAG ? r.lse_t - Bt / Zt : 0.f;
+  // a row without finite statistics is excluded: zeros in every output
+  r.dead = !(fabsf(r.lse_s) < 3.0e38f) || !(fabsf(r.lse_t) < 3.0e38f) || !(fabsf(r.kl) < 3.0e38f) ||
+           !(fabsf(r.mu) < 3.0e38f) || !(fabsf(r.ent) < 3.0e38f);
+  if (r.dead) { r.kl = 0.f; r.ent = 0.f; }
+  return r;
+}
+
+template <bool DIAG>
+__device__ __forceinline__ void fold_sums(float& ms, float& Zs, float& A, float& mt, float& Zt, float& Bt, int& cnt, int o) {
+  merge_mza(ms, Zs, A, __shfl_xor(ms, o, 64), __shfl_xor(Zs, o, 64), __shfl_xor(A, o, 64));
+  if (DIAG) {
+    merge_mza(mt, Zt, Bt, __shfl_xor(mt, o, 64), __shfl_xor(Zt, o, 64), __shfl_xor(Bt, o, 64));
+    cnt += __shfl_xor(cnt, o, 64);
+  } else {
+    merge_mz(mt, Zt, __shfl_xor(mt, o, 64), __shfl_xor(Zt, o, 64));
+  }
+}
+
+template <int THREADS, bool DIAG, int PHASE>
+__device__ __forceinline__ void short_rows(const LogitsArgs& a, const DevicePlan& pl, unsigned block) {
   constexpr int kRows = THREADS == 64 ? 4 : 1, kWaves = THREADS / 64;
   static_assert(PHASE == kWhole || kRows == 1, "a piece is a workgroup's");
   __shared__ float sh[7][kWaves];
@@ -549,9 +603,9 @@ void logits_row_short_kernel(LogitsArgs a) {
   // pieces come first, a workgroup each; kPieceSums has the T packed rows behind them, of which
   // those outside the windows are cleared
   const int64_t n_pieces = PHASE == kWhole ? 0 : a.n_adm * a.splits;
-  const bool is_piece = PHASE != kWhole && (int64_t)blockIdx.x < n_pieces;
-  int64_t t = kRows > 1 ? (int64_t)blockIdx.x * kRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
-                        : (int64_t)blockIdx.x - (is_piece ? 0 : n_pieces);
+  const bool is_piece = PHASE != kWhole && (int64_t)block < n_pieces;
+  int64_t t = kRows > 1 ? (int64_t)block * kRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                        : (int64_t)block - (is_piece ? 0 : n_pieces);
   if (t >= a.T && !is_piece) return;
   const int row_vec = a.V >> 3;
   int i, piece = 0, q0 = 0, nvec = row_vec;       // the vectors [q0, q0 + nvec) of the row
@@ -559,14 +613,14 @@ void logits_row_short_kernel(LogitsArgs a) {
   if (is_piece) {
     const int64_t r = t / a.splits;               // the r-th admitted row
     piece = (int)(t % a.splits);
-    i = wave_last_le(a.pl.comp_off, a.B + 1, r);
-    j = r - a.pl.comp_off[i];
-    t = a.pl.offsets[i] + j;
+    i = wave_last_le(pl.comp_off, a.B + 1, r);
+    j = r - pl.comp_off[i];
+    t = pl.offsets[i] + j;
     q0 = (int)((int64_t)row_vec * piece / a.splits);
     nvec = (int)((int64_t)row_vec * (piece + 1) / a.splits) - q0;
   } else {
-    i = wave_last_le(a.pl.offsets, a.B + 1, t);
-    j = t - a.pl.offsets[i];
+    i = wave_last_le(pl.offsets, a.B + 1, t);
+    j = t - pl.offsets[i];
   }
   const int row_bytes = nvec * 16, lane_off = lid * 16;
   const __amdgpu_buffer_rsrc_t bd = row_rsrc(a.dz ? a.dz + t * row_vec + q0 : nullptr, a.dz ? row_bytes : 0);
@@ -574,7 +628,7 @@ void logits_row_short_kernel(LogitsArgs a) {
     const uint4 z = {0u, 0u, 0u, 0u};
     for (int it = 0; it * THREADS < nvec; ++it) row_store16(bd, lane_off, it * THREADS * 16, z);
   };
-  if (j >= a.pl.n[i]) {   // outside the window: zero gradient row, zero KL
+  if (j >= pl.n[i]) {   // outside the window: zero gradient row, zero KL
     if (a.dz) clear_row();
     if (lid == 0) {
       if (a.kl) a.kl[t] = 0.f;
@@ -621,6 +675,9 @@ void logits_row_short_kernel(LogitsArgs a) {
   const float ms2 = ms * kLog2e, mt2 = mt * kLog2e;
   if constexpr (PHASE != kPieceGrad) static_for<kShortIters>([&](auto it_c) {
     constexpr int it = decltype(it_c)::value;
+    // unpacked again: kept from the maxima, the halves of all vectors are 80 registers more, and spilled
+    asm volatile("" : "+v"(rs[it].x), "+v"(rs[it].y), "+v"(rs[it].z), "+v"(rs[it].w));
+    asm volatile("" : "+v"(rt[it].x), "+v"(rt[it].y), "+v"(rt[it].z), "+v"(rt[it].w));
     if (it * THREADS + lid < nvec) {
       float s[8], u[8];
       unpack8(rs[it], s);
@@ -639,16 +696,8 @@ void logits_row_short_kernel(LogitsArgs a) {
       }
     }
   });
-  auto fold = [&](int o) __attribute__((always_inline)) {
-    merge_mza(ms, Zs, A, __shfl_xor(ms, o, 64), __shfl_xor(Zs, o, 64), __shfl_xor(A, o, 64));
-    if (DIAG) {
-      merge_mza(mt, Zt, Bt, __shfl_xor(mt, o, 64), __shfl_xor(Zt, o, 64), __shfl_xor(Bt, o, 64));
-      cnt += __shfl_xor(cnt, o, 64);
-    } else {
-      merge_mz(mt, Zt, __shfl_xor(mt, o, 64), __shfl_xor(Zt, o, 64));
-    }
-  };
-  float* part = PHASE == kWhole ? nullptr : a.part + (a.pl.comp_off[i] + j) * a.splits * 8;   // of the row's pieces
+  auto fold = [&](int o) __attribute__((always_inline)) { fold_sums<DIAG>(ms, Zs, A, mt, Zt, Bt, cnt, o); };
+  float* part = PHASE == kWhole ? nullptr : a.part + (pl.comp_off[i] + j) * a.splits * 8;   // of the row's pieces
   if constexpr (PHASE == kPieceGrad) {
     // up to 64 pieces, one per lane; lanes without one hold the neutral element
     uint32_t zy = 0u;
@@ -686,14 +735,9 @@ void logits_row_short_kernel(LogitsArgs a) {
     return;
   }
   // every thread has the row's sums
-  const float lse_s = ms + logf(Zs), lse_t = mt + logf(Zt);
-  const float mu = A / Zs;                       // E_{p_s}[z_s - z_t]
-  float kl = kl_from_sums(mu, ms - mt, Zs, Zt);
-  float ent = DIAG ? lse_t - Bt / Zt : 0.f;
-  // a row without finite statistics is excluded: zeros in every output
-  const bool dead = !(fabsf(lse_s) < 3.0e38f) || !(fabsf(lse_t) < 3.0e38f) || !(fabsf(kl) < 3.0e38f) ||
-                    !(fabsf(mu) < 3.0e38f) || !(fabsf(ent) < 3.0e38f);
-  if (dead) { kl = 0.f; ent = 0.f; }
+  const RowResult res = row_result<DIAG>(ms, Zs, A, mt, Zt, Bt);
+  const float lse_s = res.lse_s, lse_t = res.lse_t, mu = res.mu, kl = res.kl, ent = res.ent;
+  const bool dead = res.dead;
   const float c = has_y && !dead ? (zy_s - lse_s) - (zy_t - lse_t) : 0.f;
   if (lid == 0 && piece == 0) {
     const uint32_t flag = dead ? ADWIN_DEV_NONFINITE : (a.ids && !has_y ? ADWIN_DEV_BAD_ID : 0u);
@@ -705,12 +749,12 @@ void logits_row_short_kernel(LogitsArgs a) {
       if (a.t_logp) a.t_logp[t] = has_y && !dead ? zy_t - lse_t : 0.f;
       if (a.t_rank) a.t_rank[t] = has_y && !dead ? cnt + 1 : 0;
     }
-    a.klr[a.pl.comp_off[i] + j] = kl;
+    if (PHASE == kWhole || !a.tail_has_kl) a.klr[pl.comp_off[i] + j] = dead && a.mark ? __uint_as_float(kExcludedRow) : kl;
   }
   if (!a.dz) return;
   if (dead) return clear_row();
   // ---- dz from the registers (see logits_row_resident_kernel) ------------------------------
-  const float scale = a.grad_scale * a.pl.alpha_p[i];
+  const float scale = a.grad_scale * pl.alpha_p[i];
   const float k_s = a.sampled ? scale * c : scale;
   const float sg = k_s < 0.f ? -1.f : 1.f;
   const float sgn = a.sampled ? 0.f : sg;
@@ -734,14 +778,88 @@ void logits_row_short_kernel(LogitsArgs a) {
   });
 }
 
+// Workgroups in front of a launch's pieces, a multiple of the dies: workgroups go to them in turn, and a piece whose
+// second launch is on the die of its first finds its logits in that die's L2 (120 rows of 120,000 logits
+// in two pieces each, the second launch: 11.0 us, one workgroup further 13.2).
+__host__ __device__ constexpr unsigned lead_blocks(unsigned n) { return (n + 7) / 8 * 8; }
+
+template <int THREADS, bool DIAG, int PHASE = kWhole>
+__global__ __launch_bounds__(THREADS < 256 ? 256 : THREADS, THREADS < 1024 ? 4 : 1)
+void logits_row_short_kernel(LogitsArgs a) {
+  short_rows<THREADS, DIAG, PHASE>(a, a.pl, blockIdx.x);
+}
+template <int THREADS, bool DIAG, int PHASE = kWhole>
+__global__ __launch_bounds__(THREADS < 256 ? 256 : THREADS, THREADS < 1024 ? 4 : 1)
+void logits_row_short_setup_kernel(RowsLaunch l) {
+  if (blockIdx.x == 0)
+    return setup_body(l.setup, &l.blob, (const unsigned char*)l.blob.data, 0, 1, THREADS < 256 ? 256 : THREADS);
+  if (PHASE != kWhole && blockIdx.x < lead_blocks(1)) return;
+  short_rows<THREADS, DIAG, PHASE>(l.a, plan_of(l), blockIdx.x - (PHASE == kWhole ? 1 : lead_blocks(1)));
+}
+
+// KL_t of rollout i's rows from the sums of their pieces, with the same merges as the workgroups that write dz:
+// LANES (16 up to 16 pieces, or 64) to a row, the next row's sums on their way.
+template <bool DIAG, int LANES>
+__device__ __forceinline__ void rollout_kl(const LogitsArgs& a, int i) {
+  const int64_t r0 = a.pl.comp_off[i];
+  const int n = a.pl.n[i], g = threadIdx.x & (LANES - 1);
+  constexpr int kRows = 256 / LANES;
+  const float4 none = make_float4(kNegBig, 0.f, 0.f, kNegBig), none2 = make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 x = none, x2 = none2;
+  auto load = [&](int j) {
+    if (g < a.splits && j < n) {
+      const float* q = a.part + ((r0 + j) * a.splits + g) * 8;
+      x = *(const float4*)q;
+      x2 = *(const float4*)(q + 4);
+    }
+  };
+  load(threadIdx.x / LANES);
+  for (int first = 0; first < n; first += kRows) {
+    const int j = first + threadIdx.x / LANES;
+    float ms = x.x, Zs = x.y, A = x.z, mt = x.w, Zt = x2.x, Bt = x2.y;
+    int cnt = 0;
+    load(j + kRows);
+#pragma unroll
+    for (int o = LANES / 2; o > 0; o >>= 1) fold_sums<DIAG>(ms, Zs, A, mt, Zt, Bt, cnt, o);
+    const RowResult r = row_result<DIAG>(ms, Zs, A, mt, Zt, Bt);
+    if (g == 0 && j < n) a.klr[r0 + j] = r.kl;
+  }
+  __syncthreads();
+}
+
+// The second launch of a call of split rows without summaries: its first workgroups end the call
+// (tail_device.h), which then has two launches instead of four.  They need only KL_t, which they take from the
+// sums of the pieces themselves instead of waiting for the workgroups that write dz.  us per call, four launches /
+// two: V = 151,936, 29 rows 22.6 / 16.0, 8 rollouts of 10 to 30 rows 45.5 / 36.2; V = 100,000, 117 rows 24.5 / 17.4.
 template <bool DIAG>
-static hipError_t launch_short_rows(const LogitsArgs& a, hipStream_t st) {
-  const unsigned T = (unsigned)a.T;
-  if (a.V <= short_row_limit(64)) logits_row_short_kernel<64, DIAG><<<(T + 3) / 4, 256, 0, st>>>(a);
-  else if (a.V <= short_row_limit(256)) logits_row_short_kernel<256, DIAG><<<T, 256, 0, st>>>(a);
-  else if (a.V <= short_row_limit(512)) logits_row_short_kernel<512, DIAG><<<T, 512, 0, st>>>(a);
-  else logits_row_short_kernel<1024, DIAG><<<T, 1024, 0, st>>>(a);
+__global__ __launch_bounds__(256, 4) void logits_piece_grad_kernel(LogitsArgs a, TailArgs tail) {
+  if ((int)blockIdx.x < tail.blocks) {
+    __shared__ double sh[16];
+    __shared__ int sh_first[4];
+    if (a.splits <= 16) rollout_kl<DIAG, 16>(a, blockIdx.x);
+    else rollout_kl<DIAG, 64>(a, blockIdx.x);
+    return tail_body<false>(tail, blockIdx.x, sh, sh_first);
+  }
+  const unsigned lead = lead_blocks((unsigned)tail.blocks);
+  if (blockIdx.x >= lead) short_rows<256, DIAG, kPieceGrad>(a, a.pl, blockIdx.x - lead);
+}
+
+// `blocks` workgroups of rows; with a plan in the arguments, and the one that sets up.
+template <int THREADS, bool DIAG, int PHASE = kWhole>
+static hipError_t launch_rows(const RowsLaunch& l, unsigned blocks, hipStream_t st) {
+  constexpr int kThreads = THREADS < 256 ? 256 : THREADS;
+  if (l.blob.n16) logits_row_short_setup_kernel<THREADS, DIAG, PHASE><<<blocks + (PHASE == kWhole ? 1 : lead_blocks(1)), kThreads, 0, st>>>(l);
+  else logits_row_short_kernel<THREADS, DIAG, PHASE><<<blocks, kThreads, 0, st>>>(l.a);
   return hipGetLastError();
+}
+
+template <bool DIAG>
+static hipError_t launch_short_rows(const RowsLaunch& l, hipStream_t st) {
+  const unsigned T = (unsigned)l.a.T;
+  if (l.a.V <= short_row_limit(64)) return launch_rows<64, DIAG>(l, (T + 3) / 4, st);
+  if (l.a.V <= short_row_limit(256)) return launch_rows<256, DIAG>(l, T, st);
+  if (l.a.V <= short_row_limit(512)) return launch_rows<512, DIAG>(l, T, st);
+  return launch_rows<1024, DIAG>(l, T, st);
 }
 
 // Whether a call with diagnostics takes the streaming kernel under ADWIN_LOGITS_AUTO.
@@ -790,12 +908,12 @@ static int row_splits(int V, int64_t n_adm, bool diag, int64_t room) {
 }
 
 template <bool DIAG>
-static hipError_t launch_split_rows(const LogitsArgs& a, hipStream_t st) {
-  const unsigned pieces = (unsigned)(a.n_adm * a.splits);
-  logits_row_short_kernel<256, DIAG, kPieceSums><<<pieces + (unsigned)a.T, 256, 0, st>>>(a);
-  hipError_t e = hipGetLastError();
+static hipError_t launch_split_rows(const RowsLaunch& l, const TailArgs& tail, hipStream_t st) {
+  const unsigned pieces = (unsigned)(l.a.n_adm * l.a.splits);
+  hipError_t e = launch_rows<256, DIAG, kPieceSums>(l, pieces + (unsigned)l.a.T, st);
   if (e != hipSuccess) return e;
-  logits_row_short_kernel<256, DIAG, kPieceGrad><<<pieces, 256, 0, st>>>(a);
+  if (tail.blocks > 0) logits_piece_grad_kernel<DIAG><<<lead_blocks((unsigned)tail.blocks) + pieces, 256, 0, st>>>(l.a, tail);
+  else logits_row_short_kernel<256, DIAG, kPieceGrad><<<pieces, 256, 0, st>>>(l.a);
   return hipGetLastError();
 }
 
@@ -880,42 +998,21 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
   double* seg = (double*)(ws + L.o_seg);
 
   uint32_t* done = (uint32_t*)(ws + L.o_done);
+  const size_t room = (workspace_bytes - L.total) / kPieceBytes;
+  const bool diag = p->t_logp || p->t_entropy || p->t_rank;
+  const bool automatic = p->scheme == ADWIN_LOGITS_AUTO;
+  const int splits = automatic ? row_splits(p->V, hp.n_adm, diag, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
+  const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING ||
+                         (automatic && diag && splits == 0 && streaming_suits_diagnostics(p->V, hp.n_adm));
+  const bool shorts = !streaming && p->V <= short_row_limit(1024);
+
   SetupArgs setup(ws + L.o_plan, p->B);
   setup.clear(done, 1);
   setup.clear(p->status_dev, 1);
-  ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
-  if (p->T > 0) {
-    LogitsArgs a;
-    a.pl = pl; a.T = p->T; a.B = p->B; a.V = p->V;
-    a.z_s = (const uint4*)p->z_s; a.z_t = (const uint4*)p->z_t; a.ids = p->ids;
-    a.grad_scale = p->grad_scale;
-    a.kl = p->kl; a.c = p->c; a.dz = (uint4*)p->dz; a.klr = klr; a.status = p->status_dev;
-    a.t_logp = p->t_logp; a.t_entropy = p->t_entropy; a.t_rank = p->t_rank;
-    a.sampled = p->estimator == ADWIN_EST_SAMPLED;
-    PhaseScope scope(timer, ADWIN_PHASE_STATS);
-    a.part = (float*)(ws + L.total);
-    a.n_adm = hp.n_adm;
-    const size_t room = (workspace_bytes - L.total) / kPieceBytes;
-    const bool diag = p->t_logp || p->t_entropy || p->t_rank;
-    const bool automatic = p->scheme == ADWIN_LOGITS_AUTO;
-    a.splits = automatic ? row_splits(p->V, hp.n_adm, diag, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
-    const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING ||
-                           (automatic && diag && a.splits == 0 && streaming_suits_diagnostics(p->V, hp.n_adm));
-    if (!streaming && p->V <= short_row_limit(1024)) {
-      ADWIN_HIP_TRY(diag ? launch_short_rows<true>(a, stream) : launch_short_rows<false>(a, stream));
-    } else if (a.splits > 0) {
-      ADWIN_HIP_TRY(diag ? launch_split_rows<true>(a, stream) : launch_split_rows<false>(a, stream));
-    } else if (streaming) {
-      if (diag) logits_row_kernel<true><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
-      else logits_row_kernel<false><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
-    } else {
-      if (first_use_on_device(1)) ADWIN_HIP_TRY(logits_kernels_opt_in());
-      if (diag) logits_row_resident_kernel<true><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
-      else logits_row_resident_kernel<false><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
-    }
-    ADWIN_HIP_TRY(hipGetLastError());
-  }
-  PhaseScope scope(timer, ADWIN_PHASE_REDUCE);
+  RowsLaunch l{LogitsArgs{}, setup, SetupBlob{}};
+  // setup in the first launch of the rows; the calls of the other two kernels take 60 us and more
+  const bool together = p->T > 0 && (shorts || splits > 0) && l.blob.take(blob);
+  if (!together) ADWIN_HIP_TRY(launch_setup(setup, blob, stream));
   BatchArgs b{};
   b.pl = pl; b.B = p->B; b.H = 0; b.probe = 0; b.zero_grad = 1;
   b.klr = klr; b.rownorm = nullptr; b.seg = seg; b.loss_prefix = p->loss_prefix; b.loss_full = nullptr;
@@ -928,7 +1025,44 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
     sa.acc = (double*)(ws + L.o_summ);
     sa.first_reject = p->t_first_reject; sa.logp_mean = p->t_logp_mean;
   }
-  ADWIN_HIP_TRY(launch_tail(b, sa, CandArgs{}, nullptr, 0, stream));
+  bool ended = false;
+  if (p->T > 0) {
+    LogitsArgs& a = l.a;
+    a.pl = pl; a.T = p->T; a.B = p->B; a.V = p->V;
+    a.z_s = (const uint4*)p->z_s; a.z_t = (const uint4*)p->z_t; a.ids = p->ids;
+    a.grad_scale = p->grad_scale;
+    a.kl = p->kl; a.c = p->c; a.dz = (uint4*)p->dz; a.klr = klr; a.status = p->status_dev;
+    a.t_logp = p->t_logp; a.t_entropy = p->t_entropy; a.t_rank = p->t_rank;
+    a.sampled = p->estimator == ADWIN_EST_SAMPLED;
+    PhaseScope scope(timer, ADWIN_PHASE_STATS);
+    a.part = (float*)(ws + L.total);
+    a.n_adm = hp.n_adm;
+    a.splits = splits;
+    if (together && splits == 0 && a.status) {      // the launch that clears the status word cannot also set it
+      a.mark = 1;
+      a.status = nullptr;
+      b.status = p->status_dev; b.ids = p->ids; b.V = p->V;
+    }
+    if (shorts) {
+      ADWIN_HIP_TRY(diag ? launch_short_rows<true>(l, stream) : launch_short_rows<false>(l, stream));
+    } else if (splits > 0) {
+      TailArgs tail = make_tail(b, sa);
+      ended = !tail.with_summary;      // summaries need the rows' outputs, which the second launch writes
+      if (!ended) tail.blocks = 0;
+      a.tail_has_kl = ended;
+      ADWIN_HIP_TRY(diag ? launch_split_rows<true>(l, tail, stream) : launch_split_rows<false>(l, tail, stream));
+    } else if (streaming) {
+      if (diag) logits_row_kernel<true><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
+      else logits_row_kernel<false><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
+    } else {
+      if (first_use_on_device(1)) ADWIN_HIP_TRY(logits_kernels_opt_in());
+      if (diag) logits_row_resident_kernel<true><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
+      else logits_row_resident_kernel<false><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
+    }
+    ADWIN_HIP_TRY(hipGetLastError());
+  }
+  PhaseScope scope(timer, ADWIN_PHASE_REDUCE);
+  if (!ended) ADWIN_HIP_TRY(launch_tail(b, sa, CandArgs{}, nullptr, 0, stream));
   return ADWIN_OK;
 }
 

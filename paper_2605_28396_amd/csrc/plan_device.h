@@ -63,7 +63,11 @@ struct BatchArgs {
   uint32_t* done;       // a word that is zero when the call starts (not used with probe gradients)
   float* rho_pooled; float* rho_field; float* batch;
   int32_t* n_out; int64_t* n_adm_out; int64_t n_adm;
+  // Not NULL: the rows' status bits are still to be reported, from klr (kExcludedRow) and the ids of
+  // the rows [0, n_i) of every rollout (NULL: none); the word is zero, or holds other rollouts' bits.
+  uint32_t* status; const int32_t* ids; int32_t V;
 };
+constexpr uint32_t kExcludedRow = 0x7fffffffu;   // a NaN; KL_t of every other row is finite
 // Candidate-window audit (Sec. 4.2): alignment of the shared prefix window L_k, for every
 // candidate k, with the full-rollout gradient, from the per-row gradients of one
 // full-rollout pass.

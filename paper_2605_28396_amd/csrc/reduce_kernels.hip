@@ -357,7 +357,8 @@ hipError_t launch_upload(void* dst, const void* src_host, size_t bytes, hipStrea
   return hipSuccess;
 }
 
-// Setup in a launch of its own: calls whose plan does not fit a kernel's arguments, and the logits path.
+// Setup in a launch of its own: calls whose plan does not fit a kernel's arguments, logits calls served by the
+// long-row or the streaming kernel.
 __global__ __launch_bounds__(256) void setup_inline_kernel(const SetupArgs a, const SetupBlob b) {
   setup_body(a, &b, (const unsigned char*)b.data, blockIdx.x, gridDim.x, 256);
 }

@@ -1,6 +1,6 @@
 // What a call sets up before its first kernel that computes: the plan in the workspace, the rows of its rollouts
 // and the arrays that start at zero (SetupArgs), as device functions: in a launch of their own
-// (launch_setup) or by workgroups of the fused path's prepare_kernel.
+// (launch_setup), by workgroups of the fused path's prepare_kernel or by one of a launch of logits rows.
 // Every launch costs about 4.7 us however little it does; as separate launches the upload, the fills and the
 // row expansion were 6 of the 19 launches of a small fused call (two rollouts of 128 rows,
 // V = 4,096: 112 -> 105 us).  A plan that fits the argument block (up to about 90 rollouts) is read by

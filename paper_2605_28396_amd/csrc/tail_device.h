@@ -1,7 +1,7 @@
 // The reductions that end a call, as device functions of a 256-thread workgroup (ALIGN: with probe
 // gradients): per-rollout sums and losses, batch aggregates, rollout summaries.  Used by the launches of
 // reduce_kernels.hip and, in calls without probe gradients or summaries, by workgroups of
-// finalize_kernel: 224 rows, V = 4,096 60.4 -> 54.1 us per call, 256 rows, V = 151,936 772 -> 762.
+// logits_piece_grad_kernel and of finalize_kernel: 224 rows, V = 4,096 60.4 -> 54.1 us per call, 256 rows, V = 151,936 772 -> 762.
 #pragma once
 #include "device_utils.h"
 #include "plan_device.h"
@@ -23,6 +23,16 @@ __device__ __forceinline__ void block_sum256(double (&v)[K], double* sh /* [K][4
   __syncthreads();
 }
 
+// Sums that another workgroup of the same launch reads: past the L2 of the compute unit's die, which the
+// others do not see.  A fence instead writes back all that this L2 holds of the launch's other outputs (the tail of
+// two rollouts by itself 6.4 us with fences, 6.0 without).
+__device__ __forceinline__ void store_shared(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_shared(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Rollout i: sums of KL_t and ||g_t||^2 over the window and the rollout, the window losses, and
 // the cosines from the pooled sums and the norm sums.
 template <bool ALIGN>
@@ -32,14 +42,21 @@ __device__ __forceinline__ void rollout_body(const BatchArgs& a, int i, double* 
   const int64_t hi = a.probe ? len : ni;
   const int64_t r0 = a.pl.comp_off[i];
   double v[4] = {0.0, 0.0, 0.0, 0.0};   // kl prefix, kl full, norm prefix, norm full
+  uint32_t flags = 0u;
 #pragma unroll 4
   for (int64_t j = threadIdx.x; j < hi; j += 256) {
-    const double k = a.klr[r0 + j];
+    float kl = a.klr[r0 + j];
+    if (a.status) {
+      if (__float_as_uint(kl) == kExcludedRow) { kl = 0.f; flags |= ADWIN_DEV_NONFINITE; }
+      else if (a.ids && (uint32_t)a.ids[a.pl.offsets[i] + j] >= (uint32_t)a.V) flags |= ADWIN_DEV_BAD_ID;
+    }
+    const double k = kl;
     const double s = a.rownorm ? (double)a.rownorm[r0 + j] : 0.0;
     v[1] += k;
     v[3] += s;
     if (j < ni) { v[0] += k; v[2] += s; }
   }
+  if (flags) atomicOr(a.status, flags);
   block_sum256<4>(v, sh);
   const bool align = ALIGN && a.probe && !a.zero_grad;
   double u[3] = {0.0, 0.0, 0.0};
@@ -56,10 +73,7 @@ __device__ __forceinline__ void rollout_body(const BatchArgs& a, int i, double* 
     block_sum256<3>(u, sh);
   }
   if (threadIdx.x == 0) {
-    a.seg[i * 4 + 0] = v[0];
-    a.seg[i * 4 + 1] = v[1];
-    a.seg[i * 4 + 2] = v[2];
-    a.seg[i * 4 + 3] = v[3];
+    for (int k = 0; k < 4; ++k) store_shared(a.seg + i * 4 + k, v[k]);
     if (a.loss_prefix) a.loss_prefix[i] = ni > 0 ? (float)(v[0] / (double)ni) : 0.f;
     if (a.loss_full) a.loss_full[i] = (a.probe && len > 0) ? (float)(v[1] / (double)len) : 0.f;
     double rp = 0.0, rf = 0.0, okp = 0.0, okf = 0.0;
@@ -91,14 +105,14 @@ __device__ __forceinline__ void batch_body(const BatchArgs& a, double* sh) {
   double mf[2] = {0.0, 0.0};            // macro field sum, count
   for (int i = threadIdx.x; i < B; i += 256) {
     const double ap = a.pl.alpha_p[i], af = a.pl.alpha_f[i];
-    w[0] += ap * a.seg[i * 4 + 0];
-    if (a.probe) w[1] += af * a.seg[i * 4 + 1];
+    w[0] += ap * load_shared(a.seg + i * 4 + 0);
+    if (a.probe) w[1] += af * load_shared(a.seg + i * 4 + 1);
     if (align) {
       w[2] += a.racc[i * 4 + 0] * a.racc[i * 4 + 1];
       w[3] += a.racc[i * 4 + 1];
       mf[0] += a.racc[i * 4 + 2] * a.racc[i * 4 + 3];
       mf[1] += a.racc[i * 4 + 3];
-      const double Sp = a.seg[i * 4 + 2], Sf = a.seg[i * 4 + 3];
+      const double Sp = load_shared(a.seg + i * 4 + 2), Sf = load_shared(a.seg + i * 4 + 3);
       f[0] += ap * af * Sp;
       f[1] += ap * ap * Sp;
       f[2] += af * af * Sf;
@@ -270,12 +284,14 @@ __device__ __forceinline__ void tail_body(const TailArgs& a, int block, double* 
                                           int* sh_first /* [4] */) {
   if (!SUMMARY || block < a.b.B) rollout_body<false>(a.b, block, sh);
   else summary_rollout_body(a.s, block - a.b.B, sh, sh_first);
-  __threadfence();                      // this workgroup's sums, before it counts itself
+  if (SUMMARY && a.with_summary) __threadfence();      // this workgroup's summaries, before it counts itself
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // its sums have arrived (store_shared)
   __syncthreads();
-  if (threadIdx.x == 0) sh_first[0] = atomicAdd(a.b.done, 1u) + 1u == (uint32_t)a.blocks;
+  if (threadIdx.x == 0)
+    sh_first[0] = __hip_atomic_fetch_add(a.b.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)a.blocks;
   __syncthreads();
   if (!sh_first[0]) return;
-  __threadfence();                      // the other workgroups' sums
+  if (SUMMARY && a.with_summary) __threadfence();      // the other workgroups' summaries
   batch_body<false>(a.b, sh);
   if (SUMMARY && a.with_summary) summary_batch_body(a.s);
 }

@@ -226,3 +226,43 @@ def test_automatic_route_with_diagnostics(B, V, n):  # noqa: F811
     for k in ("kl", "c", "t_entropy", "t_logp"):
         assert torch.allclose(auto[k], ref[k], rtol=2e-6, atol=1e-5), k
     assert torch.allclose(auto["dz"].float(), ref["dz"].float(), rtol=2 * Hp.BF16_ULP, atol=1e-6 * float(ref["dz"].float().abs().max()))
+
+
+@pytest.mark.parametrize("want", [BASE, BASE + DIAG, BASE + DIAG + ("t_first_reject", "t_logp_mean")])
+@pytest.mark.parametrize("V", [8, 5128, 20488, 40968, 81928, 400008])
+def test_launches_of_a_call_share_its_work(B, V, want):  # noqa: F811
+    """A plan that fits the launch of the rows is set up by it, and the tail of split rows (16 pieces at most,
+    and more) runs in the launch of their gradient; status bits are then reported by another launch than the one
+    that finds them.  The same call with rollouts of no rows behind it, whose plan does not fit, has the same
+    rows bit for bit, and a rollout's loss is the fp32 of the mean of its rows' KL in 64 bits."""
+    offsets, window = synth._offsets([6, 0, 20, 1]), np.array([4, 3, 17, 1], np.int32)
+    g = torch.Generator().manual_seed(V)
+    z = [torch.randn((27, V), generator=g).to(torch.bfloat16) for _ in range(2)]
+    base_ids = torch.randint(0, V, (27,), generator=g, dtype=torch.int32)
+    base_ids[[4, 24]] = -1                       # outside the windows: not reported
+    z[1][5, 0] = float("nan")
+    kw = dict(reduction=O.RED_SUM, want=want, topk=3 if "t_first_reject" in want else 0)
+    for bad_id, excluded in ((False, False), (True, False), (False, True), (True, True)):
+        zs, ids = z[0].clone(), base_ids.clone()
+        ids[9] = V if bad_id else ids[9]
+        zs[8, V - 1] = float("inf") if excluded else zs[8, V - 1]
+        runs = []
+        for extra in (0, 120):
+            off = np.concatenate([offsets, np.full(extra, offsets[-1])])
+            win = np.concatenate([window, np.zeros(extra, np.int32)]).astype(np.int32)
+            runs.append(_host(B.adwin_opd_from_logits(zs.cuda(), z[1].cuda(), ids.cuda(), off, win, **kw)))
+        a, b = runs
+        status = (B.ADWIN_DEV_BAD_ID if bad_id else 0) | (B.ADWIN_DEV_NONFINITE if excluded else 0)
+        assert int(a["status_dev"][0]) == int(b["status_dev"][0]) == status
+        for k in a:
+            x, y = a[k], b[k]
+            if k == "t_logp_mean":               # its last row is the batch's
+                x, y = np.concatenate([x[:-1], x[-1:]]), np.concatenate([y[:4], y[-1:]])
+            elif k in ("loss_prefix", "n_out", "t_first_reject"):
+                y = y[:4]
+            assert np.array_equal(x, y), k
+        for i in range(4):
+            kl = a["kl"][offsets[i]:offsets[i] + min(window[i], offsets[i + 1] - offsets[i])].astype(np.float64)
+            mean = kl.mean() if kl.size else 0.0
+            assert abs(a["loss_prefix"][i] - mean) <= 2.0 ** -23 * abs(mean)
+        assert excluded == (a["kl"][8] == 0.0) and bad_id == (a["c"][9] == 0.0)
