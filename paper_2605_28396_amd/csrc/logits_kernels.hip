@@ -890,17 +890,25 @@ static bool streaming_suits_diagnostics(int V, int64_t n_adm) {
 }
 
 // Pieces per row of a call of few rows of more than 81,920 logits; 0: not split.  A piece fits the
-// registers of a workgroup; a call of very few rows takes as many as give every compute unit one.  At
-// V = 151,936 the pieces cost 20 us and 0.24 us per row, the long-row kernel 47 us per round of 256
-// rows and 15 besides (all scale with V), so that pieces also serve a few rows more than one round.  us,
-// pieces / long-row: V = 151,936: 32 rows 28 / 54, 128 rows 52 / 61, 156 rows 59 / 62, 200 rows 72 / 65,
-// 257 rows 84 / 105, 352 rows 106 / 113, 400 rows 124 / 120; V = 102,400: 128 rows 45 / 48, 156 rows 51 / 48;
-// V = 81,928: 128 rows 42 / 44, 156 rows 47 / 44.  With diagnostics the second window is the streaming
-// kernel's on shorter rows, pieces / streaming: V = 136,000: 300 rows 90 / 87; V = 151,936: 352 rows 110 / 113.
+// registers of a workgroup; a call of very few rows takes as many as give every compute unit one.  The
+// pieces cost a time for every row, the long-row kernel one for every round of 256 rows, most of it in the
+// first rows of the round: pieces serve the first part of a round, up to the rows where the two draw level.
+// us, pieces / long-row: V = 82,000: 200 rows 37 / 42, 224 rows 42 / 42, 300 rows 51 / 67, 400 rows 64 / 69,
+// 448 rows 69 / 70; V = 122,880: 200 rows 48 / 51, 224 rows 54 / 53, 300 rows 68 / 85, 400 rows 85 / 89;
+// V = 151,936: 128 rows 41 / 57, 180 rows 55 / 58, 200 rows 60 / 59, 300 rows 80 / 103, 400 rows 111 / 113,
+// 448 rows 136 / 119; V = 164,000: 180 rows 59 / 65, 224 rows 69 / 67, 400 rows 125 / 130.  The long-row kernel
+// reads twice what it cannot hold: V = 180,000: 224 rows 72 / 76, 256 rows 80 / 79; V = 200,000: 224 rows
+// 79 / 89, 256 rows 88 / 94, 300 rows 105 / 174, 400 rows 160 / 183; V = 300,000: 256 rows 155 / 220.
+// With diagnostics against the better of the streaming and the long-row kernel: V = 102,400: 128 rows 44 / 48,
+// 156 rows 50 / 49; V = 122,880: 156 rows 52 / 55, 180 rows 58 / 57, 300 rows 81 / 79; V = 151,936: 156 rows 59 / 66,
+// 180 rows 67 / 68, 200 rows 73 / 69, 300 rows 94 / 95, 352 rows 106 / 111, 400 rows 124 / 120; V = 200,000:
+// 224 rows 92 / 93, 256 rows 102 / 108, 300 rows 119 / 140, 400 rows 172 / 178.
 static int row_splits(int V, int64_t n_adm, bool diag, int64_t room) {
   if (n_adm <= 0 || V <= short_row_limit(1024)) return 0;
-  const bool few = n_adm <= (V < 122880 ? 140 : 156), one_round_more = n_adm > 256 && n_adm <= 352;
-  if (!few && !(one_round_more && (!diag || V > 144000))) return 0;
+  const int64_t round = diag ? (V < 122880 ? 140 : 165) : V < 136000 || V > 172000 ? 210 : 185;
+  const int64_t second = diag && V <= 190000 ? (V > 144000 ? 352 : 0) : 400;
+  const bool rereads = V > 190000;
+  if (n_adm > round && !(n_adm <= second && (n_adm > 256 || rereads))) return 0;
   int splits = (V + short_row_limit(256) - 1) / short_row_limit(256);
   const int64_t fill = 256 / n_adm < 16 ? 256 / n_adm : 16;
   if (splits < fill) splits = (int)fill;

@@ -266,3 +266,21 @@ def test_launches_of_a_call_share_its_work(B, V, want):  # noqa: F811
             mean = kl.mean() if kl.size else 0.0
             assert abs(a["loss_prefix"][i] - mean) <= 2.0 ** -23 * abs(mean)
         assert excluded == (a["kl"][8] == 0.0) and bad_id == (a["c"][9] == 0.0)
+
+
+@pytest.mark.parametrize("V,n_adm", [(81928, 210), (81928, 211), (81928, 400), (136008, 185), (136008, 186), (172008, 210),
+                                     (190008, 256), (190008, 400), (190008, 401)])
+def test_lines_of_split_rows(B, V, n_adm):  # noqa: F811
+    """Both sides of the lines between rows in pieces and whole ones, as in test_split_rows_match_whole_rows."""
+    z, ids = _long_rows(V, n_adm, V + n_adm)
+    off, win = np.array([0, n_adm]), np.array([n_adm], np.int32)
+    for want in (BASE, BASE + DIAG):
+        a, b = (_host(B.adwin_opd_from_logits(*z, ids, off, win, reduction=O.RED_SUM, scheme=s, want=want))
+                for s in (B.ADWIN_LOGITS_AUTO, B.ADWIN_LOGITS_STREAMING))
+        for k in a:
+            if a[k].dtype.kind == "i":
+                assert np.array_equal(a[k], b[k]), k
+            elif k == "dz":
+                assert np.all(np.abs(a[k] - b[k]) <= 2 * Hp.BF16_ULP * np.abs(b[k]) + 1e-6 * np.abs(b[k]).max())
+            else:
+                assert np.allclose(a[k], b[k], rtol=2e-5, atol=1e-5 * max(1.0, np.abs(b[k]).max())), k
