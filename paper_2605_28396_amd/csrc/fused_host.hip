@@ -586,6 +586,10 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
   b.klr = klr; b.rownorm = pooled ? rownorm : nullptr;     // only the alignment reads their sums
   b.loss_prefix = p->loss_prefix; b.loss_full = p->loss_full;
   b.seg = seg; b.up = pa.up; b.uf = pa.uf; b.racc = (double*)(ws + L.o_racc); b.done = done;
+  // in pp and pf, which lie together and were read for the last time by pool_kernel: per 256 columns (64 at least)
+  // 1 + K sums of three doubles against twice those columns of floats
+  static_assert((1 + ADWIN_MAX_CANDIDATES) * 3 * sizeof(double) <= 2 * 64 * sizeof(float), "micro fits");
+  b.micro = (double*)(ws + L.o_pp);
   b.rho_pooled = p->rho_pooled; b.rho_field = p->rho_field; b.batch = p->batch;
   b.n_out = p->n_out; b.n_adm_out = p->n_adm_out; b.n_adm = hp.n_adm;
   CandArgs ca{};

@@ -66,7 +66,9 @@ struct BatchArgs {
   // Not NULL: the rows' status bits are still to be reported, from klr (kExcludedRow) and the ids of
   // the rows [0, n_i) of every rollout (NULL: none); the word is zero, or holds other rollouts' bits.
   uint32_t* status; const int32_t* ids; int32_t V;
+  double* micro;        // [1 + K][batch_columns(H)][3] scratch of the probe's batch aggregates (micro_body)
 };
+inline __host__ __device__ int batch_columns(int H) { return (H + 255) / 256; }
 constexpr uint32_t kExcludedRow = 0x7fffffffu;   // a NaN; KL_t of every other row is finite
 // Candidate-window audit (Sec. 4.2): alignment of the shared prefix window L_k, for every
 // candidate k, with the full-rollout gradient, from the per-row gradients of one

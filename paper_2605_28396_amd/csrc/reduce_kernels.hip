@@ -158,10 +158,58 @@ __device__ __forceinline__ void cand_align_body(const CandArgs& a, int k, int i,
   }
 }
 
-// Candidate k: micro (after batch aggregation) and macro cosines.  The weights of up to kCandLds
-// rollouts are formed once (their divisions, repeated per column, were most of this kernel).
+// Columns [256 col, 256 col + 256) of the gradients aggregated over the batch, <p, f>, |p|^2 and |f|^2: the
+// batch aggregates are then sums over B and over these.  As one workgroup per slot they had all columns to
+// themselves, one group after the other, behind the launch of the rollouts instead of beside it: batch_kernel of
+// 30 rollouts with 7 candidates, H = 1536, 28.4 us (9 rollouts, H = 512: 9.8), now 7.0 and 6.1.  The weights
+// of up to kCandLds rollouts are formed once (their divisions, repeated per column, were most of the time).
 constexpr int kCandLds = 256;
-__device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double* sh, double* alpha_lds) {
+__device__ __forceinline__ void micro_body(const BatchArgs& b, const CandArgs& c, int slot, int col, double* sh,
+                                           double* alpha_lds /* [2 kCandLds] */) {
+  if (b.zero_grad) return;
+  const int B = b.B, h = col * 256 + threadIdx.x;
+  auto alpha_p = [&](int i) -> double {
+    if (slot == 0) return b.pl.alpha_p[i];
+    const int64_t len = b.pl.offsets[i + 1] - b.pl.offsets[i];
+    return cand_alpha_p(c, slot - 1, c.L[slot - 1] < len ? (int64_t)c.L[slot - 1] : len);
+  };
+  for (int i = threadIdx.x; i < B && i < kCandLds; i += 256) {
+    alpha_lds[i] = alpha_p(i);
+    alpha_lds[kCandLds + i] = b.pl.alpha_f[i];
+  }
+  __syncthreads();
+  double m[3] = {0.0, 0.0, 0.0};
+  if (h < b.H) {
+    const float* up = (slot == 0 ? b.up : c.uc + (int64_t)(slot - 1) * B * b.H) + h;
+    const float* uf = b.uf + h;
+    double sp = 0.0, sf = 0.0;
+    for (int i0 = 0; i0 < B; i0 += kBatchStep) {
+      float p[kBatchStep], f[kBatchStep];
+#pragma unroll
+      for (int q = 0; q < kBatchStep; ++q) {
+        const int64_t i = i0 + q < B ? i0 + q : B - 1;
+        p[q] = up[i * b.H];
+        f[q] = uf[i * b.H];
+      }
+#pragma unroll
+      for (int q = 0; q < kBatchStep; ++q)
+        if (i0 + q < B) {
+          const int i = i0 + q;
+          sp += (i < kCandLds ? alpha_lds[i] : alpha_p(i)) * (double)p[q];
+          sf += (i < kCandLds ? alpha_lds[kCandLds + i] : (double)b.pl.alpha_f[i]) * (double)f[q];
+        }
+    }
+    m[0] = sp * sf;
+    m[1] = sp * sp;
+    m[2] = sf * sf;
+  }
+  block_sum256<3>(m, sh);
+  if (threadIdx.x == 0)
+    for (int k = 0; k < 3; ++k) b.micro[((int64_t)slot * batch_columns(b.H) + col) * 3 + k] = m[k];
+}
+
+// Candidate k: micro (after batch aggregation) and macro cosines.
+__device__ __forceinline__ void cand_batch_body(const BatchArgs& b, const CandArgs& a, int k, double* sh) {
   const int B = a.B;
   double w[4] = {0.0, 0.0, 0.0, 0.0};   // macro pooled sum, count, macro field sum, count
   double f[3] = {0.0, 0.0, 0.0};        // field: dot, |p|^2, |f|^2
@@ -172,7 +220,6 @@ __device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double
   for (int i = threadIdx.x; i < B; i += 256) {
     const int64_t o = (int64_t)k * B + i;
     const double ap = alpha(i), af = a.pl.alpha_f[i];
-    if (i < kCandLds) alpha_lds[i] = ap;
     w[0] += a.cacc[o * 4 + 0] * a.cacc[o * 4 + 1];
     w[1] += a.cacc[o * 4 + 1];
     w[2] += a.cacc[o * 4 + 2] * a.cacc[o * 4 + 3];
@@ -181,32 +228,11 @@ __device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double
     f[1] += ap * ap * a.cS[o];
     f[2] += af * af * a.seg[i * 4 + 3];
   }
-  block_sum256<4>(w, sh);               // its barriers also publish alpha_lds
+  block_sum256<4>(w, sh);
   block_sum256<3>(f, sh);
   double m[3] = {0.0, 0.0, 0.0};
   if (!a.zero_grad) {
-    for (int h = threadIdx.x; h < a.H; h += 256) {
-      double sp = 0.0, sf = 0.0;
-      for (int i0 = 0; i0 < B; i0 += kBatchStep) {
-        float p[kBatchStep], f[kBatchStep];
-#pragma unroll
-        for (int q = 0; q < kBatchStep; ++q) {
-          const int i = i0 + q < B ? i0 + q : B - 1;
-          p[q] = a.uc[((int64_t)k * B + i) * a.H + h];
-          f[q] = a.uf[(int64_t)i * a.H + h];
-        }
-#pragma unroll
-        for (int q = 0; q < kBatchStep; ++q)
-          if (i0 + q < B) {
-            const int i = i0 + q;
-            sp += (i < kCandLds ? alpha_lds[i] : alpha(i)) * (double)p[q];
-            sf += (double)a.pl.alpha_f[i] * (double)f[q];
-          }
-      }
-      m[0] += sp * sf;
-      m[1] += sp * sp;
-      m[2] += sf * sf;
-    }
+    micro_sums(b, 1 + k, m);
   }
   block_sum256<3>(m, sh);
   if (threadIdx.x == 0 && a.batch) {
@@ -224,9 +250,9 @@ __device__ __forceinline__ void cand_batch_body(const CandArgs& a, int k, double
 // ---------------------------------------------------------------------------------------
 // The end of a call in one launch (two with probe gradients), or in that of finalize_kernel
 // (tail_device.h).  Workgroups [0, B): rollouts; the next B (with_summary): their summaries; the next
-// K B: candidates.  Each of these used to be a launch of about 4.7 us, and so were the batch
-// aggregates, which need all of them: without probe gradients (`fold`) the workgroup that finishes last
-// takes them; with them each aggregate runs over all H columns, and a launch of 1 + K workgroups
+// K B: candidates; then, with probe gradients, the columns of the batch (micro_body).  Each of these used to be a
+// launch of about 4.7 us, and so were the batch aggregates, which need all of them: without probe gradients
+// (`fold`) the workgroup that finishes last takes them; with them a launch of 1 + K workgroups
 // (batch_kernel) takes them side by side.  Logits of 24
 // rollouts with diagnostics: 425 -> 412 us; one rollout of 37 rows 52.6 -> 49.5 us; the probe
 // audit of 9 rollouts with 7 candidates, with the pooling above: 397 -> 333 us.
@@ -235,20 +261,23 @@ __global__ __launch_bounds__(256) void tail_kernel(TailArgs a) {
   __shared__ double sh[4 * (ADWIN_MAX_CANDIDATES + 1)];
   __shared__ int sh_first[4];
   if (a.fold) return tail_body<true>(a, blockIdx.x, sh, sh_first);
-  const int B = a.b.B, role = blockIdx.x / B, i = blockIdx.x % B;
-  if (role == 0) rollout_body<true>(a.b, i, sh);
+  const int B = a.b.B, role = blockIdx.x / B, i = blockIdx.x % B, aligned = B * (1 + a.with_summary + a.c.K);
+  if ((int)blockIdx.x >= aligned) {
+    __shared__ double alpha[2 * kCandLds];
+    const int cols = batch_columns(a.b.H), m = (int)blockIdx.x - aligned;
+    micro_body(a.b, a.c, m / cols, m % cols, sh, alpha);
+  } else if (role == 0) rollout_body<true>(a.b, i, sh);
   else if (role == 1 && a.with_summary) summary_rollout_body(a.s, i, sh, sh_first);
   else cand_align_body(a.c, role - 1 - a.with_summary, i, sh);
 }
 
 __global__ __launch_bounds__(256) void batch_kernel(TailArgs a) {
   __shared__ double sh[16];
-  __shared__ double alpha[kCandLds];
   if (blockIdx.x == 0) {
     batch_body<true>(a.b, sh);
     if (a.with_summary) summary_batch_body(a.s);
   } else {
-    cand_batch_body(a.c, blockIdx.x - 1, sh, alpha);
+    cand_batch_body(a.b, a.c, blockIdx.x - 1, sh);
   }
 }
 
@@ -321,7 +350,7 @@ hipError_t launch_tail(const BatchArgs& b, const SummaryArgs& s, const CandArgs&
   }
   pool_kernel<<<dim3((1 + K) * B, cols), 256, 0, st>>>(*pooled, c);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  tail_kernel<<<B * (1 + (unsigned)a.with_summary + K), 256, 0, st>>>(a);
+  tail_kernel<<<B * (1 + (unsigned)a.with_summary + K) + (1 + K) * cols, 256, 0, st>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   batch_kernel<<<1 + K, 256, 0, st>>>(a);
   return hipGetLastError();

@@ -90,11 +90,21 @@ __device__ __forceinline__ void rollout_body(const BatchArgs& a, int i, double* 
   }
 }
 
-// One workgroup: batch objectives, micro (after aggregation) and macro (mean of
-// per-rollout) alignment, integer outputs.  The sums over the rollouts run in index order, their
-// terms loaded kBatchStep rollouts ahead: one round trip per rollout made the aggregates of 200
-// rollouts at H = 1536 635 us.
+// Rollouts whose terms of a sum in index order are loaded together: one round trip per rollout made the
+// aggregates of 200 rollouts at H = 1536 635 us.
 constexpr int kBatchStep = 16;
+
+// The three sums over columns that micro_body leaves per 256 of them.  Slot 0: the call's windows, slot 1 + k: candidate k.
+__device__ __forceinline__ void micro_sums(const BatchArgs& a, int slot, double (&m)[3]) {
+  const int cols = batch_columns(a.H);
+  for (int q = threadIdx.x; q < cols; q += 256) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m[k] += a.micro[((int64_t)slot * cols + q) * 3 + k];
+  }
+}
+
+// One workgroup: batch objectives, micro (after aggregation) and macro (mean of
+// per-rollout) alignment, integer outputs.  The sums over the rollouts run in index order.
 template <bool ALIGN>
 __device__ __forceinline__ void batch_body(const BatchArgs& a, double* sh) {
   const int B = a.B;
@@ -124,27 +134,7 @@ __device__ __forceinline__ void batch_body(const BatchArgs& a, double* sh) {
   if (align) {
     block_sum256<4>(f, sh);
     block_sum256<2>(mf, sh);
-    for (int h = threadIdx.x; h < a.H; h += 256) {
-      double sp = 0.0, sf = 0.0;
-      for (int i0 = 0; i0 < B; i0 += kBatchStep) {
-        float p[kBatchStep], f[kBatchStep];
-#pragma unroll
-        for (int q = 0; q < kBatchStep; ++q) {
-          const int i = i0 + q < B ? i0 + q : B - 1;
-          p[q] = a.up[(size_t)i * a.H + h];
-          f[q] = a.uf[(size_t)i * a.H + h];
-        }
-#pragma unroll
-        for (int q = 0; q < kBatchStep; ++q)
-          if (i0 + q < B) {
-            sp += (double)a.pl.alpha_p[i0 + q] * (double)p[q];
-            sf += (double)a.pl.alpha_f[i0 + q] * (double)f[q];
-          }
-      }
-      m[0] += sp * sf;
-      m[1] += sp * sp;
-      m[2] += sf * sf;
-    }
+    micro_sums(a, 0, m);
     block_sum256<3>(m, sh);
   }
   if (a.n_out)

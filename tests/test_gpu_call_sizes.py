@@ -244,3 +244,22 @@ def test_rows_of_many_rollouts(B, nb):  # noqa: F811
                           reduction=O.RED_SEQ_MEAN, mode=mode)
         got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32)
         _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+
+
+@pytest.mark.parametrize("H_s,nb,cands", [(64, 1, list(range(1, 17))), (320, 16, [2]), (576, 17, [1, 3, 9]), (320, 270, [2, 4])])
+def test_batch_aggregates_by_columns(B, H_s, nb, cands):  # noqa: F811
+    """The aggregates over the batch are taken 256 columns at a time (the last 64 alone here, and 17 sums of the
+    smallest H in the scratch that they share), 16 rollouts at a time, their weights staged for 256 of them."""
+    g = np.random.default_rng(nb)
+    lens = g.integers(1, 7, size=nb, endpoint=True)
+    win = np.minimum(g.integers(1, 5, size=nb, endpoint=True), lens).astype(np.int32)
+    w = synth.Workload(f"columns_{nb}", 4104, H_s, 128, synth._offsets(lens), win, synth.MODE_PREFIX_AND_FULL)
+    p = synth.hidden_problem(w)
+    f = Hp.oracle_inputs(p)
+    ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                      reduction=O.RED_SEQ_MEAN, mode=w.mode)
+    aud = O.audit_candidates(ref["g"], w.offsets, cands, O.RED_SEQ_MEAN)
+    got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, candidates=cands)
+    _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+    want = np.stack([aud["micro"], aud["micro_field"], aud["macro"], aud["macro_field"]], axis=1)
+    assert np.all(np.abs(got["cand_batch"] - want) <= Hp.RHO_ABS), (got["cand_batch"], want)
