@@ -183,6 +183,7 @@ struct LogitPassArgs {
   bool narrow;                 // one token tile, of which only the first 128 rows are wanted (see DmaTile)
   int strips;                  // vocabulary strips
   Shares strip_tiles;          // vocabulary tiles of each (set by launch_logit_pass)
+  int long_first;              // the longer strips' workgroups come first (sweep_strips)
   int tg;                      // token tiles per workgroup group (share W tiles in one L2)
   int vt_total;                // vocabulary tiles (of 128)
   // pass 1 out: [5][strips][n_pad]

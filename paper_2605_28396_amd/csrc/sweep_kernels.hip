@@ -652,7 +652,16 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int strip, tt_local;
-  strip_and_tile(xcd_contiguous_id(blockIdx.x, gridDim.x), a.tg, a.strips, a.n_tiles, &strip, &tt_local);
+  {
+    int block = blockIdx.x, blocks = gridDim.x, strips = a.strips, first = 0;
+    if (a.long_first) {                       // the longer strips of all token tiles, then the others
+      const int n = a.strip_tiles.longer * a.n_tiles;
+      if (block < n) { blocks = n; strips = a.strip_tiles.longer; }
+      else { block -= n; blocks -= n; first = a.strip_tiles.longer; strips -= first; }
+    }
+    strip_and_tile(xcd_contiguous_id(block, blocks), a.tg, strips, a.n_tiles, &strip, &tt_local);
+    strip += first;
+  }
   const int tt = a.tile0 + tt_local;
   const int64_t row_tile = (int64_t)tt * kTileTokens;
   const int vt_begin = a.strip_tiles.first(strip), vt_end = a.strip_tiles.first(strip + 1);

@@ -263,3 +263,18 @@ def test_batch_aggregates_by_columns(B, H_s, nb, cands):  # noqa: F811
     _check_fused(w, got, ref, O.RED_SEQ_MEAN)
     want = np.stack([aud["micro"], aud["micro_field"], aud["macro"], aud["macro_field"]], axis=1)
     assert np.all(np.abs(got["cand_batch"] - want) <= Hp.RHO_ABS), (got["cand_batch"], want)
+
+
+@pytest.mark.parametrize("V,rows", [(11912, 3300), (16600, 5100), (16600, 3000)])
+def test_longer_strips_first(B, monkeypatch, V, rows):  # noqa: F811
+    """13 and 20 token tiles whose strips have two lengths and come in two classes, the longer ones of all token
+    tiles first, and 12 whose do not: against the oracle, and no further from 64 bits than 32 strips."""
+    w = synth.Workload(f"strip_order_{V}_{rows}", V, 128, 192, synth._offsets([rows - 40, 40]),
+                       np.array([rows - 40, 33], np.int32), synth.MODE_PREFIX_ONLY)
+    p = synth.hidden_problem(w)
+    f = Hp.oracle_inputs(p)
+    ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                      reduction=O.RED_SEQ_MEAN, mode=w.mode)
+    got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32)
+    _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+    test_strips_cost_no_accuracy(B, monkeypatch, V, 128, 192, rows)
