@@ -56,8 +56,13 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   // in a call of few rows nothing else covers the round trips (118 rows of V = 4,096: 44.1 -> 42.6 us per
   // call; large calls, where waves are many: the same within 0.3 %)
   constexpr int kTogether = TR ? 2 : 4;
+  // Rows that do not exist, of a call of few rows most of its only tile, are left as they are: what the GEMM makes
+  // of them nobody reads.  (The transposed operand is contracted over the rows, and has zeros there.)
+  // 128 rows of V = 151,936: combine pass 35 -> 19 us; 16 rows 35 -> 7.
+  const int64_t left = TR ? kTileTokens : a.n_rows - rbase;
 #pragma unroll
   for (int i0 = 0; i0 < 8; i0 += kTogether) {
+    if (!TR && i0 * 32 >= left) break;
     uint4 xs[kTogether], ys[kTogether];
     float izs[kTogether], ms[kTogether], m0s[kTogether];
     int ids[kTogether];
@@ -65,6 +70,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
     for (int j = 0; j < kTogether; ++j) {
       const int q = (i0 + j) * 256 + threadIdx.x;
       const int64_t r = rbase + (q >> 3);
+      if (!TR && (i0 + j) * 32 >= left) continue;
       ys[j] = p2[q];
       izs[j] = a.inv_z[r];
       if (SAMPLED) {
@@ -81,6 +87,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
     for (int j = 0; j < kTogether; ++j) {
       const int i = i0 + j, q = i * 256 + threadIdx.x;
       const int64_t r = rbase + (q >> 3);
+      if (!TR && i * 32 >= left) continue;
       const float iz = izs[j];
       const uint4 y = ys[j];
       float d[8];
@@ -345,9 +352,14 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
   // wave-load d of a block covers its bytes [4096 d + 1024 wave, + 1024): lane l moves the
   // 16 bytes at offset 16 l of that KiB to the same place of the LDS stage
   uint32_t voffd[8];
+  const int64_t out_row0 = rt < a.half_tiles ? a.slab_row0 + (int64_t)rt * kGradTile
+                                             : a.half_off + a.slab_row0 + (int64_t)(rt - a.half_tiles) * kGradTile;
+  const int64_t rows_left = a.out_rows - out_row0;       // >= 1
 #pragma unroll
   for (int d = 0; d < 8; ++d) {
-    voffd[d] = (uint32_t)lane * 16u + (uint32_t)wave * 1024u + (uint32_t)d * 4096u;
+    // rows that do not exist re-read the first eight (16 rows of V = 151,936, H = 3584: 234 -> 224 us)
+    const int kib = (4 * d + wave) * 8 < rows_left ? 4 * d + wave : 0;
+    voffd[d] = (uint32_t)lane * 16u + (uint32_t)kib * 1024u;
     asm volatile("" : "+v"(voffd[d]));   // kept in registers, not recomputed at every load
   }
   const char* sA = (const char*)a.slab + ((int64_t)rt * a.nk_total + k_begin) * kImgBytes;
@@ -449,11 +461,8 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
   // workgroup.  us per call: V = 4,096, H = 256 + 384, 224 rows 75.5 -> 63.3; V = 32,776, H = 1024 + 1024,
   // 1,000 rows with the head gradient 506 -> 466; V = 11,912, H = 512 + 640, 3,139 rows 294 -> 280;
   // 8,192 rows of V = 151,936 with the head gradient (19 tiles per compute unit) 23,200 -> 23,028.
-  const int64_t out_row0 = rt < a.half_tiles ? a.slab_row0 + (int64_t)rt * kGradTile
-                                             : a.half_off + a.slab_row0 + (int64_t)(rt - a.half_tiles) * kGradTile;
   char* g = (char*)(a.g + ((int64_t)split * a.g_rows + out_row0) * a.H + ht * kGradTile);
   const uint32_t ldg = (uint32_t)a.H * 4u;
-  const int64_t rows_left = a.out_rows - out_row0;
   const int rows = (int)(rows_left < kGradTile ? rows_left : kGradTile) - wm * 128, cols = a.H - ht * kGradTile - wn * 128;
   const uint32_t lane_off = (uint32_t)(wm * 128 + 4 * (lane >> 5)) * ldg + (uint32_t)(wn * 128 + (lane & 31)) * 4u;
   const __amdgpu_buffer_rsrc_t rs =

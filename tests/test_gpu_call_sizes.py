@@ -278,3 +278,18 @@ def test_longer_strips_first(B, monkeypatch, V, rows):  # noqa: F811
     got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32)
     _check_fused(w, got, ref, O.RED_SEQ_MEAN)
     test_strips_cost_no_accuracy(B, monkeypatch, V, 128, 192, rows)
+
+
+@pytest.mark.parametrize("estimator", [O.EST_EXPECTED, O.EST_SAMPLED])
+@pytest.mark.parametrize("rows", [1, 8, 31, 33, 127, 129, 250, 257, 300])
+def test_rows_that_do_not_exist(B, rows, estimator):  # noqa: F811
+    """The rows that fill up the last token tile are neither combined nor loaded nor stored: what the workspace
+    held there (NaN) reaches no output."""
+    w, p, ref, _ = _staging_problem(rows, estimator)
+    d = {k: v.cuda() for k, v in p.items()}
+    call = B.FusedCall(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window, mode=w.mode,
+                       reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator)
+    call.workspace.fill_(255)
+    assert call.run() == B.ADWIN_OK
+    torch.cuda.synchronize()
+    _check_fused(w, {k: v.cpu().numpy() for k, v in call.out.items()}, ref, O.RED_SEQ_MEAN)
