@@ -278,7 +278,7 @@ def main() -> int:
     roofline = {"bound": "mfma", "kernel": "logit_pass_dma_kernel", "achieved": ach,
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_BF16_TFLOPS,
                 "traffic": _measured_traffic(f"fused_{w.name}_hbm_counters.txt",
-                                             "adwin::logit_pass_dma_kernel<2,false>"),
+                                             "adwin::logit_pass_dma_kernel<2,false,2>"),
                 "traffic_source": f"profiles/fused_{w.name}_hbm_counters.txt (rocprofv3 --pmc, separate run)",
                 "launch_ms": launch_ms, "launches_per_call": launches,
                 "alg_flops_per_launch": f_stats}
