@@ -1235,21 +1235,41 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_inline_kernel(PrepareArg
   prepare_body<FINE, true>(a, &setup, &blob, lds);
 }
 
+// ROWS rows to a workgroup, whose threads take every 256 / ROWS-th strip of one row each.  Bound by round trips: 16 rows read
+// 64 bytes of a plane together, where a wave to a row read 4 bytes of 64 lines, and the strips of a thread are
+// loaded four at a time, so that up to kMergeStrips take one trip.  3,139 rows of 38 strips 7.4 -> 5.0 us (the
+// call, V = 11,912, 257.8 -> 255.9).  More strips belong to a call of one token tile, whose 256 rows are too few
+// for that (238 strips: 16 rows 11.6 us, four rows 9).
+constexpr int kMergeStrips = 64;
+template <int ROWS>
 __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   const MergeArgs& a = b.m;
-  const int lane = threadIdx.x & 63;
-  const int64_t r = b.row0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= b.row0 + b.rows) return;
+  __shared__ float sums[4][5][ROWS];
+  const int row = threadIdx.x % ROWS, wave = threadIdx.x >> 6;
+  const int64_t r = b.row0 + (int64_t)blockIdx.x * ROWS + row;
   const int64_t plane = (int64_t)a.strips * a.n_pad;
   const float ref_s = b.ref.of(0, r), ref_t = b.ref.of(1, r);
-  float Zs = 0.f, A = 0.f, Zt = 0.f, Bt = 0.f, cnt = 0.f;
-  for (int s = lane; s < a.strips; s += 64) {
+  const int planes = a.diag ? 5 : 3;
+  float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};     // Z_s, A, Z_t, B_t, count
+#pragma unroll 4
+  for (int s = threadIdx.x / ROWS; s < a.strips; s += 256 / ROWS) {
     const float* p = a.part + (int64_t)s * a.n_pad + r;
-    Zs += p[0]; A += p[plane]; Zt += p[2 * plane];
-    if (a.diag) { Bt += p[3 * plane]; cnt += p[4 * plane]; }
+    v[0] += p[0]; v[1] += p[plane]; v[2] += p[2 * plane];
+    if (a.diag) { v[3] += p[3 * plane]; v[4] += p[4 * plane]; }
   }
-  Zs = wave_sum(Zs); A = wave_sum(A); Zt = wave_sum(Zt);
-  if (a.diag) { Bt = wave_sum(Bt); cnt = wave_sum(cnt); }
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    if (k >= planes) break;
+#pragma unroll
+    for (int o = ROWS; o < 64; o <<= 1) v[k] += __shfl_xor(v[k], o, 64);
+    if ((threadIdx.x & 63) < ROWS) sums[wave][k][row] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x >= ROWS) return;
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+    if (k < planes) v[k] = (sums[0][k][row] + sums[1][k][row]) + (sums[2][k][row] + sums[3][k][row]);
+  const float Zs = v[0], A = v[1], Zt = v[2], Bt = v[3], cnt = v[4];
   const float lse_s = ref_s + logf(Zs), lse_t = ref_t + logf(Zt);
   const float mu = A / Zs;                  // E_{p_s}[z_s - z_t]
   float kl = kl_from_sums(mu, ref_s - ref_t, Zs, Zt);
@@ -1264,12 +1284,10 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   // must not reach the lists of heavy entries
   const bool dead = bad || r >= a.n_rows;
   if (dead) { kl = 0.f; ent = 0.f; }
-  if (lane == 0) {
-    b.mu_out[r] = dead ? 0.f : mu;
-    b.inv_z[r] = dead ? 0.f : iz;
-    a.klr[r] = kl;
-    a.lse_s[r] = dead ? 0.f : lse_s;
-  }
+  b.mu_out[r] = dead ? 0.f : mu;
+  b.inv_z[r] = dead ? 0.f : iz;
+  a.klr[r] = kl;
+  a.lse_s[r] = dead ? 0.f : lse_s;
   if (r >= a.n_rows) return;
   const int64_t t = a.row_idx[r];
   float c = 0.f, logp_t = 0.f;
@@ -1285,15 +1303,13 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
       flag |= ADWIN_DEV_BAD_ID;
     }
   }
-  if (lane == 0) {
-    if (flag && a.status) atomicOr(a.status, flag);
-    if (a.kl) a.kl[t] = kl;
-    if (a.c) a.c[t] = c;
-    if (a.t_logp) a.t_logp[t] = logp_t;
-    if (a.t_entropy) a.t_entropy[t] = ent;
-    if (a.t_rank) a.t_rank[t] = have_y ? (int32_t)cnt + 1 : 0;
-    if (a.cr) a.cr[r] = c;
-  }
+  if (flag && a.status) atomicOr(a.status, flag);
+  if (a.kl) a.kl[t] = kl;
+  if (a.c) a.c[t] = c;
+  if (a.t_logp) a.t_logp[t] = logp_t;
+  if (a.t_entropy) a.t_entropy[t] = ent;
+  if (a.t_rank) a.t_rank[t] = have_y ? (int32_t)cnt + 1 : 0;
+  if (a.cr) a.cr[r] = c;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1426,7 +1442,9 @@ hipError_t launch_merge_stats(const MergeArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_merge_single(const MergeSingleArgs& a, hipStream_t st) {
-  merge_single_kernel<<<(unsigned)((a.rows + 3) / 4), 256, 0, st>>>(a);
+  // slabs are whole token tiles
+  if (a.m.strips <= kMergeStrips) merge_single_kernel<16><<<(unsigned)(a.rows / 16), 256, 0, st>>>(a);
+  else merge_single_kernel<4><<<(unsigned)(a.rows / 4), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -293,3 +293,17 @@ def test_rows_that_do_not_exist(B, rows, estimator):  # noqa: F811
     assert call.run() == B.ADWIN_OK
     torch.cuda.synchronize()
     _check_fused(w, {k: v.cpu().numpy() for k, v in call.out.items()}, ref, O.RED_SEQ_MEAN)
+
+
+@pytest.mark.parametrize("V,rows", [(8192, 200), (8200, 200), (8200, 16), (2064, 300)])
+def test_merge_of_few_and_many_strips(B, V, rows):  # noqa: F811
+    """64 strips and 65, on either side of the line between 16 rows to a workgroup of the merge and four, and 17, one
+    more than its groups of threads."""
+    w = synth.Workload(f"merge_{V}_{rows}", V, 128, 192, synth._offsets([rows - 3, 3]), np.array([rows - 3, 2], np.int32),
+                       synth.MODE_PREFIX_ONLY)
+    p = synth.hidden_problem(w)
+    f = Hp.oracle_inputs(p)
+    ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
+                      reduction=O.RED_SEQ_MEAN, mode=w.mode)
+    got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32)
+    _check_fused(w, got, ref, O.RED_SEQ_MEAN)
