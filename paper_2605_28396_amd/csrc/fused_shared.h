@@ -24,13 +24,26 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nb) {
   return xcd * base + (xcd < rem ? xcd : rem) + loc;
 }
 
-// `total` things in `parts` contiguous shares that differ by at most one: the first of share i.  Quotient
-// and remainder are taken on the host: on the device the division, with 64-bit operands, was 100
-// instructions in front of the first load of every workgroup.
+// `total` things in `parts` contiguous shares: share i begins at floor(i total / parts), so that the longer ones,
+// of one more, are spread evenly.  Quotient, remainder and the factor of the one that is left are taken
+// on the host: on the device the division, with 64-bit operands, was 100 instructions in front of the first load of
+// every workgroup.  The boundaries enter the results (the running means of a strip, the order of the sums).
+// With per = ceil(2^32 / parts) the product's upper half is the quotient while i longer (per parts - 2^32) < 2^32,
+// and that is below parts^3.
+constexpr int kMaxShares = 1024;
 struct Shares {
   int each, longer;                // longer shares hold one more
-  void split(int total, int parts) { each = total / parts; longer = total % parts; }
-  __device__ __forceinline__ int first(int i) const { return i * each + (i < longer ? i : longer); }
+  uint32_t per;
+  void split(int total, int parts) {
+    each = total / parts;
+    longer = total % parts;
+    per = (uint32_t)(((1ull << 32) + parts - 1) / parts);       // parts = 1: not used, longer is 0
+  }
+  __host__ __device__ __forceinline__ int first(int i) const {
+    return i * each + (int)(((uint64_t)(uint32_t)(i * longer) * per) >> 32);
+  }
+  // ... the longer ones first
+  __device__ __forceinline__ int first_by_length(int i) const { return i * each + (i < longer ? i : longer); }
 };
 
 // Workgroup `vid` of a logit pass -> (strip, token tile): groups of `tg` token tiles, inside a
@@ -183,7 +196,7 @@ struct LogitPassArgs {
   bool narrow;                 // one token tile, of which only the first 128 rows are wanted (see DmaTile)
   int strips;                  // vocabulary strips
   Shares strip_tiles;          // vocabulary tiles of each (set by launch_logit_pass)
-  int long_first;              // the longer strips' workgroups come first (sweep_strips)
+  int long_first;              // the longer strips come first, and so do their workgroups (sweep_strips)
   int tg;                      // token tiles per workgroup group (share W tiles in one L2)
   int vt_total;                // vocabulary tiles (of 128)
   // pass 1 out: [5][strips][n_pad]

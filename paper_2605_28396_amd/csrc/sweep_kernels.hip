@@ -664,7 +664,8 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   }
   const int tt = a.tile0 + tt_local;
   const int64_t row_tile = (int64_t)tt * kTileTokens;
-  const int vt_begin = a.strip_tiles.first(strip), vt_end = a.strip_tiles.first(strip + 1);
+  const int vt_begin = a.long_first ? a.strip_tiles.first_by_length(strip) : a.strip_tiles.first(strip);
+  const int vt_end = a.long_first ? a.strip_tiles.first_by_length(strip + 1) : a.strip_tiles.first(strip + 1);
   if (vt_begin >= vt_end) return;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
