@@ -1236,14 +1236,19 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_inline_kernel(PrepareArg
   prepare_body<FINE, true>(a, &setup, &blob, lds);
 }
 
-// ROWS rows to a workgroup, whose threads take every 256 / ROWS-th strip of one row each.  Bound by round trips: 16 rows read
-// 64 bytes of a plane together, where a wave to a row read 4 bytes of 64 lines, and the strips of a thread are
-// loaded four at a time, so that up to kMergeStrips take one trip.  3,139 rows of 38 strips 7.4 -> 5.0 us (the
-// call, V = 11,912, 257.8 -> 255.9).  More strips belong to a call of one token tile, whose 256 rows are too few
+// ROWS rows to a workgroup.  The strips of a row are added in the order of 64 lanes, whatever ROWS is: lane s takes
+// the strips s, s + 64, ...; then the lanes 32 apart are added, 16 apart, and so on.  A thread holds kLanes of these
+// lanes, kStep apart, its wave does the next halvings and the four waves leave the last two.
+// Bound by round trips: 16 rows read 64 bytes of a plane together, where a wave to a row read 4 bytes of 64 lines, and the
+// strips of a thread are loaded together, so that up to kMergeStrips take one trip.  3,139 rows of 38 strips 7.4 -> 5.0 us
+// (the call, V = 11,912, 257.8 -> 255.9).  More strips belong to a call of one token tile, whose 256 rows are too few
 // for that (238 strips: 16 rows 11.6 us, four rows 9).
 constexpr int kMergeStrips = 64;
 template <int ROWS>
 __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
+  static_assert(ROWS == 4 || ROWS == 16, "a wave's part of 64 lanes");
+  constexpr int kStep = 256 / ROWS, kLanes = 64 / kStep, kGroupBits = ROWS == 16 ? 2 : 4;     // kStep = 4 << kGroupBits
+  constexpr int kTogether = ROWS == 16 ? 1 : 4;       // with kLanes: four strips
   const MergeArgs& a = b.m;
   __shared__ float sums[4][5][ROWS];
   const int row = threadIdx.x % ROWS, wave = threadIdx.x >> 6;
@@ -1251,15 +1256,30 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   const int64_t plane = (int64_t)a.strips * a.n_pad;
   const float ref_s = b.ref.of(0, r), ref_t = b.ref.of(1, r);
   const int planes = a.diag ? 5 : 3;
-  float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};     // Z_s, A, Z_t, B_t, count
-#pragma unroll 4
-  for (int s = threadIdx.x / ROWS; s < a.strips; s += 256 / ROWS) {
-    const float* p = a.part + (int64_t)s * a.n_pad + r;
-    v[0] += p[0]; v[1] += p[plane]; v[2] += p[2 * plane];
-    if (a.diag) { v[3] += p[3 * plane]; v[4] += p[4 * plane]; }
+  // the thread's first lane: neighbouring groups of a wave hold those that are farthest apart (bits reversed)
+  const int first = wave + 4 * (int)(__brev((threadIdx.x & 63u) / ROWS) >> (32 - kGroupBits));
+  float x[kLanes][5];                         // Z_s, A, Z_t, B_t, count
+#pragma unroll
+  for (int j = 0; j < kLanes; ++j)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) x[j][k] = 0.f;
+#pragma unroll kTogether
+  for (int s0 = first; s0 < a.strips; s0 += 64) {
+#pragma unroll
+    for (int j = 0; j < kLanes; ++j) {
+      const int s = s0 + j * kStep;
+      if (s < a.strips) {
+        const float* p = a.part + (int64_t)s * a.n_pad + r;
+        x[j][0] += p[0]; x[j][1] += p[plane]; x[j][2] += p[2 * plane];
+        if (a.diag) { x[j][3] += p[3 * plane]; x[j][4] += p[4 * plane]; }
+      }
+    }
   }
+  float v[5];
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
+    v[k] = x[0][k];
+    if constexpr (kLanes == 4) v[k] = (x[0][k] + x[2][k]) + (x[1][k] + x[3][k]);
     if (k >= planes) break;
 #pragma unroll
     for (int o = ROWS; o < 64; o <<= 1) v[k] += __shfl_xor(v[k], o, 64);
@@ -1269,7 +1289,7 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   if (threadIdx.x >= ROWS) return;
 #pragma unroll
   for (int k = 0; k < 5; ++k)
-    if (k < planes) v[k] = (sums[0][k][row] + sums[1][k][row]) + (sums[2][k][row] + sums[3][k][row]);
+    v[k] = k < planes ? (sums[0][k][row] + sums[2][k][row]) + (sums[1][k][row] + sums[3][k][row]) : 0.f;
   const float Zs = v[0], A = v[1], Zt = v[2], Bt = v[3], cnt = v[4];
   const float lse_s = ref_s + logf(Zs), lse_t = ref_t + logf(Zt);
   const float mu = A / Zs;                  // E_{p_s}[z_s - z_t]

@@ -8,7 +8,7 @@ import torch
 
 from oracle import adwin_oracle as O
 from paper_2605_28396_amd import synth
-from tests import helpers as Hp
+from tests import helpers as Hp, host_program
 from tests.test_gpu_parity import (B, WANT_HEAD, _check_fused, _grad_l2, _run_fused,  # noqa: F401  (B is a fixture)
                                    _teacher_reference)
 
@@ -307,3 +307,9 @@ def test_merge_of_few_and_many_strips(B, V, rows):  # noqa: F811
                       reduction=O.RED_SEQ_MEAN, mode=w.mode)
     got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32)
     _check_fused(w, got, ref, O.RED_SEQ_MEAN)
+
+
+def test_merge_adds_in_the_order_of_64_lanes(tmp_path):
+    """The sums over a row's strips, 16 rows to a workgroup (up to 64 strips) and four, bit for bit."""
+    status, out = host_program.run(tmp_path, "merge_order_main", link=True)
+    assert status == 0 and out.endswith("ok\n"), (status, out)
