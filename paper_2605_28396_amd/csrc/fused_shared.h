@@ -172,14 +172,22 @@ struct References {
   int32_t* yid;             // [n_pad] its id; -1: none, or out of range
   int64_t n_pad;
   int parts;
+  // log2 e times the reference, rounded: the number that the sweep takes its exponentials against and that the merge
+  // adds back.  Its rounding (2^-18 at 32 nats) is part of the reference and must be the same in both, or KL_t
+  // errs by it: the product stays a product, whatever it is added to.
+  static __device__ __forceinline__ float scaled(float m) {
+    float s = m * kLog2e;
+    asm("" : "+v"(s));
+    return s;
+  }
   __device__ __forceinline__ float of(int head, int64_t r) const {
-    if (parts == 1) return max[head][r];
+    if (parts == 1) return scaled(max[head][r]);
     float v[kMaxRefParts];                  // loaded together
 #pragma unroll
     for (int k = 0; k < kMaxRefParts; ++k) v[k] = max[head][(k < parts ? k : 0) * n_pad + r];
 #pragma unroll
     for (int k = 1; k < kMaxRefParts; ++k) v[0] = fmaxf(v[0], v[k]);
-    return v[0];
+    return scaled(v[0]);
   }
 };
 

@@ -845,8 +845,8 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
       const LdsFloat p = (LdsFloat)(uintptr_t)(ref_lds + (uint32_t)(fn * 32 + (lane & 31)) * 4u);
       float m[2] = {p[0], p[a.ref.parts * 64]};
       for (int k = 1; k < a.ref.parts; ++k) { m[0] = fmaxf(m[0], p[k * 64]); m[1] = fmaxf(m[1], p[(a.ref.parts + k) * 64]); }
-      rs2[fn] = m[0] * kLog2e;
-      rt2[fn] = m[1] * kLog2e;
+      rs2[fn] = References::scaled(m[0]);
+      rt2[fn] = References::scaled(m[1]);
     }
   }
   // 16-byte stores a wave issues per tile in its epilogue, at the least (see sweep_kstep, RELAXED)
@@ -1254,7 +1254,7 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   const int row = threadIdx.x % ROWS, wave = threadIdx.x >> 6;
   const int64_t r = b.row0 + (int64_t)blockIdx.x * ROWS + row;
   const int64_t plane = (int64_t)a.strips * a.n_pad;
-  const float ref_s = b.ref.of(0, r), ref_t = b.ref.of(1, r);
+  const float ref_s2 = b.ref.of(0, r), ref_t2 = b.ref.of(1, r);
   const int planes = a.diag ? 5 : 3;
   // the thread's first lane: neighbouring groups of a wave hold those that are farthest apart (bits reversed)
   const int first = wave + 4 * (int)(__brev((threadIdx.x & 63u) / ROWS) >> (32 - kGroupBits));
@@ -1291,9 +1291,9 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   for (int k = 0; k < 5; ++k)
     v[k] = k < planes ? (sums[0][k][row] + sums[2][k][row]) + (sums[1][k][row] + sums[3][k][row]) : 0.f;
   const float Zs = v[0], A = v[1], Zt = v[2], Bt = v[3], cnt = v[4];
-  const float lse_s = ref_s + logf(Zs), lse_t = ref_t + logf(Zt);
+  const float lse_s = ref_s2 * kLn2 + logf(Zs), lse_t = ref_t2 * kLn2 + logf(Zt);
   const float mu = A / Zs;                  // E_{p_s}[z_s - z_t]
-  float kl = kl_from_sums(mu, ref_s - ref_t, Zs, Zt);
+  float kl = kl_from_sums(mu, (ref_s2 - ref_t2) * kLn2, Zs, Zt);
   const float iz = 1.f / Zs;
   float ent = lse_t - Bt / Zt;              // H[p_t] = lse_t - E_{p_t}[z_t]; both sums share the reference
   // a row without a finite log-sum-exp, mean or KL (logits beyond the range the fixed

@@ -309,6 +309,35 @@ def test_merge_of_few_and_many_strips(B, V, rows):  # noqa: F811
     _check_fused(w, got, ref, O.RED_SEQ_MEAN)
 
 
+@pytest.mark.parametrize("rows", [100, 1500])       # finely cut references, staged ones
+def test_references_cancel(B, rows):  # noqa: F811
+    """KL_t is 0 for a teacher whose logits are the student's plus a constant.  Peaked rows (one entry of 16 to 64 nats, the
+    others within 2 of 0), logits that are exact in fp32: Z and A are the one entry's (the others
+    hold 0.4 % at the most), up to the rounding of its exponential (2^-23 for each model), of the
+    quotient and of the logarithm near 0, 2^-21 in all.  The scaled
+    references are rounded to up to 2^-18, and have to cancel to the bit."""
+    V, H, shift = 4104, 128, 0.75
+    g = torch.Generator().manual_seed(rows)
+    W_s = torch.zeros(V, H)
+    W_s[:, 1] = torch.randint(-16, 17, (V,), generator=g) / 8.0
+    token = 1000
+    W_s[token, 1:3] = torch.tensor([0.0, 1.0])
+    W_t = W_s.clone()
+    W_t[:, 0] = shift
+    h = torch.zeros(rows, H)
+    h[:, :2] = 1.0
+    top = torch.randint(128, 256, (rows,), generator=g) / 8.0       # 16 .. 32, and twice that
+    h[:, 2] = top * torch.randint(1, 3, (rows,), generator=g)
+    p = {k: v.to(torch.bfloat16).cuda() for k, v in {"h": h, "W_s": W_s, "W_t": W_t}.items()}
+    ids = torch.full((rows,), token, dtype=torch.int32, device="cuda")
+    out = B.adwin_opd_fused(p["h"], p["h"], p["W_s"], p["W_t"], ids, np.array([0, rows]), np.array([rows], np.int32),
+                            want=("kl", "c", "loss_prefix", "status_dev"))
+    torch.cuda.synchronize()
+    assert int(out["status_dev"][0]) == 0
+    worst = float(out["kl"].double().abs().max())
+    assert worst <= 2.0 ** -21, worst
+
+
 def test_merge_adds_in_the_order_of_64_lanes(tmp_path):
     """The sums over a row's strips, 16 rows to a workgroup (up to 64 strips) and four, bit for bit."""
     status, out = host_program.run(tmp_path, "merge_order_main", link=True)
