@@ -549,7 +549,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         if (sampled) {       // contract the E2 factor; c_t and W_s[y_t] enter in finalize_kernel
           ga.slab = la.slab + la.e2_off;
           ga.half_tiles = 0;                       // output rows behind the n_pad of g
-          ga.out_rows = n_pad + hp.n_rows;
+          ga.out_rows = n_pad + (int64_t)align_up((size_t)hp.n_rows, 8);   // n_pad, whole tiles, holds them
           if (head) {        // the transposed operand of the head-weight GEMMs; the slab stays as it is
             phase(ADWIN_PHASE_DZ);
             ADWIN_HIP_TRY(launch_combine(true, true, ca, ga.row_tiles, stream));
@@ -558,7 +558,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
           phase(ADWIN_PHASE_DZ);
           ADWIN_HIP_TRY(launch_combine(head, false, ca, ga.row_tiles, stream));
           ga.half_tiles = ga.row_tiles;            // output rows are those of g
-          ga.out_rows = hp.n_rows;
+          ga.out_rows = (int64_t)align_up((size_t)hp.n_rows, 8);
         }
         phase(ADWIN_PHASE_GRAD);
         ADWIN_HIP_TRY(launch_grad_gemm(ga, stream));

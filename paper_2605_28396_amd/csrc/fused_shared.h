@@ -323,7 +323,8 @@ struct GradArgs {
   Shares split_steps;       // k-steps of each piece that hold rows of B (set by launch_grad_gemm)
   int half_tiles;           // slab row tiles >= half_tiles hold the E2 factor: output rows
   int64_t half_off;         // half_off + slab_row0 + ... (single-sweep mode; else half_tiles = row_tiles)
-  int64_t out_rows;         // rows of g that exist (rows at or beyond are not stored)
+  // Rows of g that are stored: whole blocks of 8, so a multiple of 8, up to 7 more than exist where g has room for them
+  int64_t out_rows;
   int accumulate;           // add to g instead of overwriting it
 };
 

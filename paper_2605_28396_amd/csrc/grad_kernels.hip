@@ -454,8 +454,8 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
     grad_kstep<false, true>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
                             pa_lo, pa_hi, pb_lo, pb_hi);
   }
-  // Epilogue.  H and the rows that exist end on whole blocks of 32 columns and 8 rows (H is a multiple
-  // of 64, V of 8), so every bound is wave-uniform and a store takes one 32-bit lane offset, a scalar
+  // Epilogue.  H and out_rows end on whole blocks of 32 columns and 8 rows (H is a multiple of 64; the rows of a
+  // dW are V, a multiple of 8, those of g are rounded up to one within its padded planes), so every bound is wave-uniform and a store takes one 32-bit lane offset, a scalar
   // and an immediate: 256 stores in 320 instructions.  With a 64-bit address and two lane bounds per
   // store it was 4,700 instructions in 780 blocks, fetched from a cold instruction cache by every
   // workgroup.  us per call: V = 4,096, H = 256 + 384, 224 rows 75.5 -> 63.3; V = 32,776, H = 1024 + 1024,
@@ -680,6 +680,7 @@ hipError_t launch_combine(bool transposed, bool sampled, const CombineArgs& a, i
 }
 
 hipError_t launch_grad_gemm(const GradArgs& p, hipStream_t st) {
+  if (p.out_rows & 7) return hipErrorInvalidValue;       // rows are stored by eights
   GradArgs a = p;
   a.split_steps.split((int)((a.k_rows + kBK - 1) / kBK), a.ksplit);
   grad_gemm_kernel<<<(unsigned)(a.row_tiles * a.h_tiles * a.ksplit), 256, kGradLds, st>>>(a);

@@ -1,5 +1,6 @@
-"""The argument block of a call's first launch holds a fixed number of arrays to clear: one more is refused
-by the launcher instead of being written past the end (host code; nothing is launched)."""
+"""What the launchers check of their argument blocks before they launch anything (host code): the first launch of a call holds
+a fixed number of arrays to clear, and one more is refused instead of being written past the end; the gradient GEMM
+stores rows by eights."""
 import os
 import shutil
 import subprocess
@@ -7,6 +8,7 @@ import subprocess
 import pytest
 
 from paper_2605_28396_amd import binding
+from tests import host_program
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ROCM = "/opt/rocm"
@@ -25,3 +27,8 @@ def test_one_array_too_many_is_refused(tmp_path):
     assert r.returncode == 0, r.stderr[-4000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip() == "kept refused", (r.returncode, r.stdout, r.stderr)
+
+
+def test_gradient_rows_that_are_no_multiple_of_eight_are_refused(tmp_path):
+    status, out = host_program.run(tmp_path, "grad_args_main", link=True)
+    assert status == 0 and out.strip() == "refused", (status, out)
