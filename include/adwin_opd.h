@@ -386,7 +386,8 @@ int adwin_opd_from_logits_static(const adwin_opd_logits_problem* p, void* hip_st
  * statistics pass (Eq. 2 terms), per-row merge (KL_t, c_t), logit-gradient pass (Eq. 4 in
  * expectation), gradient contraction with W_s, and scatter plus window reductions
  * (Sec. 4.1 losses, Sec. 4.2 alignment).  The logits-given variant reports its single
- * streaming kernel under ADWIN_PHASE_STATS and the reductions under ADWIN_PHASE_REDUCE.
+ * streaming kernel under ADWIN_PHASE_STATS and the reductions under ADWIN_PHASE_REDUCE, in a
+ * launch of their own also where an unprofiled call has them share one with its rows.
  */
 #define ADWIN_PHASE_SETUP   0
 #define ADWIN_PHASE_STATS   1

@@ -1055,7 +1055,8 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
       ADWIN_HIP_TRY(diag ? launch_short_rows<true>(l, stream) : launch_short_rows<false>(l, stream));
     } else if (splits > 0) {
       TailArgs tail = make_tail(b, sa);
-      ended = !tail.with_summary;      // summaries need the rows' outputs, which the second launch writes
+      // summaries need the rows' outputs, which the second launch writes; a profile times the reductions by themselves
+      ended = !tail.with_summary && !timer;
       if (!ended) tail.blocks = 0;
       a.tail_has_kl = ended;
       ADWIN_HIP_TRY(diag ? launch_split_rows<true>(l, tail, stream) : launch_split_rows<false>(l, tail, stream));

@@ -2,6 +2,7 @@
 what they time (the copy copies) and report rates a real MI355X can have."""
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
@@ -51,3 +52,25 @@ def test_profiling_entry_points_time_the_same_call(B):
     lcall = B.LogitsCall(lo["z_s"], lo["z_t"], lo["ids"], w.offsets, w.window)
     ph = B.adwin_opd_from_logits_profile(lcall)
     assert ph["stats"] > 0.0 and ph["grad"] == 0.0 and ph["dz"] == 0.0
+
+
+def test_profile_of_split_rows_times_the_reductions(B):
+    """Rows in pieces whose reductions share a launch with the gradient: the profile still times them as such.
+    Against the streaming scheme, which has the same reductions in a launch of their own; 2,000 rollouts make them longer
+    than what two events cost."""
+    V, nb = 81928, 2000
+    g = torch.Generator().manual_seed(V)
+    z = [torch.randn((4, V), generator=g).to(torch.bfloat16).cuda() for _ in range(2)]
+    ids = torch.randint(0, V, (4,), generator=g, dtype=torch.int32).cuda()
+    off = np.concatenate([[0, 1, 3], np.full(nb, 4)])
+    win = np.ones(len(off) - 1, np.int32)
+    reduce = {}
+    for scheme in (B.ADWIN_LOGITS_AUTO, B.ADWIN_LOGITS_STREAMING):
+        call = B.LogitsCall(*z, ids, off, win, scheme=scheme)
+        assert call.run() == 0
+        torch.cuda.synchronize()
+        plain = {k: v.clone() for k, v in call.out.items()}
+        reduce[scheme] = min(B.adwin_opd_from_logits_profile(call)["reduce"] for _ in range(5))
+        for k, v in call.out.items():
+            assert torch.equal(v, plain[k]), k
+    assert reduce[B.ADWIN_LOGITS_AUTO] > 0.5 * reduce[B.ADWIN_LOGITS_STREAMING] > 0.0, reduce
