@@ -256,8 +256,8 @@ static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) 
   L.o_mu0t = take((L.single && p->estimator != ADWIN_EST_SAMPLED)
                       ? sizeof(float) * (size_t)vt_total * (size_t)bound_slab : 0);
   L.o_invz = take(sizeof(float) * (size_t)n_pad);
-  L.o_lse2 = take(sizeof(float) * (size_t)n_pad);
-  L.o_mu = take(sizeof(float) * (size_t)n_pad);
+  L.o_lse2 = take(L.single ? 0 : sizeof(float) * (size_t)n_pad);
+  L.o_mu = take(L.single ? 0 : sizeof(float) * (size_t)n_pad);
   L.o_klr = take(sizeof(float) * (size_t)n_pad);
   L.o_rownorm = take(sizeof(float) * (size_t)n_pad);
   const bool both_factors_diag = (p->t_entropy || p->t_rank) && p->estimator != ADWIN_EST_SAMPLED;
@@ -478,14 +478,13 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
       // token (without ids: id -1 on every row, which the diagnostics sweep expects)
       ADWIN_HIP_TRY(launch_prepare(pr, L.single, n_tiles, setup, blob, stream));
     }
-    LogitPassArgs la;
+    LogitPassArgs la{};
     la.h_s = (const __bf16*)p->h_s; la.h_t = (const __bf16*)p->h_t;
     la.W_s = (const __bf16*)p->W_s; la.W_t = (const __bf16*)p->W_t;
     la.H_s = p->H_s; la.H_t = p->H_t; la.V = p->V;
     la.row_idx = pl.row_idx; la.n_pad = n_pad;
     la.vt_total = vt_total;
     la.part = (float*)(ws + L.o_part);
-    la.lse2 = (const float*)(ws + L.o_lse2); la.mu = (const float*)(ws + L.o_mu);
     la.slab = (__bf16*)(ws + L.o_slab); la.Vp = L.Vp;
     la.ref = ref; la.e2_off = 0;
     la.mu0t = (L.single && !sampled && need_g) ? (float*)(ws + L.o_mu0t) : nullptr; la.mu0t_stride = L.slab_rows;
@@ -494,12 +493,12 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     la.ht_img = (const char*)(ws + L.o_ht_img); la.hs_img = (const char*)(ws + L.o_hs_img);
     la.long_first = 0;
     la.heavy = heavy; la.narrow = false; la.direct_w = L.direct_w; la.rotate = rotate_k(n_tiles, p->H_s, p->H_t);
-    MergeArgs m;
+    MergeArgs m{};
     m.part = la.part; m.strips = L.strips; m.n_pad = n_pad; m.n_rows = hp.n_rows;
     m.row_idx = pl.row_idx;
     m.h_s = la.h_s; m.h_t = la.h_t; m.W_s = la.W_s; m.W_t = la.W_t;
     m.H_s = p->H_s; m.H_t = p->H_t; m.V = p->V; m.ids = p->ids;
-    m.lse2 = (float*)(ws + L.o_lse2); m.mu = (float*)(ws + L.o_mu); m.klr = klr;
+    m.klr = klr;
     m.lse_s = (float*)(ws + L.o_lse_s); m.alive = (float*)(ws + L.o_invz);
     m.kl = p->kl; m.c = p->c; m.status = p->status_dev;
     m.diag = diag ? 1 : 0; m.t_logp = p->t_logp; m.t_entropy = p->t_entropy; m.t_rank = p->t_rank;
@@ -586,6 +585,8 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     } else {
       // Two sweeps: statistics over all token tiles, merge, then per row slab the dz sweep
       // and its GEMM with W_s.
+      m.lse2 = (float*)(ws + L.o_lse2); m.mu = (float*)(ws + L.o_mu);
+      la.lse2 = m.lse2; la.mu = m.mu;
       phase(ADWIN_PHASE_STATS);
       {
         la.tile0 = 0; la.n_tiles = n_tiles; la.strips = L.strips;
