@@ -77,7 +77,7 @@ static bool needs_gradient(const adwin_opd_problem* p) {
 // tiles of 1187 lost 1.5 %).  us per call, without / with: 3,300 rows, V = 12,000, H = 512 + 640 271 / 263 (probe),
 // 143.5 / 135.0 (statistics); 5,100 rows, V = 16,600, H = 1024 + 1024 statistics 380 / 362; V = 50,000,
 // H = 512 + 512 1250 / 1226; 7,600 rows, H = 512 + 1024 2137 / 2124.
-static int sweep_strips(int n_tiles, int vt_total, int* long_first) {
+int sweep_strips(int n_tiles, int vt_total, int* long_first) {
   const int most = vt_total < kMaxSweepStrips ? vt_total : kMaxSweepStrips;
   auto cost = [&](int s) {
     const int per_xcd = (n_tiles * s + 7) / 8, rounds = (per_xcd + 31) / 32;

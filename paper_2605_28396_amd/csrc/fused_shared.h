@@ -24,26 +24,37 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nb) {
   return xcd * base + (xcd < rem ? xcd : rem) + loc;
 }
 
+// Quotients by a number that the host knows: with per = ceil(2^32 / d) the upper half of n per is n / d while
+// n (per d - 2^32) < 2^32, for which n < 2^32 / d is enough.  On the device the division, with 64-bit operands,
+// was 100 instructions in front of the first load of every workgroup.
+struct Quotient {
+  uint32_t per = 0;                // 0: d = 1
+  void by(int d) { per = d > 0 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; }
+  __host__ __device__ __forceinline__ int operator()(int n) const {
+    return per ? (int)(((uint64_t)(uint32_t)n * per) >> 32) : n;
+  }
+};
+
 // `total` things in `parts` contiguous shares: share i begins at floor(i total / parts), so that the longer ones,
-// of one more, are spread evenly.  Quotient, remainder and the factor of the one that is left are taken
-// on the host: on the device the division, with 64-bit operands, was 100 instructions in front of the first load of
-// every workgroup.  The boundaries enter the results (the running means of a strip, the order of the sums).
-// With per = ceil(2^32 / parts) the product's upper half is the quotient while i longer (per parts - 2^32) < 2^32,
-// and that is below parts^3.
+// of one more, are spread evenly.  The boundaries enter the results (the running means of a strip, the order
+// of the sums).  No quotient is taken of more than parts^2.
 constexpr int kMaxShares = 1024;
 struct Shares {
-  int each, longer;                // longer shares hold one more
-  uint32_t per;
-  void split(int total, int parts) {
-    each = total / parts;
-    longer = total % parts;
-    per = (uint32_t)(((1ull << 32) + parts - 1) / parts);       // parts = 1: not used, longer is 0
+  int parts, each, longer;         // longer shares hold one more
+  Quotient of_parts, of_longer, of_shorter;
+  void split(int total, int n) {
+    parts = n;
+    each = total / n;
+    longer = total % n;
+    of_parts.by(n);
+    of_longer.by(longer);
+    of_shorter.by(n - longer);
   }
-  __host__ __device__ __forceinline__ int first(int i) const {
-    return i * each + (int)(((uint64_t)(uint32_t)(i * longer) * per) >> 32);
+  __host__ __device__ __forceinline__ int first(int i) const { return i * each + of_parts(i * longer); }
+  // the i-th share in the order: longer ones, then the others
+  __host__ __device__ __forceinline__ int by_length(int i) const {
+    return i < longer ? of_longer((i + 1) * parts - 1) : of_shorter((i - longer) * parts);
   }
-  // ... the longer ones first
-  __device__ __forceinline__ int first_by_length(int i) const { return i * each + (i < longer ? i : longer); }
 };
 
 // Workgroup `vid` of a logit pass -> (strip, token tile): groups of `tg` token tiles, inside a
@@ -204,7 +215,7 @@ struct LogitPassArgs {
   bool narrow;                 // one token tile, of which only the first 128 rows are wanted (see DmaTile)
   int strips;                  // vocabulary strips
   Shares strip_tiles;          // vocabulary tiles of each (set by launch_logit_pass)
-  int long_first;              // the longer strips come first, and so do their workgroups (sweep_strips)
+  int long_first;              // the longer strips' workgroups of all token tiles come first (sweep_strips)
   int tg;                      // token tiles per workgroup group (share W tiles in one L2)
   int vt_total;                // vocabulary tiles (of 128)
   // pass 1 out: [5][strips][n_pad]
@@ -349,6 +360,8 @@ struct FinalizeArgs {
 // ---------------------------------------------------------------------------------------
 // Launchers (asynchronous on `st`; the return value is that of the launch)
 // ---------------------------------------------------------------------------------------
+// fused_host.hip
+int sweep_strips(int n_tiles, int vt_total, int* long_first);   // vocabulary strips of a sweep, and their order
 // sweep_kernels.hip
 hipError_t sweep_kernels_opt_in();       // large dynamic LDS of the logit kernels, once per device
 hipError_t launch_row_image(const RowImageArgs& a, unsigned tiles, hipStream_t st);

@@ -340,8 +340,8 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
   const int wm = wave >> 1, wn = wave & 1;
   int vid = xcd_contiguous_id(blockIdx.x, gridDim.x);
   const int tiles = a.row_tiles * a.h_tiles;
-  const int split = vid / tiles;
-  vid -= split * tiles;
+  const int nth = vid / tiles, split = a.split_steps.by_length(nth);
+  vid -= nth * tiles;
   const int rt = vid / a.h_tiles, ht = vid % a.h_tiles;
   // k-steps that hold rows of B: the A blocks are padded to whole vocabulary tiles, of which the
   // last k-step may lie beyond k_rows altogether (its A entries are exact zeros)

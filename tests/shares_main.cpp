@@ -1,4 +1,5 @@
-// Shares::first against the division that it stands for, floor(i total / parts): every number of parts up to `most`.
+// Shares against what they stand for, every number of parts up to kMaxShares: share i begins at floor(i total / parts),
+// and by_length lists the longer shares and then the others, each in index order.
 #include <cstdio>
 
 #include "fused_shared.h"
@@ -13,6 +14,12 @@ int main() {
       Shares s;
       s.split(total, parts);
       for (int i = 0; i <= parts; ++i, ++checked) bad += s.first(i) != (int)((long long)i * total / parts);
+      int at[2] = {0, s.longer};
+      for (int i = 0; i < parts; ++i) {
+        const bool longer = s.first(i + 1) - s.first(i) > s.each;
+        bad += s.by_length(at[longer ? 0 : 1]++) != i;
+      }
+      bad += at[0] != s.longer || at[1] != parts;
     };
     for (int total : totals) check(total);
     for (int rest = 0; rest < parts; rest += 1 + parts / 64) check(3 * parts + rest);

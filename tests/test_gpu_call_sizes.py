@@ -1,5 +1,6 @@
 """Calls of few rows: the launch geometry, the operand staging and the split of the work follow
 the number of token tiles, so the sizes on both sides of each rule are compared with the oracle."""
+import ctypes as C
 import functools
 
 import numpy as np
@@ -263,6 +264,36 @@ def test_batch_aggregates_by_columns(B, H_s, nb, cands):  # noqa: F811
     _check_fused(w, got, ref, O.RED_SEQ_MEAN)
     want = np.stack([aud["micro"], aud["micro_field"], aud["macro"], aud["macro_field"]], axis=1)
     assert np.all(np.abs(got["cand_batch"] - want) <= Hp.RHO_ABS), (got["cand_batch"], want)
+
+
+def _sweep_strips(B, rows, V):  # noqa: F811
+    """(strips, whether the longer ones come first) of a sweep over one slab of `rows` rows."""
+    chosen = getattr(B.lib, "_ZN5adwin12sweep_stripsEiiPi")
+    long_first = C.c_int(0)
+    return chosen((rows + 255) // 256, (V + 127) // 128, C.byref(long_first)), bool(long_first.value)
+
+
+@pytest.mark.parametrize("V,rows", [(12416, 4096), (5632, 3000), (7680, 2300)])
+def test_order_of_strips_is_no_part_of_the_result(B, monkeypatch, V, rows):  # noqa: F811
+    """32 strips whose longer ones come first have the boundaries of the 32 strips of every other call: the same
+    outputs bit for bit as with the order forced (W as tile images, and row-major)."""
+    assert _sweep_strips(B, rows, V) == (32, True)
+    for H_s, H_t, more in ((128, 192, DIAGNOSTICS), (512, 256, ())):
+        w = synth.Workload(f"order_{V}", V, H_s, H_t, synth._offsets([rows - 300, 300]), np.array([rows, 290], np.int32),
+                           synth.MODE_PREFIX_ONLY)
+        d = {k: v.cuda() for k, v in synth.hidden_problem(w).items()}
+        outs = []
+        for forced in (False, True):
+            if forced:
+                monkeypatch.setenv("ADWIN_STRIPS2", "32")
+                assert _sweep_strips(B, rows, V) == (32, False)
+            else:
+                monkeypatch.delenv("ADWIN_STRIPS2", raising=False)
+            outs.append(B.adwin_opd_fused(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window,
+                                          mode=w.mode, want=B.FusedCall.DEFAULT_OUTPUTS + more))
+            torch.cuda.synchronize()
+        for k in outs[0]:
+            assert torch.equal(outs[0][k], outs[1][k]), k
 
 
 @pytest.mark.parametrize("V,rows", [(11912, 3300), (16600, 5100), (16600, 3000)])
