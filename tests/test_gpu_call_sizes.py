@@ -42,17 +42,22 @@ def test_few_rows_match_oracle(B, V, H_s, H_t, lens, win, estimator):  # noqa: F
     (4616, 192, 2048, [230], [201]),             # ... and the other way round
 ])
 def test_strips_begin_at_different_k_steps(B, V, H_s, H_t, lens, win):  # noqa: F811
-    """One token tile and rows of 4 KiB: the contraction of strip s begins at k-step s.  Held to the bound of
-    their own summands: a row of g over 4,616 entries errs by 2.1e-3 of its norm (three roundings
-    of 2^-9 on the entries that carry it), the same before the strips were spread."""
+    """One token tile and rows of 4 KiB: the contraction of strip s begins at k-step s, in the single sweep and in both of
+    the two-sweep scheme.  Held to the bound of their own summands: a row of g over 4,616 entries errs
+    by 2.1e-3 of its norm (three roundings of 2^-9 on the entries that carry it), the same before the strips
+    were spread."""
     w = synth.Workload("rotated", V, H_s, H_t, synth._offsets(lens), np.array(win, np.int32), synth.MODE_PREFIX_ONLY)
     p = synth.hidden_problem(w)
     f = Hp.oracle_inputs(p)
-    for estimator in (O.EST_EXPECTED, O.EST_SAMPLED):
+    for estimator, schemes in ((O.EST_EXPECTED, (B.ADWIN_SCHEME_SINGLE, B.ADWIN_SCHEME_TWO_SWEEP)),
+                               (O.EST_SAMPLED, (B.ADWIN_SCHEME_SINGLE,))):
         ref = O.supervise(f["h_s"], f["h_t"], f["W_s"], f["W_t"], f["ids"], w.offsets, w.window,
                           reduction=O.RED_SEQ_MEAN, mode=w.mode, estimator=estimator)
-        got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator)
-        _check_fused(w, got, ref, O.RED_SEQ_MEAN, grad_l2=_grad_l2(f, w, ref, O.RED_SEQ_MEAN, estimator=estimator))
+        l2 = _grad_l2(f, w, ref, O.RED_SEQ_MEAN, estimator=estimator)
+        for scheme in schemes:
+            got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator,
+                             scheme=scheme)
+            _check_fused(w, got, ref, O.RED_SEQ_MEAN, grad_l2=l2)
 
 
 @pytest.mark.parametrize("V", [104, 4104])
@@ -90,6 +95,7 @@ def _kl_in_64_bits(d, V):
     (8000, 512, 512, 4900),       # 20 token tiles
     (11912, 192, 256, 2305),      # 10 token tiles
     (50000, 128, 256, 300),       # 2 token tiles: a strip per compute unit
+    (32000, 128, 256, 3800),      # 15 token tiles, 50 strips, all of one length
 ])
 def test_strips_cost_no_accuracy(B, monkeypatch, V, H_s, H_t, rows):  # noqa: F811
     """A strip's sums are fp32 chains as long as the strip: whatever number of strips fills the
@@ -149,8 +155,8 @@ H_SUM = 128 + 192
 
 
 @functools.lru_cache(maxsize=2)
-def _staging_problem(rows, estimator):
-    w = synth.Workload(f"staging_{rows}", 4104, 128, 192, synth._offsets([rows - min(rows, 100), min(rows, 100)]),
+def _staging_problem(rows, estimator, V=4104, H_s=128, H_t=192):
+    w = synth.Workload(f"staging_{rows}", V, H_s, H_t, synth._offsets([rows - min(rows, 100), min(rows, 100)]),
                        np.array([rows, 100], np.int32), synth.MODE_PREFIX_ONLY)
     p = synth.hidden_problem(w)
     f = Hp.oracle_inputs(p)
@@ -176,9 +182,9 @@ def test_narrow_token_tile_in_every_sweep_mode(B, what, rows):  # noqa: F811
     _check_sweep_mode(B, what, rows)
 
 
-def _check_sweep_mode(B, what, rows):  # noqa: F811
+def _check_sweep_mode(B, what, rows, **kw):  # noqa: F811
     estimator = O.EST_SAMPLED if what.startswith("sampled") else O.EST_EXPECTED
-    w, p, ref, (ent, logp, lo, hi) = _staging_problem(rows, estimator)
+    w, p, ref, (ent, logp, lo, hi) = _staging_problem(rows, estimator, **kw)
     stats, diag = what.startswith("stats"), what.endswith("diag")
     want = (STATS if stats else B.FusedCall.DEFAULT_OUTPUTS) + (DIAGNOSTICS if diag else ())
     got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32, estimator=estimator, want=want,
@@ -296,10 +302,12 @@ def test_order_of_strips_is_no_part_of_the_result(B, monkeypatch, V, rows):  # n
             assert torch.equal(outs[0][k], outs[1][k]), k
 
 
-@pytest.mark.parametrize("V,rows", [(11912, 3300), (16600, 5100), (16600, 3000)])
-def test_longer_strips_first(B, monkeypatch, V, rows):  # noqa: F811
-    """13 and 20 token tiles whose strips have two lengths and come in two classes, the longer ones of all token
-    tiles first, and 12 whose do not: against the oracle, and no further from 64 bits than 32 strips."""
+@pytest.mark.parametrize("V,rows,strips,long_first", [
+    (11912, 3300, 38, True), (16600, 5100, 35, True), (16600, 3000, 37, True), (11912, 3500, 32, False)])
+def test_longer_strips_first(B, monkeypatch, V, rows, strips, long_first):  # noqa: F811
+    """Strips of two lengths in two classes, the longer ones of all token tiles first, and some that do not gain by
+    it: against the oracle, and no further from 64 bits than 32 strips."""
+    assert _sweep_strips(B, rows, V) == (strips, long_first)
     w = synth.Workload(f"strip_order_{V}_{rows}", V, 128, 192, synth._offsets([rows - 40, 40]),
                        np.array([rows - 40, 33], np.int32), synth.MODE_PREFIX_ONLY)
     p = synth.hidden_problem(w)
@@ -309,6 +317,15 @@ def test_longer_strips_first(B, monkeypatch, V, rows):  # noqa: F811
     got = _run_fused(B, w, p, "cuda", reduction=O.RED_SEQ_MEAN, dh_dtype=B.ADWIN_DT_F32)
     _check_fused(w, got, ref, O.RED_SEQ_MEAN)
     test_strips_cost_no_accuracy(B, monkeypatch, V, 128, 192, rows)
+
+
+@pytest.mark.parametrize("H_s,H_t", [(128, 192), (320, 384)])       # W as tile images, and row-major
+@pytest.mark.parametrize("what", ["train", "train_diag", "stats", "stats_diag", "two_sweep", "sampled", "sampled_diag"])
+def test_longer_strips_first_in_every_sweep_mode(B, what, H_s, H_t):  # noqa: F811
+    """Nine token tiles of 61 vocabulary tiles, the last one of 8 entries: 28 strips of two tiles and then five of one."""
+    V, rows = 7688, 2300
+    assert _sweep_strips(B, rows, V) == (33, True)
+    _check_sweep_mode(B, what, rows, V=V, H_s=H_s, H_t=H_t)
 
 
 @pytest.mark.parametrize("estimator", [O.EST_EXPECTED, O.EST_SAMPLED])
