@@ -382,7 +382,7 @@ int adwin_opd_from_logits_static(const adwin_opd_logits_problem* p, void* hip_st
  * Profiling variants: identical work and results, but every kernel launch is bracketed
  * with HIP events on the stream, the call waits for the stream to drain, and the summed
  * milliseconds per phase are written to phase_ms (host float[ADWIN_N_PHASES]).  Phases
- * follow the steps of the path: setup (plan upload, W_s transpose), full-vocabulary
+ * follow the steps of the path: setup (plan, references, operand images), full-vocabulary
  * statistics pass (Eq. 2 terms), per-row merge (KL_t, c_t), logit-gradient pass (Eq. 4 in
  * expectation), gradient contraction with W_s, and scatter plus window reductions
  * (Sec. 4.1 losses, Sec. 4.2 alignment).  The logits-given variant reports its single

@@ -898,7 +898,8 @@ static bool streaming_suits_diagnostics(int V, int64_t n_adm) {
 // V = 151,936: 128 rows 41 / 57, 180 rows 55 / 58, 200 rows 60 / 59, 300 rows 80 / 103, 400 rows 111 / 113,
 // 448 rows 136 / 119; V = 164,000: 180 rows 59 / 65, 224 rows 69 / 67, 400 rows 125 / 130.  The long-row kernel
 // reads twice what it cannot hold: V = 180,000: 224 rows 72 / 76, 256 rows 80 / 79; V = 200,000: 224 rows
-// 79 / 89, 256 rows 88 / 94, 300 rows 105 / 174, 400 rows 160 / 183; V = 300,000: 256 rows 155 / 220.
+// 79 / 89, 256 rows 88 / 94, 300 rows 105 / 174, 400 rows 160 / 183; V = 300,000: 256 rows 155 / 220.  (211 to 256 rows
+// of 172,001 to 190,000 logits go to the long-row kernel whole: it is 5 % behind at 224 rows and 1 % ahead at 256.)
 // With diagnostics against the better of the streaming and the long-row kernel: V = 102,400: 128 rows 44 / 48,
 // 156 rows 50 / 49; V = 122,880: 156 rows 52 / 55, 180 rows 58 / 57, 300 rows 81 / 79; V = 151,936: 156 rows 59 / 66,
 // 180 rows 67 / 68, 200 rows 73 / 69, 300 rows 94 / 95, 352 rows 106 / 111, 400 rows 124 / 120; V = 200,000:

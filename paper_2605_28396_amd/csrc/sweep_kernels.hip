@@ -3,15 +3,15 @@
 // reverse KL (Eq. 2 at token level) and the factors of the logit gradient (Eq. 4 in
 // expectation, App. A.1).  The logits themselves are never written anywhere.
 //
-// Single sweep (the default): per-row references are fixed in advance (online statistics
-// of vocabulary tile 0 and the sampled token's logits), so one pass over the vocabulary
+// Single sweep (the default): per-row references are fixed in advance (the largest logit
+// of vocabulary tile 0 and the sampled token), so one pass over the vocabulary
 // yields the sums Z_s, A = sum e_s (z_s - z_t), Z_t and two bf16 gradient factors
 // D = (z_s - z_t) - mu0 and E2 = e_s per logit, written as tile images into a bounded row
 // slab; the merge gives lse, mu, KL_t, c_t per row, and the combine pass (grad_kernels.hip)
 // turns the factors into dz = p_s ((z_s - z_t) - mu).
 // Two sweeps (fallback): running-max statistics, merge, then the logits again for dz.
 //
-// For a 256-token tile a workgroup walks vocabulary tiles of 128; per tile two MFMA GEMMs
+// For a token tile (256, or the 128 of a call of few rows) a workgroup walks vocabulary tiles of 128; per tile two MFMA GEMMs
 // (teacher, then student) into fp32 accumulators, then the epilogue on the registers.
 // MFMA operand roles: v_mfma_f32_32x32x16_bf16 computes D[i][j] += sum_k A[i][k] B[k][j]
 // with i in registers and j = lane % 32.  A = W tile (i = vocabulary) and B = h tile
@@ -442,16 +442,16 @@ __global__ __launch_bounds__(256) void logit_pass_kernel(LogitPassArgs a) {
 // Logit passes, direct global->LDS staging.
 //
 // Same tile, MFMA roles and epilogues as logit_pass_kernel, but the k-tiles are moved by
-// global_load_lds_dwordx4 (no register staging) into a three-stage LDS ring, two k-steps
-// ahead of the MFMAs, from tile images that already have the LDS layout (row_image_kernel
+// global_load_lds_dwordx4 (no register staging) into an LDS ring of kStages stages, kAhead
+// k-steps ahead of the MFMAs (DmaTile), from tile images that already have the LDS layout (row_image_kernel
 // below): one wave instruction moves 1 KiB of consecutive bytes, lane l its 16 bytes at 16 l.
 // The teacher and student k-loops form one pipeline of H_t/64 + H_s/64 steps per vocabulary
 // tile.
 //
 // The loads are written as inline assembly (M0 = LDS destination of the wave, 64-bit scalar
 // base + 32-bit lane offset within the block) and waited for with explicit
-// s_waitcnt vmcnt(N): the loads return in order, so "at most the 12 loads of the next stage
-// outstanding" means this stage has landed.  Compiler-issued loads in between only make the
+// s_waitcnt vmcnt(N): the loads return in order, so "at most the loads of the kAhead - 1 later stages
+// outstanding", kPerWave each, means this stage has landed.  Compiler-issued loads in between only make the
 // count larger, i.e. the wait longer.
 // ---------------------------------------------------------------------------------------
 // FN = 2: tiles of 256 tokens, 64 to a wave, and a ring of three stages.  FN = 1, for calls of up to 128 rows:
@@ -508,12 +508,12 @@ __global__ __launch_bounds__(256) void row_image_kernel(RowImageArgs a) {
 constexpr int kImgABytes = kTileVocab * kRowBytes;    // 16 KiB: one W block
 constexpr int kImgBBytes = kTileTokens * kRowBytes;   // 32 KiB: one h block
 
-// Wave-load I (0..11) of this wave for one stage: KiB (wave + 4 I) of the A block, then of
+// Wave-load I (0 .. kPerWave - 1) of this wave for one stage: KiB (wave + 4 I) of the A block, then of
 // the B block; lane l moves bytes 16 l .. 16 l + 15 of that KiB.  lds_wave = the stage's LDS
 // address + 1024 wave; voffw[j] = 16 lane + 1024 (wave + 4 j): the wave's part of both addresses
 // is folded into operands that are set up once, the rest is a literal.  voffa: the same for the
 // A block, or the lane's offsets in the row-major W (direct staging).
-template <int I>       // I < DmaTile::kPerWave
+template <int I>
 __device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voffa)[4], const uint32_t (&voffw)[8],
                                         const char* sA, const char* sB) {
   if constexpr (I < kTileVocab / 32)
@@ -522,22 +522,22 @@ __device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voff
     dma16_at<(kTileVocab / 8 + 4 * (I - kTileVocab / 32)) * 1024>(lds_wave, voffw[I - kTileVocab / 32], sB);
 }
 
-// One staged k-step (4 sub-steps of 8 MFMAs) of the 128 x 64 wave tile.  On entry fa[0],
+// One staged k-step (4 sub-steps of 4 FN MFMAs) of the 128 x 32 FN wave tile.  On entry fa[0],
 // fb[0] hold the fragments of sub-step 0.  The instruction order is pinned: after each MFMA
 // one or two side operations are issued in its shadow -- an LDS read of a fragment of the
-// next sub-step (fragments are double-buffered), one of the 12 global->LDS loads of the
-// stage two k-steps ahead (every k-step loads) or a piece of the pipeline's bookkeeping -- so
+// next sub-step (fragments are double-buffered), one of the kPerWave global->LDS loads of the
+// stage kAhead k-steps on (every k-step loads) or a piece of the pipeline's bookkeeping -- so
 // that neither the LDS latency nor the vector-memory issue holds up the matrix pipe.  The one
 // barrier of the k-step sits before the last sub-step: by then every fragment of this stage is
 // in registers, and the last sub-step's MFMAs cover the reads of the next stage's first
-// fragments (the following ring slot, whose loads were issued one k-step earlier and are waited
-// for here).  LAST: no next stage in this vocabulary tile; no barrier and no fragment reads.
+// fragments (the following ring slot, whose loads were issued kAhead - 1 k-steps earlier and are waited
+// for here: kYounger younger ones may be outstanding).  LAST: no next stage in this vocabulary tile; no barrier and no fragment reads.
 // FRESH: the k-step starts a new accumulation (first k-step of a head): its first MFMA on each
 // block takes a zero addend, so the accumulators are never cleared.
 // RELAXED > 0 (with `relaxed` set): the wait before the barrier lets RELAXED more operations
 // stay in flight.  The counter takes loads and stores in the order of issue; the first k-step
 // of a tile follows an epilogue that issued at least RELAXED stores after the loads this wait is
-// for, and waiting for "all but this step's 9 loads" would mean waiting for every one of them.
+// for, and waiting for "all but the kYounger youngest" would mean waiting for every one of them.
 // Ring and load state: r_rd = address (LDS base + 1024 wave + slot) of the slot consumed, on
 // return that of the next k-step; swA/swB = the lane's fragment offsets from such an address
 // per sub-step; (a_lo, a_hi), (b_lo, b_hi) = the blocks that the previous k-step loaded, on
@@ -777,9 +777,9 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   }
 
   // The k-steps of all vocabulary tiles of the strip form one pipeline: per tile nk_t
-  // teacher steps, then nk_s student steps; step g is staged into ring slot g % 3 two steps
-  // before it is consumed, also across head and tile boundaries (the next tile's first two steps
-  // are loaded during this tile's last two, i.e. before and under the epilogue).  ld*: the step
+  // teacher steps, then nk_s student steps; step g is staged into ring slot g % kStages kAhead steps
+  // before it is consumed, also across head and tile boundaries (the next tile's first kAhead steps
+  // are loaded during this tile's last ones, i.e. before and under the epilogue).  ld*: the step
   // whose loads were issued last; past the strip's last step the walk wraps to the strip's first
   // tile, so that every k-step loads (those last blocks land in slots nobody reads any more).
   // (a, b) = the blocks of that step; a k-step moves them on by one block before it loads, so
@@ -905,7 +905,7 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   }
 #undef ADWIN_COUNT_LOADS
 #undef ADWIN_SET_BLOCKS
-  wait_vm<0>();      // the strip's last two k-steps loaded blocks nobody reads: landed before the LDS is released
+  wait_vm<0>();      // the strip's last kAhead k-steps loaded blocks nobody reads: landed before the LDS is released
   const int64_t row0 = row_tile + wave * (32 * FN);
   if (MODE == kModeStats) write_partials(st, a.part, a.strips, strip, a.n_pad, row0, lane);
   else if (kSingle) write_sums<kDiag, FN>(sm, a.part, a.strips, strip, a.n_pad, row0, lane);
