@@ -1241,7 +1241,7 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_inline_kernel(PrepareArg
 // the strips s, s + 64, ...; then the lanes 32 apart are added, 16 apart, and so on.  A thread holds kLanes of these
 // lanes, kStep apart, its wave does the next halvings and the four waves leave the last two.
 // Bound by round trips: 16 rows read 64 bytes of a plane together, where a wave to a row read 4 bytes of 64 lines, and the
-// strips of a thread are loaded together, so that up to kMergeStrips take one trip.  3,139 rows of 38 strips 7.4 -> 5.0 us
+// strips of a thread are loaded together, so that up to kMergeStrips take one trip.  3,139 rows of 38 strips 7.4 -> 5.6 us
 // (the call, V = 11,912, 257.8 -> 255.9).  More strips belong to a call of one token tile, whose 256 rows are too few
 // for that (238 strips: 16 rows 11.6 us, four rows 9).
 constexpr int kMergeStrips = 64;
@@ -1259,7 +1259,7 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
   const int planes = a.diag ? 5 : 3;
   // the thread's first lane: neighbouring groups of a wave hold those that are farthest apart (bits reversed)
   const int first = wave + 4 * (int)(__brev((threadIdx.x & 63u) / ROWS) >> (32 - kGroupBits));
-  float x[kLanes][5];                         // Z_s, A, Z_t, B_t, count
+  float x[kLanes][5], y[kLanes][5];           // Z_s, A, Z_t, B_t, count
 #pragma unroll
   for (int j = 0; j < kLanes; ++j)
 #pragma unroll
@@ -1269,12 +1269,18 @@ __global__ __launch_bounds__(256) void merge_single_kernel(MergeSingleArgs b) {
 #pragma unroll
     for (int j = 0; j < kLanes; ++j) {
       const int s = s0 + j * kStep;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) y[j][k] = 0.f;
       if (s < a.strips) {
         const float* p = a.part + (int64_t)s * a.n_pad + r;
-        x[j][0] += p[0]; x[j][1] += p[plane]; x[j][2] += p[2 * plane];
-        if (a.diag) { x[j][3] += p[3 * plane]; x[j][4] += p[4 * plane]; }
+        y[j][0] = p[0]; y[j][1] = p[plane]; y[j][2] = p[2 * plane];
+        if (a.diag) { y[j][3] = p[3 * plane]; y[j][4] = p[4 * plane]; }
       }
     }
+#pragma unroll
+    for (int j = 0; j < kLanes; ++j)          // behind all of the loads
+#pragma unroll
+      for (int k = 0; k < 5; ++k) x[j][k] += y[j][k];
   }
   float v[5];
 #pragma unroll
