@@ -295,7 +295,7 @@ __device__ __forceinline__ uint4 row_load16(__amdgpu_buffer_rsrc_t r, int lane_o
 __device__ __forceinline__ void row_store16(__amdgpu_buffer_rsrc_t r, int lane_off, int iter_off, const uint4& v) {
   u32x4 x;
   x.x = v.x; x.y = v.y; x.z = v.z; x.w = v.w;
-  __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off, iter_off, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off + iter_off, 0, 0);
 }
 
 // Bt = sum e^{z_t - m_t} z_t and cnt = entries above zy, the teacher's logit of y_t: diagnostics only.

@@ -216,19 +216,21 @@ __device__ __forceinline__ float acc_read(const float& a) {
 }
 
 // The two slab blocks of a logit tile through a buffer descriptor: the lane's offset is one
-// 32-bit register and the block, the token column group and the chunk are immediates or
-// scalars, so the stores need no 64-bit address registers.
+// 32-bit register, so the stores need no 64-bit address registers.  No part of it is given as the instruction's scalar
+// offset: the compiler puts two wait states between a 16-byte buffer store and an instruction that overwrites its
+// data registers, but none if the store has one, and stores of this epilogue were seen to write the register's next
+// contents (an accumulator read right behind the store) once a second wave shared the SIMD.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_rsrc(__bf16* blk) {
   // extent: the tile's two blocks; flag word: the raw-buffer setting of the gfx9 family
   // (32-bit data format, no swizzle)
   return __builtin_amdgcn_make_buffer_rsrc(blk, 0, 2 * kImgBytesSlab, 0x00020000);
 }
-__device__ __forceinline__ void slab_store16(__amdgpu_buffer_rsrc_t r, int lane_off, int block_off, const float (&x)[8]) {
+__device__ __forceinline__ void slab_store16(__amdgpu_buffer_rsrc_t r, int off, const float (&x)[8]) {
   u32x4 o;
   o.x = pack_bf16(x[0], x[1]); o.y = pack_bf16(x[2], x[3]);
   o.z = pack_bf16(x[4], x[5]); o.w = pack_bf16(x[6], x[7]);
-  __builtin_amdgcn_raw_buffer_store_b128(o, r, lane_off, block_off, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(o, r, off, 0, 0);
 }
 
 template <bool TAIL, bool DIAG, bool WRITE_D, bool WRITE_E2, int FN>
@@ -242,6 +244,12 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const
   const int half = lane >> 5, vlane = v0 + 16 * half, key2 = ((lane >> 1) & 7) ^ (2 * half);
   // byte offset of chunk cb of the lane's row (fn = 0, first block): rowb ^ (cb << 4)
   const int rowb = (wrow + (lane & 31)) * kRowBytes + (key2 << 4);
+  // with diagnostics formed again for every store: kept, the sixteen offsets made the kernel spill
+  auto offset = [&](int fn, int fm, int p) __attribute__((always_inline)) {
+    int b = rowb;
+    if (DIAG) asm volatile("" : "+v"(b));
+    return (b ^ (((fm & 1) * 4 + p) << 4)) + (fm >> 1) * kImgBytesSlab + fn * 32 * kRowBytes;
+  };
   const __amdgpu_buffer_rsrc_t rd = slab_rsrc(blk), re = slab_rsrc(blk + e2_off);
   float Zs[2], As[2], Zt[2], Bt[2];
   int cnt[2], vy[2];
@@ -272,7 +280,7 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const
       e2[e] = es;
     }
     if (WRITE_E2)
-      slab_store16(re, rowb ^ (((fm & 1) * 4 + p) << 4), (fm >> 1) * kImgBytesSlab + fn * 32 * kRowBytes, e2);
+      slab_store16(re, offset(fn, fm, p), e2);
   };
   // Second factor: D = d - mu0 with mu0 the strip's running mean of d = z_s - z_t under the
   // student weights, this tile included (both half-columns of the row).  A heavy entry
@@ -291,7 +299,7 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const
 #pragma unroll
     for (int e = 0; e < 8; ++e)
       dd[e] = (acc_read(zs[fm][fn][p * 8 + e]) - m0) - acc_read(zt[fm][fn][p * 8 + e]);
-    slab_store16(rd, rowb ^ (((fm & 1) * 4 + p) << 4), (fm >> 1) * kImgBytesSlab + fn * 32 * kRowBytes, dd);
+    slab_store16(rd, offset(fn, fm, p), dd);
   };
   // The stores of D have little arithmetic of their own to hide behind, so column 0's second
   // pass is interleaved with column 1's first pass, whose exponentials cover them.

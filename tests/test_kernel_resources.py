@@ -31,3 +31,49 @@ def test_no_kernel_uses_scratch(tmp_path):
     assert any("grad_gemm_kernel" in n for n in seen) and any("logit_pass_dma_kernel" in n for n in seen)
     over = {n: s for n, s in seen.items() if s > max([b for k, b in ALLOWED.items() if k in n], default=0)}
     assert not over, over
+
+
+def _overwritten(text):
+    """(kernel, store, instruction) where an instruction writes a data register of a 16-byte buffer store with fewer than two
+    wait states in between: the store may write what comes after."""
+    found, kernel, pending = [], None, []
+    for line in text.splitlines():
+        m = re.match(r"[0-9a-f]+ <(\w+)>:", line)
+        if m:
+            kernel, pending = m[1], []
+            continue
+        m = re.match(r"\s+([a-z]\w+)\s*([^/]*)", line)
+        if not m:
+            continue
+        op, args = m[1], m[2].strip()
+        written = re.match(r"v(\d+)\b|v\[(\d+):(\d+)\]", args) if op.startswith("v_") and not op.startswith("v_cmp") else None
+        if written:
+            lo, hi = int(written[1] or written[2]), int(written[1] or written[3])
+            found += [(kernel, s, line.strip()) for s, a, b, left in pending if left > 0 and a <= hi and b >= lo]
+        states = int(args) + 1 if op == "s_nop" else 1
+        pending = [(s, a, b, left - states) for s, a, b, left in pending if left > states]
+        data = re.match(r"v\[(\d+):(\d+)\]", args) if re.fullmatch(r"buffer_store_(dwordx[34]|format_xyzw?)", op) else None
+        if data:
+            pending.append((line.strip(), int(data[1]), int(data[2]), 2))
+    return found
+
+
+@pytest.mark.skipif(not os.path.exists(os.path.join(LLVM, "llvm-objdump")), reason="no ROCm LLVM tools")
+def test_no_store_loses_its_data(tmp_path):
+    """In the code of this build: two wait states behind every wide buffer store before its data registers are written."""
+    bad = _overwritten("0 <k>:\n\tbuffer_store_dwordx4 v[4:7], v1, s[0:3], s9 offen // 0\n\tv_mov_b32_e32 v5, v2 // 4\n")
+    assert len(bad) == 1                    # the check sees what it is for
+    assert not _overwritten("0 <k>:\n\tbuffer_store_dwordx4 v[4:7], v1, s[0:3], 0 offen\n\ts_nop 1\n\tv_mov_b32_e32 v5, v2\n")
+    lib = shutil.copy(binding.LIB_PATH, tmp_path / "lib.so")
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", str(lib)], cwd=tmp_path, check=True,
+                   capture_output=True)
+    images = list(tmp_path.glob("lib.so.*gfx950"))
+    assert images
+    found, stores = [], 0
+    for f in images:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(f)], check=True,
+                              capture_output=True, text=True).stdout
+        stores += text.count("buffer_store_dwordx4")
+        found += _overwritten(text)
+    assert stores > 100
+    assert not found, found[:5]
