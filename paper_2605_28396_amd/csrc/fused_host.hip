@@ -538,6 +538,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         ga.row_tiles = (int)(rows / kGradTile);
         CombineArgs ca;
         ca.slab = (uint4*)la.slab; ca.e2_vec = la.e2_off / 8;
+        ca.past_cache = rows * L.Vp * 2 * (sampled ? 1 : 2) > kPastCacheBytes;
         ca.mu = ms.mu_out; ca.inv_z = ms.inv_z; ca.row0 = r0; ca.nk = ga.nk_total;
         ca.mu0t = la.mu0t; ca.mu0t_stride = la.mu0t_stride;
         ca.dzT_p = p->dW_prefix ? (uint4*)(ws + L.o_dzT_p) : nullptr;

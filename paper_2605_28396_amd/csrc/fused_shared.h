@@ -13,6 +13,7 @@ namespace adwin {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRowBytes = kBK * 2;   // 128 B of k per staged row
 
@@ -235,6 +236,10 @@ struct LogitPassArgs {
   HeavyList heavy;             // second sweep of the two-sweep scheme: entries taken out of dz
 };
 
+// Factors of a slab beyond this are in memory again by the time the next launch reads them, and go past the caches: a
+// quarter more than the last-level cache of 256 MiB.  Combine pass, us, kept / past: 297 MiB 74 / 76, 451 MiB 138 / 121.
+constexpr int64_t kPastCacheBytes = (int64_t)320 << 20;
+
 constexpr int kNarrowRows = kTileTokens / 2;
 
 // Modes of the direct-to-LDS logit kernel.
@@ -294,6 +299,7 @@ struct PrepareArgs {
 // Combine pass over one slab (see combine_kernel).
 struct CombineArgs {
   uint4* slab; int64_t e2_vec;          // E2 lies e2_vec 16-byte vectors after D
+  bool past_cache;                      // the factors exceed kPastCacheBytes
   const float* mu; const float* inv_z;      // per computed row
   const float* mu0t; int64_t mu0t_stride;   // reference of D per (vocabulary tile, slab row)
   int64_t row0;                         // computed-row index of slab row 0

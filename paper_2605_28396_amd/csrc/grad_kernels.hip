@@ -26,9 +26,26 @@ namespace adwin {
 // collapse into the logit gradient itself, dz = E2 (D - (mu - mu0)) / Z_s = p_s (d - mu),
 // written over D in the same image order, and the gradient GEMM runs on one factor.  A
 // streaming pass: 4 B read + 2 B written per slab element.
+// PAST: all of that past the caches (non-temporal), for slabs that exceed the last-level one (kPastCacheBytes): whatever
+// line is kept for the factors or for dz is evicted before anything asks for it.  us per pass, kept / past: 4,096
+// rows of V = 151,936 760 / 635 (4.9 and 5.9 TB/s), 24,000 rows 4540 / 3760, 1,286 rows 242 / 198; with the transposed copy,
+// 8,192 rows, 2050 / 1859; the GEMM that reads dz next 4090 / 4020 for the 24,000 rows (with the loads alone past the caches
+// the pass takes 4180 and the GEMM is 2 % slower).  3,139 rows of V = 11,912, a slab of 150 MB: 37 / 41.
 // ---------------------------------------------------------------------------------------
+template <bool PAST>
+__device__ __forceinline__ uint4 slab_load(const uint4* p) {
+  if constexpr (!PAST) return *p;
+  const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+template <bool PAST>
+__device__ __forceinline__ void slab_store(uint4* p, const uint4& v) {
+  if constexpr (!PAST) { *p = v; return; }
+  const u32x4 x = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(x, (u32x4*)p);
+}
 
-template <bool TR, bool SAMPLED = false>
+template <bool TR, bool SAMPLED, bool PAST>
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   // one workgroup per block (row tile rt = blockIdx.y, kt = blockIdx.x): 2048 vectors of 8
   // entries; vector q holds row q / 8, chunk position q % 8
@@ -71,13 +88,13 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
       const int q = (i0 + j) * 256 + threadIdx.x;
       const int64_t r = rbase + (q >> 3);
       if (!TR && (i0 + j) * 32 >= left) continue;
-      ys[j] = p2[q];
+      ys[j] = slab_load<PAST>(p2 + q);
       izs[j] = a.inv_z[r];
       if (SAMPLED) {
         ms[j] = a.cr[r];
         ids[j] = a.yid[r];
       } else {
-        xs[j] = p1[q];
+        xs[j] = slab_load<PAST>(p1 + q);
         ms[j] = a.mu[r];
         m0s[j] = a.mu0t[(int64_t)(kt >> 1) * a.mu0t_stride + rt * kTileTokens + (q >> 3)];
       }
@@ -133,7 +150,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
         uint4 o;
         o.x = pack_bf16(d[0], d[1]); o.y = pack_bf16(d[2], d[3]);
         o.z = pack_bf16(d[4], d[5]); o.w = pack_bf16(d[6], d[7]);
-        p1[q] = o;
+        slab_store<PAST>(p1 + q, o);
       }
     }
   }
@@ -173,7 +190,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
         o.y = tile[rl + 2][vl] | ((uint32_t)tile[rl + 3][vl] << 16);
         o.z = tile[rl + 4][vl] | ((uint32_t)tile[rl + 5][vl] << 16);
         o.w = tile[rl + 6][vl] | ((uint32_t)tile[rl + 7][vl] << 16);
-        dst[(((int64_t)vt * a.nkr + 4 * rt + j) * kGradTile + imgrow) * 8 + pos] = o;
+        slab_store<PAST>(dst + (((int64_t)vt * a.nkr + 4 * rt + j) * kGradTile + imgrow) * 8 + pos, o);
       }
     }
   }
@@ -668,14 +685,14 @@ hipError_t launch_hs_gather(const HsGatherArgs& a, int64_t rows, hipStream_t st)
 
 hipError_t launch_combine(bool transposed, bool sampled, const CombineArgs& a, int row_tiles, hipStream_t st) {
   const dim3 grid((unsigned)a.nk, (unsigned)row_tiles);
-  if (sampled) {
-    if (!transposed) return hipErrorInvalidValue;   // the sampled estimator contracts E2 as stored
-    combine_kernel<true, true><<<grid, 256, 0, st>>>(a);
-  } else if (transposed) {
-    combine_kernel<true><<<grid, 256, 0, st>>>(a);
-  } else {
-    combine_kernel<false><<<grid, 256, 0, st>>>(a);
-  }
+  if (sampled && !transposed) return hipErrorInvalidValue;   // the sampled estimator contracts E2 as stored
+#define ADWIN_LAUNCH(TR, SAMPLED)                                                  \
+  if (a.past_cache) combine_kernel<TR, SAMPLED, true><<<grid, 256, 0, st>>>(a);    \
+  else combine_kernel<TR, SAMPLED, false><<<grid, 256, 0, st>>>(a);
+  if (sampled) { ADWIN_LAUNCH(true, true) }
+  else if (transposed) { ADWIN_LAUNCH(true, false) }
+  else { ADWIN_LAUNCH(false, false) }
+#undef ADWIN_LAUNCH
   return hipGetLastError();
 }
 

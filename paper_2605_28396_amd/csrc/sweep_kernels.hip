@@ -220,7 +220,6 @@ __device__ __forceinline__ float acc_read(const float& a) {
 // offset: the compiler puts two wait states between a 16-byte buffer store and an instruction that overwrites its
 // data registers, but none if the store has one, and stores of this epilogue were seen to write the register's next
 // contents (an accumulator read right behind the store) once a second wave shared the SIMD.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_rsrc(__bf16* blk) {
   // extent: the tile's two blocks; flag word: the raw-buffer setting of the gfx9 family
   // (32-bit data format, no swizzle)

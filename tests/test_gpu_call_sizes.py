@@ -390,3 +390,40 @@ def test_merge_adds_in_the_order_of_64_lanes(tmp_path):
     """The sums over a row's strips, 16 rows to a workgroup (up to 64 strips) and four, bit for bit."""
     status, out = host_program.run(tmp_path, "merge_order_main", link=True)
     assert status == 0 and out.endswith("ok\n"), (status, out)
+
+
+@pytest.mark.parametrize("want", [(), DIAGNOSTICS, ("dW_prefix",)])
+@pytest.mark.parametrize("estimator", [O.EST_EXPECTED, O.EST_SAMPLED])
+@pytest.mark.parametrize("rows,V", [(520, 110000), (2100, 39000)])        # W row-major, and as tile images
+def test_slabs_past_the_caches(B, monkeypatch, rows, V, estimator, want):  # noqa: F811
+    """A slab whose factors exceed the last-level cache (320 MiB), and the same rows in slabs of 256, whose factors do not: the
+    statistics bit for bit, the gradients up to the order of their fp32 sums (V or `rows` terms, the partial sums
+    exact to 2^-24 each).  The last token tile holds 8 or 52 rows, the last vocabulary tile 48, 88 or (twice V, for the
+    one factor of the sampled estimator) 96 or 48 entries."""
+    factors = 1 if estimator == O.EST_SAMPLED else 2
+    V = V * 2 // factors
+    assert 2 * factors * ((V + 127) // 128 * 128) * ((rows + 255) // 256 * 256) > 320 << 20 > \
+        2 * factors * ((V + 127) // 128 * 128) * 256
+    monkeypatch.setenv("ADWIN_STRIPS2", "33")
+    w = synth.Workload(f"past_{V}", V, 128, 192, synth._offsets([rows - 100, 100]), np.array([rows - 100, 90], np.int32),
+                       synth.MODE_PREFIX_ONLY)
+    d = {k: v.cuda() for k, v in synth.hidden_problem(w).items()}
+    outs = []
+    for forced in (False, True):
+        if forced:
+            monkeypatch.setenv("ADWIN_SLAB_ROWS", "256")
+        c = B.FusedCall(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window, mode=w.mode,
+                        want=B.FusedCall.DEFAULT_OUTPUTS + want, estimator=estimator, reduction=O.RED_SUM)
+        assert (B.adwin_opd_fused_launch_info(c.p)["slabs"] > 1) == forced
+        c.workspace.fill_(255)
+        assert c.run() == B.ADWIN_OK
+        torch.cuda.synchronize()
+        outs.append(c.out)
+    for k in outs[0]:
+        a, b = outs[0][k], outs[1][k]
+        if k in ("dh_prefix", "dW_prefix"):
+            assert float(b.abs().max()) > 0
+            terms = V if k == "dh_prefix" else rows
+            assert (a - b).abs().max() <= terms ** 0.5 * 2.0 ** -24 * 8 * b.abs().max(), k
+        elif k != "batch":
+            assert torch.equal(a, b), k
