@@ -219,6 +219,14 @@ static bool rotate_k(int64_t n_tiles, int H_s, int H_t) {
   return n_tiles == 1 && (H_s > H_t ? H_s : H_t) >= 2048;
 }
 
+// Whether a sweep whose slab exceeds the caches stores the factors as whole lines past them (single_epilogue).  The shorter
+// the contraction, the more of a sweep are its stores.  us per sweep, plain pieces / lines, V = 151,936: H = 640 + 256,
+// 24,000 rows 8710 / 7790; 1536 + 1536, 16,384 rows 13830 / 13320; 8,192 rows of 1152 + 1792 (V = 124,200) 5515 / 5215, of
+// 1536 + 2048 7940 / 7640, of 2048 + 2048 8730 / 8430, of 2560 + 2560 10880 / 10640.  With 2048 + 4096 it depends on the
+// GPU, 24.8 / 24.6 ms to 24.6 / 25.6 for 16,384 rows.  The sweep with both factors and diagnostics has no registers for
+// the group on its way and loses (2800 / 3070).
+static bool sweep_whole_lines(int H) { return H <= 4096; }
+
 static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) {
   FusedLayout L;
   const int64_t n_pad = hp.n_pad > 0 ? hp.n_pad : kTileTokens;
@@ -517,6 +525,8 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         const int64_t rows = (n_pad - r0 < L.slab_rows) ? n_pad - r0 : L.slab_rows;
         la.tile0 = (int)(r0 / kTileTokens); la.n_tiles = (int)(rows / kTileTokens);
         la.e2_off = rows * L.Vp;
+        const bool past_cache = rows * L.Vp * 2 * (sampled ? 1 : 2) > kPastCacheBytes;
+        la.lines = past_cache && sweep_whole_lines(p->H_s + p->H_t);
         la.strips = sweep_strips(la.n_tiles, vt_total, &la.long_first);
         la.part = (float*)(ws + L.o_part) - r0; la.n_pad = rows;       // partials of this slab's rows
         la.narrow = L.direct_w && la.n_tiles == 1 && hp.n_rows - r0 <= kNarrowRows;
@@ -538,7 +548,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         ga.row_tiles = (int)(rows / kGradTile);
         CombineArgs ca;
         ca.slab = (uint4*)la.slab; ca.e2_vec = la.e2_off / 8;
-        ca.past_cache = rows * L.Vp * 2 * (sampled ? 1 : 2) > kPastCacheBytes;
+        ca.past_cache = past_cache;
         ca.mu = ms.mu_out; ca.inv_z = ms.inv_z; ca.row0 = r0; ca.nk = ga.nk_total;
         ca.mu0t = la.mu0t; ca.mu0t_stride = la.mu0t_stride;
         ca.dzT_p = p->dW_prefix ? (uint4*)(ws + L.o_dzT_p) : nullptr;

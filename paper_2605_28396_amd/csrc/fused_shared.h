@@ -227,6 +227,7 @@ struct LogitPassArgs {
   // single-sweep mode: fixed per-row references and the offset of the second slab half
   References ref;
   int64_t e2_off;
+  bool lines;                  // factors as whole lines, past the caches (sweep_whole_lines)
   // per-(vocabulary tile, slab row) reference mu0 of the D factor, written by the sweep
   float* mu0t; int64_t mu0t_stride;
   // direct-to-LDS kernel: tile images of the four operands (see row_image_kernel)

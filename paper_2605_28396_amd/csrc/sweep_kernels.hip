@@ -225,20 +225,34 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_rsrc(__bf16* blk) {
   // (32-bit data format, no swizzle)
   return __builtin_amdgcn_make_buffer_rsrc(blk, 0, 2 * kImgBytesSlab, 0x00020000);
 }
-__device__ __forceinline__ void slab_store16(__amdgpu_buffer_rsrc_t r, int off, const float (&x)[8]) {
+__device__ __forceinline__ u32x4 pack_chunk(const float (&x)[8]) {
   u32x4 o;
   o.x = pack_bf16(x[0], x[1]); o.y = pack_bf16(x[2], x[3]);
   o.z = pack_bf16(x[4], x[5]); o.w = pack_bf16(x[6], x[7]);
-  __builtin_amdgcn_raw_buffer_store_b128(o, r, off, 0, 0);
+  return o;
+}
+__device__ __forceinline__ void slab_store16(__amdgpu_buffer_rsrc_t r, int off, const float (&x)[8]) {
+  __builtin_amdgcn_raw_buffer_store_b128(pack_chunk(x), r, off, 0, 0);
 }
 
-template <bool TAIL, bool DIAG, bool WRITE_D, bool WRITE_E2, int FN>
+// LINES: the factors as whole lines, past the caches (sweep_whole_lines says when).  A lane has 16 bytes of one row at a time,
+// so that a store as above is 64 pieces of 16 bytes in 32 lines, which only the L2 can put together.  Here the wave lays the
+// chunks of 32 rows x 64 entries (a group, 4 KiB) into the LDS, in image order, and stores it as four instructions of
+// 1 KiB in one piece, 8 lines each; the operations of a wave on the LDS take effect in order, so the next group may be
+// written over it at once.  What gains is not the fewer pieces (kept in the caches, whole lines take as long as
+// pieces) but that the lines of a slab that the caches cannot hold no longer push W and h out of the L2; non-temporal pieces
+// take up to 1.8 times as long as plain ones.
+typedef __attribute__((address_space(3))) u32x4* LdsVecPtr;
+__device__ __forceinline__ LdsVecPtr lds_vec(uint32_t addr) { return (LdsVecPtr)(uintptr_t)addr; }
+constexpr int kGroupBytes = 32 * kRowBytes;
+
+template <bool TAIL, bool DIAG, bool WRITE_D, bool WRITE_E2, int FN, bool LINES>
 __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const f32x16 (&zt)[4][FN],
                                                 LaneSums& sm, const float (&rs2)[2],
                                                 const float (&rt2)[2], float (&mu0)[2],
                                                 const float (&zyt)[2], const int (&yid)[2],
                                                 __bf16* blk, int64_t e2_off, int wrow,
-                                                int v0, int V, int lane, float* mu0_out) {
+                                                int v0, int V, int lane, float* mu0_out, uint32_t side) {
   // lane's entries of block fm: v0 + fm*32 + 16*half + e, e = 0..15; chunk positions as in dz_epilogue
   const int half = lane >> 5, vlane = v0 + 16 * half, key2 = ((lane >> 1) & 7) ^ (2 * half);
   // byte offset of chunk cb of the lane's row (fn = 0, first block): rowb ^ (cb << 4)
@@ -250,6 +264,29 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const
     return (b ^ (((fm & 1) * 4 + p) << 4)) + (fm >> 1) * kImgBytesSlab + fn * 32 * kRowBytes;
   };
   const __amdgpu_buffer_rsrc_t rd = slab_rsrc(blk), re = slab_rsrc(blk + e2_off);
+  // chunk cb of the lane's row in the LDS: row_lds ^ (cb << 4)
+  const uint32_t row_lds = side + (uint32_t)((lane & 31) * kRowBytes + (key2 << 4));
+  u32x4 group[4];                          // a group out of the LDS, stored when the next one is under way
+  int group_off = -1;
+  bool group_is_d = false;
+  auto store_group = [&]() __attribute__((always_inline)) {
+    if (group_off < 0) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      __builtin_amdgcn_raw_buffer_store_b128(group[j], group_is_d ? rd : re,
+                                             wrow * kRowBytes + lane * 16 + group_off + j * 1024, 0, 2);
+    group_off = -1;
+  };
+  auto fetch_group = [&](bool d, int fn, int pair) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) group[j] = *lds_vec(side + (uint32_t)(j * 1024 + lane * 16));
+    group_is_d = d;
+    group_off = pair * kImgBytesSlab + fn * kGroupBytes;
+  };
+  auto put = [&](bool d, int fn, int fm, int p, const float (&x)[8]) __attribute__((always_inline)) {
+    if constexpr (LINES) *lds_vec(row_lds ^ (uint32_t)(((fm & 1) * 4 + p) << 4)) = pack_chunk(x);
+    else slab_store16(d ? rd : re, offset(fn, fm, p), x);
+  };
   float Zs[2], As[2], Zt[2], Bt[2];
   int cnt[2], vy[2];
 #pragma unroll
@@ -278,8 +315,7 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const
       }
       e2[e] = es;
     }
-    if (WRITE_E2)
-      slab_store16(re, offset(fn, fm, p), e2);
+    if (WRITE_E2) put(false, fn, fm, p, e2);
   };
   // Second factor: D = d - mu0 with mu0 the strip's running mean of d = z_s - z_t under the
   // student weights, this tile included (both half-columns of the row).  A heavy entry
@@ -298,31 +334,56 @@ __device__ __forceinline__ void single_epilogue(const f32x16 (&zs)[4][FN], const
 #pragma unroll
     for (int e = 0; e < 8; ++e)
       dd[e] = (acc_read(zs[fm][fn][p * 8 + e]) - m0) - acc_read(zt[fm][fn][p * 8 + e]);
-    slab_store16(rd, offset(fn, fm, p), dd);
+    put(true, fn, fm, p, dd);
   };
-  // The stores of D have little arithmetic of their own to hide behind, so column 0's second
-  // pass is interleaved with column 1's first pass, whose exponentials cover them.
-#pragma unroll
-  for (int fm = 0; fm < 4; ++fm)
-#pragma unroll
-    for (int p = 0; p < 2; ++p) sums8(0, fm, p);
-  float m0 = 0.f;
-  if (WRITE_D) m0 = mean_of(0);
-  if constexpr (FN == 2) {
+  if constexpr (LINES) {
+    float m0[2] = {0.f, 0.f};
+    auto group_e = [&](int fn, int pair) __attribute__((always_inline)) {
+      sums8(fn, 2 * pair, 0);
+      store_group();
+      sums8(fn, 2 * pair, 1); sums8(fn, 2 * pair + 1, 0); sums8(fn, 2 * pair + 1, 1);
+      fetch_group(false, fn, pair);
+    };
+    auto group_d = [&](int fn, int pair) __attribute__((always_inline)) {
+      if (!WRITE_D) return;
+      factor8(fn, 2 * pair, 0, m0[fn]);
+      store_group();
+      factor8(fn, 2 * pair, 1, m0[fn]); factor8(fn, 2 * pair + 1, 0, m0[fn]); factor8(fn, 2 * pair + 1, 1, m0[fn]);
+      fetch_group(true, fn, pair);
+    };
+    // column 0's second pass between column 1's groups of the first (as below)
+    group_e(0, 0); group_e(0, 1);
+    if (WRITE_D) m0[0] = mean_of(0);
+    group_e(FN - 1, 0); group_d(0, 0);
+    group_e(FN - 1, 1); group_d(0, 1);
+    if (WRITE_D) m0[FN - 1] = mean_of(FN - 1);
+    group_d(FN - 1, 0); group_d(FN - 1, 1);
+    store_group();
+  } else {
+    // The stores of D have little arithmetic of their own to hide behind, so column 0's second
+    // pass is interleaved with column 1's first pass, whose exponentials cover them.
 #pragma unroll
     for (int fm = 0; fm < 4; ++fm)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        sums8(1, fm, p);
-        if (WRITE_D) factor8(0, fm, p, m0);
-      }
-    if (WRITE_D) m0 = mean_of(1);
-  }
-  if (WRITE_D) {
+      for (int p = 0; p < 2; ++p) sums8(0, fm, p);
+    float m0 = 0.f;
+    if (WRITE_D) m0 = mean_of(0);
+    if constexpr (FN == 2) {
 #pragma unroll
-    for (int fm = 0; fm < 4; ++fm)
+      for (int fm = 0; fm < 4; ++fm)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) factor8(FN - 1, fm, p, m0);
+        for (int p = 0; p < 2; ++p) {
+          sums8(1, fm, p);
+          if (WRITE_D) factor8(0, fm, p, m0);
+        }
+      if (WRITE_D) m0 = mean_of(1);
+    }
+    if (WRITE_D) {
+#pragma unroll
+      for (int fm = 0; fm < 4; ++fm)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) factor8(FN - 1, fm, p, m0);
+    }
   }
 #pragma unroll
   for (int fn = 0; fn < FN; ++fn) {
@@ -473,7 +534,10 @@ struct DmaTile {
   static constexpr int kTokens = 128 * FN, kStages = FN == 2 ? 3 : 4;
   static constexpr int kStage = (kTileVocab + kTokens) * kRowBytes;     // 48 KiB, 32 KiB
   static constexpr int kRing = kStages * kStage;                        // 144 KiB, 128 KiB
-  static constexpr int kRefLds = kRing + 4 * 2 * kMaxRefParts * 256;    // ... and the references of the single sweep
+  // behind the ring, 4 KiB to a wave: the references of the single sweep, then (LINES) rows on their way to the slab
+  static constexpr int kSideLds = 4096;
+  static_assert(2 * kMaxRefParts * 256 <= kSideLds, "the references of a wave");
+  static constexpr int kRefLds = kRing + 4 * kSideLds;
   static constexpr int kPerWave = (kTileVocab + kTokens) / 8 / 4;       // wave-loads per stage: 12, 8
   static constexpr int kAhead = kStages - 1;                            // k-steps from a load to its use
 };
@@ -652,10 +716,11 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][FN], bf16x8 (&fa)[2
 // takes its 8 rows' 128 bytes from 8 rows of W, the lane offsets following the image's row
 // permutation and chunk swizzle, so that the LDS holds the same bytes; rows beyond V repeat the
 // last one (their logits are masked like the image's zero rows).
-template <int MODE, bool DIRECT, int FN = 2>
+template <int MODE, bool DIRECT, int FN = 2, bool LINES = false>
 __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   extern __shared__ __align__(16) char lds[];
   typedef DmaTile<FN> Tile;
+  static_assert(!LINES || FN == 2, "groups of two token columns");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int strip, tt_local;
@@ -773,12 +838,12 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   }
   // The references go into the LDS behind the ring, ahead of the first stages: loaded into registers they
   // made every workgroup wait for one more round trip before it asked for its first stage.
-  const uint32_t ref_lds = lds0 + Tile::kRing + (uint32_t)wave * (2 * kMaxRefParts * 256);
+  const uint32_t side_lds = lds0 + Tile::kRing + (uint32_t)wave * Tile::kSideLds;
   if (kSingle) {
     const uint32_t row = (uint32_t)(lane & (32 * FN - 1)) * 4u;
     for (int k = 0; k < 2 * a.ref.parts; ++k) {
       const int head = k >= a.ref.parts, plane = head ? k - a.ref.parts : k;
-      dma4_at<0>(ref_lds + (uint32_t)k * 256u, row,
+      dma4_at<0>(side_lds + (uint32_t)k * 256u, row,
                  (const char*)(a.ref.max[head] + plane * a.ref.n_pad + row_tile + wave * (32 * FN)));
     }
   }
@@ -850,7 +915,7 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     wait_vm<Tile::kAhead * Tile::kPerWave>();  // all but the stages
 #pragma unroll
     for (int fn = 0; fn < FN; ++fn) {
-      const LdsFloat p = (LdsFloat)(uintptr_t)(ref_lds + (uint32_t)(fn * 32 + (lane & 31)) * 4u);
+      const LdsFloat p = (LdsFloat)(uintptr_t)(side_lds + (uint32_t)(fn * 32 + (lane & 31)) * 4u);
       float m[2] = {p[0], p[a.ref.parts * 64]};
       for (int k = 1; k < a.ref.parts; ++k) { m[0] = fmaxf(m[0], p[k * 64]); m[1] = fmaxf(m[1], p[(a.ref.parts + k) * 64]); }
       rs2[fn] = References::scaled(m[0]);
@@ -904,9 +969,9 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     } else {
       float* m0t = a.mu0t ? a.mu0t + (int64_t)vt * a.mu0t_stride + (int64_t)(tt - a.tile0) * kTileTokens + wave_row : nullptr;
       if (tail) {
-        single_epilogue<true, kDiag, kWriteD, kWriteE2, FN>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave_row, v0, a.V, lane, m0t);
+        single_epilogue<true, kDiag, kWriteD, kWriteE2, FN, LINES>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave_row, v0, a.V, lane, m0t, side_lds);
       } else {
-        single_epilogue<false, kDiag, kWriteD, kWriteE2, FN>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave_row, v0, a.V, lane, m0t);
+        single_epilogue<false, kDiag, kWriteD, kWriteE2, FN, LINES>(zs, zt, sm, rs2, rt2, mu, zyt, yid, blk, a.e2_off, wave_row, v0, a.V, lane, m0t, side_lds);
       }
     }
   }
@@ -1376,6 +1441,13 @@ hipError_t sweep_kernels_opt_in() {
   ADWIN_OPT_IN_MODE(kModeSingleFwd)
   ADWIN_OPT_IN_MODE(kModeSingleFwdDiag)
 #undef ADWIN_OPT_IN_MODE
+#define ADWIN_OPT_IN_MODE(M)                                                          \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, false, 2, true>), DmaTile<2>::kRefLds)       \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true, 2, true>), DmaTile<2>::kRefLds)
+  ADWIN_OPT_IN_MODE(kModeSingle)
+  ADWIN_OPT_IN_MODE(kModeSingleE2)
+  ADWIN_OPT_IN_MODE(kModeSingleE2Diag)
+#undef ADWIN_OPT_IN_MODE
 #undef ADWIN_OPT_IN
   return hipSuccess;
 }
@@ -1416,14 +1488,22 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStre
     if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
     else logit_pass_dma_kernel<M, false><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);            \
     break;
+#define ADWIN_CASE_WRITES(M)                                                                \
+  case M:                                                                                   \
+    if (a.lines && a.direct_w) logit_pass_dma_kernel<M, true, 2, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
+    else if (a.lines) logit_pass_dma_kernel<M, false, 2, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
+    else if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
+    else logit_pass_dma_kernel<M, false><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);            \
+    break;
     ADWIN_CASE(kModeStats)
     ADWIN_CASE(kModeDz)
-    ADWIN_CASE(kModeSingle)
+    ADWIN_CASE_WRITES(kModeSingle)
     ADWIN_CASE(kModeSingleDiag)
-    ADWIN_CASE(kModeSingleE2)
-    ADWIN_CASE(kModeSingleE2Diag)
+    ADWIN_CASE_WRITES(kModeSingleE2)
+    ADWIN_CASE_WRITES(kModeSingleE2Diag)
     ADWIN_CASE(kModeSingleFwd)
     ADWIN_CASE(kModeSingleFwdDiag)
+#undef ADWIN_CASE_WRITES
 #undef ADWIN_CASE
     default: return hipErrorInvalidValue;
   }
