@@ -219,6 +219,23 @@ static bool rotate_k(int64_t n_tiles, int H_s, int H_t) {
   return n_tiles == 1 && (H_s > H_t ? H_s : H_t) >= 2048;
 }
 
+// Where the sweep of `n_tiles` token tiles gets W from.  With one token tile no other workgroup asks for its lines of W, and
+// they displace the hidden states (3 MB at H = 2048 + 4096) that every workgroup of a die reads again for every tile: 20 %
+// of those reads missed the L2.  Lines of W past the caches: us per sweep, kept / past, V = 151,936: 256 rows, H = 2048 + 4096
+// 525 / 496; 100 rows 423 / 406; 230 rows, 1024 + 1024 208 / 190; statistics of 60 rows, 2048 + 2048 256 / 245.
+// Not where both weights fit the last-level cache, which may hold them from the call before (100 rows of V = 100,000,
+// 512 + 512 134 / 138 per call, statistics with 512 + 768 71 / 87); and W_s, which the gradient GEMM reads again, only
+// if that exceeds the cache (per call, W_t past / both: 16,000 entries of 3584 + 4608 152 / 158, 60 rows of V = 151,936,
+// 512 + 768 182 / 182; 230 rows of 1024 + 1024, 297 MiB of W_s, 363 / 353).  With two token tiles and more, whose workgroups
+// share the lines, nothing or up to 10 % worse (4,096 rows).  A row of W is whole lines (H is a multiple of 64) if
+// the first one begins a line; else neighbouring pieces of a row share lines, which would be fetched twice.
+static int sweep_stage(const adwin_opd_problem* p, bool direct_w, int n_tiles, bool need_g) {
+  if (!direct_w) return kStageImages;
+  const int64_t student = 2 * (int64_t)p->V * p->H_s, teacher = 2 * (int64_t)p->V * p->H_t;
+  if (n_tiles > 1 || student + teacher <= kPastCacheBytes || (((uintptr_t)p->W_s | (uintptr_t)p->W_t) & 127)) return kStageRows;
+  return !need_g || student > ((int64_t)256 << 20) ? kStageRowsOnce : kStageTeacherOnce;
+}
+
 // Whether a sweep whose slab exceeds the caches stores the factors as whole lines past them (single_epilogue).  The shorter
 // the contraction, the more of a sweep are its stores.  us per sweep, plain pieces / lines, V = 151,936: H = 640 + 256,
 // 24,000 rows 8710 / 7790; 1536 + 1536, 16,384 rows 13830 / 13320; 8,192 rows of 1152 + 1792 (V = 124,200) 5515 / 5215, of
@@ -500,7 +517,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     la.Wt_img = (const char*)(ws + L.o_wt_img); la.Ws_img = (const char*)(ws + L.o_ws_img);
     la.ht_img = (const char*)(ws + L.o_ht_img); la.hs_img = (const char*)(ws + L.o_hs_img);
     la.long_first = 0;
-    la.heavy = heavy; la.narrow = false; la.direct_w = L.direct_w; la.rotate = rotate_k(n_tiles, p->H_s, p->H_t);
+    la.heavy = heavy; la.narrow = false; la.stage = L.direct_w ? kStageRows : kStageImages; la.rotate = rotate_k(n_tiles, p->H_s, p->H_t);
     MergeArgs m{};
     m.part = la.part; m.strips = L.strips; m.n_pad = n_pad; m.n_rows = hp.n_rows;
     m.row_idx = pl.row_idx;
@@ -529,6 +546,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
         la.lines = past_cache && sweep_whole_lines(p->H_s + p->H_t);
         la.strips = sweep_strips(la.n_tiles, vt_total, &la.long_first);
         la.part = (float*)(ws + L.o_part) - r0; la.n_pad = rows;       // partials of this slab's rows
+        la.stage = sweep_stage(p, L.direct_w, la.n_tiles, need_g);
         la.narrow = L.direct_w && la.n_tiles == 1 && hp.n_rows - r0 <= kNarrowRows;
         phase(ADWIN_PHASE_STATS);
         const int sweep_mode = !need_g ? (diag ? kModeSingleFwdDiag : kModeSingleFwd)

@@ -78,10 +78,15 @@ __device__ __forceinline__ void strip_and_tile(int vid, int tg, int strips, int 
 // straight into M0, and the callers keep the wave's share of both addresses in operands that
 // are set up once, so that a load costs three instructions: a wave issues one instruction at a
 // time and the loads share the shadow of an MFMA with LDS reads.
-template <int IMM>
+// ONCE: lines that nobody reads again, the first to be evicted.
+template <int IMM, bool ONCE = false>
 __device__ __forceinline__ void dma16_at(uint32_t lds_base, uint32_t voff, const char* sbase) {
-  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_base), "v"(voff), "s"(sbase), "n"(IMM) : "memory", "scc");
+  if constexpr (ONCE)
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :: "s"(lds_base), "v"(voff), "s"(sbase), "n"(IMM) : "memory", "scc");
+  else
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds_base), "v"(voff), "s"(sbase), "n"(IMM) : "memory", "scc");
 }
 
 // Wave-uniform bookkeeping of a k-step pipeline, written as instructions at a fixed place:
@@ -232,16 +237,21 @@ struct LogitPassArgs {
   float* mu0t; int64_t mu0t_stride;
   // direct-to-LDS kernel: tile images of the four operands (see row_image_kernel)
   const char* Wt_img; const char* Ws_img; const char* ht_img; const char* hs_img;
-  bool direct_w;               // stage W from W_s / W_t themselves; there are no W images
+  int stage;                   // kStage*: where the W tiles come from
   bool rotate;                 // ... the heads of strip s from k-step s on, the first ones last (see rotate_k)
   HeavyList heavy;             // second sweep of the two-sweep scheme: entries taken out of dz
 };
 
 // Factors of a slab beyond this are in memory again by the time the next launch reads them, and go past the caches: a
 // quarter more than the last-level cache of 256 MiB.  Combine pass, us, kept / past: 297 MiB 74 / 76, 451 MiB 138 / 121.
+// The weights of a call likewise (sweep_stage).
 constexpr int64_t kPastCacheBytes = (int64_t)320 << 20;
 
 constexpr int kNarrowRows = kTileTokens / 2;
+
+// Where the W tiles of the direct-to-LDS logit kernel come from: tile images; the row-major weights; those, of a single token
+// tile, with all lines of W or the teacher's past the caches (sweep_stage).
+constexpr int kStageImages = 0, kStageRows = 1, kStageRowsOnce = 2, kStageTeacherOnce = 3;
 
 // Modes of the direct-to-LDS logit kernel.
 constexpr int kModeStats = 0;   // online (running-max) statistics only

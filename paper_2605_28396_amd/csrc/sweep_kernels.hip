@@ -584,11 +584,11 @@ constexpr int kImgBBytes = kTileTokens * kRowBytes;   // 32 KiB: one h block
 // address + 1024 wave; voffw[j] = 16 lane + 1024 (wave + 4 j): the wave's part of both addresses
 // is folded into operands that are set up once, the rest is a literal.  voffa: the same for the
 // A block, or the lane's offsets in the row-major W (direct staging).
-template <int I>
+template <int I, bool ONCE>
 __device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voffa)[4], const uint32_t (&voffw)[8],
                                         const char* sA, const char* sB) {
   if constexpr (I < kTileVocab / 32)
-    dma16_at<4 * I * 1024>(lds_wave, voffa[I], sA);
+    dma16_at<4 * I * 1024, ONCE>(lds_wave, voffa[I], sA);
   else
     dma16_at<(kTileVocab / 8 + 4 * (I - kTileVocab / 32)) * 1024>(lds_wave, voffw[I - kTileVocab / 32], sB);
 }
@@ -614,7 +614,7 @@ __device__ __forceinline__ void dma_one(uint32_t lds_wave, const uint32_t (&voff
 // per sub-step; (a_lo, a_hi), (b_lo, b_hi) = the blocks that the previous k-step loaded, on
 // return those that this one loaded.
 // A_STEP: bytes from one A block to the next (a W image's block, or a row-major W's 64 entries).
-template <bool LAST, bool FRESH, int RELAXED, int A_STEP, int FN>
+template <bool LAST, bool FRESH, int RELAXED, int A_STEP, int FN, bool ONCE>
 __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][FN], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][FN],
                                             uint32_t& r_rd, uint32_t ring_begin, uint32_t ring_end,
                                             const uint32_t (&swA)[4], const uint32_t (&swB)[4],
@@ -634,7 +634,7 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][FN], bf16x8 (&fa)[2
   acc[FMI][FNI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[(KK) & 1][FMI], fb[(KK) & 1][FNI], \
                                                           (FRESH && (KK) == 0) ? kZeroTile : acc[FMI][FNI], 0, 0, 0); \
   ADWIN_FENCE
-#define ADWIN_DMA(I) dma_one<I>(r_wr, voffa, voffw, addr_of(a_lo, a_hi), addr_of(b_lo, b_hi)); ADWIN_FENCE
+#define ADWIN_DMA(I) dma_one<I, ONCE>(r_wr, voffa, voffw, addr_of(a_lo, a_hi), addr_of(b_lo, b_hi)); ADWIN_FENCE
   // sub-step KK: 8 MFMAs; reads of the next sub-step's fragments from slot R when READ; H0..H3:
   // bookkeeping in the shadows of the first four MFMAs.  xa, xb: the lane's LDS addresses of its
   // first A and B fragment, formed once (and kept from being re-associated with the fragments'
@@ -712,14 +712,16 @@ __device__ __forceinline__ void sweep_kstep(f32x16 (&acc)[4][FN], bf16x8 (&fa)[2
 #undef ADWIN_FENCE
 }
 
-// DIRECT: the W tiles are staged from the row-major weights instead of their images: wave-load I
+// STAGE, where the W tiles come from.  Rows: the row-major weights instead of their images: wave-load I
 // takes its 8 rows' 128 bytes from 8 rows of W, the lane offsets following the image's row
 // permutation and chunk swizzle, so that the LDS holds the same bytes; rows beyond V repeat the
-// last one (their logits are masked like the image's zero rows).
-template <int MODE, bool DIRECT, int FN = 2, bool LINES = false>
+// last one (their logits are masked like the image's zero rows).  Rows once: the same, of a single token tile, whose lines
+// of W go past the L2; or those of the teacher only (sweep_stage).
+template <int MODE, int STAGE, int FN = 2, bool LINES = false>
 __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   extern __shared__ __align__(16) char lds[];
   typedef DmaTile<FN> Tile;
+  constexpr bool DIRECT = STAGE != kStageImages, kOnce = STAGE >= kStageRowsOnce;
   static_assert(!LINES || FN == 2, "groups of two token columns");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -900,13 +902,13 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     addr_advance<kImgBBytes>(b_lo, b_hi);
     const char* ldA = addr_of(a_lo, a_hi);
     const char* ldB = addr_of(b_lo, b_hi);
-    dma_one<0>(dst, voffa, voffw, ldA, ldB); dma_one<1>(dst, voffa, voffw, ldA, ldB);
-    dma_one<2>(dst, voffa, voffw, ldA, ldB); dma_one<3>(dst, voffa, voffw, ldA, ldB);
-    dma_one<4>(dst, voffa, voffw, ldA, ldB); dma_one<5>(dst, voffa, voffw, ldA, ldB);
-    dma_one<6>(dst, voffa, voffw, ldA, ldB); dma_one<7>(dst, voffa, voffw, ldA, ldB);
+    dma_one<0, kOnce>(dst, voffa, voffw, ldA, ldB); dma_one<1, kOnce>(dst, voffa, voffw, ldA, ldB);
+    dma_one<2, kOnce>(dst, voffa, voffw, ldA, ldB); dma_one<3, kOnce>(dst, voffa, voffw, ldA, ldB);
+    dma_one<4, kOnce>(dst, voffa, voffw, ldA, ldB); dma_one<5, kOnce>(dst, voffa, voffw, ldA, ldB);
+    dma_one<6, kOnce>(dst, voffa, voffw, ldA, ldB); dma_one<7, kOnce>(dst, voffa, voffw, ldA, ldB);
     if constexpr (FN == 2) {
-      dma_one<8>(dst, voffa, voffw, ldA, ldB); dma_one<9>(dst, voffa, voffw, ldA, ldB);
-      dma_one<10>(dst, voffa, voffw, ldA, ldB); dma_one<11>(dst, voffa, voffw, ldA, ldB);
+      dma_one<8, kOnce>(dst, voffa, voffw, ldA, ldB); dma_one<9, kOnce>(dst, voffa, voffw, ldA, ldB);
+      dma_one<10, kOnce>(dst, voffa, voffw, ldA, ldB); dma_one<11, kOnce>(dst, voffa, voffw, ldA, ldB);
     }
     ADWIN_COUNT_LOADS()
   }
@@ -927,17 +929,20 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
   f32x16 zt[4][FN], zs[4][FN];
   bf16x8 fa[2][4], fb[2][FN];
   // one k-step: consume slot r_rd, prefetch fragments from the following slot, load into the one after
-  auto step = [&](auto last_c, auto fresh_c, auto relaxed_c, f32x16 (&acc)[4][FN], bool relaxed)
+  auto step = [&](auto last_c, auto fresh_c, auto relaxed_c, auto once_c, f32x16 (&acc)[4][FN], bool relaxed)
                   __attribute__((always_inline)) {
     constexpr bool kLast = decltype(last_c)::value, kFresh = decltype(fresh_c)::value;
     constexpr int kRelaxed = decltype(relaxed_c)::value;
-    sweep_kstep<kLast, kFresh, kRelaxed, kAStep, FN>(acc, fa, fb, r_rd, ring_begin, ring_end, swA, swB, voffa, voffw,
+    sweep_kstep<kLast, kFresh, kRelaxed, kAStep, FN, decltype(once_c)::value>(acc, fa, fb, r_rd, ring_begin, ring_end, swA, swB, voffa, voffw,
                                          a_lo, a_hi, b_lo, b_hi, relaxed);
     ADWIN_COUNT_LOADS()
   };
   const std::true_type yes{};
   const std::false_type no{};
   const std::integral_constant<int, 0> strict{};
+  // the loads of a head's steps, of which the last kAhead already ask for the other's blocks
+  const std::integral_constant<bool, kOnce> once_t{};
+  const std::integral_constant<bool, STAGE == kStageRowsOnce> once_s{};
   const std::integral_constant<int, kEpilogueStores> after_epilogue{};
   for (int vt = vt_begin; vt < vt_end; ++vt) {
     const int v0 = vt * kTileVocab;
@@ -953,11 +958,11 @@ __global__ __launch_bounds__(256) void logit_pass_dma_kernel(LogitPassArgs a) {
     for (int i = 0; i < FN; ++i) fb[0][i] = lds_frag(r_rd + swB[0])[i * 32 * kRowBytes / 16];
     // teacher: nk_t k-steps (the first on a zero addend; after an epilogue its wait leaves that
     // epilogue's stores in flight), then student: nk_s k-steps, the last without a barrier
-    step(no, yes, after_epilogue, zt, vt != vt_begin);
-    for (int s = 1; s < nk_t; ++s) step(no, no, strict, zt, false);
-    step(no, yes, strict, zs, false);
-    for (int s = 1; s + 1 < nk_s; ++s) step(no, no, strict, zs, false);
-    step(yes, no, strict, zs, false);
+    step(no, yes, after_epilogue, once_t, zt, vt != vt_begin);
+    for (int s = 1; s < nk_t; ++s) step(no, no, strict, once_t, zt, false);
+    step(no, yes, strict, once_s, zs, false);
+    for (int s = 1; s + 1 < nk_s; ++s) step(no, no, strict, once_s, zs, false);
+    step(yes, no, strict, once_s, zs, false);
     wait_vm<(Tile::kAhead - 1) * Tile::kPerWave>();      // the next tile's step 0 (see the top of the loop)
     const bool tail = v0 + kTileVocab > a.V;
     const int wave_row = wave * (32 * FN);                // of the 256-row image
@@ -1425,15 +1430,17 @@ hipError_t sweep_kernels_opt_in() {
   ADWIN_OPT_IN(logit_pass_kernel<false>, kLogitLds)
   ADWIN_OPT_IN(logit_pass_kernel<true>, kLogitLds)
 #define ADWIN_OPT_IN_MODE(M)                                                  \
-  ADWIN_OPT_IN((logit_pass_dma_kernel<M, false>), DmaTile<2>::kRefLds)        \
-  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true>), DmaTile<2>::kRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageImages>), DmaTile<2>::kRefLds) \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageRows>), DmaTile<2>::kRefLds)
   ADWIN_OPT_IN_MODE(kModeStats)
   ADWIN_OPT_IN_MODE(kModeDz)
 #undef ADWIN_OPT_IN_MODE
 #define ADWIN_OPT_IN_MODE(M)                                                  \
-  ADWIN_OPT_IN((logit_pass_dma_kernel<M, false>), DmaTile<2>::kRefLds)        \
-  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true>), DmaTile<2>::kRefLds)         \
-  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true, 1>), DmaTile<1>::kRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageImages>), DmaTile<2>::kRefLds) \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageRows>), DmaTile<2>::kRefLds)   \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageRowsOnce>), DmaTile<2>::kRefLds)    \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageRows, 1>), DmaTile<1>::kRefLds)     \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageRowsOnce, 1>), DmaTile<1>::kRefLds)
   ADWIN_OPT_IN_MODE(kModeSingle)
   ADWIN_OPT_IN_MODE(kModeSingleDiag)
   ADWIN_OPT_IN_MODE(kModeSingleE2)
@@ -1442,9 +1449,17 @@ hipError_t sweep_kernels_opt_in() {
   ADWIN_OPT_IN_MODE(kModeSingleFwdDiag)
 #undef ADWIN_OPT_IN_MODE
 #define ADWIN_OPT_IN_MODE(M)                                                          \
-  ADWIN_OPT_IN((logit_pass_dma_kernel<M, false, 2, true>), DmaTile<2>::kRefLds)       \
-  ADWIN_OPT_IN((logit_pass_dma_kernel<M, true, 2, true>), DmaTile<2>::kRefLds)
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageImages, 2, true>), DmaTile<2>::kRefLds) \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageRows, 2, true>), DmaTile<2>::kRefLds)
   ADWIN_OPT_IN_MODE(kModeSingle)
+  ADWIN_OPT_IN_MODE(kModeSingleE2)
+  ADWIN_OPT_IN_MODE(kModeSingleE2Diag)
+#undef ADWIN_OPT_IN_MODE
+#define ADWIN_OPT_IN_MODE(M)                                                          \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageTeacherOnce>), DmaTile<2>::kRefLds)    \
+  ADWIN_OPT_IN((logit_pass_dma_kernel<M, kStageTeacherOnce, 1>), DmaTile<1>::kRefLds)
+  ADWIN_OPT_IN_MODE(kModeSingle)
+  ADWIN_OPT_IN_MODE(kModeSingleDiag)
   ADWIN_OPT_IN_MODE(kModeSingleE2)
   ADWIN_OPT_IN_MODE(kModeSingleE2Diag)
 #undef ADWIN_OPT_IN_MODE
@@ -1467,47 +1482,53 @@ hipError_t launch_logit_pass(int mode, bool dma, const LogitPassArgs& p, hipStre
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
-  if (a.narrow) {
-    if (!a.direct_w || a.n_tiles != 1) return hipErrorInvalidValue;
-    switch (mode) {
-#define ADWIN_CASE(M) case M: logit_pass_dma_kernel<M, true, 1><<<grid, 256, DmaTile<1>::kRefLds, st>>>(a); break;
-      ADWIN_CASE(kModeSingle)
-      ADWIN_CASE(kModeSingleDiag)
-      ADWIN_CASE(kModeSingleE2)
-      ADWIN_CASE(kModeSingleE2Diag)
-      ADWIN_CASE(kModeSingleFwd)
-      ADWIN_CASE(kModeSingleFwdDiag)
-#undef ADWIN_CASE
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+  if (a.narrow && (a.stage == kStageImages || a.n_tiles != 1)) return hipErrorInvalidValue;
+  // a kernel for each mode and staging that fused_host.hip may ask for
+#define ADWIN_LAUNCH(FN, ...) logit_pass_dma_kernel<__VA_ARGS__><<<grid, 256, DmaTile<FN>::kRefLds, st>>>(a)
+#define ADWIN_ROWS(M, S)                                                       \
+  if (a.stage == S) {                                                          \
+    if (a.narrow) ADWIN_LAUNCH(1, M, S, 1);                                    \
+    else ADWIN_LAUNCH(2, M, S);                                                \
+    return hipGetLastError();                                                  \
   }
+#define ADWIN_STAGES(M)                                                        \
+  ADWIN_ROWS(M, kStageRows)                                                    \
+  ADWIN_ROWS(M, kStageRowsOnce)                                                \
+  if (a.stage != kStageImages) return hipErrorInvalidValue;                    \
+  ADWIN_LAUNCH(2, M, kStageImages);                                            \
+  return hipGetLastError();
+#define ADWIN_STAGES_GRADIENT(M)                                               \
+  ADWIN_ROWS(M, kStageTeacherOnce)                                             \
+  ADWIN_STAGES(M)
+#define ADWIN_STAGES_LINES(M)                                                  \
+  if (a.lines && !a.narrow && a.stage <= kStageRows) {                         \
+    if (a.stage == kStageImages) ADWIN_LAUNCH(2, M, kStageImages, 2, true);    \
+    else ADWIN_LAUNCH(2, M, kStageRows, 2, true);                              \
+    return hipGetLastError();                                                  \
+  }                                                                            \
+  ADWIN_STAGES_GRADIENT(M)
+#define ADWIN_STAGES_TWO_SWEEP(M)                                              \
+  if (a.narrow || a.stage > kStageRows) return hipErrorInvalidValue;           \
+  if (a.stage == kStageImages) ADWIN_LAUNCH(2, M, kStageImages);               \
+  else ADWIN_LAUNCH(2, M, kStageRows);                                         \
+  return hipGetLastError();
   switch (mode) {
-#define ADWIN_CASE(M)                                                                       \
-  case M:                                                                                   \
-    if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
-    else logit_pass_dma_kernel<M, false><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);            \
-    break;
-#define ADWIN_CASE_WRITES(M)                                                                \
-  case M:                                                                                   \
-    if (a.lines && a.direct_w) logit_pass_dma_kernel<M, true, 2, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
-    else if (a.lines) logit_pass_dma_kernel<M, false, 2, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
-    else if (a.direct_w) logit_pass_dma_kernel<M, true><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);  \
-    else logit_pass_dma_kernel<M, false><<<grid, 256, DmaTile<2>::kRefLds, st>>>(a);            \
-    break;
-    ADWIN_CASE(kModeStats)
-    ADWIN_CASE(kModeDz)
-    ADWIN_CASE_WRITES(kModeSingle)
-    ADWIN_CASE(kModeSingleDiag)
-    ADWIN_CASE_WRITES(kModeSingleE2)
-    ADWIN_CASE_WRITES(kModeSingleE2Diag)
-    ADWIN_CASE(kModeSingleFwd)
-    ADWIN_CASE(kModeSingleFwdDiag)
-#undef ADWIN_CASE_WRITES
-#undef ADWIN_CASE
+    case kModeStats: ADWIN_STAGES_TWO_SWEEP(kModeStats)
+    case kModeDz: ADWIN_STAGES_TWO_SWEEP(kModeDz)
+    case kModeSingle: ADWIN_STAGES_LINES(kModeSingle)
+    case kModeSingleDiag: ADWIN_STAGES_GRADIENT(kModeSingleDiag)
+    case kModeSingleE2: ADWIN_STAGES_LINES(kModeSingleE2)
+    case kModeSingleE2Diag: ADWIN_STAGES_LINES(kModeSingleE2Diag)
+    case kModeSingleFwd: ADWIN_STAGES(kModeSingleFwd)
+    case kModeSingleFwdDiag: ADWIN_STAGES(kModeSingleFwdDiag)
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+#undef ADWIN_STAGES_TWO_SWEEP
+#undef ADWIN_STAGES_LINES
+#undef ADWIN_STAGES_GRADIENT
+#undef ADWIN_STAGES
+#undef ADWIN_ROWS
+#undef ADWIN_LAUNCH
 }
 
 // The finely cut references serve calls of up to kFineRefTiles token tiles (References::parts is set by the

@@ -427,3 +427,30 @@ def test_slabs_past_the_caches(B, monkeypatch, rows, V, estimator, want):  # noq
             assert (a - b).abs().max() <= terms ** 0.5 * 2.0 ** -24 * 8 * b.abs().max(), k
         elif k != "batch":
             assert torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("rows", [100, 250])                             # half a token tile, and a whole one
+@pytest.mark.parametrize("H_s,H_t", [(192, 2432), (2112, 512)])          # the teacher's lines go past the caches, and all
+def test_weights_past_the_caches(B, rows, H_s, H_t):  # noqa: F811
+    """One token tile and weights beyond 320 MiB in all (W_s beyond 256 MiB or not): their lines go past the caches, the
+    same bits as with weights whose rows begin inside a line, which do not.  The last vocabulary tile holds 88 entries."""
+    V = 66008
+    assert 2 * V * (H_s + H_t) > 320 << 20 and (2 * V * H_s > 256 << 20) == (H_s > H_t)
+    w = synth.Workload(f"once_{H_s}", V, H_s, H_t, synth._offsets([rows + 30]), np.array([rows], np.int32),
+                       synth.MODE_PREFIX_ONLY)
+    d = synth.hidden_problem(w, "cuda")
+    shifted = {}
+    for k in ("W_s", "W_t"):
+        shifted[k] = torch.empty(d[k].numel() + 8, dtype=torch.bfloat16, device="cuda")[8:].view(d[k].shape)
+        shifted[k].copy_(d[k])
+        assert d[k].data_ptr() % 128 == 0 and shifted[k].data_ptr() % 128 == 16
+    for estimator in (O.EST_EXPECTED, O.EST_SAMPLED):
+        for want in (B.FusedCall.DEFAULT_OUTPUTS, B.FusedCall.DEFAULT_OUTPUTS + DIAGNOSTICS, STATS, STATS + DIAGNOSTICS):
+            outs = []
+            for W in (d, shifted):
+                outs.append(B.adwin_opd_fused(d["h_s"], d["h_t"], W["W_s"], W["W_t"], d["ids"], w.offsets, w.window, mode=w.mode,
+                                              want=want, estimator=estimator))
+                torch.cuda.synchronize()
+            assert int(outs[0]["status_dev"][0]) == 0 and float(outs[0]["kl"].abs().max()) > 0
+            for k in outs[0]:
+                assert torch.equal(outs[0][k], outs[1][k]), (k, estimator)
