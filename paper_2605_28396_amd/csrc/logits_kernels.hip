@@ -288,14 +288,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* row, int 
   // flag word: the raw-buffer setting of the gfx9 family (32-bit data format, no swizzle)
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, bytes, 0x00020000);
 }
+// PAST: past the caches (non-temporal), see past_caches.
+template <bool PAST = false>
 __device__ __forceinline__ uint4 row_load16(__amdgpu_buffer_rsrc_t r, int lane_off, int iter_off) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, iter_off, 0);
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, iter_off, PAST ? 2 : 0);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+template <bool PAST = false>
 __device__ __forceinline__ void row_store16(__amdgpu_buffer_rsrc_t r, int lane_off, int iter_off, const uint4& v) {
   u32x4 x;
   x.x = v.x; x.y = v.y; x.z = v.z; x.w = v.w;
-  __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off + iter_off, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off, iter_off, PAST ? 2 : 0);
 }
 
 // Bt = sum e^{z_t - m_t} z_t and cnt = entries above zy, the teacher's logit of y_t: diagnostics only.
@@ -365,7 +368,7 @@ __device__ __forceinline__ uint4 dz_vector(const uint4& qs, const uint4& qt, flo
   return o;
 }
 
-template <bool DIAG>
+template <bool DIAG, bool PAST>
 __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(LogitsArgs a) {
   extern __shared__ __align__(16) char lds_raw[];
   uint4* lds_t = (uint4*)lds_raw;
@@ -420,9 +423,9 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
       static_for<kResBatch>([&](auto g_c) {
         constexpr int g = decltype(g_c)::value;
         constexpr int it = b * kResBatch + g;
-        rs[it] = row_load16(bs, lane_off, it * kResThreads * 16);
-        if constexpr (it < kResTLds) tb[b % (kResDepth + 1)][g] = row_load16(bt, lane_off, it * kResThreads * 16);
-        else rt[it - kResTLds] = row_load16(bt, lane_off, it * kResThreads * 16);
+        rs[it] = row_load16<PAST>(bs, lane_off, it * kResThreads * 16);
+        if constexpr (it < kResTLds) tb[b % (kResDepth + 1)][g] = row_load16<PAST>(bt, lane_off, it * kResThreads * 16);
+        else rt[it - kResTLds] = row_load16<PAST>(bt, lane_off, it * kResThreads * 16);
       });
     }
   };
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(kResThreads, 1) void logits_row_resident_kernel(Log
     if (it * kResThreads < nvec) {
       uint4 qt;
       if constexpr (it < kResTLds) qt = lds_t[it * kResThreads + tid]; else qt = rt[it - kResTLds];
-      row_store16(bd, lane_off, it * kResThreads * 16, dz_vector(rs[it], qt, lse2, sgn, nmu));
+      row_store16<PAST>(bd, lane_off, it * kResThreads * 16, dz_vector(rs[it], qt, lse2, sgn, nmu));
     }
   });
   for (int q = kResVec + tid; q < nvec; q += kResThreads)
@@ -862,6 +865,14 @@ static hipError_t launch_short_rows(const RowsLaunch& l, hipStream_t st) {
   return launch_rows<1024, DIAG>(l, T, st);
 }
 
+// Whether the long-row kernel reads the logits and writes dz (`bytes` of it) past the caches: an array beyond the last-level
+// cache of 256 MiB is in memory again before anybody can find it there, and its lines displace those that other
+// workgroups are about to complete.  us per call, kept / past: V = 151,936: 2,615 of 3,901 rows 624 / 581, with diagnostics
+// 2,321 of 3,877 642 / 567, 6,505 of 9,708 1678 / 1426, 25,043 of 37,215 5467 / 5447; V = 100,032: 911 / 861.  Rows must
+// begin lines (`align`): pieces of a line that two instructions share are written one by one, and read twice.  (Short rows, four
+// waves to a SIMD, gain 0 to 2 % by it, dz alone, and lose up to 5 % with the logits.)
+static bool past_caches(int64_t bytes, uintptr_t align) { return bytes > (int64_t)320 << 20 && !(align & 127); }
+
 // Whether a call with diagnostics takes the streaming kernel under ADWIN_LOGITS_AUTO.
 // Diagnostics add arithmetic, which a workgroup that holds a row of more than 40,960 logits and has its
 // compute unit to itself (1024 threads, or the long-row kernel's 256) hides less well than the streaming
@@ -880,12 +891,14 @@ static hipError_t launch_short_rows(const RowsLaunch& l, hipStream_t st) {
 // 1066 / 988; V = 50,000: 700 rows 76 / 66, 2,048 rows 184 / 187, 8,192 rows 623 / 619; V = 81,928: 1,352 rows
 // 230 / 227), and so does the long-row kernel far beyond the 153,600 logits that stay on chip, where it
 // reads twice as well (V = 176,000: 1,024 rows 327 / 367; V = 200,000: 447 / 415; V = 262,144: 682 / 531).
-static bool streaming_suits_diagnostics(int V, int64_t n_adm) {
+// Past the caches (`past`) the long-row kernel is up to a sixth faster than that: V = 82,048: 3,542 rows 498 / 609, 15,847 rows
+// 2000 / 2460; V = 86,016: 505 / 637; V = 102,400: 2,914 rows 452 / 633; V = 196,608: 2,346 rows 948 / 1013.
+static bool streaming_suits_diagnostics(int V, int64_t n_adm, bool past) {
   const int64_t mib = 4 * n_adm * V >> 20;
   const bool third_round = n_adm > 512 && n_adm <= 560;
   if (V <= short_row_limit(1024))
     return V > short_row_limit(512) && n_adm > 256 && (V <= 51200 || third_round || (V <= 69632 && mib < 240));
-  if (V <= 86016 || V > 180224) return true;
+  if ((V <= 86016 && !past) || V > (past ? 196608 : 180224)) return true;
   return n_adm <= 256 ? n_adm <= 216 : mib < 256 || third_round;
 }
 
@@ -927,11 +940,13 @@ static hipError_t launch_split_rows(const RowsLaunch& l, const TailArgs& tail, h
 }
 
 hipError_t logits_kernels_opt_in() {
-  hipError_t e = hipFuncSetAttribute((const void*)logits_row_resident_kernel<false>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void*)logits_row_resident_kernel<true>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
+  const void* kernels[] = {(const void*)logits_row_resident_kernel<false, false>, (const void*)logits_row_resident_kernel<false, true>,
+                           (const void*)logits_row_resident_kernel<true, false>, (const void*)logits_row_resident_kernel<true, true>};
+  for (const void* k : kernels) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 constexpr size_t kPieceBytes = 32;       // the sums of one piece: 8 words
@@ -1011,8 +1026,9 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
   const bool diag = p->t_logp || p->t_entropy || p->t_rank;
   const bool automatic = p->scheme == ADWIN_LOGITS_AUTO;
   const int splits = automatic ? row_splits(p->V, hp.n_adm, diag, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
+  const bool past = past_caches(2 * p->T * p->V, al | (uintptr_t)(2 * (int64_t)p->V));
   const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING ||
-                         (automatic && diag && splits == 0 && streaming_suits_diagnostics(p->V, hp.n_adm));
+                         (automatic && diag && splits == 0 && streaming_suits_diagnostics(p->V, hp.n_adm, past));
   const bool shorts = !streaming && p->V <= short_row_limit(1024);
 
   SetupArgs setup(ws + L.o_plan, p->B);
@@ -1066,8 +1082,12 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
       else logits_row_kernel<false><<<(unsigned)p->T, kRowThreads, 0, stream>>>(a);
     } else {
       if (first_use_on_device(1)) ADWIN_HIP_TRY(logits_kernels_opt_in());
-      if (diag) logits_row_resident_kernel<true><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
-      else logits_row_resident_kernel<false><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a);
+#define ADWIN_LAUNCH(...) logits_row_resident_kernel<__VA_ARGS__><<<(unsigned)p->T, kResThreads, kResLdsBytes, stream>>>(a)
+      if (diag && past) ADWIN_LAUNCH(true, true);
+      else if (diag) ADWIN_LAUNCH(true, false);
+      else if (past) ADWIN_LAUNCH(false, true);
+      else ADWIN_LAUNCH(false, false);
+#undef ADWIN_LAUNCH
     }
     ADWIN_HIP_TRY(hipGetLastError());
   }

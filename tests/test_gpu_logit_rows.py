@@ -284,3 +284,27 @@ def test_lines_of_split_rows(B, V, n_adm):  # noqa: F811
                 assert np.all(np.abs(a[k] - b[k]) <= 2 * Hp.BF16_ULP * np.abs(b[k]) + 1e-6 * np.abs(b[k]).max())
             else:
                 assert np.allclose(a[k], b[k], rtol=2e-5, atol=1e-5 * max(1.0, np.abs(b[k]).max())), k
+
+
+@pytest.mark.parametrize("V,n", [(82048, 2050), (151936, 1110), (163840, 1030)])
+def test_long_rows_past_the_caches(B, V, n):  # noqa: F811
+    """Long rows that begin lines, with a gradient of more than 320 MiB, go past the caches: the bits of the same kernel on
+    logits that begin 16 bytes into a line, which do not; rows outside the windows, too.  (V = 163,840: more logits than
+    stay on chip.)"""
+    assert 2 * n * V > 320 << 20 and V % 64 == 0
+    z, ids = _long_rows(V, n, V)
+    shifted = []
+    for x in z:
+        shifted.append(torch.empty(x.numel() + 8, dtype=torch.bfloat16, device="cuda")[8:].view(x.shape))
+        shifted[-1].copy_(x)
+    off, win = np.array([0, 7, n]), np.array([5, n - 20], np.int32)
+    for est in (O.EST_EXPECTED, O.EST_SAMPLED):
+        for want in (BASE, BASE + DIAG):
+            a, b = (B.adwin_opd_from_logits(*x, ids, off, win, reduction=O.RED_SUM, estimator=est,
+                                            scheme=B.ADWIN_LOGITS_RESIDENT, want=want)
+                    for x in (z, shifted))
+            for k in a:
+                assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), (k, est)
+            assert float(a["kl"].abs().max()) > 0 and not a["dz"][5:7].any() and not a["dz"][n - 13:].any()
+            auto = B.adwin_opd_from_logits(*z, ids, off, win, reduction=O.RED_SUM, estimator=est, want=want)
+            assert torch.equal(a["dz"].view(torch.uint8), auto["dz"].view(torch.uint8))      # it serves them all
