@@ -274,16 +274,18 @@ class FusedCall:
                 "t_first_reject": ((B,), torch.int32), "t_logp_mean": ((B + 1, 2), torch.float32),
                 "cand_loss_share": ((K,), torch.float32),
             }
+            # The sizes go to torch.empty one by one: as a tuple it parses them 0.35 us slower per tensor, of the
+            # 51 us that a small call takes with its 12 tensors (27 us with 8, of logits) on the host.
             for k in want:
                 if k in ("dh_full", "dW_full") and mode != ADWIN_PREFIX_AND_FULL:
                     continue
                 shp, dt = shapes[k]
-                self.out[k] = torch.empty(shp, dtype=dt, device=dev)
+                self.out[k] = torch.empty(*shp, dtype=dt, device=dev)
                 setattr(p, k, _ptr(self.out[k]))
             if K and cand_outputs:     # the audit's alignment outputs; cand_loss_share goes through `want`
                 for k, shp in (("cand_rho_pooled", (K, B)), ("cand_rho_field", (K, B)),
                                ("cand_batch", (K, 4))):
-                    self.out[k] = torch.empty(shp, dtype=torch.float32, device=dev)
+                    self.out[k] = torch.empty(*shp, dtype=torch.float32, device=dev)
                     setattr(p, k, _ptr(self.out[k]))
             self.workspace_bytes = adwin_opd_workspace_bytes(p)
             self.workspace = torch.empty(self.workspace_bytes + 256, dtype=torch.uint8, device=dev)
@@ -368,7 +370,7 @@ class LogitsCall:
             }
             for k in want:
                 shp, dt = shapes[k]
-                self.out[k] = torch.empty(shp, dtype=dt, device=dev)
+                self.out[k] = torch.empty(*shp, dtype=dt, device=dev)
                 setattr(p, k, _ptr(self.out[k]))
             self.workspace_bytes = adwin_opd_logits_workspace_bytes(p)
             if workspace:       # run_static() needs none
