@@ -244,6 +244,22 @@ static int sweep_stage(const adwin_opd_problem* p, bool direct_w, int n_tiles, b
 // the group on its way and loses (2800 / 3070).
 static bool sweep_whole_lines(int H) { return H <= 4096; }
 
+// Whether the gradient GEMM takes the two factors themselves and collapses them on their way into the LDS, instead of dz from
+// a combine pass.  That spares a pass of 6 bytes per entry, and costs every column tile the conversion: a k-step
+// takes 2.3 us for 1.4 (grad_kstep_factors).  us per call, combine pass / none, H_t = 256, rows x V:
+//   H_s = 256:  700 x 50,000 151 / 141; 4,000 x 50,000 667 / 518; 1,500 x 151,936 783 / 576; 16,000 x 11,912 673 / 554;
+//               16,000 x 4,096 318 / 311; 1,500 x 11,912 97 / 101; 60 x 151,936 112 / 130
+//   H_s = 512:  4,000 x 151,936 2289 / 1987; 700 x 50,000 193 / 187; 16,000 x 11,912 805 / 765; 1,500 x 11,912 115 / 126;
+//               16,000 x 4,096 372 / 394
+//   H_s = 768:  4,000 x 151,936 2748 / 2603; 1,500 x 50,000 415 / 404; 16,000 x 11,912 988 / 1071
+//   H_s = 1024: 4,000 x 151,936 3154 / 3129; 16,000 x 11,912 1107 / 1197.  H_s = 2048: 4,096 x 151,936 8753 / 9205
+// So for up to three column tiles, each with the k-steps that make up for its longer prologue, and from 32 Mi entries on.
+// (The descriptors of the kernel address a row tile of up to 1 GiB.)
+static bool collapse_in_gemm(int64_t rows, int V, int h_tiles, int nk) {
+  const int least = h_tiles == 1 ? 64 : h_tiles == 2 ? 128 : 512;
+  return h_tiles <= 3 && nk >= least && nk <= 32768 && rows * V >= (int64_t)32 << 20;
+}
+
 static FusedLayout fused_layout(const adwin_opd_problem* p, const HostPlan& hp) {
   FusedLayout L;
   const int64_t n_pad = hp.n_pad > 0 ? hp.n_pad : kTileTokens;
@@ -531,7 +547,7 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
     GradArgs ga;
     ga.slab = la.slab; ga.Bm = (const __bf16*)p->W_s; ga.nk_total = (int)(L.Vp / kBK); ga.k_rows = p->V;
     ga.g = gws; ga.H = p->H_s; ga.h_tiles = h_tiles; ga.ksplit = L.ksplit;
-    ga.out_rows = (int64_t)1 << 62; ga.accumulate = 0;
+    ga.out_rows = (int64_t)1 << 62; ga.accumulate = 0; ga.e2_bytes = 0; ga.past_cache = false;
     if (L.single) {
       // Single sweep, the references fixed: per row slab one sweep over the vocabulary producing
       // the strip sums and the gradient factors, the merge of the slab's rows, the combine pass
@@ -583,8 +599,15 @@ static int fused_impl(const adwin_opd_problem* p, void* workspace, size_t worksp
             ADWIN_HIP_TRY(launch_combine(true, true, ca, ga.row_tiles, stream));
           }
         } else {
-          phase(ADWIN_PHASE_DZ);
-          ADWIN_HIP_TRY(launch_combine(head, false, ca, ga.row_tiles, stream));
+          const int64_t left = hp.n_rows - r0;
+          if (!head && collapse_in_gemm(left < rows ? left : rows, p->V, h_tiles, ga.nk_total)) {
+            ga.e2_bytes = 2 * la.e2_off; ga.past_cache = past_cache; ga.heavy = heavy;
+            ga.mu = ms.mu_out; ga.inv_z = ms.inv_z; ga.mu0t = la.mu0t; ga.mu0t_stride = la.mu0t_stride;
+          } else {
+            ga.e2_bytes = 0;
+            phase(ADWIN_PHASE_DZ);
+            ADWIN_HIP_TRY(launch_combine(head, false, ca, ga.row_tiles, stream));
+          }
           ga.half_tiles = ga.row_tiles;            // output rows are those of g
           ga.out_rows = (int64_t)align_up((size_t)hp.n_rows, 8);
         }

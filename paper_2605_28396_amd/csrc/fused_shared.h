@@ -354,6 +354,13 @@ struct GradArgs {
   // Rows of g that are stored: whole blocks of 8, so a multiple of 8, up to 7 more than exist where g has room for them
   int64_t out_rows;
   int accumulate;           // add to g instead of overwriting it
+  // A as the two factors of the single sweep: bytes from D to E2 (0: A is the operand itself), and what collapses
+  // them (see CombineArgs)
+  int64_t e2_bytes;
+  const float* mu; const float* inv_z;      // per computed row
+  const float* mu0t; int64_t mu0t_stride;   // reference of D per (vocabulary tile, slab row)
+  HeavyList heavy;
+  bool past_cache;                          // the factors exceed kPastCacheBytes
 };
 
 // Scale + scatter of the row gradients (see finalize_kernel).

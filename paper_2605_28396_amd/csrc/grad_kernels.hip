@@ -343,6 +343,165 @@ __device__ __forceinline__ void grad_kstep(f32x16 (&acc)[4][4], bf16x8 (&fa)[2][
 #undef ADWIN_FENCE
 }
 
+// The factors D and E2 of a k-step on their way to an A block (grad_gemm_kernel<true>, which has no combine pass before
+// it): they are loaded into registers, a k-step ahead of their conversion, and dz = E2 (D - (mu - mu0)) / Z_s goes
+// into the LDS two k-steps ahead of its use.  Each of the eight vectors that a lane has in flight is loaded again as soon
+// as it has been converted.  Vector j of a lane belongs at byte 4096 j + 1024 wave + 16 lane of the block, i.e. to
+// row 8 (4 j + wave) + lane / 8.  PAST: the lines of the factors past the caches, where one column tile reads them once.
+template <bool PAST>
+struct FactorLoads {
+  uint4 x[8], y[8];            // D and E2
+  float m0[8];                 // the reference of D: one per row and vocabulary tile
+  float mu[8], iz[8];          // of the row, the whole piece long; iz = inf: a row that is excluded or not there
+  __amdgpu_buffer_rsrc_t rx, ry, rm;
+  uint32_t off_m;              // of the lane's first row in the references
+  uint32_t soff;               // of the k-step that is loaded next
+  int kt; uint32_t m0_step;    // its number in the contraction, bytes per vocabulary tile in the references
+
+  __device__ __forceinline__ void load(int j, uint32_t voff) {
+    x[j] = row_load(rx, voff);
+    y[j] = row_load(ry, voff);
+    m0[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rm, (int)(off_m + j * 128), (int)((uint32_t)(kt >> 1) * m0_step), 0));
+  }
+  __device__ __forceinline__ uint4 row_load(__amdgpu_buffer_rsrc_t r, uint32_t voff) const {
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, PAST ? 2 : 0);
+    return make_uint4(v.x, v.y, v.z, v.w);
+  }
+  __device__ __forceinline__ void next() { soff += kImgBytes; ++kt; }
+};
+
+// Entries of a vector that do not go into the product: those of a row that is excluded, and the heavy ones, which
+// the workgroups of the first column tile list.
+__device__ __forceinline__ void collapse_rare(const GradArgs& a, const uint4& y, float iz, int64_t row, int v0, bool list, uint32_t (&o)[4]) {
+  int r = (int)row;
+  asm volatile("" : "+v"(r));        // the addresses of the lists are formed here: kept by the loop, they spilled
+  if (iz == __builtin_inff()) {
+    o[0] = o[1] = o[2] = o[3] = 0u;
+    return;
+  }
+#pragma unroll 1
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t yw = w == 0 ? y.x : w == 1 ? y.y : w == 2 ? y.z : y.w;
+    uint32_t keep = 0xffffffffu;
+    if (bf16_lo(yw) * iz >= kHeavyP && (!list || heavy_push(a.heavy, r, v0 + 2 * w))) keep &= 0xffff0000u;
+    if (bf16_hi(yw) * iz >= kHeavyP && (!list || heavy_push(a.heavy, r, v0 + 2 * w + 1))) keep &= 0x0000ffffu;
+    if (w == 0) o[0] &= keep; else if (w == 1) o[1] &= keep; else if (w == 2) o[2] &= keep; else o[3] &= keep;
+  }
+}
+
+// A k-step of grad_gemm_kernel<true>.  LOADS: load the factors of k-step s + 3.  MORE: convert those of k-step s + 2, one
+// entry behind each MFMA, and load its B block.  The A blocks are written from sub-step 0 on, into the third buffer of
+// their ring, so it is the B blocks that have the ring of two here and are loaded behind the barrier.
+// What bounds it is the issue of instructions: 650 in a k-step (370 of them convert), 2,600 cycles of a lone wave for
+// the 2,048 that the matrix pipe needs, and as many waits for results as leave it busy half of the 4,150 cycles that a
+// k-step takes (SQ_ACTIVE_INST_ANY, SQ_WAIT_INST_ANY; H_s = 2048).  It is not the latency of the factors: touching their
+// lines a k-step or two ahead made it 11 % slower.  4,000 rows of V = 50,000, H_s = 256: combine pass and GEMM
+// 305 us, this 169 (178 with the factors' lines kept); 6,000 rows of V = 151,936, H_s = 512: 1645 and 1200.
+template <bool LOADS, bool MORE, bool LAST, bool PAST>
+__device__ __forceinline__ void grad_kstep_factors(const GradArgs& a, FactorLoads<PAST>& f, f32x16 (&acc)[4][4], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][4],
+                                           uint32_t& r_a, uint32_t& r_b, uint32_t a_begin, uint32_t a_end,
+                                           uint32_t b_begin, uint32_t b_end, const uint32_t (&swA)[4],
+                                           const uint32_t (&swB)[4], const uint32_t (&voffd)[8],
+                                           const uint32_t (&voffb)[8], uint32_t b_step,
+                                           uint32_t& pb_lo, uint32_t& pb_hi, int64_t row0, int v0, bool list) {
+  uint32_t r_a_nx = 0, r_b_nx = 0, r_a_wr = 0;
+  uint32_t xa = 0, xb[4];
+  float ndl = 0.f, pm = 0.f, even = 0.f;
+  uint32_t o[4];
+  const uint32_t lane16 = (threadIdx.x & 63) * 16u;
+#define ADWIN_FENCE __builtin_amdgcn_sched_barrier(0);
+#define ADWIN_MM(KK, I, J)                                                                    \
+  acc[I][J] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[(KK) & 1][I], fb[(KK) & 1][J],       \
+                                                      acc[I][J], 0, 0, 0);                    \
+  ADWIN_FENCE
+#define ADWIN_SIDE(KK, M)                                                                           \
+  if constexpr ((M) < 8 && ((KK) < 3 || !LAST)) {                                                   \
+    constexpr int ad_n = ((KK) + 1) & 3, ad_f = ((M) >> 1) & 3;                                     \
+    if constexpr ((M) == 0) {                                                                       \
+      xa = ((KK) < 3 ? r_a : r_a_nx) + swA[ad_n];                                                   \
+      asm volatile("" : "+v"(xa));                                                                  \
+    }                                                                                               \
+    if constexpr (((M) & 1) == 0) {                                                                 \
+      fa[ad_n & 1][ad_f] = lds_frag(xa)[ad_f * 32 * kRowBytes / 16];                                \
+      if constexpr ((KK) == 0 || (KK) == 3) {                                                       \
+        xb[ad_f] = ((KK) < 3 ? r_b : r_b_nx) + swB[ad_f];                                           \
+        asm volatile("" : "+v"(xb[ad_f]));                                                          \
+      }                                                                                             \
+    } else {                                                                                        \
+      fb[ad_n & 1][ad_f] = lds_frag_tr<ad_n * kGradSubBytes>(xb[ad_f]);                             \
+    }                                                                                               \
+    if constexpr ((KK) == 0 && (M) == 0 && !LAST) r_b_nx = ring_next<kImgBytes>(r_b, b_begin, b_end); \
+    if constexpr ((KK) == 0 && (M) == 1 && !LAST) r_a_nx = ring_next<kImgBytes>(r_a, a_begin, a_end); \
+    if constexpr ((KK) == 0 && (M) == 2 && MORE) r_a_wr = ring_next<kImgBytes>(r_a_nx, a_begin, a_end); \
+    if constexpr ((KK) == 0 && (M) == 3 && MORE) addr_advance(pb_lo, pb_hi, b_step);               \
+  }                                                                                                 \
+  if constexpr (MORE) {                                                                             \
+    constexpr int ad_j = 2 * (KK) + ((M) >> 3), ad_e = (M) & 7, ad_w = ad_e >> 1;                   \
+    if constexpr (ad_e == 0) { ndl = (f.m0[ad_j] - f.mu[ad_j]) * f.iz[ad_j]; pm = 0.f; }            \
+    const uint32_t ad_x = ad_w == 0 ? f.x[ad_j].x : ad_w == 1 ? f.x[ad_j].y : ad_w == 2 ? f.x[ad_j].z : f.x[ad_j].w; \
+    const uint32_t ad_y = ad_w == 0 ? f.y[ad_j].x : ad_w == 1 ? f.y[ad_j].y : ad_w == 2 ? f.y[ad_j].z : f.y[ad_j].w; \
+    const float ad_yv = (ad_e & 1) ? bf16_hi(ad_y) : bf16_lo(ad_y);                                 \
+    const float ad_d = ad_yv * fmaf((ad_e & 1) ? bf16_hi(ad_x) : bf16_lo(ad_x), f.iz[ad_j], ndl);   \
+    pm = fmaxf(pm, ad_yv);                                                                          \
+    if constexpr ((ad_e & 1) == 0) even = ad_d; else o[ad_w] = pack_bf16(even, ad_d);               \
+    if constexpr (ad_e == 7) {                                                                      \
+      if (__builtin_expect(!(pm * f.iz[ad_j] < kHeavyP), 0))                                        \
+        collapse_rare(a, f.y[ad_j], f.iz[ad_j], row0 + ad_j * 32, v0, list, o);                     \
+      u32x4 ad_o; ad_o.x = o[0]; ad_o.y = o[1]; ad_o.z = o[2]; ad_o.w = o[3];                       \
+      *((__attribute__((address_space(3))) u32x4*)(uintptr_t)(r_a_wr + lane16) + ad_j * 4096 / 16) = ad_o; \
+      if constexpr (LOADS) f.load(ad_j, voffd[ad_j]);                                               \
+    }                                                                                               \
+    if constexpr ((KK) == 3 && (M) >= 8)                                                            \
+      dma16_at<((M) - 8) * 4096>(r_b, voffb[((M) - 8) & 7], addr_of(pb_lo, pb_hi));                 \
+  }                                                                                                 \
+  ADWIN_FENCE
+#define ADWIN_ROW(KK, I, M0)                                                    \
+  ADWIN_MM(KK, I, 0) { ADWIN_SIDE(KK, (M0) + 0) } ADWIN_MM(KK, I, 1) { ADWIN_SIDE(KK, (M0) + 1) } \
+  ADWIN_MM(KK, I, 2) { ADWIN_SIDE(KK, (M0) + 2) } ADWIN_MM(KK, I, 3) { ADWIN_SIDE(KK, (M0) + 3) }
+#define ADWIN_SUB(KK) ADWIN_ROW(KK, 0, 0) ADWIN_ROW(KK, 1, 4) ADWIN_ROW(KK, 2, 8) ADWIN_ROW(KK, 3, 12)
+  ADWIN_FENCE
+  ADWIN_SUB(0)
+  ADWIN_SUB(1)
+  ADWIN_SUB(2)
+  if constexpr (!LAST) {
+    // The B block of the next k-step was asked for in the last sub-step of the previous one; behind it came the
+    // loads of six vectors, three each.
+    if constexpr (LOADS) asm volatile("s_waitcnt vmcnt(18) lgkmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+  ADWIN_FENCE
+  ADWIN_SUB(3)
+  if constexpr (!LAST) { r_a = r_a_nx; r_b = r_b_nx; }
+#undef ADWIN_SUB
+#undef ADWIN_ROW
+#undef ADWIN_SIDE
+#undef ADWIN_MM
+#undef ADWIN_FENCE
+}
+
+// A whole A block from its factors: the first two of a piece.
+template <class F>
+__device__ __forceinline__ void collapse_block(const GradArgs& a, const F& f, const uint4 (&x)[8], const uint4 (&y)[8], const float (&m0)[8],
+                                               uint32_t lds, int64_t row0, int v0, bool list) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float iz = f.iz[j], ndl = (m0[j] - f.mu[j]) * iz;
+    const uint32_t xw[4] = {x[j].x, x[j].y, x[j].z, x[j].w}, yw[4] = {y[j].x, y[j].y, y[j].z, y[j].w};
+    uint32_t o[4];
+    float pm = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float lo = bf16_lo(yw[w]), hi = bf16_hi(yw[w]);
+      o[w] = pack_bf16(lo * fmaf(bf16_lo(xw[w]), iz, ndl), hi * fmaf(bf16_hi(xw[w]), iz, ndl));
+      pm = fmaxf(pm, fmaxf(lo, hi));
+    }
+    if (__builtin_expect(!(pm * iz < kHeavyP), 0)) collapse_rare(a, y[j], iz, row0 + j * 32, v0, list, o);
+    u32x4 v; v.x = o[0]; v.y = o[1]; v.z = o[2]; v.w = o[3];
+    *((__attribute__((address_space(3))) u32x4*)(uintptr_t)lds + j * 4096 / 16) = v;
+  }
+}
+
 // The eight wave-loads of one 32 KiB block into the buffer at lds_wave (its address + 1024 wave).
 template <int... D>
 __device__ __forceinline__ void dma_block(uint32_t lds_wave, const uint32_t (&voffd)[8], const char* blk,
@@ -350,6 +509,9 @@ __device__ __forceinline__ void dma_block(uint32_t lds_wave, const uint32_t (&vo
   (dma16_at<D * 4096>(lds_wave, voffd[D], blk), ...);
 }
 
+// FACTORS: A is the two factors of the single sweep, collapsed on their way into the LDS (FactorLoads; collapse_in_gemm says
+// when).
+template <bool FACTORS, bool PAST = false>
 __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -402,25 +564,76 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
   };
   b_rows(k_begin);
   const uint32_t ldsw = lds0 + (uint32_t)wave * 1024u;
-  // the ring of three (offset 0) holds the B blocks, the ring of two the slab blocks
-  const uint32_t b_begin = ldsw, b_end = ldsw + kGradRing3 * kImgBytes;
-  const uint32_t a_begin = ldsw + kGradRing2Off, a_end = a_begin + 2 * kImgBytes;
+  // the ring of three (offset 0) holds the B blocks, the ring of two the slab blocks; FACTORS: the other way round
+  const uint32_t ring3 = ldsw, ring3_end = ldsw + kGradRing3 * kImgBytes, ring2 = ldsw + kGradRing2Off, ring2_end = ring2 + 2 * kImgBytes;
+  const uint32_t b_begin = FACTORS ? ring2 : ring3, b_end = FACTORS ? ring2_end : ring3_end;
+  const uint32_t a_begin = FACTORS ? ring3 : ring2, a_end = FACTORS ? ring3_end : ring2_end;
   const std::make_integer_sequence<int, 8> all8{};
 
   f32x16 acc[4][4];
+  FactorLoads<PAST> f;
+  const int64_t row0 = a.slab_row0 + (int64_t)rt * kGradTile + 8 * wave + (lane >> 3);   // of the lane's first vector
+  const int chunk = 8 * ((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7));                   // its entry in the k-step
+  if constexpr (FACTORS) {
+    const int64_t tile_bytes = (int64_t)a.nk_total * kImgBytes;
+    f.rx = __builtin_amdgcn_make_buffer_rsrc((char*)a.slab + rt * tile_bytes, 0, (int)tile_bytes, 0x00020000);
+    f.ry = __builtin_amdgcn_make_buffer_rsrc((char*)a.slab + a.e2_bytes + rt * tile_bytes, 0, (int)tile_bytes, 0x00020000);
+    f.m0_step = (uint32_t)a.mu0t_stride * 4u;
+    f.rm = __builtin_amdgcn_make_buffer_rsrc((char*)(a.mu0t + (int64_t)rt * kGradTile), 0,
+                                             (int)(((uint32_t)(a.nk_total / 2 - 1)) * f.m0_step + kGradTile * 4), 0x00020000);
+    f.off_m = (uint32_t)(8 * wave + (lane >> 3)) * 4u;
+    f.kt = k_begin; f.soff = (uint32_t)k_begin * kImgBytes;
 #pragma unroll
-  for (int fm = 0; fm < 4; ++fm)
-#pragma unroll
-    for (int fn = 0; fn < 4; ++fn)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[fm][fn][e] = 0.f;
-
+    for (int j = 0; j < 8; ++j) {
+      f.mu[j] = a.mu[row0 + j * 32];
+      f.iz[j] = a.inv_z[row0 + j * 32];
+      if (f.iz[j] == 0.f || (4 * j + wave) * 8 >= rows_left) f.iz[j] = __builtin_inff();
+    }
+  }
   if (nk > 0) {
     // first the blocks of k-step 0, then its first fragments
+    uint64_t pb = (uint64_t)sB;
     dma_block(b_begin, voffb, sB, all8);
-    dma_block(a_begin, voffd, sA, all8);
-    wait_vm<0>();
+    if constexpr (FACTORS) {
+      uint4 x[8], y[8];
+      float m0[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) { f.load(j, voffd[j]); x[j] = f.x[j]; y[j] = f.y[j]; m0[j] = f.m0[j]; }
+      f.next();
+      if (nk > 1) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { f.load(j, voffd[j]); __builtin_amdgcn_sched_barrier(0); }
+        f.next();
+        pb += b_step;
+        if (nk == 2) b_rows(k_end - 1);
+        dma_block(b_begin + kImgBytes, voffb, (const char*)pb, all8);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      collapse_block(a, f, x, y, m0, a_begin + (uint32_t)lane * 16u, row0, k_begin * kBK + chunk, ht == 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (nk > 1) {
+        collapse_block(a, f, f.x, f.y, f.m0, a_begin + kImgBytes + (uint32_t)lane * 16u, row0, (k_begin + 1) * kBK + chunk, ht == 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (nk > 2) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { f.load(j, voffd[j]); __builtin_amdgcn_sched_barrier(0); }
+        f.next();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (nk > 2) asm volatile("s_waitcnt vmcnt(24) lgkmcnt(0)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    } else {
+      dma_block(a_begin, voffd, sA, all8);
+      wait_vm<0>();
+    }
     __syncthreads();
+#pragma unroll
+    for (int fm = 0; fm < 4; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < 4; ++fn)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[fm][fn][e] = 0.f;
     bf16x8 fa[2][4], fb[2][4];
     uint32_t swA[4], swB[4];
     {
@@ -446,30 +659,50 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
       fa[0][i] = lds_frag(r_a + swA[0])[i * 32 * kRowBytes / 16];
       fb[0][i] = lds_frag_tr<0>(r_b + swB[i]);
     }
-    // blocks of k-step 1 (k-step s of the loop loads those of k-step s + 2)
-    uint64_t pa = (uint64_t)sA, pb = (uint64_t)sB;
-    if (nk > 1) {
-      pa += kImgBytes; pb += b_step;
-      if (nk == 2) b_rows(k_end - 1);
-      dma_block(b_begin + kImgBytes, voffb, (const char*)pb, all8);
-      dma_block(a_begin + kImgBytes, voffd, (const char*)pa, all8);
-    }
-    uint32_t pa_lo = (uint32_t)pa, pa_hi = (uint32_t)(pa >> 32), pb_lo = (uint32_t)pb, pb_hi = (uint32_t)(pb >> 32);
     int s = 0;
-    for (; s + 3 < nk; ++s)
-      grad_kstep<true, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
+    if constexpr (FACTORS) {
+      uint32_t pb_lo = (uint32_t)pb, pb_hi = (uint32_t)(pb >> 32);
+#define ADWIN_KSTEP(...) grad_kstep_factors<__VA_ARGS__>(a, f, acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, \
+                                                        b_step, pb_lo, pb_hi, row0, (k_begin + s + 2) * kBK + chunk, ht == 0)
+      for (; s + 3 < nk; ++s) {
+        ADWIN_KSTEP(true, true, false, PAST);
+        f.next();
+      }
+      if (s + 2 < nk) {           // the step that loads the last k-step, which may hold fewer rows
+        b_rows(k_end - 1);
+        ADWIN_KSTEP(false, true, false, PAST);
+        ++s;
+      }
+      if (s + 1 < nk) ADWIN_KSTEP(false, false, false, PAST);
+      ADWIN_KSTEP(false, false, true, PAST);
+#undef ADWIN_KSTEP
+    } else {
+      // blocks of k-step 1 (k-step s of the loop loads those of k-step s + 2)
+      uint64_t pa = (uint64_t)sA;
+      if (nk > 1) {
+        pa += kImgBytes; pb += b_step;
+        if (nk == 2) b_rows(k_end - 1);
+        dma_block(b_begin + kImgBytes, voffb, (const char*)pb, all8);
+        dma_block(a_begin + kImgBytes, voffd, (const char*)pa, all8);
+      }
+      uint32_t pa_lo = (uint32_t)pa, pa_hi = (uint32_t)(pa >> 32), pb_lo = (uint32_t)pb, pb_hi = (uint32_t)(pb >> 32);
+      for (; s + 3 < nk; ++s)
+        grad_kstep<true, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
+                                pa_lo, pa_hi, pb_lo, pb_hi);
+      if (s + 2 < nk) {           // the step that loads the last k-step, which may hold fewer rows
+        b_rows(k_end - 1);
+        grad_kstep<true, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
+                                pa_lo, pa_hi, pb_lo, pb_hi);
+        ++s;
+      }
+      if (s + 1 < nk)
+        grad_kstep<false, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
+                                 pa_lo, pa_hi, pb_lo, pb_hi);
+      grad_kstep<false, true>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
                               pa_lo, pa_hi, pb_lo, pb_hi);
-    if (s + 2 < nk) {           // the step that loads the last k-step, which may hold fewer rows
-      b_rows(k_end - 1);
-      grad_kstep<true, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
-                              pa_lo, pa_hi, pb_lo, pb_hi);
-      ++s;
     }
-    if (s + 1 < nk)
-      grad_kstep<false, false>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
-                               pa_lo, pa_hi, pb_lo, pb_hi);
-    grad_kstep<false, true>(acc, fa, fb, r_a, r_b, a_begin, a_end, b_begin, b_end, swA, swB, voffd, voffb, b_step,
-                            pa_lo, pa_hi, pb_lo, pb_hi);
+  } else {
+    for (auto& row : acc) for (auto& tile : row) tile = f32x16{};
   }
   // Epilogue.  H and out_rows end on whole blocks of 32 columns and 8 rows (H is a multiple of 64; the rows of a
   // dW are V, a multiple of 8, those of g are rounded up to one within its padded planes), so every bound is wave-uniform and a store takes one 32-bit lane offset, a scalar
@@ -674,8 +907,11 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, TailArgs 
 // Launchers
 // ---------------------------------------------------------------------------------------
 hipError_t grad_kernels_opt_in() {
-  return hipFuncSetAttribute((const void*)grad_gemm_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             kGradLds);
+  for (const void* k : {(const void*)grad_gemm_kernel<false>, (const void*)grad_gemm_kernel<true>, (const void*)grad_gemm_kernel<true, true>}) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kGradLds);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_hs_gather(const HsGatherArgs& a, int64_t rows, hipStream_t st) {
@@ -700,7 +936,10 @@ hipError_t launch_grad_gemm(const GradArgs& p, hipStream_t st) {
   if (p.out_rows & 7) return hipErrorInvalidValue;       // rows are stored by eights
   GradArgs a = p;
   a.split_steps.split((int)((a.k_rows + kBK - 1) / kBK), a.ksplit);
-  grad_gemm_kernel<<<(unsigned)(a.row_tiles * a.h_tiles * a.ksplit), 256, kGradLds, st>>>(a);
+  const unsigned grid = (unsigned)(a.row_tiles * a.h_tiles * a.ksplit);
+  if (a.e2_bytes && a.past_cache && a.h_tiles == 1) grad_gemm_kernel<true, true><<<grid, 256, kGradLds, st>>>(a);
+  else if (a.e2_bytes) grad_gemm_kernel<true><<<grid, 256, kGradLds, st>>>(a);
+  else grad_gemm_kernel<false><<<grid, 256, kGradLds, st>>>(a);
   return hipGetLastError();
 }
 

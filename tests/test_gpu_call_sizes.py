@@ -454,3 +454,34 @@ def test_weights_past_the_caches(B, rows, H_s, H_t):  # noqa: F811
             assert int(outs[0]["status_dev"][0]) == 0 and float(outs[0]["kl"].abs().max()) > 0
             for k in outs[0]:
                 assert torch.equal(outs[0][k], outs[1][k]), (k, estimator)
+
+
+@pytest.mark.parametrize("H_s,V,rows", [
+    (192, 4104, 8300),       # one column tile, 65 k-steps, the last of which holds 8 entries
+    (128, 131080, 300),      # ... and pieces of one row tile; 44 rows in the second, which repeats its first eight
+    (128, 110000, 800),      # ... factors of more than 320 MiB
+    (320, 33000, 1100),      # two column tiles
+    (576, 32776, 1050),      # three; 513 k-steps
+])
+def test_factors_collapsed_in_the_gemm(B, H_s, V, rows):  # noqa: F811
+    """Calls whose gradient GEMM converts the factors itself, against the same call with the head gradient, which keeps the
+    combine pass: rows with heavy entries, and one excluded.  The two round dz in fp32 in another order, by up to 3 x 2^-24, before
+    it goes to bf16, so that at most 6 x 2^-24 / 2^-8 of the entries go to the other neighbour, 2^-8 away:
+    2^-8 sqrt(6 x 2^-16) = 3.7e-5 of the norm."""
+    w = synth.Workload(f"factors_{V}", V, H_s, 128, synth._offsets([rows + 20]), np.array([rows], np.int32),
+                       synth.MODE_PREFIX_ONLY)
+    d = synth.hidden_problem(w, "cuda")
+    W_y = d["W_s"][d["ids"].long()].float()
+    peaked = torch.arange(rows + 20, device="cuda") % 3 == 0
+    a = 1.2 * np.log(V) / W_y.square().sum(1, keepdim=True) * peaked[:, None]
+    d["h_s"] = (d["h_s"].float() + a * W_y).to(torch.bfloat16)
+    d["h_s"][rows // 2, 3] = float("inf")
+    outs = [B.adwin_opd_fused(d["h_s"], d["h_t"], d["W_s"], d["W_t"], d["ids"], w.offsets, w.window, mode=w.mode,
+                              want=B.FusedCall.DEFAULT_OUTPUTS + more) for more in ((), ("dW_prefix",))]
+    torch.cuda.synchronize()
+    a, b = (o["dh_prefix"].double() for o in outs)
+    assert torch.equal(outs[0]["kl"], outs[1]["kl"]) and torch.equal(outs[0]["status_dev"], outs[1]["status_dev"])
+    assert float(b[rows // 2].abs().max()) == 0 == float(a[rows // 2].abs().max())
+    assert float(b.abs().max()) > 0
+    for m in (peaked, ~peaked):
+        assert float((a[m] - b[m]).norm()) <= 3.7e-5 * float(b[m].norm())
