@@ -243,15 +243,20 @@ constexpr int kGradSubBytes = 16 * kGradRowBytes;             // the 16 rows of 
 
 // A B fragment: 8 consecutive rows (k-entries) of one column, as two transposing reads of four.
 // addr: the lane's address in rows 0..3 of its half of sub-step 0; OFF: the sub-step.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 template <int OFF>
-__device__ __forceinline__ bf16x8 lds_frag_tr(uint32_t addr) {
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef short s16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ s16x4 lds_read_tr(uint32_t addr) {
   typedef __attribute__((address_space(3))) s16x4* Ptr;
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Ptr)(uintptr_t)addr + OFF / 8);
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Ptr)(uintptr_t)addr + (OFF + 4 * kGradRowBytes) / 8);
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((Ptr)(uintptr_t)addr + OFF / 8);
+}
+__device__ __forceinline__ bf16x8 tr_frag(s16x4 lo, s16x4 hi) {
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
   const s16x8 f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8, f);
+}
+template <int OFF>
+__device__ __forceinline__ bf16x8 lds_frag_tr(uint32_t addr) {
+  return tr_frag(lds_read_tr<OFF>(addr), lds_read_tr<OFF + 4 * kGradRowBytes>(addr));
 }
 
 // LOADS: in k-step s the B block of k-step s + 2 is loaded in sub-steps 1 and 2, four
@@ -358,10 +363,13 @@ struct FactorLoads {
   uint32_t soff;               // of the k-step that is loaded next
   int kt; uint32_t m0_step;    // its number in the contraction, bytes per vocabulary tile in the references
 
+  __device__ __forceinline__ void load_part(int part, int j, uint32_t voff) {
+    if (part == 1) x[j] = row_load(rx, voff);
+    else if (part == 2) y[j] = row_load(ry, voff);
+    else m0[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rm, (int)(off_m + j * 128), (int)((uint32_t)(kt >> 1) * m0_step), 0));
+  }
   __device__ __forceinline__ void load(int j, uint32_t voff) {
-    x[j] = row_load(rx, voff);
-    y[j] = row_load(ry, voff);
-    m0[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rm, (int)(off_m + j * 128), (int)((uint32_t)(kt >> 1) * m0_step), 0));
+    load_part(1, j, voff); load_part(2, j, voff); load_part(3, j, voff);
   }
   __device__ __forceinline__ uint4 row_load(__amdgpu_buffer_rsrc_t r, uint32_t voff) const {
     const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, PAST ? 2 : 0);
@@ -389,14 +397,17 @@ __device__ __forceinline__ void collapse_rare(const GradArgs& a, const uint4& y,
   }
 }
 
-// A k-step of grad_gemm_kernel<true>.  LOADS: load the factors of k-step s + 3.  MORE: convert those of k-step s + 2, one
-// entry behind each MFMA, and load its B block.  The A blocks are written from sub-step 0 on, into the third buffer of
+// A k-step of grad_gemm_kernel<true>.  LOADS: load the factors of k-step s + 3.  MORE: convert those of k-step s + 2 behind
+// the MFMAs, and load its B block.  The A blocks are written from sub-step 0 on, into the third buffer of
 // their ring, so it is the B blocks that have the ring of two here and are loaded behind the barrier.
 // What bounds it is the issue of instructions: 650 in a k-step (370 of them convert), 2,600 cycles of a lone wave for
-// the 2,048 that the matrix pipe needs, and as many waits for results as leave it busy half of the 4,150 cycles that a
-// k-step takes (SQ_ACTIVE_INST_ANY, SQ_WAIT_INST_ANY; H_s = 2048).  It is not the latency of the factors: touching their
-// lines a k-step or two ahead made it 11 % slower.  4,000 rows of V = 50,000, H_s = 256: combine pass and GEMM
-// 305 us, this 169 (178 with the factors' lines kept); 6,000 rows of V = 151,936, H_s = 512: 1645 and 1200.
+// the 2,048 that the matrix pipe needs, and waits that leave that busy half of the 4,150 cycles that a
+// k-step takes (SQ_ACTIVE_INST_ANY, SQ_WAIT_INST_ANY, SQ_WAIT_ANY; H_s = 2048).  It is not the latency of the factors:
+// touching their lines a k-step or two ahead made it 11 % slower.  Two entries at a time, their last products
+// behind the MFMA after the one that covers the first ones, the loads behind three MFMAs and one fragment read
+// to each of twelve: 2,500 rows of V = 151,936, H_s = 768 724 -> 696 us, 1,000 rows, H_s = 512 207 -> 200, against an entry
+// at a time from end to end.  Combine pass and GEMM / this: 4,096 rows of V = 50,000, H_s = 256 305 / 170 us (180 with the
+// factors' lines kept); 6,000 rows of V = 151,936, H_s = 512 1645 / 1172.
 template <bool LOADS, bool MORE, bool LAST, bool PAST>
 __device__ __forceinline__ void grad_kstep_factors(const GradArgs& a, FactorLoads<PAST>& f, f32x16 (&acc)[4][4], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][4],
                                            uint32_t& r_a, uint32_t& r_b, uint32_t a_begin, uint32_t a_end,
@@ -406,7 +417,8 @@ __device__ __forceinline__ void grad_kstep_factors(const GradArgs& a, FactorLoad
                                            uint32_t& pb_lo, uint32_t& pb_hi, int64_t row0, int v0, bool list) {
   uint32_t r_a_nx = 0, r_b_nx = 0, r_a_wr = 0;
   uint32_t xa = 0, xb[4];
-  float ndl = 0.f, pm = 0.f, even = 0.f;
+  float ndl = 0.f, pm = 0.f, x_lo = 0.f, x_hi = 0.f, y_lo = 0.f, y_hi = 0.f;
+  s16x4 tr_lo;
   uint32_t o[4];
   const uint32_t lane16 = (threadIdx.x & 63) * 16u;
 #define ADWIN_FENCE __builtin_amdgcn_sched_barrier(0);
@@ -415,20 +427,27 @@ __device__ __forceinline__ void grad_kstep_factors(const GradArgs& a, FactorLoad
                                                       acc[I][J], 0, 0, 0);                    \
   ADWIN_FENCE
 #define ADWIN_SIDE(KK, M)                                                                           \
-  if constexpr ((M) < 8 && ((KK) < 3 || !LAST)) {                                                   \
-    constexpr int ad_n = ((KK) + 1) & 3, ad_f = ((M) >> 1) & 3;                                     \
+  if constexpr ((M) < 12 && ((KK) < 3 || !LAST)) {                                                  \
+    /* one read of a fragment of the next sub-step: A 0, the two halves of B 0 .. 3, A 1 .. 3 */    \
+    constexpr int ad_n = ((KK) + 1) & 3;                                                            \
     if constexpr ((M) == 0) {                                                                       \
       xa = ((KK) < 3 ? r_a : r_a_nx) + swA[ad_n];                                                   \
       asm volatile("" : "+v"(xa));                                                                  \
     }                                                                                               \
-    if constexpr (((M) & 1) == 0) {                                                                 \
+    if constexpr ((M) == 0 || (M) > 8) {                                                            \
+      constexpr int ad_f = (M) == 0 ? 0 : (M) & 3;                                                  \
       fa[ad_n & 1][ad_f] = lds_frag(xa)[ad_f * 32 * kRowBytes / 16];                                \
-      if constexpr ((KK) == 0 || (KK) == 3) {                                                       \
-        xb[ad_f] = ((KK) < 3 ? r_b : r_b_nx) + swB[ad_f];                                           \
-        asm volatile("" : "+v"(xb[ad_f]));                                                          \
-      }                                                                                             \
     } else {                                                                                        \
-      fb[ad_n & 1][ad_f] = lds_frag_tr<ad_n * kGradSubBytes>(xb[ad_f]);                             \
+      constexpr int ad_f = (((M) - 1) >> 1) & 3;                                                    \
+      if constexpr (((M) & 1) == 1) {                                                               \
+        if constexpr ((KK) == 0 || (KK) == 3) {                                                     \
+          xb[ad_f] = ((KK) < 3 ? r_b : r_b_nx) + swB[ad_f];                                         \
+          asm volatile("" : "+v"(xb[ad_f]));                                                        \
+        }                                                                                           \
+        tr_lo = lds_read_tr<ad_n * kGradSubBytes>(xb[ad_f]);                                        \
+      } else {                                                                                      \
+        fb[ad_n & 1][ad_f] = tr_frag(tr_lo, lds_read_tr<ad_n * kGradSubBytes + 4 * kGradRowBytes>(xb[ad_f])); \
+      }                                                                                             \
     }                                                                                               \
     if constexpr ((KK) == 0 && (M) == 0 && !LAST) r_b_nx = ring_next<kImgBytes>(r_b, b_begin, b_end); \
     if constexpr ((KK) == 0 && (M) == 1 && !LAST) r_a_nx = ring_next<kImgBytes>(r_a, a_begin, a_end); \
@@ -436,25 +455,41 @@ __device__ __forceinline__ void grad_kstep_factors(const GradArgs& a, FactorLoad
     if constexpr ((KK) == 0 && (M) == 3 && MORE) addr_advance(pb_lo, pb_hi, b_step);               \
   }                                                                                                 \
   if constexpr (MORE) {                                                                             \
-    constexpr int ad_j = 2 * (KK) + ((M) >> 3), ad_e = (M) & 7, ad_w = ad_e >> 1;                   \
-    if constexpr (ad_e == 0) { ndl = (f.m0[ad_j] - f.mu[ad_j]) * f.iz[ad_j]; pm = 0.f; }            \
-    const uint32_t ad_x = ad_w == 0 ? f.x[ad_j].x : ad_w == 1 ? f.x[ad_j].y : ad_w == 2 ? f.x[ad_j].z : f.x[ad_j].w; \
-    const uint32_t ad_y = ad_w == 0 ? f.y[ad_j].x : ad_w == 1 ? f.y[ad_j].y : ad_w == 2 ? f.y[ad_j].z : f.y[ad_j].w; \
-    const float ad_yv = (ad_e & 1) ? bf16_hi(ad_y) : bf16_lo(ad_y);                                 \
-    const float ad_d = ad_yv * fmaf((ad_e & 1) ? bf16_hi(ad_x) : bf16_lo(ad_x), f.iz[ad_j], ndl);   \
-    pm = fmaxf(pm, ad_yv);                                                                          \
-    if constexpr ((ad_e & 1) == 0) even = ad_d; else o[ad_w] = pack_bf16(even, ad_d);               \
-    if constexpr (ad_e == 7) {                                                                      \
-      if (__builtin_expect(!(pm * f.iz[ad_j] < kHeavyP), 0))                                        \
-        collapse_rare(a, f.y[ad_j], f.iz[ad_j], row0 + ad_j * 32, v0, list, o);                     \
-      u32x4 ad_o; ad_o.x = o[0]; ad_o.y = o[1]; ad_o.z = o[2]; ad_o.w = o[3];                       \
-      *((__attribute__((address_space(3))) u32x4*)(uintptr_t)(r_a_wr + lane16) + ad_j * 4096 / 16) = ad_o; \
-      if constexpr (LOADS) f.load(ad_j, voffd[ad_j]);                                               \
-    }                                                                                               \
     if constexpr ((KK) == 3 && (M) >= 8)                                                            \
       dma16_at<((M) - 8) * 4096>(r_b, voffb[((M) - 8) & 7], addr_of(pb_lo, pb_hi));                 \
+    constexpr int ad_j = 2 * (KK) + ((M) >> 3), ad_e = (M) & 7, ad_w = ad_e >> 1;                   \
+    /* the pair before: the products of an entry wait for no result that was only just asked for */ \
+    if constexpr ((ad_e & 1) == 0 && (ad_j > 0 || ad_e > 0)) ADWIN_PAIR_END((ad_w + 3) & 3)         \
+    if constexpr (ad_e == 0 && ad_j > 0) ADWIN_VECTOR_END((ad_j + 7) & 7)                           \
+    if constexpr (LOADS && ad_j > 0 && ad_e >= 1 && ad_e <= 3) f.load_part(ad_e, (ad_j + 7) & 7, voffd[(ad_j + 7) & 7]); \
+    const uint32_t ad_x = ad_w == 0 ? f.x[ad_j].x : ad_w == 1 ? f.x[ad_j].y : ad_w == 2 ? f.x[ad_j].z : f.x[ad_j].w; \
+    const uint32_t ad_y = ad_w == 0 ? f.y[ad_j].x : ad_w == 1 ? f.y[ad_j].y : ad_w == 2 ? f.y[ad_j].z : f.y[ad_j].w; \
+    if constexpr ((ad_e & 1) == 0) {                                                                \
+      if constexpr (ad_e == 0) { ndl = (f.m0[ad_j] - f.mu[ad_j]) * f.iz[ad_j]; pm = 0.f; }          \
+      x_lo = bf16_lo(ad_x); x_hi = bf16_hi(ad_x);                                                   \
+    } else {                                                                                        \
+      y_lo = bf16_lo(ad_y); y_hi = bf16_hi(ad_y);                                                   \
+      x_lo = fmaf(x_lo, f.iz[ad_j], ndl); x_hi = fmaf(x_hi, f.iz[ad_j], ndl);                       \
+      pm = fmaxf(fmaxf(pm, y_lo), y_hi);                                                            \
+    }                                                                                               \
+    if constexpr (ad_j == 7 && ad_e == 7) {                                                         \
+      ADWIN_PAIR_END(3)                                                                             \
+      ADWIN_VECTOR_END(7)                                                                           \
+      if constexpr (LOADS) f.load(7, voffd[7]);                                                     \
+    }                                                                                               \
   }                                                                                                 \
   ADWIN_FENCE
+#define ADWIN_PAIR_END(W) {                                                                         \
+    asm volatile("" : "+v"(x_lo), "+v"(x_hi));      /* here, not right behind what they wait for */  \
+    o[W] = pack_bf16(y_lo * x_lo, y_hi * x_hi);                                                     \
+  }
+#define ADWIN_VECTOR_END(J) {                                                                       \
+    if (__builtin_expect(__any(!(pm * f.iz[J] < kHeavyP)), 0)) {                                    \
+      if (!(pm * f.iz[J] < kHeavyP)) collapse_rare(a, f.y[J], f.iz[J], row0 + (J) * 32, v0, list, o); \
+    }                                                                                               \
+    u32x4 ad_o; ad_o.x = o[0]; ad_o.y = o[1]; ad_o.z = o[2]; ad_o.w = o[3];                         \
+    *((__attribute__((address_space(3))) u32x4*)(uintptr_t)(r_a_wr + lane16) + (J) * 4096 / 16) = ad_o; \
+  }
 #define ADWIN_ROW(KK, I, M0)                                                    \
   ADWIN_MM(KK, I, 0) { ADWIN_SIDE(KK, (M0) + 0) } ADWIN_MM(KK, I, 1) { ADWIN_SIDE(KK, (M0) + 1) } \
   ADWIN_MM(KK, I, 2) { ADWIN_SIDE(KK, (M0) + 2) } ADWIN_MM(KK, I, 3) { ADWIN_SIDE(KK, (M0) + 3) }
@@ -475,6 +510,8 @@ __device__ __forceinline__ void grad_kstep_factors(const GradArgs& a, FactorLoad
   if constexpr (!LAST) { r_a = r_a_nx; r_b = r_b_nx; }
 #undef ADWIN_SUB
 #undef ADWIN_ROW
+#undef ADWIN_VECTOR_END
+#undef ADWIN_PAIR_END
 #undef ADWIN_SIDE
 #undef ADWIN_MM
 #undef ADWIN_FENCE
