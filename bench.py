@@ -165,7 +165,7 @@ def _bench_logits(B, synth, dev, steps, cpu_rows, estimator):
         "roofline": {"bound": "hbm", "kernel": "logits_row_resident_kernel + zero-fill of the rows outside the windows",
                      "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": ach / PEAK_HBM_GBS,
-                     "traffic": _measured_traffic("logits_given_hbm_counters.txt", "adwin::logits_row_resident_kernel<false>"),
+                     "traffic": _measured_traffic("logits_given_hbm_counters.txt", "adwin::logits_row_resident_kernel<false,true>"),
                      "traffic_source": "profiles/logits_given_hbm_counters.txt (rocprofv3 --pmc, separate run)",
                      "launch_ms": kernel_ms, "alg_bytes_per_launch": alg_bytes,
                      "whole_call_frac": alg_bytes / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS},
@@ -278,7 +278,7 @@ def main() -> int:
     roofline = {"bound": "mfma", "kernel": "logit_pass_dma_kernel", "achieved": ach,
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_BF16_TFLOPS,
                 "traffic": _measured_traffic(f"fused_{w.name}_hbm_counters.txt",
-                                             "adwin::logit_pass_dma_kernel<2,false,2>"),
+                                             "adwin::logit_pass_dma_kernel<2,0,2,false>"),
                 "traffic_source": f"profiles/fused_{w.name}_hbm_counters.txt (rocprofv3 --pmc, separate run)",
                 "launch_ms": launch_ms, "launches_per_call": launches,
                 "alg_flops_per_launch": f_stats}

@@ -247,12 +247,12 @@ static bool sweep_whole_lines(int H) { return H <= 4096; }
 // Whether the gradient GEMM takes the two factors themselves and collapses them on their way into the LDS, instead of dz from
 // a combine pass.  That spares a pass of 6 bytes per entry, and costs every column tile the conversion: a k-step
 // takes 2.3 us for 1.4 (grad_kstep_factors).  us per call, combine pass / none, H_t = 256, rows x V:
-//   H_s = 256:  700 x 50,000 151 / 141; 4,000 x 50,000 667 / 518; 1,500 x 151,936 783 / 576; 16,000 x 11,912 673 / 554;
-//               16,000 x 4,096 318 / 311; 1,500 x 11,912 97 / 101; 60 x 151,936 112 / 130
-//   H_s = 512:  4,000 x 151,936 2289 / 1987; 700 x 50,000 193 / 187; 16,000 x 11,912 805 / 765; 1,500 x 11,912 115 / 126;
-//               16,000 x 4,096 372 / 394
-//   H_s = 768:  4,000 x 151,936 2748 / 2603; 1,500 x 50,000 415 / 404; 16,000 x 11,912 988 / 1071
-//   H_s = 1024: 4,000 x 151,936 3154 / 3129; 16,000 x 11,912 1107 / 1197.  H_s = 2048: 4,096 x 151,936 8753 / 9205
+//   H_s = 256:  700 x 50,000 152 / 140; 3,000 x 50,000 514 / 397; 1,500 x 151,936 783 / 583; 16,000 x 11,912 680 / 560;
+//               16,000 x 4,096 326 / 315; 8,000 x 4,096 168 / 171; 1,500 x 11,912 97 / 101
+//   H_s = 512:  3,000 x 151,936 1782 / 1555; 700 x 50,000 194 / 185; 16,000 x 11,912 822 / 767; 8,000 x 8,192 330 / 326;
+//               16,000 x 4,096 378 / 396; 1,500 x 11,912 115 / 126
+//   H_s = 768:  3,000 x 151,936 2186 / 2009; 1,500 x 32,776 295 / 278; 8,000 x 20,000 849 / 873; 16,000 x 11,912 999 / 1072
+//   H_s = 1024: 3,000 x 151,936 2498 / 2454; 8,000 x 32,776 1464 / 1470.  H_s = 1280: 3,000 x 151,936 2876 / 2920
 // So for up to three column tiles, each with the k-steps that make up for its longer prologue, and from 32 Mi entries on.
 // (The descriptors of the kernel address a row tile of up to 1 GiB.)
 static bool collapse_in_gemm(int64_t rows, int V, int h_tiles, int nk) {
