@@ -278,8 +278,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // Row access through buffer descriptors: base = the row, extent = its bytes.  Every 16-byte
-// access is then one instruction with a lane offset shared by all of them (16 * thread index)
-// and a scalar offset per iteration, no 64-bit address per access to compute or to keep in
+// load is then one instruction with a lane offset shared by all of them (16 * thread index)
+// and a scalar offset per iteration (a store: one with their 32-bit sum), no 64-bit address per access to compute or to keep in
 // vector registers (with 150 accesses per sweep those addresses, computed ahead by the
 // compiler, crowded the row itself out of the register file); an access beyond the extent reads
 // zeros / is dropped by the hardware, which is what the ragged last iteration needs.
@@ -294,11 +294,14 @@ __device__ __forceinline__ uint4 row_load16(__amdgpu_buffer_rsrc_t r, int lane_o
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, iter_off, PAST ? 2 : 0);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+// No scalar offset: the compiler puts two wait states between a 16-byte buffer store and an instruction that overwrites its
+// data registers, but none if the store has one, and such stores of the sweep were seen to write the registers' next
+// contents where two waves shared a SIMD.
 template <bool PAST = false>
 __device__ __forceinline__ void row_store16(__amdgpu_buffer_rsrc_t r, int lane_off, int iter_off, const uint4& v) {
   u32x4 x;
   x.x = v.x; x.y = v.y; x.z = v.z; x.w = v.w;
-  __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off, iter_off, PAST ? 2 : 0);
+  __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off + iter_off, 0, PAST ? 2 : 0);
 }
 
 // Bt = sum e^{z_t - m_t} z_t and cnt = entries above zy, the teacher's logit of y_t: diagnostics only.
