@@ -868,13 +868,16 @@ static hipError_t launch_short_rows(const RowsLaunch& l, hipStream_t st) {
   return launch_rows<1024, DIAG>(l, T, st);
 }
 
-// Whether the long-row kernel reads the logits and writes dz (`bytes` of it) past the caches: an array beyond the last-level
-// cache of 256 MiB is in memory again before anybody can find it there, and its lines displace those that other
-// workgroups are about to complete.  us per call, kept / past: V = 151,936: 2,615 of 3,901 rows 624 / 581, with diagnostics
-// 2,321 of 3,877 642 / 567, 6,505 of 9,708 1678 / 1426, 25,043 of 37,215 5467 / 5447; V = 100,032: 911 / 861.  Rows must
-// begin lines (`align`): pieces of a line that two instructions share are written one by one, and read twice.  (Short rows, four
-// waves to a SIMD, gain 0 to 2 % by it, dz alone, and lose up to 5 % with the logits.)
-static bool past_caches(int64_t bytes, uintptr_t align) { return bytes > (int64_t)320 << 20 && !(align & 127); }
+// Whether the long-row kernel reads the logits and writes dz past the caches: each of these arrays, T x V, is beyond the
+// last-level cache of 256 MiB, so it is in memory again before anybody can find it there, and its lines displace those that
+// other workgroups are about to complete.  us per call, kept / past: V = 151,936: 2,615 of 3,901 rows 624 / 581, with diagnostics
+// 2,321 of 3,877 642 / 567, 6,505 of 9,708 1678 / 1426, 20,000 rows 4171 / 3787; V = 100,032: 911 / 861; few of the rows
+// admitted, V = 151,936, 450 of 4,000 345 / 327; no dz, 1,110 rows 159 / 145.  The line was drawn by rows that are whole lines of
+// an array that begins one.  Where the array begins is no part of it: the rule also decides which kernel serves calls with
+// diagnostics, and the same logits give the same bits wherever they lie.  (16 bytes into a line: 1,110 rows 272 / 239,
+// 20,000 rows 4117 / 3935, V = 82,048, 2,050 rows with diagnostics 333 / 275.)  Short rows, four waves to a SIMD, gain 0 to 2 % by it,
+// dz alone, and lose up to 5 % with the logits.
+static bool past_caches(int64_t T, int V) { return 2 * T * V > ((int64_t)320 << 20) && V % 64 == 0; }
 
 // Whether a call with diagnostics takes the streaming kernel under ADWIN_LOGITS_AUTO.
 // Diagnostics add arithmetic, which a workgroup that holds a row of more than 40,960 logits and has its
@@ -1029,7 +1032,7 @@ static int logits_impl(const adwin_opd_logits_problem* p, void* workspace, size_
   const bool diag = p->t_logp || p->t_entropy || p->t_rank;
   const bool automatic = p->scheme == ADWIN_LOGITS_AUTO;
   const int splits = automatic ? row_splits(p->V, hp.n_adm, diag, (int64_t)(room < kMaxPieces ? room : kMaxPieces)) : 0;
-  const bool past = past_caches(2 * p->T * p->V, al | (uintptr_t)(2 * (int64_t)p->V));
+  const bool past = past_caches(p->T, p->V);
   const bool streaming = p->scheme == ADWIN_LOGITS_STREAMING ||
                          (automatic && diag && splits == 0 && streaming_suits_diagnostics(p->V, hp.n_adm, past));
   const bool shorts = !streaming && p->V <= short_row_limit(1024);

@@ -288,23 +288,44 @@ def test_lines_of_split_rows(B, V, n_adm):  # noqa: F811
 
 @pytest.mark.parametrize("V,n", [(82048, 2050), (151936, 1110), (163840, 1030)])
 def test_long_rows_past_the_caches(B, V, n):  # noqa: F811
-    """Long rows that begin lines, with a gradient of more than 320 MiB, go past the caches: the bits of the same kernel on
-    logits that begin 16 bytes into a line, which do not; rows outside the windows, too.  (V = 163,840: more logits than
-    stay on chip.)"""
-    assert 2 * n * V > 320 << 20 and V % 64 == 0
+    """Logits of more than 320 MiB, in long rows of whole lines, go past the caches: the bits of the same kernel on the same
+    rows in two calls, which keep them; rows outside the windows, too.  (V = 163,840: more logits than stay on chip.)"""
+    assert 2 * n * V > 320 << 20 > n // 2 * 2 * V and V % 64 == 0
+    z, ids = _long_rows(V, n, V)
+    adm = np.zeros(n, bool)
+    adm[:5] = adm[7:n - 13] = True
+    kw = dict(reduction=O.RED_SUM, scheme=B.ADWIN_LOGITS_RESIDENT)
+
+    def run(lo, hi, off, win, **more):
+        return B.adwin_opd_from_logits(z[0][lo:hi], z[1][lo:hi], ids[lo:hi], np.array(off), np.array(win, np.int32), **{**kw, **more})
+
+    for est in (O.EST_EXPECTED, O.EST_SAMPLED):
+        for want in (BASE, BASE + DIAG):
+            a = run(0, n, [0, 7, n], [5, n - 20], want=want, estimator=est)
+            m = n // 2
+            parts = [run(0, m, [0, 7, m], [5, m], want=want, estimator=est),
+                     run(m, n, [0, n - m], [n - 13 - m], want=want, estimator=est)]
+            for k in ("kl", "c", "dz") + (DIAG if "t_rank" in want else ()):
+                b = torch.cat([x[k] for x in parts])
+                assert torch.equal(a[k].view(torch.uint8), b.view(torch.uint8)), (k, est)
+                assert not a[k][torch.from_numpy(~adm)].any()
+            assert float(a["kl"].abs().max()) > 0
+            auto = run(0, n, [0, 7, n], [5, n - 20], want=want, estimator=est, scheme=B.ADWIN_LOGITS_AUTO)
+            assert torch.equal(a["dz"].view(torch.uint8), auto["dz"].view(torch.uint8))      # it serves them all
+
+
+@pytest.mark.parametrize("V,n", [(82048, 2050), (86016, 1960), (151936, 1110), (180288, 940), (196608, 860)])
+def test_results_do_not_depend_on_the_address(B, V, n):  # noqa: F811
+    """Long rows of more than 320 MiB, at the lines of the rule that chooses between the streaming and the long-row kernel
+    with diagnostics: the same bits from logits that begin a line and from logits that begin 16 bytes into one."""
     z, ids = _long_rows(V, n, V)
     shifted = []
     for x in z:
         shifted.append(torch.empty(x.numel() + 8, dtype=torch.bfloat16, device="cuda")[8:].view(x.shape))
         shifted[-1].copy_(x)
+        assert x.data_ptr() % 128 == 0 and shifted[-1].data_ptr() % 128 == 16
     off, win = np.array([0, 7, n]), np.array([5, n - 20], np.int32)
-    for est in (O.EST_EXPECTED, O.EST_SAMPLED):
-        for want in (BASE, BASE + DIAG):
-            a, b = (B.adwin_opd_from_logits(*x, ids, off, win, reduction=O.RED_SUM, estimator=est,
-                                            scheme=B.ADWIN_LOGITS_RESIDENT, want=want)
-                    for x in (z, shifted))
-            for k in a:
-                assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), (k, est)
-            assert float(a["kl"].abs().max()) > 0 and not a["dz"][5:7].any() and not a["dz"][n - 13:].any()
-            auto = B.adwin_opd_from_logits(*z, ids, off, win, reduction=O.RED_SUM, estimator=est, want=want)
-            assert torch.equal(a["dz"].view(torch.uint8), auto["dz"].view(torch.uint8))      # it serves them all
+    for want in (BASE, BASE + DIAG):
+        a, b = (B.adwin_opd_from_logits(*x, ids, off, win, reduction=O.RED_SUM, want=want) for x in (z, shifted))
+        for k in a:
+            assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), k
