@@ -44,6 +44,8 @@
  *     a fixed order (where the head-weight gradient adds one slab's contribution to
  *     the previous ones with the hardware's floating-point add, each element is added
  *     to by exactly one lane per launch and the launches are ordered on the stream).
+ *     The kernels that serve a call follow its sizes and the outputs that it asks for, so
+ *     two calls that ask for different outputs may differ in a gradient's last bits.
  */
 #ifndef ADWIN_OPD_H
 #define ADWIN_OPD_H

@@ -239,9 +239,9 @@ static int sweep_stage(const adwin_opd_problem* p, bool direct_w, int n_tiles, b
 // Whether a sweep whose slab exceeds the caches stores the factors as whole lines past them (single_epilogue).  The shorter
 // the contraction, the more of a sweep are its stores.  us per sweep, plain pieces / lines, V = 151,936: H = 640 + 256,
 // 24,000 rows 8710 / 7790; 1536 + 1536, 16,384 rows 13830 / 13320; 8,192 rows of 1152 + 1792 (V = 124,200) 5515 / 5215, of
-// 1536 + 2048 7940 / 7640, of 2048 + 2048 8730 / 8430, of 2560 + 2560 10880 / 10640.  With 2048 + 4096 it depends on the
-// GPU, 24.8 / 24.6 ms to 24.6 / 25.6 for 16,384 rows.  The sweep with both factors and diagnostics has no registers for
-// the group on its way and loses (2800 / 3070).
+// 1536 + 2048 7940 / 7640, of 2048 + 2048 8730 / 8430.  The gain shrinks with the length, 2.2 % of 2560 + 2560 (10880 / 10640), and
+// with 2048 + 4096 it depends on the GPU, 24.8 / 24.6 ms to 24.6 / 25.6 for 16,384 rows: the line lies below both.  The sweep
+// with both factors and diagnostics has no registers for the group on its way and loses (2800 / 3070).
 static bool sweep_whole_lines(int H) { return H <= 4096; }
 
 // Whether the gradient GEMM takes the two factors themselves and collapses them on their way into the LDS, instead of dz from
@@ -253,7 +253,8 @@ static bool sweep_whole_lines(int H) { return H <= 4096; }
 //               16,000 x 4,096 378 / 396; 1,500 x 11,912 115 / 126
 //   H_s = 768:  3,000 x 151,936 2186 / 2009; 1,500 x 32,776 295 / 278; 8,000 x 20,000 849 / 873; 16,000 x 11,912 999 / 1072
 //   H_s = 1024: 3,000 x 151,936 2498 / 2454; 8,000 x 32,776 1464 / 1470.  H_s = 1280: 3,000 x 151,936 2876 / 2920
-// So for up to three column tiles, each with the k-steps that make up for its longer prologue, and from 32 Mi entries on.
+// So for up to three column tiles, each number from a length of the contraction on (k-steps of the whole vocabulary, of which a
+// piece takes its share: below it the longer prologue of the pieces weighs too much), and from 32 Mi entries on.
 // (The descriptors of the kernel address a row tile of up to 1 GiB.)
 static bool collapse_in_gemm(int64_t rows, int V, int h_tiles, int nk) {
   const int least = h_tiles == 1 ? 64 : h_tiles == 2 ? 128 : 512;

@@ -349,9 +349,12 @@ __device__ __forceinline__ void grad_kstep(f32x16 (&acc)[4][4], bf16x8 (&fa)[2][
 }
 
 // The factors D and E2 of a k-step on their way to an A block (grad_gemm_kernel<true>, which has no combine pass before
-// it): they are loaded into registers, a k-step ahead of their conversion, and dz = E2 (D - (mu - mu0)) / Z_s goes
-// into the LDS two k-steps ahead of its use.  Each of the eight vectors that a lane has in flight is loaded again as soon
-// as it has been converted.  Vector j of a lane belongs at byte 4096 j + 1024 wave + 16 lane of the block, i.e. to
+// it): they are loaded into registers, asked for a k-step ahead of their conversion, and dz = E2 (D - (mu - mu0)) / Z_s
+// goes into the LDS two k-steps ahead of its use.  Each of the eight vectors that a lane has in flight is loaded again as soon
+// as it has been converted.  The compiler's waits for them do not count the eight loads of the B block (inline assembly) that
+// are asked for between them: vmcnt(21) before vector 0 and vmcnt(18) before the others stand where 29 and 26 loads are
+// younger, so that each also waits for up to eight younger loads, vector 0 for those of vector 3, and the time that a load
+// has is two sub-steps, half a k-step.  Vector j of a lane belongs at byte 4096 j + 1024 wave + 16 lane of the block, i.e. to
 // row 8 (4 j + wave) + lane / 8.  PAST: the lines of the factors past the caches, where one column tile reads them once.
 template <bool PAST>
 struct FactorLoads {
@@ -379,7 +382,8 @@ struct FactorLoads {
 };
 
 // Entries of a vector that do not go into the product: those of a row that is excluded, and the heavy ones, which
-// the workgroups of the first column tile list.
+// the workgroups of the first column tile list.  (The others need not ask whether the list had room: 33 entries of
+// p >= 1/32, each up to 2^-9 too large as a bf16, would add up to more than 1.)
 __device__ __forceinline__ void collapse_rare(const GradArgs& a, const uint4& y, float iz, int64_t row, int v0, bool list, uint32_t (&o)[4]) {
   int r = (int)row;
   asm volatile("" : "+v"(r));        // the addresses of the lists are formed here: kept by the loop, they spilled
@@ -400,10 +404,12 @@ __device__ __forceinline__ void collapse_rare(const GradArgs& a, const uint4& y,
 // A k-step of grad_gemm_kernel<true>.  LOADS: load the factors of k-step s + 3.  MORE: convert those of k-step s + 2 behind
 // the MFMAs, and load its B block.  The A blocks are written from sub-step 0 on, into the third buffer of
 // their ring, so it is the B blocks that have the ring of two here and are loaded behind the barrier.
-// What bounds it is the issue of instructions: 650 in a k-step (370 of them convert), 2,600 cycles of a lone wave for
-// the 2,048 that the matrix pipe needs, and waits that leave that busy half of the 4,150 cycles that a
-// k-step takes (SQ_ACTIVE_INST_ANY, SQ_WAIT_INST_ANY, SQ_WAIT_ANY; H_s = 2048).  It is not the latency of the factors:
-// touching their lines a k-step or two ahead made it 11 % slower.  Two entries at a time, their last products
+// What bounds it, 4,000 rows of V = 151,936, H_s = 512 (2,500 rows, H_s = 768 the same): the wave, alone on its SIMD, issues
+// 62 % of the time (SQ_ACTIVE_INST_ANY; 650 instructions in a k-step, 370 of them convert), waits 24 % for loads and LDS reads
+// (SQ_WAIT_ANY; 9 % in the GEMM on dz) and 14 % for its turn to issue; the matrix pipe is busy half of the time, and
+// a k-step takes 2.3 us for 1.4 after a combine pass.  3,139 rows of V = 11,912, 21 k-steps to a workgroup: 49, 36 and 15 %, pipe
+// 32 %: prologue and epilogue.  4,096 rows of V = 50,000, H_s = 256, past the caches: 49, 27 and 24 %, pipe 37 %.  Touching
+// the factors' lines a k-step or two ahead made it 11 % slower, in the same queue of loads.  Two entries at a time, their last products
 // behind the MFMA after the one that covers the first ones, the loads behind three MFMAs and one fragment read
 // to each of twelve: 2,500 rows of V = 151,936, H_s = 768 724 -> 696 us, 1,000 rows, H_s = 512 207 -> 200, against an entry
 // at a time from end to end.  Combine pass and GEMM / this: 4,096 rows of V = 50,000, H_s = 256 305 / 170 us (180 with the
